@@ -1256,6 +1256,11 @@ WgradPlan wgrad_plan(long P, int tiles, long E) {
 bool mfma_conv_ok(int dt, int cin, int cout) {
   return dt == 0 && cin % 64 == 0 && cout % 64 == 0;
 }
+// Shapes conv_forward_mfma takes: those, and 3x3 layers of the
+// rectangular-tile kernel.
+bool mfma_fwd_ok(int dt, const ConvShape& s) {
+  return mfma_conv_ok(dt, s.cin, s.cout) || (dt == 0 && conv_tile_ok(s));
+}
 
 // Forward tile configurations.  A configuration is chosen per shape by
 // fwd_config() (a pure function of the shape, so recomputation reuses the
@@ -1456,6 +1461,11 @@ PersTile pers_tile(int cfg) {
 FwdPlan fwd_plan(const ConvShape& s) {
   const long P = 4L * s.H * s.W;
   FwdPlan pl{0, 1};
+  if (s.cin % 64 || s.cout % 64) {   // the kernel that takes any multiple of 8
+    pl.cfg = 500;
+    if (g_fwd_variant >= 500) pl.cfg = g_fwd_variant;
+    return pl;
+  }
   // Measured per shape (3x3, kernel time in a step): the nine-tap
   // whole-row kernel is fastest on images of 48 x 48 and up, and from 24 x 24
   // where one micro-batch gives it at least 48 tiles (at 24 x 24 a paired
@@ -1477,11 +1487,17 @@ FwdPlan fwd_plan(const ConvShape& s) {
     pl.cfg = 207;  // persistent row-stage, 128 x 256, 8 waves
   } else if (conv1x1_res_ok(s)) {
     pl.cfg = 150;  // 1x1, all weights resident in LDS
+  } else if (conv_tile_ok(s)) {
+    pl.cfg = 500;  // rectangular tiles
   } else {
     pl.cfg = 100;
   }
   if (g_fwd_variant > 0) pl.cfg = g_fwd_variant;
   if (pl.cfg == 150 && !conv1x1_res_ok(s)) pl.cfg = 100;
+  if (pl.cfg >= 500) {
+    if (!conv_tile_ok(s)) pl.cfg = 100;
+    return pl;
+  }
   if (pl.cfg >= 400) {
     g_rows32_cfg = pl.cfg >= 401 ? pl.cfg - 401 : -1;
     if (!conv_rows32_ok(s)) pl.cfg = 100;
@@ -1524,8 +1540,18 @@ FwdPlan fwd_plan(const ConvShape& s) {
   return pl;
 }
 
+// The rectangular-tile kernel, in the configuration a forced plan names.
+static hipError_t launch_tile_cfg(int cfg, int n, const void* const* x, const void* w,
+                                  const float* b, void* const* y, const ConvShape& s, int relu,
+                                  hipStream_t st) {
+  g_tile_cfg = cfg >= 501 ? cfg - 501 : -1;
+  const hipError_t e = conv_forward_tile(n, x, w, b, y, s, relu, st);
+  g_tile_cfg = -1;
+  return e;
+}
+
 size_t conv_forward_partial_floats(int dt, const ConvShape& s) {
-  if (!mfma_conv_ok(dt, s.cin, s.cout)) return 0;
+  if (!mfma_fwd_ok(dt, s)) return 0;
   FwdPlan pl = fwd_plan(s);
   const bool splits = pl.cfg < 100 || (pl.cfg >= 200 && pl.cfg < 300);   // per-tap and row-tiled never split
   return splits && pl.S > 1 ? (size_t)pl.S * s.pixels() * s.cout : 0;
@@ -1543,6 +1569,7 @@ hipError_t conv_forward_mfma(const void* x, const void* w, const float* b, void*
   const FwdPlan pl = fwd_plan(s);
   const bool wide = s.cout % 128 == 0;
   if (pl.cfg == 150) return launch_1x1_res(1, &x, Wt, b, &y, s, relu, st);
+  if (pl.cfg >= 500) return launch_tile_cfg(pl.cfg, 1, &x, w, b, &y, s, relu, st);
   if (pl.cfg >= 400) {
     g_rows32_cfg = pl.cfg >= 401 ? pl.cfg - 401 : -1;
     const hipError_t e = conv_forward_rows32(1, &x, w, b, &y, s, relu, st);
@@ -1610,8 +1637,26 @@ static bool use_wgrad_rows(const ConvShape& s) {
   return (g_rowtile_mask >> 2 & 1) && wgrad_rows_ok(s);
 }
 
+// 3x3 layers of no fixed width: the rectangular-stage kernel.  Where the
+// per-tap kernel can run too (channels in multiples of 64), small layers stay
+// with it: its many short blocks start and end sooner.  Measured, four or two
+// micro-batches a launch / one: 128 -> 128 at 56 x 56 x 8 52 / 45 us against
+// 65 / 45, 512 -> 512 at 14 x 14 x 4 31 / 28 against 49 / 25, 128 -> 192 at 45
+// x 61 x 3 29 / 29 against 32 / 26; 64 -> 64 at 56 x 56 x 4 20 (one) against
+// 12, x 1 15 against 8.  The line lies at 48 thousand pixel x item products.
+static bool use_wgrad_tile(const ConvShape& s) {
+  if (!wgrad_tile_ok(s)) return false;
+  return s.cin % 64 || s.cout % 64 ||
+         s.pixels() * (s.cin / 64) * (s.cout / 64) >= 48 * 1024;
+}
+// Shapes conv_wgrad_mfma takes.
+bool mfma_wgrad_ok(int dt, const ConvShape& s) {
+  return mfma_conv_ok(dt, s.cin, s.cout) || (dt == 0 && wgrad_tile_ok(s));
+}
+
 size_t wgrad_mfma_partial_floats(const ConvShape& s) {
   if (use_wgrad_rows(s)) return wgrad_rows_partial_floats(s);
+  if (use_wgrad_tile(s)) return wgrad_tile_partial_floats(s);
   int tiles = s.taps * (s.cin / 64) * (s.cout / 64);
   if (s.cin % 128 == 0 && s.cout % 128 == 0) tiles = s.taps * (s.cin / 128) * (s.cout / 128);
   long E = (long)s.cout * s.taps * s.cin;
@@ -1670,6 +1715,15 @@ hipError_t conv_wgrad_mfma(const void* x, const void* dz, float* dw, float* part
                            ReduceJob* defer) {
   if (use_wgrad_rows(s)) return conv_wgrad_rows_launch(x, dz, dw, partial, s, st, extra, defer);
   long E = (long)s.cout * s.taps * s.cin;
+  if (use_wgrad_tile(s)) {
+    ReduceJob job;
+    ReduceJob* const jp = defer ? defer : &job;
+    const hipError_t e = conv_wgrad_tile_launch(1, &x, &dz, &dw, &partial, s, st, &jp);
+    if (e != hipSuccess) return e;
+    if (defer) return extra ? hipErrorInvalidValue : hipSuccess;
+    if (job.S > 1) return splitk_reduce_launch(job.part, dw, E, job.S, st, extra);
+    return extra ? splitk_reduce_launch(extra->part, extra->out, extra->E, extra->S, st) : hipSuccess;
+  }
   WgradPlan pl;
   hipError_t e = launch_wgrad_mfma(1, &x, &dz, &dw, &partial, s, pl, st);
   if (e != hipSuccess) return e;
@@ -1753,6 +1807,7 @@ hipError_t conv_forward_mfma_n(int n, const void* const* x, const void* w, const
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
   const FwdPlan pl = fwd_plan(s);
   if (pl.cfg == 150) return launch_1x1_res(n, x, (const bf16_t*)w, b, y, s, relu, st);
+  if (pl.cfg >= 500) return launch_tile_cfg(pl.cfg, n, x, w, b, y, s, relu, st);
   if (pl.cfg >= 400) {
     g_rows32_cfg = pl.cfg >= 401 ? pl.cfg - 401 : -1;
     const hipError_t e = conv_forward_rows32(n, x, w, b, y, s, relu, st);
@@ -1776,6 +1831,7 @@ hipError_t conv_wgrad_mfma_n(int n, const void* const* x, const void* const* dz,
                              hipStream_t st, ReduceJob* const* defer) {
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
   if (use_wgrad_rows(s)) return conv_wgrad_rows_launch_n(n, x, dz, dw, part, s, st, defer);
+  if (use_wgrad_tile(s)) return conv_wgrad_tile_launch(n, x, dz, dw, part, s, st, defer);
   const long E = (long)s.cout * s.taps * s.cin;
   WgradPlan pl;
   float* pp[kMaxGroup];

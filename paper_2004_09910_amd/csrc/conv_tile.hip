@@ -1,0 +1,424 @@
+// bf16 3x3 convolution (forward, and data gradient on the rotated,
+// transposed weights) for any image size and any channel counts that are
+// multiples of 8, on 32 x 32 x 16 MFMA with rectangular pixel tiles and all
+// nine taps per stage.
+//
+// An output tile is BN output channels x (R rows x TW columns) of one sample.
+// R and TW are launch arguments: an image is cut into equal column strips and
+// row blocks so that a tile fills the kernel's pixel fragments as well as the
+// image allows.  The K loop runs over 16-channel chunks of the input; a stage
+// holds in LDS, for one chunk, the weights of all nine taps for the BN
+// channels (tap-major) and the R + 2 input rows of the tile, each as a block
+// of BWP LDS rows (TW + 2 rounded up to a multiple of 16, the first and last
+// pixel being the halo).  Every LDS row is 16 channels (32 bytes), its
+// 16-byte halves swapped when bit 3 of the row index is set: a fragment of 32
+// consecutive rows is then read without bank conflicts from any start row,
+// and a filter-row shift is a constant offset.  Pixels outside the image,
+// channels past Cin and output channels past Cout are buffer reads at
+// out-of-range offsets and hold zeros; the stores leave them out.
+//
+// What bounds it: operands into LDS and out of it.  Per tap a wave reads
+// MT + FW fragments of 1 KiB for MT FW MFMAs, so wide layers take MT = 2,
+// FW = 4 (128 channels x 512 pixels a block); few tiles or few channels take
+// the smaller tiles.  The sum of an output runs over (chunk, tap, channel) in
+// every configuration, so the choice does not change values and a
+// recomputation is bit-identical.
+#include "common.h"
+#include "kernels.h"
+#include "mfma_util.h"
+#include "prof.h"
+
+namespace tgpk {
+namespace {
+
+constexpr int CT_OOB = (int)0x80000000;   // byte offset that reads as out of range
+
+typedef __bf16 bf16x2_ct __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ unsigned pack2_ct(float a, float b) {
+  const bf16x2_ct h = {(__bf16)a, (__bf16)b};
+  return __builtin_bit_cast(unsigned, h);
+}
+
+// The micro-batches of one launch (nb samples each, the same weights); their
+// tiles share the persistent grid.  A larger group runs as launches of eight.
+constexpr int kTileGroup = 8;
+struct TileIo {
+  const bf16_t* x[kTileGroup];
+  bf16_t* y[kTileGroup];
+};
+// How an image is cut: R rows x TW columns a tile, BWP LDS rows per input
+// row, nrb row blocks and ns column strips; inv = ceil(2^20 / TW), invB =
+// ceil(2^20 / BWP) (exact quotients for a tile's pixels and a slot's rows).
+struct TileCut {
+  int R, TW, BWP, nrb, ns, inv, invB;
+};
+
+// WC x WP waves; a wave covers MT 32-channel tiles x FW pixel fragments.  LW
+// is the DMA instructions of a wave per stage (1 KiB each), which fixes the
+// slot size; chunks past the stage's rows read zeros.
+template <int MT, int WC, int WP, int FW, int LW, int NS>
+__global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
+    TileIo io, int ng, const bf16_t* __restrict__ Wt, const float* __restrict__ bias, int nb,
+    int H, int W, int Cin, int Cout, int relu, TileCut cut) {
+  constexpr int NW = WC * WP;
+  constexpr int BN = 32 * MT * WC;
+  constexpr int AR = 9 * BN;                                    // weight rows per stage
+  constexpr int ACH = AR / 32;                                  // ... in 1 KiB chunks
+  constexpr int SB = LW * NW * 1024;                            // slot bytes
+  static_assert(NS * SB + (NS + 1) * 1024 <= 160 * 1024, "LDS ring and bias slots");
+  static_assert(NW * 2048 * MT <= SB, "epilogue staging fits a slot");
+  __shared__ __attribute__((aligned(16))) unsigned char ring[NS * SB + (NS + 1) * 1024];
+  unsigned char* const bslots = ring + NS * SB;                 // BN bias values per tile in flight
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int pg = wave % WP, wc = wave / WP;                     // pixel group, channel group
+  const int R = cut.R, TW = cut.TW, BWP = cut.BWP;
+  const int nct = (Cout + BN - 1) / BN;
+  const int per_n = cut.nrb * cut.ns * nct;                     // tiles per sample
+  const int items = ng * nb * per_n;
+  const int G = gridDim.x;
+  const int lb = xcd_remap(blockIdx.x, G);
+  const int n_items = lb < items ? (items - lb + G - 1) / G : 0;
+  const int nk = (Cin + 15) / 16;                               // stages per tile
+  const int total = n_items * nk;
+
+  const int xbytes = nb * H * W * Cin * 2;                      // one micro-batch's input
+  const u32x4 rw = make_rsrc(Wt, Cout * 9 * Cin * 2);
+  const u32x4 rbias = make_rsrc(bias, bias ? Cout * 4 : 0);     // no bias reads zeros
+
+  // DMA: instruction u of this wave fills stage chunk k = NW u + wave; lane l
+  // the 16 bytes at + 16 l: row k * 32 + l / 2, physical half l % 2, which
+  // holds logical half lh (the same for every chunk of the lane).
+  const int lh = (lane & 1) ^ ((lane >> 4) & 1);
+  int doff[LW], drc[LW];                                        // byte offset; rr | wp << 16
+#pragma unroll
+  for (int u = 0; u < LW; ++u) {
+    const int k = NW * u + wave;
+    const int row = k * 32 + (lane >> 1);
+    if (k < ACH) {
+      const int tap = row / BN, co = row - tap * BN;
+      doff[u] = ((co * 9 + tap) * Cin + 8 * lh) * 2;
+      drc[u] = 0;
+    } else {
+      const int q = row - AR;
+      const int rr = (q * cut.invB) >> 20, wp = q - rr * BWP;   // q / BWP
+      const bool ok = rr < R + 2 && wp < TW + 2;
+      doff[u] = ok ? ((rr * W + wp - 1) * Cin + 8 * lh) * 2 : 0;
+      drc[u] = ok ? rr | (wp << 16) : -1;
+    }
+  }
+
+  // Fragment addresses (bytes within a stage).  A: weight row tap BN + 32 (MT
+  // wc + i) + l % 32 at logical half l / 32.  B: pixel tp of the tile at
+  // column tap s is LDS row rho BWP + w + s of the input region; filter row r
+  // adds r BWP rows.
+  const int abase = (wc * MT * 32 + (lane & 31)) * 32 +
+                    (((lane >> 5) ^ ((lane >> 3) & 1)) << 4);
+  int bq[FW][3];
+#pragma unroll
+  for (int j = 0; j < FW; ++j) {
+    int tp = (pg * FW + j) * 32 + (lane & 31);
+    tp = min(tp, R * TW - 1);                                   // clamped copy past the tile
+    const int rho = (tp * cut.inv) >> 20, w = tp - rho * TW;   // tp / TW
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      const int q = rho * BWP + w + s;
+      bq[j][s] = AR * 32 + q * 32 + (((lane >> 5) ^ ((q >> 3) & 1)) << 4);
+    }
+  }
+
+  // item -> micro-batch gi, its sample n, first row h0 and column w0, first
+  // output channel co0
+  auto coords = [&](int it, int& gi, int& n, int& h0, int& w0, int& co0)
+      __attribute__((always_inline)) {
+    const int item = lb + it * G;
+    const int smp = item / per_n;
+    int t = item - smp * per_n;
+    const int ct = t % nct;
+    t /= nct;
+    const int sx = t % cut.ns;
+    gi = smp / nb;
+    n = smp - gi * nb;
+    h0 = (t / cut.ns) * R;
+    w0 = sx * TW;
+    co0 = ct * BN;
+  };
+
+  int i_it = 0, i_ks = 0, i_gi = 0, i_n = 0, i_h0 = 0, i_w0 = 0, i_co0 = 0;
+  if (total > 0) coords(0, i_gi, i_n, i_h0, i_w0, i_co0);
+  u32x4 rxg = make_rsrc(pickg(io.x, i_gi), xbytes);            // the issuing item's input
+  auto issue_part = [&](int slot, int u0, int u1) __attribute__((always_inline)) {
+    const int c0 = i_ks * 16;
+    const int soff_a = (i_co0 * 9 * Cin + c0) * 2;
+    const int hb = i_h0 - 1;                                    // input row of block row 0
+    const int base_b = (((i_n * H + hb) * W + i_w0) * Cin + c0) * 2;   // negative for hb = -1
+    const bool cok = c0 + 8 * lh < Cin;                         // the last chunk may hold 8 channels
+    // the tile's bias values, ahead of its first stage (whose wait covers
+    // them): a load in the epilogue would wait for the DMA in flight, and
+    // held in registers they spill the widest configuration
+    if (u0 == 0 && i_ks == 0 && wave == 0)
+      dma16(rbias, TGP_LDS(bslots + (i_it % (NS + 1)) * 1024),
+            lane < BN / 4 ? (i_co0 + 4 * lane) * 4 : CT_OOB, 0);
+#pragma unroll
+    for (int u = 0; u < LW; ++u) {
+      if (u < u0 || u >= u1) continue;
+      const int k = NW * u + wave;
+      auto* dst = TGP_LDS(ring + slot * SB + k * 1024);
+      if (k < ACH) {                                            // wave-uniform
+        dma16(rw, dst, cok ? doff[u] : CT_OOB, cok ? soff_a : 0);
+      } else {
+        const int rr = drc[u] & 0xffff, col = i_w0 + (drc[u] >> 16) - 1;
+        const bool ok = drc[u] >= 0 && cok && (unsigned)(hb + rr) < (unsigned)H &&
+                        (unsigned)col < (unsigned)W;
+        dma16(rxg, dst, ok ? base_b + doff[u] : CT_OOB, 0);
+      }
+    }
+  };
+  auto issue_done = [&]() __attribute__((always_inline)) {
+    if (++i_ks == nk) {
+      i_ks = 0;
+      if (++i_it < n_items) {
+        coords(i_it, i_gi, i_n, i_h0, i_w0, i_co0);
+        rxg = make_rsrc(pickg(io.x, i_gi), xbytes);
+      }
+    }
+  };
+
+#pragma unroll
+  for (int k = 0; k < NS - 1; ++k)
+    if (k < total) {
+      issue_part(k, 0, LW);
+      issue_done();
+    }
+
+  int idx = 0;
+  for (int c_it = 0; c_it < n_items; ++c_it) {
+    int gi, n, h0, w0, co0;
+    coords(c_it, gi, n, h0, w0, co0);
+    f32x16_t acc[MT][FW];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < FW; ++j) acc[i][j] = f32x16_t{};
+
+    for (int ks = 0; ks < nk; ++ks, ++idx) {
+      // loads complete in order: stage idx is in once at most the stages
+      // issued after it are pending (epilogue stores only lengthen the wait)
+      wait_stages<NS, LW>(min(NS - 2, total - 1 - idx));
+      ring_barrier();
+      const bool fill = idx + NS - 1 < total;                   // refill the slot freed last stage
+      const int fslot = (idx + NS - 1) % NS;
+      const unsigned char* st = ring + (idx % NS) * SB;
+      // nine taps; tap t + 1's fragments are read while tap t's MFMAs run
+      bf16x8_t fa[2][MT], fb[2][FW];
+      auto load = [&](int t, int buf) __attribute__((always_inline)) {
+        const int r = t / 3, s = t - 3 * (t / 3);
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+          fa[buf][i] = as_bf16x8(*(const u32x4*)(st + abase + (t * BN + 32 * i) * 32));
+#pragma unroll
+        for (int j = 0; j < FW; ++j)
+          fb[buf][j] = as_bf16x8(*(const u32x4*)(st + bq[j][s] + r * BWP * 32));
+      };
+      load(0, 0);
+      constexpr int NQ = MT * FW;                               // MFMAs per tap
+#pragma unroll
+      for (int t = 0; t < 9; ++t) {
+        // reads for tap t + 1, half of tap t's MFMAs, this tap's share of the
+        // next stage's DMA, the other half of the MFMAs
+        if (t + 1 < 9) load(t + 1, (t + 1) & 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+          if (q < (NQ + 1) / 2)
+            acc[q % MT][q / MT] = mfma32(fa[t & 1][q % MT], fb[t & 1][q / MT], acc[q % MT][q / MT]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (fill) issue_part(fslot, t * LW / 9, (t + 1) * LW / 9);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+          if (q >= (NQ + 1) / 2)
+            acc[q % MT][q / MT] = mfma32(fa[t & 1][q % MT], fb[t & 1][q / MT], acc[q % MT][q / MT]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (fill) issue_done();
+    }
+
+    // Epilogue, staged through LDS so that every store writes whole runs of
+    // one pixel's channels.  The slot of the stage just consumed is free once
+    // every wave is past its last reads; its refill is issued only after the
+    // next stage's barrier.  Per fragment each wave uses its own 32 pixel rows
+    // of 32 MT channels, 16-byte chunk c of row p at position c ^ (p % NCK).
+    // Element v of lane l of acc[i][j] is channel 32 i + 8 (v / 4) + 4 (l /
+    // 32) + v % 4 of pixel l % 32.
+    ring_barrier();
+    constexpr int ROWB = 64 * MT;                               // staged bytes per pixel
+    constexpr int NCK = 4 * MT;                                 // 16-byte chunks per pixel
+    constexpr int PPI = 64 / NCK;                               // pixels per read
+    unsigned char* ep = ring + ((idx - 1) % NS) * SB + wave * 32 * ROWB;
+    const unsigned char* bl =
+        bslots + (c_it % (NS + 1)) * 1024 + (32 * MT * wc + 4 * (lane >> 5)) * 4;
+    bf16_t* const Yg = pickg(io.y, gi);
+    const int pw = lane & 31, hw = lane >> 5;
+#pragma unroll
+    for (int j = 0; j < FW; ++j) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x4_t bv = *(const f32x4_t*)(bl + (32 * i + 8 * g) * 4);
+          float v[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            v[e] = acc[i][j][4 * g + e] + bv[e];
+            if (relu) v[e] = fmaxf(v[e], 0.0f);
+          }
+          uint2 o;
+          o.x = pack2_ct(v[0], v[1]);
+          o.y = pack2_ct(v[2], v[3]);
+          *(uint2*)(ep + pw * ROWB + (((4 * i + g) ^ (pw & (NCK - 1))) << 4) + 8 * hw) = o;
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 32 / PPI; ++q) {
+        const int p = lane / NCK + PPI * q, c = lane % NCK;
+        const u32x4 val = *(const u32x4*)(ep + p * ROWB + ((c ^ (p & (NCK - 1))) << 4));
+        const int tp = (pg * FW + j) * 32 + p;
+        const int rho = (tp * cut.inv) >> 20, w = tp - rho * TW;   // tp / TW (tp < 1024)
+        const int co = co0 + wc * MT * 32 + 8 * c;
+        if (rho < R && h0 + rho < H && w0 + w < W && co < Cout)
+          *(u32x4*)(Yg + ((long)(n * H + h0 + rho) * W + w0 + w) * Cout + co) = val;
+      }
+    }
+  }
+}
+
+// Configurations, with what one round of blocks costs (measured in us: `a`
+// per tile and `b` per 16-channel stage; 128 channels at 56 x 56 and 256 at
+// 28 x 28, 32 samples).
+struct TileCfg { int MT, WC, WP, FW, LW, NS; double a, b; };
+constexpr TileCfg kTileCfgs[] = {
+    {2, 2, 4, 2, 7, 2, 4.8, 2.0},    // 128 channels x 256 pixels
+    {1, 2, 4, 4, 5, 3, 4.0, 1.94},   // 64 x 512
+    {1, 2, 4, 2, 4, 4, 1.5, 1.2},    // 64 x 256
+    {1, 2, 4, 1, 4, 4, 2.0, 0.8},    // 64 x 128
+    {1, 1, 8, 2, 4, 4, 2.4, 1.07},   // 32 x 512
+    {1, 1, 8, 1, 3, 4, 1.8, 0.69},   // 32 x 256
+    {1, 1, 4, 1, 5, 3, 1.5, 0.5},    // 32 x 128, four waves
+};
+constexpr int kTileN = sizeof(kTileCfgs) / sizeof(kTileCfgs[0]);
+// blocks of a configuration that a CU's 160 KiB of LDS hold
+constexpr int tile_occ(const TileCfg& k) {
+  return (k.NS * k.LW * k.WC * k.WP + k.NS + 1) * 2 <= 160 ? 2 : 1;
+}
+
+// The cut of an H x W image with the fewest tiles of at most px pixels whose
+// R + 2 input rows fit `rows` LDS rows (the widest strips of those).
+bool tile_cut(int H, int W, int px, int rows, TileCut& c) {
+  long best = 0;
+  for (int ns = 1; ns <= W; ++ns) {
+    const int TW = (W + ns - 1) / ns;
+    if (ns > 1 && TW < 8) break;
+    const int BWP = (TW + 2 + 15) / 16 * 16;
+    int R = px / TW;
+    if (R > rows / BWP - 2) R = rows / BWP - 2;
+    if (R > H) R = H;
+    if (R < 1) continue;
+    const int nrb = (H + R - 1) / R;
+    const long tiles = (long)nrb * ((W + TW - 1) / TW);
+    if (best == 0 || tiles < best) {
+      best = tiles;
+      R = (H + nrb - 1) / nrb;                    // even row blocks
+      c = TileCut{R, TW, BWP, nrb, (W + TW - 1) / TW, ((1 << 20) + TW - 1) / TW,
+                  ((1 << 20) + BWP - 1) / BWP};
+    }
+    if (TW <= 8) break;
+  }
+  return best > 0;
+}
+
+}  // namespace
+
+int g_tile_cfg = -1;   // >= 0 forces a configuration (tests and measurement)
+
+// Configuration for ng micro-batches of a shape: the least estimated time,
+// rounds of blocks times what a round costs.
+static int tile_pick(const ConvShape& s, int ng, TileCut& cut) {
+  int best = -1;
+  double best_cost = 0;
+  const int nk = (s.cin + 15) / 16;
+  for (int c = 0; c < kTileN; ++c) {
+    const TileCfg k = kTileCfgs[c];
+    if (g_tile_cfg >= 0 && g_tile_cfg != c) continue;
+    const int NW = k.WC * k.WP, BN = 32 * k.MT * k.WC;
+    TileCut t;
+    if (!tile_cut(s.H, s.W, 32 * k.WP * k.FW, k.LW * NW * 32 - 9 * BN, t)) continue;
+    const long items = (long)ng * s.nb * t.nrb * t.ns * ((s.cout + BN - 1) / BN);
+    const long rounds = (items + 255) / 256;
+    const double cost = rounds * (k.a + nk * k.b) / (rounds > 1 && tile_occ(k) > 1 ? 1.4 : 1.0);
+    if (best < 0 || cost < best_cost) {
+      best = c;
+      best_cost = cost;
+      cut = t;
+    }
+  }
+  return best;
+}
+
+bool conv_tile_ok(const ConvShape& s) {
+  return s.taps == 9 && s.cin % 8 == 0 && s.cout % 8 == 0 && s.pixels() > 0 &&
+         (double)s.pixels() * s.cin * 2 < 2147483648.0 &&
+         (double)s.cout * 9 * s.cin * 2 < 2147483648.0;
+}
+
+template <int MT, int WC, int WP, int FW, int LW, int NS>
+static hipError_t launch_tile(const TileIo& io, int ng, const bf16_t* Wt, const float* b,
+                              const ConvShape& s, int relu, const TileCut& cut, hipStream_t st) {
+  static char name[64];
+  if (!name[0]) snprintf(name, sizeof name, "conv3x3_tile<%d,%d,%d,%d,%d,%d>", MT, WC, WP, FW, LW, NS);
+  constexpr int BN = 32 * MT * WC, NW = WC * WP;
+  const long items = (long)ng * s.nb * cut.nrb * cut.ns * ((s.cout + BN - 1) / BN);
+  constexpr int occ = tile_occ(TileCfg{MT, WC, WP, FW, LW, NS, 0, 0});
+  const int G = (int)(items < 256 * occ ? items : 256 * occ);
+  const long P = (long)ng * s.pixels();
+  ProfScope ps(name, 2.0 * P * s.cout * 9 * s.cin,
+               2.0 * ((double)P * s.cin + 9.0 * s.cin * s.cout + (double)P * s.cout), st);
+  TGP_LAUNCH(ps, (conv3x3_tile<MT, WC, WP, FW, LW, NS>), dim3(G), dim3(NW * 64), 0, st, io, ng, Wt,
+             b, s.nb, s.H, s.W, s.cin, s.cout, relu, cut);
+  return launch_status();
+}
+
+hipError_t conv_forward_tile(int n, const void* const* x, const void* w, const float* b,
+                             void* const* y, const ConvShape& s, int relu, hipStream_t st) {
+  if (n < 1 || n > kMaxGroup || !conv_tile_ok(s)) return hipErrorInvalidValue;
+  if (n > kTileGroup) {
+    for (int k0 = 0; k0 < n; k0 += kTileGroup) {
+      const int c = n - k0 < kTileGroup ? n - k0 : kTileGroup;
+      const hipError_t e = conv_forward_tile(c, x + k0, w, b, y + k0, s, relu, st);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  TileCut cut{};
+  const int c = tile_pick(s, n, cut);
+  if (c < 0) return hipErrorInvalidValue;
+  TileIo io{};
+  for (int k = 0; k < kTileGroup; ++k) {   // unused entries repeat micro-batch 0
+    io.x[k] = (const bf16_t*)x[k < n ? k : 0];
+    io.y[k] = (bf16_t*)y[k < n ? k : 0];
+    if (!io.x[k] || !io.y[k]) return hipErrorInvalidValue;
+  }
+  const bf16_t* Wt = (const bf16_t*)w;
+  switch (c) {
+#define CT_CASE(i)                                                                          \
+  case i:                                                                                   \
+    return launch_tile<kTileCfgs[i].MT, kTileCfgs[i].WC, kTileCfgs[i].WP, kTileCfgs[i].FW,  \
+                       kTileCfgs[i].LW, kTileCfgs[i].NS>(io, n, Wt, b, s, relu, cut, st);
+    CT_CASE(0) CT_CASE(1) CT_CASE(2) CT_CASE(3) CT_CASE(4) CT_CASE(5) CT_CASE(6)
+#undef CT_CASE
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace tgpk

@@ -9,7 +9,8 @@
 
 namespace tgpk {
 
-bool mfma_conv_ok(int dt, int cin, int cout);
+bool mfma_fwd_ok(int dt, const ConvShape& s);
+bool mfma_wgrad_ok(int dt, const ConvShape& s);
 hipError_t conv_forward_mfma(const void* x, const void* w, const float* b, void* y,
                              const ConvShape& s, int relu, float* part, size_t part_cap,
                              hipStream_t st);
@@ -1060,7 +1061,7 @@ static bool small1x1_ok(int dt, const ConvShape& s, const void* x) {
 hipError_t conv_forward(int dt, const void* x, const void* w, const float* b, void* y,
                         const ConvShape& s, int relu, float* part, size_t part_cap,
                         hipStream_t st) {
-  if (mfma_conv_ok(dt, s.cin, s.cout))
+  if (mfma_fwd_ok(dt, s))
     return conv_forward_mfma(x, w, b, y, s, relu, part, part_cap, st);
   if (small1x1_ok(dt, s, x)) {
     const long P = s.pixels();
@@ -1088,7 +1089,9 @@ hipError_t conv_forward(int dt, const void* x, const void* w, const float* b, vo
   return launch_status();
 }
 
-bool conv_dgrad_uses_wt(int dt, const ConvShape& s) { return mfma_conv_ok(dt, s.cout, s.cin); }
+bool conv_dgrad_uses_wt(int dt, const ConvShape& s) {
+  return mfma_fwd_ok(dt, ConvShape{s.nb, s.H, s.W, s.cout, s.cin, s.taps});
+}
 
 hipError_t conv_dgrad(int dt, const void* dz, const void* w, const void* wt, void* dx,
                       const ConvShape& s, float* part, size_t part_cap, hipStream_t st) {
@@ -1114,7 +1117,7 @@ hipError_t conv_dgrad(int dt, const void* dz, const void* w, const void* wt, voi
 }
 
 size_t conv_wgrad_partial_floats(int dt, const ConvShape& s) {
-  if (mfma_conv_ok(dt, s.cin, s.cout)) return wgrad_mfma_partial_floats(s);
+  if (mfma_wgrad_ok(dt, s)) return wgrad_mfma_partial_floats(s);
   const int N = dt == 0 ? 8 : 4;
   if (small1x1_ok(dt, s, (const void*)16)) {   // (alignment is checked per call)
     const size_t direct = (size_t)direct_wgrad_splits(s.pixels()) * s.cout * s.taps * s.cin;
@@ -1128,7 +1131,7 @@ hipError_t conv_wgrad(int dt, const void* x, const void* dz, float* dw, float* p
                       const ConvShape& s, hipStream_t st, const ReduceJob* extra,
                       ReduceJob* defer) {
   if (defer && extra) return hipErrorInvalidValue;
-  if (mfma_conv_ok(dt, s.cin, s.cout))
+  if (mfma_wgrad_ok(dt, s))
     return conv_wgrad_mfma(x, dz, dw, partial, s, st, extra, defer);
   if (small1x1_ok(dt, s, x)) {
     const long P = s.pixels(), E = (long)s.cout * s.cin;
@@ -1180,7 +1183,7 @@ hipError_t conv_forward_n(int dt, int n, const void* const* x, const void* w, co
                           void* const* y, const ConvShape& s, int relu, float* const* part,
                           size_t part_cap, hipStream_t st) {
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
-  if (mfma_conv_ok(dt, s.cin, s.cout))
+  if (mfma_fwd_ok(dt, s))
     return conv_forward_mfma_n(n, x, w, b, y, s, relu, part, part_cap, st);
   for (int k = 0; k < n; ++k) {
     const hipError_t e = conv_forward(dt, x[k], w, b, y[k], s, relu, part[k], part_cap, st);
@@ -1213,7 +1216,7 @@ hipError_t conv_wgrad_n(int dt, int n, const void* const* x, const void* const* 
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
   for (int k = 0; k < n; ++k)
     if (!defer[k]) return hipErrorInvalidValue;
-  if (mfma_conv_ok(dt, s.cin, s.cout)) return conv_wgrad_mfma_n(n, x, dz, dw, part, s, st, defer);
+  if (mfma_wgrad_ok(dt, s)) return conv_wgrad_mfma_n(n, x, dz, dw, part, s, st, defer);
   for (int k = 0; k < n; ++k) {
     const hipError_t e = conv_wgrad(dt, x[k], dz[k], dw[k], part[k], s, st, nullptr, defer[k]);
     if (e != hipSuccess) return e;

@@ -42,6 +42,12 @@ int conv_rows32_tiles(const ConvShape& s);
 bool conv_rows32_ok(const ConvShape& s);
 hipError_t conv_forward_rows32(int n, const void* const* x, const void* w, const float* b,
                                void* const* y, const ConvShape& s, int relu, hipStream_t st);
+// 32x32x16-MFMA 3x3 convolution on rectangular tiles (bf16; any image size,
+// Cin and Cout multiples of 8), same contract.
+bool conv_tile_ok(const ConvShape& s);
+hipError_t conv_forward_tile(int n, const void* const* x, const void* w, const float* b,
+                             void* const* y, const ConvShape& s, int relu, hipStream_t st);
+extern int g_tile_cfg;
 extern int g_rows32_cfg;
 extern int g_rows32_ch;
 extern int g_wgrad_ks;
@@ -72,6 +78,13 @@ hipError_t conv_wgrad_rows_launch(const void* x, const void* dz, float* dw, floa
 hipError_t conv_wgrad_rows_launch_n(int n, const void* const* x, const void* const* dz,
                                     float* const* dw, float* const* partial, const ConvShape& s,
                                     hipStream_t st, ReduceJob* const* defer);
+// The same weight gradient for any image size and channel counts that are
+// multiples of 8, same contracts.
+bool wgrad_tile_ok(const ConvShape& s);
+size_t wgrad_tile_partial_floats(const ConvShape& s);
+hipError_t conv_wgrad_tile_launch(int n, const void* const* x, const void* const* dz,
+                                  float* const* dw, float* const* partial, const ConvShape& s,
+                                  hipStream_t st, ReduceJob* const* defer);
 
 // Whether the data-gradient kernel for this shape reads the transformed
 // weight wt = [cin][taps][cout] (taps rotated by 180 degrees).

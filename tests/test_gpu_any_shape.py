@@ -1,0 +1,95 @@
+"""Kernels for shapes outside the fixed tables: image sizes and channel
+counts of any kind, single layers against the oracle (2e-2 max-rel in bf16,
+1e-4 in fp32, as every single-layer run), at the sizes where a tile, a strip
+or a chunk ends."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2004_09910_amd as tgp
+from gpu_util import check_stage, gpu_stage, oracle_stage, say
+from paper_2004_09910_amd.harness import Session
+from workloads import specs
+from workloads.specs import BF16, CONV3X3, Layer, Net
+from workloads.synth import NORMAL
+
+pytestmark = pytest.mark.gpu
+
+
+def one_layer(L, h, w):
+    return Net("one", (L,), L.cin, h, w)
+
+
+def run_and_check(L, h, w, dtype, B, m, what, **kw):
+    say(what)
+    net = one_layer(L, h, w)
+    got = gpu_stage(net, dtype, B, m, 0, (1,), 1, **kw)
+    ref = oracle_stage(net, dtype, 0, 1, got["xv"], got["G"])
+    check_stage(got, ref, dtype, what, NORMAL)
+    got["sess"].close()
+    return got
+
+
+@pytest.mark.parametrize("cin,cout,h,w,B,m", [
+    (8, 8, 1, 1, 1, 1),          # one pixel, half a 16-channel chunk
+    (24, 40, 17, 33, 4, 2),      # a last chunk of 8 channels, ragged units
+    (72, 136, 13, 9, 2, 1),      # past one 64-channel item and one 128-channel tile
+    (16, 8, 3, 130, 2, 2),       # column strips
+    (40, 64, 2, 600, 1, 1),      # many strips, two rows
+    (64, 64, 57, 56, 4, 2),      # 64-multiples at a width of no table
+    (64, 192, 40, 61, 12, 2),    # the rectangular-stage weight gradient, odd units
+    (264, 16, 7, 7, 2, 2),       # many chunks, few pixels
+])
+def test_conv3x3_any_shape(cin, cout, h, w, B, m):
+    run_and_check(Layer(CONV3X3, cin, cout), h, w, BF16, B, m,
+                  f"conv3x3 {cin}->{cout} @{h}x{w} B={B} m={m}")
+
+
+@pytest.mark.parametrize("cfg", range(7))
+def test_conv3x3_tile_configurations(cfg):
+    """Each configuration of the rectangular-tile kernel, forced, with ragged
+    tiles on both sides; all sum in one order, so their bits agree."""
+    net = one_layer(Layer(CONV3X3, 40, 72), 21, 37)
+    base = gpu_stage(net, BF16, 2, 1, 0, (1,), 1)
+    tgp.debug_set_fwd_variant(501 + cfg)
+    try:
+        got = run_and_check(Layer(CONV3X3, 40, 72), 21, 37, BF16, 2, 1, f"tile cfg {cfg}")
+    finally:
+        tgp.debug_set_fwd_variant(0)
+    assert torch.equal(got["y"], base["y"]) and torch.equal(got["dx"], base["dx"])
+
+
+def test_conv3x3_any_shape_groups_are_bitwise():
+    """A group of nine micro-batches (launches of eight and one) gives the
+    bits of one micro-batch per launch."""
+    net = one_layer(Layer(CONV3X3, 48, 80), 19, 23)
+    one = gpu_stage(net, BF16, 9, 9, 0, (1,), 1)
+    grp = gpu_stage(net, BF16, 9, 9, 0, (1,), 1, lanes=9, group=9, serial=True)
+    assert torch.equal(one["y"], grp["y"]) and torch.equal(one["dx"], grp["dx"])
+    for a, b in zip(one["grads"][0], grp["grads"][0]):
+        np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("h,w", [(45, 61), (10, 20), (7, 33)])
+def test_wgrad_padding_keeps_infinities_apart(h, w):
+    """Input pixels of the last row and column pair with no output at filter
+    row 0 / column 0: an infinity there must not reach those taps through the
+    stage's zero padding."""
+    net = one_layer(Layer(CONV3X3, 64, 128, relu=False), h, w)
+    sess = Session(net, BF16)
+    sess.plan(3, 1, specs.CKPT_NEVER)
+    torch.manual_seed(3)
+    x = torch.randn(3, h, w, 64, device="cuda").bfloat16()
+    dy = torch.randn(3, h, w, 128, device="cuda").bfloat16()
+    y = torch.empty_like(dy)
+    out = []
+    for v in (0.0, float("inf")):
+        x[:, -1, :, 5] = v
+        x[:, :, -1, 5] = v
+        sess.stage_step(1, x, y, dy, None, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        out.append(sess.params[0]["dw"].clone())          # cout, kh, kw, cin
+    assert torch.equal(out[0][:, 0, 0, 5], out[1][:, 0, 0, 5])
+    assert torch.equal(out[0][..., :5], out[1][..., :5])
+    assert not torch.isfinite(out[1][:, 2, 2, 5]).any()
+    sess.close()
