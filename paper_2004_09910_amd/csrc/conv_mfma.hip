@@ -1543,11 +1543,27 @@ FwdPlan fwd_plan(const ConvShape& s) {
 // The rectangular-tile kernel, in the configuration a forced plan names.
 static hipError_t launch_tile_cfg(int cfg, int n, const void* const* x, const void* w,
                                   const float* b, void* const* y, const ConvShape& s, int relu,
-                                  hipStream_t st) {
+                                  bool dg, hipStream_t st) {
   g_tile_cfg = cfg >= 501 ? cfg - 501 : -1;
-  const hipError_t e = conv_forward_tile(n, x, w, b, y, s, relu, st);
+  const hipError_t e = conv_forward_tile(n, x, w, b, y, s, relu, dg, st);
   g_tile_cfg = -1;
   return e;
+}
+
+// Whether a shape's data gradient (t: its transposed shape) runs on the
+// rectangular-tile kernel, which reads the forward weights, and that launch
+// (also where a forced plan names another kernel but no transformed weights
+// were planned for).
+bool conv_dgrad_tile_planned(const ConvShape& t) {
+  t_in_dgrad = 1;
+  const bool r = fwd_plan(t).cfg >= 500;
+  t_in_dgrad = 0;
+  return r;
+}
+hipError_t conv_dgrad_tile(int n, const void* const* dz, const void* w, void* const* dx,
+                           const ConvShape& t, hipStream_t st) {
+  return launch_tile_cfg(g_fwd_variant >= 500 ? g_fwd_variant : 500, n, dz, w, nullptr, dx, t, 0,
+                         true, st);
 }
 
 size_t conv_forward_partial_floats(int dt, const ConvShape& s) {
@@ -1569,7 +1585,7 @@ hipError_t conv_forward_mfma(const void* x, const void* w, const float* b, void*
   const FwdPlan pl = fwd_plan(s);
   const bool wide = s.cout % 128 == 0;
   if (pl.cfg == 150) return launch_1x1_res(1, &x, Wt, b, &y, s, relu, st);
-  if (pl.cfg >= 500) return launch_tile_cfg(pl.cfg, 1, &x, w, b, &y, s, relu, st);
+  if (pl.cfg >= 500) return launch_tile_cfg(pl.cfg, 1, &x, w, b, &y, s, relu, false, st);
   if (pl.cfg >= 400) {
     g_rows32_cfg = pl.cfg >= 401 ? pl.cfg - 401 : -1;
     const hipError_t e = conv_forward_rows32(1, &x, w, b, &y, s, relu, st);
@@ -1635,6 +1651,15 @@ hipError_t weight_transform_batch(int dt, WtBatch b, hipStream_t st) {
 // Bit 2 of g_rowtile_mask selects the row-blocked weight-gradient kernel.
 static bool use_wgrad_rows(const ConvShape& s) {
   return (g_rowtile_mask >> 2 & 1) && wgrad_rows_ok(s);
+}
+
+// Split count of the general weight gradients (per-tap, or direct where the
+// channels are no multiples of 64): what a plan's slices may take.
+int wgrad_general_splits(const ConvShape& s) {
+  if (s.cin % 64 || s.cout % 64) return direct_wgrad_splits(s.pixels());
+  const int t = s.cin % 128 == 0 && s.cout % 128 == 0 ? 128 : 64;
+  return wgrad_plan<2, 2>(s.pixels(), s.taps * (s.cin / t) * (s.cout / t),
+                          (long)s.cout * s.taps * s.cin).S;
 }
 
 // 3x3 layers of no fixed width: the rectangular-stage kernel.  Where the
@@ -1807,7 +1832,7 @@ hipError_t conv_forward_mfma_n(int n, const void* const* x, const void* w, const
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
   const FwdPlan pl = fwd_plan(s);
   if (pl.cfg == 150) return launch_1x1_res(n, x, (const bf16_t*)w, b, y, s, relu, st);
-  if (pl.cfg >= 500) return launch_tile_cfg(pl.cfg, n, x, w, b, y, s, relu, st);
+  if (pl.cfg >= 500) return launch_tile_cfg(pl.cfg, n, x, w, b, y, s, relu, false, st);
   if (pl.cfg >= 400) {
     g_rows32_cfg = pl.cfg >= 401 ? pl.cfg - 401 : -1;
     const hipError_t e = conv_forward_rows32(n, x, w, b, y, s, relu, st);

@@ -1,7 +1,6 @@
-// bf16 3x3 convolution (forward, and data gradient on the rotated,
-// transposed weights) for any image size and any channel counts that are
-// multiples of 8, on 32 x 32 x 16 MFMA with rectangular pixel tiles and all
-// nine taps per stage.
+// bf16 3x3 convolution (forward and data gradient) for any image size and any
+// channel counts that are multiples of 8, on 32 x 32 x 16 MFMA with
+// rectangular pixel tiles and all nine taps per stage.
 //
 // An output tile is BN output channels x (R rows x TW columns) of one sample.
 // R and TW are launch arguments: an image is cut into equal column strips and
@@ -16,6 +15,13 @@
 // and a filter-row shift is a constant offset.  Pixels outside the image,
 // channels past Cin and output channels past Cout are buffer reads at
 // out-of-range offsets and hold zeros; the stores leave them out.
+//
+// The data gradient (DG) is the same sum with the filter rotated and its
+// channels exchanged.  It reads the forward weights as they are: a stage's
+// weights are then rows of BN channels for each (tap, sum channel), and the
+// transpose loads gather a fragment's sum channels from them.  So no
+// transposed copy of the weights is made or kept (64 -> 64 channels at 56 x
+// 56, one sample: one launch of 4 us less of a step of 32).
 //
 // What bounds it: operands into LDS and out of it.  Per tap a wave reads
 // MT + FW fragments of 1 KiB for MT FW MFMAs, so wide layers take MT = 2,
@@ -32,6 +38,14 @@ namespace tgpk {
 namespace {
 
 constexpr int CT_OOB = (int)0x80000000;   // byte offset that reads as out of range
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+// Transpose read: within each group of 16 lanes, lane i receives element
+// i % 4 of the 8-byte blocks addressed by lanes 4 e + i / 4, e = 0..3.
+__device__ __forceinline__ uint2 tr16c(const unsigned char* p) {
+  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)TGP_LDS(p)));
+}
 
 typedef __bf16 bf16x2_ct __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ unsigned pack2_ct(float a, float b) {
@@ -56,7 +70,7 @@ struct TileCut {
 // WC x WP waves; a wave covers MT 32-channel tiles x FW pixel fragments.  LW
 // is the DMA instructions of a wave per stage (1 KiB each), which fixes the
 // slot size; chunks past the stage's rows read zeros.
-template <int MT, int WC, int WP, int FW, int LW, int NS>
+template <int MT, int WC, int WP, int FW, int LW, int NS, bool DG>
 __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
     TileIo io, int ng, const bf16_t* __restrict__ Wt, const float* __restrict__ bias, int nb,
     int H, int W, int Cin, int Cout, int relu, TileCut cut) {
@@ -84,6 +98,10 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
   const int total = n_items * nk;
 
   const int xbytes = nb * H * W * Cin * 2;                      // one micro-batch's input
+  constexpr int RAB = 2 * BN;                                   // (DG) bytes of a weight row
+  constexpr int RPC = 1024 / RAB;                               // ... rows per 1 KiB chunk
+  // swizzle of a weight row's 16-byte chunks, for rows of 128 bytes and more
+  auto wswz = [](int row) __attribute__((always_inline)) { return BN >= 64 ? 2 * (row & 3) : 0; };
   const u32x4 rw = make_rsrc(Wt, Cout * 9 * Cin * 2);
   const u32x4 rbias = make_rsrc(bias, bias ? Cout * 4 : 0);     // no bias reads zeros
 
@@ -96,7 +114,14 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
   for (int u = 0; u < LW; ++u) {
     const int k = NW * u + wave;
     const int row = k * 32 + (lane >> 1);
-    if (k < ACH) {
+    if (k < ACH && DG) {
+      // weight row (tap, sum channel kk) of the rotated filter
+      const int wr = k * RPC + lane / (64 / RPC);
+      const int tap = wr / 16, kk = wr - 16 * tap;
+      const int lc = lane % (64 / RPC) ^ wswz(wr);
+      doff[u] = ((kk * 9 + 8 - tap) * Cout + 8 * lc) * 2;
+      drc[u] = kk | (lc << 16);
+    } else if (k < ACH) {
       const int tap = row / BN, co = row - tap * BN;
       doff[u] = ((co * 9 + tap) * Cin + 8 * lh) * 2;
       drc[u] = 0;
@@ -113,8 +138,20 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
   // wc + i) + l % 32 at logical half l / 32.  B: pixel tp of the tile at
   // column tap s is LDS row rho BWP + w + s of the input region; filter row r
   // adds r BWP rows.
-  const int abase = (wc * MT * 32 + (lane & 31)) * 32 +
-                    (((lane >> 5) ^ ((lane >> 3) & 1)) << 4);
+  // (DG: lane group g = lane / 16 holds channels 16 (g % 2) .. + 15 and sum
+  // channels 8 (g / 2) .. + 7; lane j of it addresses row j / 4, channels 4 (j
+  // % 4) .. + 3 of the block of 16.)
+  const int kb = 8 * (lane >> 5) + ((lane & 15) >> 2);
+  int abase[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+    if constexpr (DG) {
+      const int cb = ((wc * MT + i) * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
+      abase[i] = kb * RAB + (((cb >> 4) ^ wswz(kb)) << 4) + (cb & 15);
+    } else {
+      abase[i] = ((wc * MT + i) * 32 + (lane & 31)) * 32 + (((lane >> 5) ^ ((lane >> 3) & 1)) << 4);
+    }
+  }
   int bq[FW][3];
 #pragma unroll
   for (int j = 0; j < FW; ++j) {
@@ -150,7 +187,7 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
   u32x4 rxg = make_rsrc(pickg(io.x, i_gi), xbytes);            // the issuing item's input
   auto issue_part = [&](int slot, int u0, int u1) __attribute__((always_inline)) {
     const int c0 = i_ks * 16;
-    const int soff_a = (i_co0 * 9 * Cin + c0) * 2;
+    const int soff_a = DG ? (c0 * 9 * Cout + i_co0) * 2 : (i_co0 * 9 * Cin + c0) * 2;
     const int hb = i_h0 - 1;                                    // input row of block row 0
     const int base_b = (((i_n * H + hb) * W + i_w0) * Cin + c0) * 2;   // negative for hb = -1
     const bool cok = c0 + 8 * lh < Cin;                         // the last chunk may hold 8 channels
@@ -166,7 +203,8 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
       const int k = NW * u + wave;
       auto* dst = TGP_LDS(ring + slot * SB + k * 1024);
       if (k < ACH) {                                            // wave-uniform
-        dma16(rw, dst, cok ? doff[u] : CT_OOB, cok ? soff_a : 0);
+        const bool wok = DG ? c0 + (drc[u] & 0xffff) < Cin && i_co0 + 8 * (drc[u] >> 16) < Cout : cok;
+        dma16(rw, dst, wok ? doff[u] + soff_a : CT_OOB, 0);
       } else {
         const int rr = drc[u] & 0xffff, col = i_w0 + (drc[u] >> 16) - 1;
         const bool ok = drc[u] >= 0 && cok && (unsigned)(hb + rr) < (unsigned)H &&
@@ -216,7 +254,13 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
         const int r = t / 3, s = t - 3 * (t / 3);
 #pragma unroll
         for (int i = 0; i < MT; ++i)
-          fa[buf][i] = as_bf16x8(*(const u32x4*)(st + abase + (t * BN + 32 * i) * 32));
+          if constexpr (DG) {
+            const unsigned char* pa = st + abase[i] + t * 16 * RAB;
+            const uint2 lo = tr16c(pa), hi = tr16c(pa + 4 * RAB);
+            fa[buf][i] = as_bf16x8(u32x4{lo.x, lo.y, hi.x, hi.y});
+          } else {
+            fa[buf][i] = as_bf16x8(*(const u32x4*)(st + abase[i] + t * BN * 32));
+          }
 #pragma unroll
         for (int j = 0; j < FW; ++j)
           fb[buf][j] = as_bf16x8(*(const u32x4*)(st + bq[j][s] + r * BWP * 32));
@@ -372,11 +416,11 @@ bool conv_tile_ok(const ConvShape& s) {
          (double)s.cout * 9 * s.cin * 2 < 2147483648.0;
 }
 
-template <int MT, int WC, int WP, int FW, int LW, int NS>
+template <int MT, int WC, int WP, int FW, int LW, int NS, bool DG>
 static hipError_t launch_tile(const TileIo& io, int ng, const bf16_t* Wt, const float* b,
                               const ConvShape& s, int relu, const TileCut& cut, hipStream_t st) {
   static char name[64];
-  if (!name[0]) snprintf(name, sizeof name, "conv3x3_tile<%d,%d,%d,%d,%d,%d>", MT, WC, WP, FW, LW, NS);
+  if (!name[0]) snprintf(name, sizeof name, "conv3x3_tile<%d,%d,%d,%d,%d,%d%s>", MT, WC, WP, FW, LW, NS, DG ? ",dg" : "");
   constexpr int BN = 32 * MT * WC, NW = WC * WP;
   const long items = (long)ng * s.nb * cut.nrb * cut.ns * ((s.cout + BN - 1) / BN);
   constexpr int occ = tile_occ(TileCfg{MT, WC, WP, FW, LW, NS, 0, 0});
@@ -384,18 +428,22 @@ static hipError_t launch_tile(const TileIo& io, int ng, const bf16_t* Wt, const 
   const long P = (long)ng * s.pixels();
   ProfScope ps(name, 2.0 * P * s.cout * 9 * s.cin,
                2.0 * ((double)P * s.cin + 9.0 * s.cin * s.cout + (double)P * s.cout), st);
-  TGP_LAUNCH(ps, (conv3x3_tile<MT, WC, WP, FW, LW, NS>), dim3(G), dim3(NW * 64), 0, st, io, ng, Wt,
+  TGP_LAUNCH(ps, (conv3x3_tile<MT, WC, WP, FW, LW, NS, DG>), dim3(G), dim3(NW * 64), 0, st, io, ng, Wt,
              b, s.nb, s.H, s.W, s.cin, s.cout, relu, cut);
   return launch_status();
 }
 
+// y = act(conv(x, w) + b), or with dg the data gradient: x = dz, s the
+// transposed shape (cin: its sum channels, the forward layer's outputs), and w
+// the forward layer's weights.
 hipError_t conv_forward_tile(int n, const void* const* x, const void* w, const float* b,
-                             void* const* y, const ConvShape& s, int relu, hipStream_t st) {
-  if (n < 1 || n > kMaxGroup || !conv_tile_ok(s)) return hipErrorInvalidValue;
+                             void* const* y, const ConvShape& s, int relu, bool dg,
+                             hipStream_t st) {
+  if (n < 1 || n > kMaxGroup || !conv_tile_ok(s) || !w) return hipErrorInvalidValue;
   if (n > kTileGroup) {
     for (int k0 = 0; k0 < n; k0 += kTileGroup) {
       const int c = n - k0 < kTileGroup ? n - k0 : kTileGroup;
-      const hipError_t e = conv_forward_tile(c, x + k0, w, b, y + k0, s, relu, st);
+      const hipError_t e = conv_forward_tile(c, x + k0, w, b, y + k0, s, relu, dg, st);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -411,12 +459,14 @@ hipError_t conv_forward_tile(int n, const void* const* x, const void* w, const f
   }
   const bf16_t* Wt = (const bf16_t*)w;
   switch (c) {
-#define CT_CASE(i)                                                                          \
-  case i:                                                                                   \
-    return launch_tile<kTileCfgs[i].MT, kTileCfgs[i].WC, kTileCfgs[i].WP, kTileCfgs[i].FW,  \
-                       kTileCfgs[i].LW, kTileCfgs[i].NS>(io, n, Wt, b, s, relu, cut, st);
+#define CT_GO(i, D)                                                                         \
+  launch_tile<kTileCfgs[i].MT, kTileCfgs[i].WC, kTileCfgs[i].WP, kTileCfgs[i].FW,           \
+              kTileCfgs[i].LW, kTileCfgs[i].NS, D>(io, n, Wt, b, s, relu, cut, st)
+#define CT_CASE(i) \
+  case i: return dg ? CT_GO(i, true) : CT_GO(i, false);
     CT_CASE(0) CT_CASE(1) CT_CASE(2) CT_CASE(3) CT_CASE(4) CT_CASE(5) CT_CASE(6)
 #undef CT_CASE
+#undef CT_GO
     default: return hipErrorInvalidValue;
   }
 }

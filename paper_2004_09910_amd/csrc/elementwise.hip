@@ -11,6 +11,9 @@ namespace tgpk {
 
 bool mfma_fwd_ok(int dt, const ConvShape& s);
 bool mfma_wgrad_ok(int dt, const ConvShape& s);
+bool conv_dgrad_tile_planned(const ConvShape& t);
+hipError_t conv_dgrad_tile(int n, const void* const* dz, const void* w, void* const* dx,
+                           const ConvShape& t, hipStream_t st);
 hipError_t conv_forward_mfma(const void* x, const void* w, const float* b, void* y,
                              const ConvShape& s, int relu, float* part, size_t part_cap,
                              hipStream_t st);
@@ -225,7 +228,6 @@ __global__ __launch_bounds__(256) void wgrad1x1_small_k(const T* __restrict__ x,
 }
 
 long direct_wgrad_pps(long P) { return P < 256 ? 256 : (P + 63) / 64; }
-int direct_wgrad_splits(long P) { return (int)((P + direct_wgrad_pps(P) - 1) / direct_wgrad_pps(P)); }
 
 // ---------------------------------------------------------------- depthwise
 
@@ -269,7 +271,8 @@ __global__ __launch_bounds__(256) void dw_dgrad_k(const T* __restrict__ dz, cons
   Elt<T>::st(dx + e, acc);
 }
 
-// Depthwise 3x3 over bf16 NHWC with C % 8 == 0 and C / 8 dividing 256.
+// Depthwise 3x3 over bf16 NHWC with C % 8 == 0 and C / 8 at most 256; a block
+// is a whole number of columns (CP threads each, up to 256).
 // Thread q of block (chunk, strip) owns column wc = q / CP and channel pack
 // cp = q % CP (CP = C / 8, eight channels per 16-byte pack) and produces the
 // output rows [h0, h0 + RS) of that column: the 3 x 3 window of input packs
@@ -284,8 +287,8 @@ __global__ __launch_bounds__(256) void dw_dgrad_k(const T* __restrict__ dz, cons
 // MASK (data gradient only): the result stored is the ReLU backward of the
 // layer below, whose output m[k] masks it (its dz), and the block's column
 // sums of the stored values go to part[k] (row blockIdx.y gridDim.x +
-// blockIdx.x, C floats): that layer's bias-gradient partials.  It needs every
-// thread of a block inside the image (W C / 8 a multiple of 256).
+// blockIdx.x, C floats): that layer's bias-gradient partials (the threads past
+// the last column add zeros).
 struct DwIo {
   const bf16_t* x[kMaxGroup];
   bf16_t* y[kMaxGroup];
@@ -299,9 +302,9 @@ __global__ __launch_bounds__(256) void dw3_rows_k(DwIo io, const bf16_t* __restr
   const bf16_t* __restrict__ x = pickg(io.x, blockIdx.z);
   bf16_t* __restrict__ y = pickg(io.y, blockIdx.z);
   const int CP = C >> 3;
-  const int q = blockIdx.x * 256 + threadIdx.x;
+  const int q = blockIdx.x * blockDim.x + threadIdx.x;
   const int wc = q / CP, cp = q - (q / CP) * CP;
-  if (wc >= W) return;
+  if (!MASK && wc >= W) return;
   const int strips = (H + RS - 1) / RS;
   const int n = blockIdx.y / strips, h0 = (blockIdx.y - n * strips) * RS;
   float wt[9][8];
@@ -338,7 +341,7 @@ __global__ __launch_bounds__(256) void dw3_rows_k(DwIo io, const bf16_t* __restr
     win[1][s] = ld(h0, wc + s - 1);
     win[2][s] = ld(h0 + 1, wc + s - 1);
   }
-  const int h1 = min(h0 + RS, H);
+  const int h1 = wc < W ? min(h0 + RS, H) : h0;   // (MASK) no rows past the last column
   float bsum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // MASK: this thread's column sums
   for (int h = h0; h < h1; ++h) {
 #pragma unroll
@@ -392,7 +395,7 @@ __global__ __launch_bounds__(256) void dw3_rows_k(DwIo io, const bf16_t* __restr
       float s8[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) s8[i] = red[threadIdx.x * 8 + i];
-      for (int l = 1; l < 256 / CP; ++l)
+      for (int l = 1; l < (int)blockDim.x / CP; ++l)
 #pragma unroll
         for (int i = 0; i < 8; ++i) s8[i] += red[(l * CP + threadIdx.x) * 8 + i];
       float* pr = pickg(io.part, blockIdx.z) + ((long)blockIdx.y * gridDim.x + blockIdx.x) * C +
@@ -408,11 +411,12 @@ __global__ __launch_bounds__(256) void dw3_rows_k(DwIo io, const bf16_t* __restr
 // dz[p] * x[p + tap] over the rows [h0, h0 + RS) of its column for its
 // eight channels and nine taps (x through the sliding window, the next
 // row's window and dz loaded while the current row's products run); the
-// block then adds its 256 / CP column groups in order in LDS, taps 0-4 and
+// block then adds its column groups in order in LDS, taps 0-4 and
 // then 5-8 through one buffer of a 41-float row per thread (the odd row
 // length keeps both the writes and the reads free of bank conflicts), and
-// writes part[blk][c * 9 + t], blk = strip block * chunks + chunk.  The partials are summed in block order
-// afterwards, so the result is deterministic.
+// writes part[blk][c * 9 + t], blk = blockIdx.y * chunks + chunk.  A block
+// takes the strips blockIdx.y, + gridDim.y, .. one after another.  The partials
+// are summed in block order afterwards, so the result is deterministic.
 // gridDim.z (1 .. kMaxGroup) micro-batches: blockIdx.z selects (x[k],
 // dz[k], part[k]).
 struct DwWgIo {
@@ -421,7 +425,7 @@ struct DwWgIo {
   float* part[kMaxGroup];
 };
 template <int RS>
-__global__ __launch_bounds__(256) void dw3_wgrad_rows_k(DwWgIo io, int H, int W, int C) {
+__global__ __launch_bounds__(256) void dw3_wgrad_rows_k(DwWgIo io, int nb, int H, int W, int C) {
   const bf16_t* __restrict__ x = pickg(io.x, blockIdx.z);
   const bf16_t* __restrict__ dz = pickg(io.dz, blockIdx.z);
   float* __restrict__ part = pickg(io.part, blockIdx.z);
@@ -429,16 +433,16 @@ __global__ __launch_bounds__(256) void dw3_wgrad_rows_k(DwWgIo io, int H, int W,
   constexpr int RW = TH * 8 + 1;             // floats per thread row
   __shared__ float red[256][RW];
   const int CP = C >> 3;
-  const int q = blockIdx.x * 256 + threadIdx.x;
+  const int q = blockIdx.x * blockDim.x + threadIdx.x;
   const int wc = q / CP, cp = q - (q / CP) * CP;
   const int strips = (H + RS - 1) / RS;
-  const int n = blockIdx.y / strips, h0 = (blockIdx.y - n * strips) * RS;
   float acc[9][8];
 #pragma unroll
   for (int t = 0; t < 9; ++t)
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[t][i] = 0.f;
-  if (wc < W) {
+  for (int strip = blockIdx.y; wc < W && strip < nb * strips; strip += gridDim.y) {
+    const int n = strip / strips, h0 = (strip - n * strips) * RS;
     // buffer loads over the sample's image: an offset outside it reads
     // zeros, so the halo needs no branches (a branch per load made the
     // compiler wait for every load in flight, the prefetch included)
@@ -490,7 +494,7 @@ __global__ __launch_bounds__(256) void dw3_wgrad_rows_k(DwWgIo io, int H, int W,
       dzc = dzn;
     }
   }
-  const int E = C * 9, NG = 256 / CP;
+  const int E = C * 9, NG = blockDim.x / CP;
   float* out = part + ((long)blockIdx.y * gridDim.x + blockIdx.x) * E;
 #pragma unroll
   for (int pass = 0; pass < 2; ++pass) {
@@ -502,7 +506,7 @@ __global__ __launch_bounds__(256) void dw3_wgrad_rows_k(DwWgIo io, int H, int W,
 #pragma unroll
         for (int i = 0; i < 8; ++i) red[threadIdx.x][t * 8 + i] = acc[t0 + t][i];
     __syncthreads();
-    for (int e = threadIdx.x; e < C * nt; e += 256) {
+    for (int e = threadIdx.x; e < C * nt; e += blockDim.x) {
       const int c = e / nt, t = e - (e / nt) * nt, pk = c >> 3, i = c & 7;
       float s = 0.f;
       for (int g = 0; g < NG; ++g) s += red[g * CP + pk][t * 8 + i];
@@ -514,18 +518,36 @@ __global__ __launch_bounds__(256) void dw3_wgrad_rows_k(DwWgIo io, int H, int W,
 constexpr int kDwRows = 8;       // output rows per thread, forward and data gradient
 constexpr int kDwWgradRows = 8;  // rows per thread of the weight gradient
 
-// The row-window depthwise kernels apply: bf16, whole 16-byte packs, a pack
-// count dividing the block, 16-byte aligned tensors and weights, and a
-// sample image under 2 GiB (their buffer loads take 32-bit offsets).
+// The row-window depthwise kernels apply: bf16, whole 16-byte packs, at most
+// 256 of them, 16-byte aligned tensors and weights, and a sample image under
+// 2 GiB (their buffer loads take 32-bit offsets).
+static bool dw3_rows_shape(int nb, int H, int W, int C) {
+  return C > 0 && C % 8 == 0 && C / 8 <= 256 && (long)nb * cdiv(H, kDwRows) <= 65535 &&
+         2.0 * H * W * C < 2147483648.0;
+}
 static bool dw3_rows_ok(int dt, int nb, int H, int W, int C, const void* a, const void* b2,
                         const void* c2) {
   auto al = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
-  return dt == 0 && C > 0 && C % 8 == 0 && 256 % (C / 8) == 0 && al(a) && al(b2) && al(c2) &&
-         (long)nb * cdiv(H, kDwRows) <= 65535 && 2.0 * H * W * C < 2147483648.0;
+  return dt == 0 && dw3_rows_shape(nb, H, W, C) && al(a) && al(b2) && al(c2);
+}
+
+// Threads of a block (whole columns of C / 8 packs) and blocks along a row.
+static int dw3_threads(int C) { return 256 / (C / 8) * (C / 8); }
+static int dw3_chunks(int W, int C) { return (int)cdiv((long)W * (C / 8), dw3_threads(C)); }
+// Blocks of the weight gradient along y: one per strip of a sample.  Where
+// the pack count divides no 256-thread block, at most 32 blocks in all (one
+// for fewer than 256 pixels; they loop over the strips), so that the partials
+// and the layer's bias sums take no more room than the per-element kernel's
+// 64 splits; 0 where a row alone has more blocks (that kernel runs).
+static int dw3_wgrad_gy(int nb, int H, int W, int C) {
+  const long strips = (long)nb * cdiv(H, kDwWgradRows);
+  if (256 % (C / 8) == 0) return (int)strips;
+  const long cap = ((long)nb * H * W < 256 ? 1 : 32) / dw3_chunks(W, C);
+  return (int)(strips < cap ? strips : cap);
 }
 
 static int dw3_wgrad_blocks(int nb, int H, int W, int C) {
-  return (int)cdiv((long)W * (C / 8), 256) * nb * (int)cdiv(H, kDwWgradRows);
+  return dw3_chunks(W, C) * dw3_wgrad_gy(nb, H, W, C);
 }
 
 // ---------------------------------------------------------------- elementwise
@@ -563,9 +585,10 @@ __global__ __launch_bounds__(256) void relu_bwd_k(const T* __restrict__ dy, cons
 
 // dz = (dy [+ dskip]) * [y > 0] with the bias gradient's column partial sums
 // fused in: block b covers rows [b*rows, (b+1)*rows); thread t handles the
-// 16-byte channel pack t % CP for rows t / CP, t / CP + 256 / CP, ...
+// 16-byte channel pack t % CP for rows t / CP, t / CP + nl, ...
 // (serial, fixed order); row lanes are then added in order in LDS and
-// part[b][c] is written.  Needs 256 % CP == 0 (CP = C / pack).  A launch
+// part[b][c] is written.  A block is CP nl threads, nl = 256 / CP row lanes
+// (CP = C / pack, at most 256): all 256 where CP is a power of two.  A launch
 // covers gridDim.y (1 .. kMaxGroup) micro-batches of the same shape;
 // blockIdx.y selects the pointer set.
 template <typename T>
@@ -603,7 +626,7 @@ __global__ __launch_bounds__(256) void relu_bwd_bias_k(RbGroup<T> ga, int relu, 
   constexpr int N = Pk<T>::N;
   __shared__ float red[256 * N];
   const int CP = C / N;
-  const int cp = threadIdx.x % CP, rl = threadIdx.x / CP, nl = 256 / CP;
+  const int cp = threadIdx.x % CP, rl = threadIdx.x / CP, nl = blockDim.x / CP;
   const long p0 = (long)blockIdx.x * rows, p1 = p0 + rows < P ? p0 + rows : P;
   float sum[N];
 #pragma unroll
@@ -643,7 +666,7 @@ __global__ __launch_bounds__(256) void relu_bwd_bias_k(RbGroup<T> ga, int relu, 
 // relu_bwd_bias_k for a layer whose output feeds a 2x2/2 max pool: dy is
 // the pool gradient dp routed to the first maximal element of each window
 // of y.  Block b covers pooled pixels [b*rows, (b+1)*rows); thread t handles
-// channel pack t % CP of windows t / CP, t / CP + 256 / CP, ... (the four
+// channel pack t % CP of windows t / CP, t / CP + nl, ... (the four
 // pixels of a window in row-major order), then row lanes are added in order
 // in LDS and part[b][c] is written.
 template <typename T>
@@ -658,7 +681,7 @@ __global__ __launch_bounds__(256) void pool_relu_bwd_bias_k(RbGroup<T> ga, int r
   constexpr int N = Pk<T>::N;
   __shared__ float red[256 * N];
   const int CP = C / N;
-  const int cp = threadIdx.x % CP, rl = threadIdx.x / CP, nl = 256 / CP;
+  const int cp = threadIdx.x % CP, rl = threadIdx.x / CP, nl = blockDim.x / CP;
   const int H2 = H / 2, W2 = W / 2;
   const long P2 = (long)nb * H2 * W2;
   const long q0 = (long)blockIdx.x * rows, q1 = q0 + rows < P2 ? q0 + rows : P2;
@@ -1048,7 +1071,9 @@ inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 
 // ---------------------------------------------------------------- dispatch
 
-static long relu_bias_rows(long P, int C, int N);
+int direct_wgrad_splits(long P) { return (int)((P + direct_wgrad_pps(P) - 1) / direct_wgrad_pps(P)); }
+
+static long relu_bias_rows(long P, int C, int N, int cap);
 
 // The 1x1 path for few output channels (the network head).
 static bool small1x1_ok(int dt, const ConvShape& s, const void* x) {
@@ -1090,13 +1115,15 @@ hipError_t conv_forward(int dt, const void* x, const void* w, const float* b, vo
 }
 
 bool conv_dgrad_uses_wt(int dt, const ConvShape& s) {
-  return mfma_fwd_ok(dt, ConvShape{s.nb, s.H, s.W, s.cout, s.cin, s.taps});
+  const ConvShape t{s.nb, s.H, s.W, s.cout, s.cin, s.taps};
+  return mfma_fwd_ok(dt, t) && !conv_dgrad_tile_planned(t);
 }
 
 hipError_t conv_dgrad(int dt, const void* dz, const void* w, const void* wt, void* dx,
                       const ConvShape& s, float* part, size_t part_cap, hipStream_t st) {
-  if (conv_dgrad_uses_wt(dt, s)) {
-    ConvShape t{s.nb, s.H, s.W, s.cout, s.cin, s.taps};
+  const ConvShape t{s.nb, s.H, s.W, s.cout, s.cin, s.taps};
+  if (mfma_fwd_ok(dt, t)) {
+    if (!wt || conv_dgrad_tile_planned(t)) return conv_dgrad_tile(1, &dz, w, &dx, t, st);
     t_in_dgrad = 1;
     const hipError_t e = conv_forward_mfma(dz, wt, nullptr, dx, t, 0, part, part_cap, st);
     t_in_dgrad = 0;
@@ -1121,7 +1148,7 @@ size_t conv_wgrad_partial_floats(int dt, const ConvShape& s) {
   const int N = dt == 0 ? 8 : 4;
   if (small1x1_ok(dt, s, (const void*)16)) {   // (alignment is checked per call)
     const size_t direct = (size_t)direct_wgrad_splits(s.pixels()) * s.cout * s.taps * s.cin;
-    const size_t small = (size_t)cdiv(s.pixels(), relu_bias_rows(s.pixels(), s.cin, N)) * s.cout * s.cin;
+    const size_t small = (size_t)cdiv(s.pixels(), relu_bias_rows(s.pixels(), s.cin, N, 1024)) * s.cout * s.cin;
     return direct > small ? direct : small;
   }
   return (size_t)direct_wgrad_splits(s.pixels()) * s.cout * s.taps * s.cin;
@@ -1135,7 +1162,7 @@ hipError_t conv_wgrad(int dt, const void* x, const void* dz, float* dw, float* p
     return conv_wgrad_mfma(x, dz, dw, partial, s, st, extra, defer);
   if (small1x1_ok(dt, s, x)) {
     const long P = s.pixels(), E = (long)s.cout * s.cin;
-    const long rows = relu_bias_rows(P, s.cin, dt == 0 ? 8 : 4);
+    const long rows = relu_bias_rows(P, s.cin, dt == 0 ? 8 : 4, 1024);
     const int nbk = cdiv(P, rows);
     {
       ProfScope ps("wgrad1x1_small", 2.0 * P * E,
@@ -1196,8 +1223,9 @@ hipError_t conv_dgrad_n(int dt, int n, const void* const* dz, const void* w, con
                         void* const* dx, const ConvShape& s, float* const* part,
                         size_t part_cap, hipStream_t st) {
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
-  if (conv_dgrad_uses_wt(dt, s)) {
-    ConvShape t{s.nb, s.H, s.W, s.cout, s.cin, s.taps};
+  const ConvShape t{s.nb, s.H, s.W, s.cout, s.cin, s.taps};
+  if (mfma_fwd_ok(dt, t)) {
+    if (!wt || conv_dgrad_tile_planned(t)) return conv_dgrad_tile(n, dz, w, dx, t, st);
     t_in_dgrad = 1;
     const hipError_t e = conv_forward_mfma_n(n, dz, wt, nullptr, dx, t, 0, part, part_cap, st);
     t_in_dgrad = 0;
@@ -1229,6 +1257,11 @@ bool dw_rows_ok(int dt, int nb, int H, int W, int C, const void* a, const void* 
   return dw3_rows_ok(dt, nb, H, W, C, a, b, c);
 }
 
+bool dw_wgrad_rows_ok(int dt, int nb, int H, int W, int C, const void* a, const void* b,
+                      const void* c) {
+  return dw3_rows_ok(dt, nb, H, W, C, a, b, c) && dw3_wgrad_gy(nb, H, W, C) > 0;
+}
+
 hipError_t dw_forward_n(int n, const void* const* x, const void* w, const float* b,
                         void* const* y, int nb, int H, int W, int C, int relu, hipStream_t st) {
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
@@ -1239,9 +1272,9 @@ hipError_t dw_forward_n(int n, const void* const* x, const void* w, const float*
     io.x[k] = (const bf16_t*)x[k < n ? k : 0];
     io.y[k] = (bf16_t*)y[k < n ? k : 0];
   }
-  const dim3 g((unsigned)cdiv((long)W * (C / 8), 256), (unsigned)(nb * cdiv(H, kDwRows)), n);
+  const dim3 g((unsigned)dw3_chunks(W, C), (unsigned)(nb * cdiv(H, kDwRows)), n);
   ProfScope ps("dw3_rows_fwd", n * 18.0 * P * C, n * 4.0 * P * C, st);
-  TGP_LAUNCH(ps, (dw3_rows_k<kDwRows, false>), g, dim3(256), 0, st, io, (const bf16_t*)w, b, H,
+  TGP_LAUNCH(ps, (dw3_rows_k<kDwRows, false>), g, dim3(dw3_threads(C)), 0, st, io, (const bf16_t*)w, b, H,
              W, C, relu);
   return launch_status();
 }
@@ -1256,20 +1289,19 @@ hipError_t dw_dgrad_n(int n, const void* const* dz, const void* w, void* const* 
     io.x[k] = (const bf16_t*)dz[k < n ? k : 0];
     io.y[k] = (bf16_t*)dx[k < n ? k : 0];
   }
-  const dim3 g((unsigned)cdiv((long)W * (C / 8), 256), (unsigned)(nb * cdiv(H, kDwRows)), n);
+  const dim3 g((unsigned)dw3_chunks(W, C), (unsigned)(nb * cdiv(H, kDwRows)), n);
   ProfScope ps("dw3_rows_dgrad", n * 18.0 * P * C, n * 4.0 * P * C, st);
-  TGP_LAUNCH(ps, (dw3_rows_k<kDwRows, true>), g, dim3(256), 0, st, io, (const bf16_t*)w,
+  TGP_LAUNCH(ps, (dw3_rows_k<kDwRows, true>), g, dim3(dw3_threads(C)), 0, st, io, (const bf16_t*)w,
              (const float*)nullptr, H, W, C, 0);
   return launch_status();
 }
 
 bool dw_dgrad_mask_ok(int nb, int H, int W, int C) {
-  return C % 8 == 0 && 256 % (C / 8) == 0 && (long)W * (C / 8) % 256 == 0 &&
-         (long)nb * cdiv(H, kDwRows) <= 65535 && 2.0 * nb * H * W * C < 2147483648.0;
+  return dw3_rows_shape(nb, H, W, C) && 2.0 * nb * H * W * C < 2147483648.0;
 }
 
 int dw_dgrad_mask_rows(int nb, int H, int W, int C) {
-  return (int)((long)W * (C / 8) / 256 * nb * cdiv(H, kDwRows));
+  return (int)((long)dw3_chunks(W, C) * nb * cdiv(H, kDwRows));
 }
 
 hipError_t dw_dgrad_mask_n(int n, const void* const* dz, const void* w, void* const* dx,
@@ -1287,9 +1319,9 @@ hipError_t dw_dgrad_mask_n(int n, const void* const* dz, const void* w, void* co
     io.part[k] = part[q];
     if (!io.x[k] || !io.y[k] || !io.m[k] || !io.part[k]) return hipErrorInvalidValue;
   }
-  const dim3 g((unsigned)((long)W * (C / 8) / 256), (unsigned)(nb * cdiv(H, kDwRows)), n);
+  const dim3 g((unsigned)dw3_chunks(W, C), (unsigned)(nb * cdiv(H, kDwRows)), n);
   ProfScope ps("dw3_rows_dgrad_mask", n * 18.0 * P * C, n * 6.0 * P * C, st);
-  TGP_LAUNCH(ps, (dw3_rows_k<kDwRows, true, true>), g, dim3(256), 0, st, io, (const bf16_t*)w,
+  TGP_LAUNCH(ps, (dw3_rows_k<kDwRows, true, true>), g, dim3(dw3_threads(C)), 0, st, io, (const bf16_t*)w,
              (const float*)nullptr, H, W, C, 0);
   return launch_status();
 }
@@ -1308,10 +1340,10 @@ hipError_t dw_wgrad_n(int n, const void* const* x, const void* const* dz, float*
     io.dz[k] = (const bf16_t*)dz[k < n ? k : 0];
     io.part[k] = part[k < n ? k : 0];
   }
-  const dim3 g((unsigned)cdiv((long)W * (C / 8), 256), (unsigned)(nb * cdiv(H, kDwWgradRows)), n);
+  const dim3 g((unsigned)dw3_chunks(W, C), (unsigned)dw3_wgrad_gy(nb, H, W, C), n);
   {
     ProfScope ps("dw3_wgrad_rows", n * 18.0 * P * C, n * (4.0 * P * C + 4.0 * S * E), st);
-    TGP_LAUNCH(ps, (dw3_wgrad_rows_k<kDwWgradRows>), g, dim3(256), 0, st, io, H, W, C);
+    TGP_LAUNCH(ps, (dw3_wgrad_rows_k<kDwWgradRows>), g, dim3(dw3_threads(C)), 0, st, io, nb, H, W, C);
   }
   hipError_t e = launch_status();
   if (defer) {   // left to the caller's accumulation, in the same order
@@ -1365,9 +1397,7 @@ hipError_t dw_dgrad(int dt, const void* dz, const void* w, void* dx, int nb, int
 size_t dw_wgrad_partial_floats(int nb, int H, int W, int C) {
   long P = (long)nb * H * W;
   const size_t direct = (size_t)direct_wgrad_splits(P) * C * 9;
-  const size_t rows = (C % 8 == 0 && C > 0 && 256 % (C / 8) == 0)
-                          ? (size_t)dw3_wgrad_blocks(nb, H, W, C) * C * 9
-                          : 0;
+  const size_t rows = dw3_rows_shape(nb, H, W, C) ? (size_t)dw3_wgrad_blocks(nb, H, W, C) * C * 9 : 0;
   return direct > rows ? direct : rows;
 }
 
@@ -1375,7 +1405,7 @@ hipError_t dw_wgrad(int dt, const void* x, const void* dz, float* dw, float* par
                     int H, int W, int C, hipStream_t st) {
   long P = (long)nb * H * W;
   long E = (long)C * 9;
-  if (dw3_rows_ok(dt, nb, H, W, C, x, dz, partial) && P > 0)
+  if (dw_wgrad_rows_ok(dt, nb, H, W, C, x, dz, partial) && P > 0)
     return dw_wgrad_n(1, &x, &dz, &dw, &partial, nb, H, W, C, st);
   long pps = direct_wgrad_pps(P);
   int S = direct_wgrad_splits(P);
@@ -1414,29 +1444,31 @@ size_t colsum_partial_floats(long P, int C) {
   return (size_t)cdiv(P, colsum_rows(P)) * C;
 }
 
+// Threads of a block over CP channel packs: whole rows of packs.
+static int pack_threads(int CP) { return 256 / CP * CP; }
 // Rows per block of the fused ReLU-backward / bias kernel: about 1024 blocks
 // (a multiple of the block's row lanes), so deep layers with few pixels and
-// many channels still fill the chip.
-static long relu_bias_rows(long P, int C, int N) {
-  int nl = 256 / (C / N);
-  long r = (P + 1023) / 1024;
+// many channels still fill the chip.  Where the pack count divides no
+// 256-thread block (192 channels: 24 packs), at most `cap` blocks, which the
+// plan sets so that their sums fit the room it already had.
+static long relu_bias_rows(long P, int C, int N, int cap) {
+  const int CP = C / N, nl = 256 / CP;
+  const long blocks = 256 % CP ? cap : 1024;
+  long r = (P + blocks - 1) / blocks;
   r = (r + nl - 1) / nl * nl;
   return r < nl ? nl : r;
 }
 bool relu_bias_fusable(int dt, int C, const void* dy, const void* dskip, const void* y,
                        const void* dz) {
   int N = dt == 0 ? 8 : 4;
-  if (C % N) return false;
-  int CP = C / N;
-  return CP <= 256 && 256 % CP == 0 && al16(dy) && al16(dz) && (!dskip || al16(dskip)) &&
-         al16(y);
+  return C % N == 0 && C / N <= 256 && al16(dy) && al16(dz) && (!dskip || al16(dskip)) && al16(y);
 }
-size_t relu_bias_partial_floats(int dt, long P, int C) {
+size_t relu_bias_partial_floats(int dt, long P, int C, int cap) {
   const int N = dt == 0 ? 8 : 4;
-  if (C % N || C / N > 256 || 256 % (C / N)) return 0;   // not fusable
+  if (C % N || C / N > 256) return 0;   // not fusable
   // blocks over P pixels, or over the P / 4 windows of the pooled variant
-  const long b1 = cdiv(P, relu_bias_rows(P, C, N));
-  const long b2 = cdiv(P / 4, relu_bias_rows(P / 4, C, N));
+  const long b1 = cdiv(P, relu_bias_rows(P, C, N, cap));
+  const long b2 = cdiv(P / 4, relu_bias_rows(P / 4, C, N, cap));
   return (size_t)(b1 > b2 ? b1 : b2) * C;
 }
 bool pool_relu_bias_fusable(int dt, int C, int H, int W, const void* dp, const void* dskip,
@@ -1483,10 +1515,11 @@ static hipError_t rb_finish(int n, const RbArgs* a, long C, int nblk, hipStream_
   return hipSuccess;
 }
 
-hipError_t relu_backward_bias_n(int dt, int n, const RbArgs* a, int relu, long P, int C,
+hipError_t relu_backward_bias_n(int dt, int n, const RbArgs* a, int relu, long P, int C, int cap,
                                 hipStream_t st) {
   if (!rb_group_ok(n, a)) return hipErrorInvalidValue;
-  long rows = relu_bias_rows(P, C, dt == 0 ? 8 : 4);
+  const int N = dt == 0 ? 8 : 4;
+  long rows = relu_bias_rows(P, C, N, cap);
   int nb = cdiv(P, rows);
   {
     ProfScope ps("relu_backward_bias", 0.0,
@@ -1494,10 +1527,10 @@ hipError_t relu_backward_bias_n(int dt, int n, const RbArgs* a, int relu, long P
                       4.0 * nb * C),
                  st);
     if (dt == 0)
-      TGP_LAUNCH(ps, relu_bwd_bias_k<bf16_t>, dim3(nb, n), dim3(256), 0, st,
+      TGP_LAUNCH(ps, relu_bwd_bias_k<bf16_t>, dim3(nb, n), dim3(pack_threads(C / N)), 0, st,
                  rb_group<bf16_t>(n, a), relu, P, C, rows);
     else
-      TGP_LAUNCH(ps, relu_bwd_bias_k<float>, dim3(nb, n), dim3(256), 0, st,
+      TGP_LAUNCH(ps, relu_bwd_bias_k<float>, dim3(nb, n), dim3(pack_threads(C / N)), 0, st,
                  rb_group<float>(n, a), relu, P, C, rows);
   }
   hipError_t e = launch_status();
@@ -1506,20 +1539,21 @@ hipError_t relu_backward_bias_n(int dt, int n, const RbArgs* a, int relu, long P
 }
 
 hipError_t relu_backward_bias(int dt, const void* dy, const void* dskip, const void* y, void* dz,
-                              int relu, float* db, float* partial, long P, int C,
+                              int relu, float* db, float* partial, long P, int C, int cap,
                               hipStream_t st, ReduceJob* defer) {
   const RbArgs a{dy, dskip, y, dz, db, partial, defer};
-  return relu_backward_bias_n(dt, 1, &a, relu, P, C, st);
+  return relu_backward_bias_n(dt, 1, &a, relu, P, C, cap, st);
 }
 
 hipError_t pool_relu_backward_bias_n(int dt, int n, const RbArgs* a, int relu, int nb, int H,
-                                     int W, int C, hipStream_t st) {
+                                     int W, int C, int cap, hipStream_t st) {
   if (!rb_group_ok(n, a)) return hipErrorInvalidValue;
   for (int k = 0; k < n; ++k)
     if (!pool_relu_bias_fusable(dt, C, H, W, a[k].dy, a[k].dskip, a[k].y, a[k].dz))
       return hipErrorInvalidValue;
   const long P2 = (long)nb * (H / 2) * (W / 2);
-  const long rows = relu_bias_rows(P2, C, dt == 0 ? 8 : 4);
+  const int N = dt == 0 ? 8 : 4;
+  const long rows = relu_bias_rows(P2, C, N, cap);
   const int nbk = cdiv(P2, rows);
   {
     const double esz = dt == 0 ? 2.0 : 4.0;
@@ -1528,10 +1562,10 @@ hipError_t pool_relu_backward_bias_n(int dt, int n, const RbArgs* a, int relu, i
                       4.0 * nbk * C),
                  st);
     if (dt == 0)
-      TGP_LAUNCH(ps, pool_relu_bwd_bias_k<bf16_t>, dim3(nbk, n), dim3(256), 0, st,
+      TGP_LAUNCH(ps, pool_relu_bwd_bias_k<bf16_t>, dim3(nbk, n), dim3(pack_threads(C / N)), 0, st,
                  rb_group<bf16_t>(n, a), relu, nb, H, W, C, rows);
     else
-      TGP_LAUNCH(ps, pool_relu_bwd_bias_k<float>, dim3(nbk, n), dim3(256), 0, st,
+      TGP_LAUNCH(ps, pool_relu_bwd_bias_k<float>, dim3(nbk, n), dim3(pack_threads(C / N)), 0, st,
                  rb_group<float>(n, a), relu, nb, H, W, C, rows);
   }
   hipError_t e = launch_status();
@@ -1541,9 +1575,9 @@ hipError_t pool_relu_backward_bias_n(int dt, int n, const RbArgs* a, int relu, i
 
 hipError_t pool_relu_backward_bias(int dt, const void* dp, const void* dskip, const void* y,
                                    void* dz, int relu, float* db, float* partial, int nb, int H,
-                                   int W, int C, hipStream_t st, ReduceJob* defer) {
+                                   int W, int C, int cap, hipStream_t st, ReduceJob* defer) {
   const RbArgs a{dp, dskip, y, dz, db, partial, defer};
-  return pool_relu_backward_bias_n(dt, 1, &a, relu, nb, H, W, C, st);
+  return pool_relu_backward_bias_n(dt, 1, &a, relu, nb, H, W, C, cap, st);
 }
 
 hipError_t bias_grad(int dt, const void* dz, float* db, float* partial, long P, int C,

@@ -43,10 +43,12 @@ bool conv_rows32_ok(const ConvShape& s);
 hipError_t conv_forward_rows32(int n, const void* const* x, const void* w, const float* b,
                                void* const* y, const ConvShape& s, int relu, hipStream_t st);
 // 32x32x16-MFMA 3x3 convolution on rectangular tiles (bf16; any image size,
-// Cin and Cout multiples of 8), same contract.
+// Cin and Cout multiples of 8), same contract, or (dg) the data gradient from
+// the forward weights w = [cin][taps][cout], s being the transposed shape.
 bool conv_tile_ok(const ConvShape& s);
 hipError_t conv_forward_tile(int n, const void* const* x, const void* w, const float* b,
-                             void* const* y, const ConvShape& s, int relu, hipStream_t st);
+                             void* const* y, const ConvShape& s, int relu, bool dg,
+                             hipStream_t st);
 extern int g_tile_cfg;
 extern int g_rows32_cfg;
 extern int g_rows32_ch;
@@ -81,13 +83,15 @@ hipError_t conv_wgrad_rows_launch_n(int n, const void* const* x, const void* con
 // The same weight gradient for any image size and channel counts that are
 // multiples of 8, same contracts.
 bool wgrad_tile_ok(const ConvShape& s);
+int wgrad_general_splits(const ConvShape& s);
+int direct_wgrad_splits(long P);   // of P pixels, the per-element kernels
 size_t wgrad_tile_partial_floats(const ConvShape& s);
 hipError_t conv_wgrad_tile_launch(int n, const void* const* x, const void* const* dz,
                                   float* const* dw, float* const* partial, const ConvShape& s,
                                   hipStream_t st, ReduceJob* const* defer);
 
-// Whether the data-gradient kernel for this shape reads the transformed
-// weight wt = [cin][taps][cout] (taps rotated by 180 degrees).
+// Whether the data-gradient kernel planned for this shape reads the
+// transformed weight wt = [cin][taps][cout] (taps rotated by 180 degrees).
 bool conv_dgrad_uses_wt(int dt, const ConvShape& s);
 // Builds those transformed weights, wt[ci][tap'][co] = w[co][taps-1-tap'][ci],
 // for up to kMaxWt tensors in one launch (passed by value).
@@ -142,6 +146,8 @@ size_t dw_wgrad_partial_floats(int nb, int H, int W, int C);
 // in *defer[k].
 bool dw_rows_ok(int dt, int nb, int H, int W, int C, const void* a, const void* b,
                 const void* c);
+bool dw_wgrad_rows_ok(int dt, int nb, int H, int W, int C, const void* a, const void* b,
+                      const void* c);   // the same for dw_wgrad_n
 hipError_t dw_forward_n(int n, const void* const* x, const void* w, const float* b,
                         void* const* y, int nb, int H, int W, int C, int relu, hipStream_t st);
 hipError_t dw_dgrad_n(int n, const void* const* dz, const void* w, void* const* dx, int nb,
@@ -222,10 +228,11 @@ struct AccBatch {
 hipError_t grad_accumulate_batch(AccBatch b, int overwrite, hipStream_t st);
 
 // relu_backward fused with the bias gradient's column sums (fixed-order
-// two-stage reduction), for layers where relu_bias_fusable() holds.
+// two-stage reduction), for layers where relu_bias_fusable() holds.  `cap`
+// bounds the blocks (partial sums) where the channels are no power of two.
 bool relu_bias_fusable(int dt, int C, const void* dy, const void* dskip, const void* y,
                        const void* dz);
-size_t relu_bias_partial_floats(int dt, long P, int C);
+size_t relu_bias_partial_floats(int dt, long P, int C, int cap);
 // With `defer`, the bias gradient's column sums are left in `partial` and
 // *defer describes the sum still to run (the caller passes it to conv_wgrad).
 // One micro-batch's tensors for the fused ReLU-backward / bias-sum kernels
@@ -241,22 +248,23 @@ struct RbArgs {
 };
 // n (1 .. kMaxGroup) micro-batches of the same shape in one launch; all
 // with or all without a skip gradient.
-hipError_t relu_backward_bias_n(int dt, int n, const RbArgs* a, int relu, long P, int C,
+hipError_t relu_backward_bias_n(int dt, int n, const RbArgs* a, int relu, long P, int C, int cap,
                                 hipStream_t st);
 hipError_t pool_relu_backward_bias_n(int dt, int n, const RbArgs* a, int relu, int nb, int H,
-                                     int W, int C, hipStream_t st);
+                                     int W, int C, int cap, hipStream_t st);
 hipError_t relu_backward_bias(int dt, const void* dy, const void* dskip, const void* y, void* dz,
-                              int relu, float* db, float* partial, long P, int C,
+                              int relu, float* db, float* partial, long P, int C, int cap,
                               hipStream_t st, ReduceJob* defer = nullptr);
 // The same for a layer whose output y (nb x H x W x C, H and W even) feeds a
 // 2x2/2 max pool, taking the pool's gradient dp (nb x H/2 x W/2 x C): dy is
 // dp routed to the first maximal element of each window of y (the pool's
 // backward, maxpool_backward), formed on the fly.  Same dz and partial-sum
-// contract (its partials fit relu_bias_partial_floats(dt, nb H W, C)).
+// contract (its partials fit relu_bias_partial_floats(dt, nb H W, C, cap)).
 bool pool_relu_bias_fusable(int dt, int C, int H, int W, const void* dp, const void* dskip,
                             const void* y, const void* dz);
 hipError_t pool_relu_backward_bias(int dt, const void* dp, const void* dskip, const void* y,
                                    void* dz, int relu, float* db, float* partial, int nb, int H,
-                                   int W, int C, hipStream_t st, ReduceJob* defer = nullptr);
+                                   int W, int C, int cap, hipStream_t st,
+                                   ReduceJob* defer = nullptr);
 
 }  // namespace tgpk

@@ -91,6 +91,7 @@ struct LayerRt {
   // mask_below: this (depthwise) layer's data gradient is stored as the ReLU
   // backward of the layer below, with that layer's bias column sums
   bool mask_below = false;
+  int rb_cap = 0;   // most blocks of the ReLU-backward / bias pass (no power of two channels)
 };
 
 }  // namespace
@@ -532,7 +533,8 @@ tgp_status run_backward_g(tgp_net* N, int j, int cnt, const int* iv,
       const void* dps[MG];
       for (int k = 0; k < cnt; ++k) dps[k] = M[k].dy_pool;
       fill_ra(dps);
-      HIPCHK(tgpk::pool_relu_backward_bias_n(N->dt, cnt, ra, d.relu, N->b, Lr.H, Lr.W, d.cout, st),
+      HIPCHK(tgpk::pool_relu_backward_bias_n(N->dt, cnt, ra, d.relu, N->b, Lr.H, Lr.W, d.cout,
+                                               Lr.rb_cap, st),
              "pool_relu_backward_bias");
       for (int k = 0; k < cnt; ++k) {
         ran(k);
@@ -545,8 +547,8 @@ tgp_status run_backward_g(tgp_net* N, int j, int cnt, const int* iv,
           tgpk::pool_relu_bias_fusable(N->dt, d.cout, Lr.H, Lr.W, B.dy_pool, dskipk[k], yk[k],
                                        B.dz)) {
         HIPCHK(tgpk::pool_relu_backward_bias(N->dt, B.dy_pool, dskipk[k], yk[k], B.dz, d.relu,
-                                             gbk[k], bpartk[k], N->b, Lr.H, Lr.W, d.cout, st,
-                                             bdeferk[k]),
+                                             gbk[k], bpartk[k], N->b, Lr.H, Lr.W, d.cout,
+                                             Lr.rb_cap, st, bdeferk[k]),
                "pool_relu_backward_bias");
         ran(k);
         B.dy_pool = nullptr;
@@ -565,7 +567,7 @@ tgp_status run_backward_g(tgp_net* N, int j, int cnt, const int* iv,
       const void* dys[MG];
       for (int k = 0; k < cnt; ++k) dys[k] = M[k].dy;
       fill_ra(dys);
-      HIPCHK(tgpk::relu_backward_bias_n(N->dt, cnt, ra, d.relu, P, d.cout, st),
+      HIPCHK(tgpk::relu_backward_bias_n(N->dt, cnt, ra, d.relu, P, d.cout, Lr.rb_cap, st),
              "relu_backward_bias");
       for (int k = 0; k < cnt; ++k) ran(k);
     }
@@ -575,7 +577,7 @@ tgp_status run_backward_g(tgp_net* N, int j, int cnt, const int* iv,
       if (pj[1].S == 0 && d.bias && Lr.o_gcol_floats &&
           tgpk::relu_bias_fusable(N->dt, d.cout, B.dy, dskipk[k], yk[k], B.dz)) {
         HIPCHK(tgpk::relu_backward_bias(N->dt, B.dy, dskipk[k], yk[k], B.dz, d.relu, gbk[k],
-                                        bpartk[k], P, d.cout, st, bdeferk[k]),
+                                        bpartk[k], P, d.cout, Lr.rb_cap, st, bdeferk[k]),
                "relu_backward_bias");
         ran(k);
       } else if (pj[1].S == 0 && !d.relu && !d.bias && !dskipk[k]) {
@@ -602,8 +604,8 @@ tgp_status run_backward_g(tgp_net* N, int j, int cnt, const int* iv,
     for (int k = 0; k < cnt; ++k) {
       dw_parts[k] = d.kind == TGP_DWCONV3X3 && Lr.defer_w ? (float*)G_(N, M[k].i, Lr.o_gpart)
                                                           : M[k].part;
-      dw_wrows = dw_wrows && tgpk::dw_rows_ok(N->dt, N->b, Lr.H, Lr.W, d.cout, cin_ptr[k], dzk[k],
-                                              dw_parts[k]);
+      dw_wrows = dw_wrows && tgpk::dw_wgrad_rows_ok(N->dt, N->b, Lr.H, Lr.W, d.cout, cin_ptr[k],
+                                                    dzk[k], dw_parts[k]);
     }
     if (d.kind != TGP_DWCONV3X3 && cnt > 1 && Lr.defer_w) {
       float* gws[MG];
@@ -1212,7 +1214,6 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
   // per-micro-batch gradients g_i and transformed weights
   size_t max_part = 0, max_col = 0;
   for (auto& Lr : N->L) {
-    Lr.o_gw = takeG(Lr.w_elems * 4);
     Lr.o_gb = Lr.d.bias ? takeG(Lr.d.cout * 4) : 0;
     tgpk::ConvShape s{N->b, Lr.H, Lr.W, Lr.d.cin, Lr.d.cout, Lr.taps};
     Lr.has_wt = Lr.d.kind != TGP_DWCONV3X3 && tgpk::conv_dgrad_uses_wt(N->dt, s);
@@ -1224,22 +1225,35 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
     constexpr size_t kDeferBytes = 32u << 20;
     const long P = (long)N->b * Lr.H * Lr.W;
     Lr.defer_w = false;
-    Lr.o_gpart = 0;
+    size_t pf = 0;   // floats of the weight gradient's partial slices
     if (Lr.d.kind == TGP_DWCONV3X3) {
       // the row-window kernel's partials stay in the slot for the
       // accumulation (its sum order differs from the immediate reduction's,
       // so the choice is made here, for every call of the plan)
-      const size_t pf = tgpk::dw_wgrad_partial_floats(N->b, Lr.H, Lr.W, Lr.d.cout);
-      max_part = std::max(max_part, pf);
+      pf = tgpk::dw_wgrad_partial_floats(N->b, Lr.H, Lr.W, Lr.d.cout);
       Lr.defer_w = N->dt == TGP_BF16 && pf * 4 <= kDeferBytes;
-      if (Lr.defer_w) Lr.o_gpart = takeG(std::max<size_t>(pf, 1) * 4);
+      max_part = std::max(max_part, pf);
     } else {
-      const size_t pf = tgpk::conv_wgrad_partial_floats(N->dt, s);
+      pf = tgpk::conv_wgrad_partial_floats(N->dt, s);
       Lr.defer_w = pf * 4 <= kDeferBytes;
-      if (Lr.defer_w) Lr.o_gpart = takeG(std::max<size_t>(pf, 1) * 4);
-      else max_part = std::max(max_part, pf);
+      if (!Lr.defer_w) max_part = std::max(max_part, pf);
     }
-    Lr.o_gcol_floats = Lr.d.bias ? tgpk::relu_bias_partial_floats(N->dt, P, Lr.d.cout) : 0;
+    // The gradient itself and its partial slices share their place: where the
+    // slices stay in the slot, the gradient is written only when it is whole.
+    Lr.o_gw = takeG(std::max<size_t>(Lr.defer_w ? pf : 0, Lr.w_elems) * 4);
+    Lr.o_gpart = Lr.o_gw;
+    // Blocks of the bias sums of a layer whose channels are no power of two
+    // (240 read at about 4 TB/s): kept in the slot where, with its slices, they
+    // take no more room than the gradient and the slices of the general
+    // kernels, else reduced at once through the lane's temporaries (below).
+    const long Ec = Lr.d.kind == TGP_DWCONV3X3 ? 9 : (long)Lr.d.cin * Lr.taps;   // weights per channel
+    const long general = Lr.d.kind == TGP_DWCONV3X3 ? tgpk::direct_wgrad_splits(P)
+                                                     : tgpk::wgrad_general_splits(s);
+    const long spare = Lr.defer_w && (pf || general > 1)
+                           ? general + 1 - std::max(1L, (long)(pf / Lr.w_elems)) : 0;
+    Lr.rb_cap = spare > 0 ? (int)std::min(240L, Ec * spare) : 240;
+    Lr.o_gcol_floats =
+        Lr.d.bias ? tgpk::relu_bias_partial_floats(N->dt, P, Lr.d.cout, Lr.rb_cap) : 0;
     {
       // this layer's ReLU backward folded into the data gradient of a
       // depthwise layer above it in the partition (bf16, no prologue there,
@@ -1252,27 +1266,34 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
                        Lr.d.relu && Lr.d.bias && Lr.d.stash_id < 0 && Lr.o_gcol_floats &&
                        U.H == Lr.H && U.W == Lr.W && U.d.cin == Lr.d.cout &&
                        tgpk::dw_dgrad_mask_ok(N->b, U.H, U.W, U.d.cout);
+        // where a block's last column may be past the image, only if its sums
+        // fit the room of the separate pass
+        if (U.mask_below && (long)U.W * (U.d.cout / 8) % 256)
+          U.mask_below = (size_t)tgpk::dw_dgrad_mask_rows(N->b, U.H, U.W, U.d.cout) * Lr.d.cout <=
+                         Lr.o_gcol_floats;
         if (U.mask_below)
           Lr.o_gcol_floats = std::max<size_t>(
               Lr.o_gcol_floats,
               (size_t)tgpk::dw_dgrad_mask_rows(N->b, U.H, U.W, U.d.cout) * Lr.d.cout);
       }
     }
-    Lr.defer_b = Lr.o_gcol_floats && Lr.o_gcol_floats * 4 <= kDeferBytes;
+    const int packs = Lr.d.cout / vecN(N->dt);
+    Lr.defer_b = Lr.o_gcol_floats && Lr.o_gcol_floats * 4 <= kDeferBytes &&
+                 (spare > 0 || packs == 0 || 256 % packs == 0);
     {
       const size_t li = (size_t)(&Lr - &N->L[0]);
       if (li + 1 < N->L.size() && N->L[li + 1].mask_below && !Lr.defer_b)
         N->L[li + 1].mask_below = false;   // its sums need the slot
     }
     Lr.o_gcol = Lr.defer_b ? takeG(Lr.o_gcol_floats * 4) : 0;
-    if (Lr.o_gcol_floats && !Lr.defer_b) max_col = std::max(max_col, Lr.o_gcol_floats);
-    max_col = std::max(max_col, tgpk::colsum_partial_floats(P, Lr.d.cout));
+    if (Lr.o_gcol_floats && !Lr.defer_b && (packs == 0 || 256 % packs == 0))
+      max_col = std::max(max_col, Lr.o_gcol_floats);
+    if (Lr.d.bias) max_col = std::max(max_col, tgpk::colsum_partial_floats(P, Lr.d.cout));
   }
   N->o_g0 = takeL(max_act);
   N->o_g1 = takeL(max_act);
   N->o_dz = takeL(max_act);
   N->o_dinp = takeL(std::max<size_t>(max_pro, 16));
-  N->o_part = takeL(std::max<size_t>(max_part, 1) * 4);
   size_t max_fpart = 0;   // split-K partials of forward / data-gradient convolutions
   for (auto& Lr : N->L) {
     if (Lr.d.kind == TGP_DWCONV3X3) continue;
@@ -1282,8 +1303,18 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
                           tgpk::conv_forward_partial_floats(N->dt, d)});
   }
   N->fpart_floats = max_fpart;
-  N->o_fpart = takeL(std::max<size_t>(max_fpart, 4) * 4);
-  N->o_colpart = takeL(max_col * 4);
+  // split-K partials of a convolution, and weight and bias partials reduced at
+  // once: each is read back by the launch after the one that wrote it, so one
+  // buffer serves them in turn
+  const size_t tmp_floats = std::max({max_fpart, max_part, max_col, (size_t)4});
+  N->o_fpart = N->o_part = N->o_colpart = takeL(tmp_floats * 4);
+  for (auto& Lr : N->L) {   // blocks of the bias sums reduced at once, in that room
+    const int packs = Lr.d.cout / vecN(N->dt);
+    if (!Lr.o_gcol_floats || Lr.defer_b || packs == 0 || 256 % packs == 0) continue;
+    Lr.rb_cap = (int)std::min<size_t>(240, std::max<size_t>(1, tmp_floats / Lr.d.cout));
+    Lr.o_gcol_floats = tgpk::relu_bias_partial_floats(N->dt, (long)N->b * Lr.H * Lr.W, Lr.d.cout,
+                                                      Lr.rb_cap);
+  }
   const LayerRt& last = N->L.back();
   long out_mb = (long)N->b * last.H * last.W * last.d.cout;
   N->out_bytes_mb = out_mb * N->esz;

@@ -324,7 +324,8 @@ constexpr int kWtRows = kWtLW * kWtNW * 8;      // LDS rows of a slot
 //  - K ranges: about kItems items per micro-batch (a launch over four then
 //    fills two rounds of blocks; one micro-batch alone runs on half the CUs),
 //    at most 8 MB of slices (their write and re-read otherwise cost more than
-//    the parallelism gains).  A function of one micro-batch's shape, so a
+//    the parallelism gains) and no more slices than the general kernels
+//    write, so that a plan needs no more room than with those.  A function of one micro-batch's shape, so a
 //    group gives the bits of single launches.
 constexpr double kStageSteps = 4.0;
 constexpr int kItems = 128;
@@ -353,7 +354,7 @@ WtCut wt_cut(const ConvShape& s) {
   const long E = (long)s.cout * 9 * s.cin;
   long nK = (kItems + per_k - 1) / per_k;
   nK = std::min(nK, std::max(1L, (8L << 20) / (4 * E)));
-  nK = std::min(nK, (long)best.T);
+  nK = std::min({nK, (long)best.T, (long)wgrad_general_splits(s)});
   best.spk = (int)((best.T + nK - 1) / nK);
   best.nK = (best.T + best.spk - 1) / best.spk;
   return best;

@@ -10,8 +10,8 @@ import paper_2004_09910_amd as tgp
 from gpu_util import check_stage, gpu_stage, oracle_stage, say
 from paper_2004_09910_amd.harness import Session
 from workloads import specs
-from workloads.specs import BF16, CONV3X3, Layer, Net
-from workloads.synth import NORMAL
+from workloads.specs import BF16, CONV3X3, DWCONV3X3, FP32, PRO_MAXPOOL2, Layer, Net
+from workloads.synth import EXACT, NORMAL
 
 pytestmark = pytest.mark.gpu
 
@@ -93,3 +93,41 @@ def test_wgrad_padding_keeps_infinities_apart(h, w):
     assert torch.equal(out[0][..., :5], out[1][..., :5])
     assert not torch.isfinite(out[1][:, 2, 2, 5]).any()
     sess.close()
+
+
+@pytest.mark.parametrize("c,h,w,relu,bias", [
+    (24, 9, 13, True, True),       # 3 packs: 255 threads, partly filled rows
+    (192, 28, 28, True, True),     # 24 packs, several strips and chunks
+    (2000, 3, 5, False, True),     # 250 packs: one column a block
+    (2056, 3, 5, True, True),      # past 256 packs: the per-element kernels
+    (40, 40, 30, False, False),
+])
+def test_depthwise_any_channels(c, h, w, relu, bias):
+    run_and_check(Layer(DWCONV3X3, c, c, relu=relu, bias=bias), h, w, BF16, 4, 2,
+                  f"depthwise {c} @{h}x{w}")
+
+
+@pytest.mark.parametrize("dtype,c,h,w", [(BF16, 192, 18, 14), (BF16, 24, 34, 22), (FP32, 12, 10, 6),
+                                         (FP32, 100, 40, 30)])
+def test_bias_sums_any_channels(dtype, c, h, w):
+    """ReLU backward with its bias sums, and its pooled form inside a
+    partition, where the channel packs divide no block; exact inputs."""
+    cin = 64 if dtype == BF16 else 8
+    net = Net("two", (Layer(CONV3X3, cin, c), Layer(CONV3X3, c, 64, prologue=PRO_MAXPOOL2)), cin,
+              h, w)
+    got = gpu_stage(net, dtype, 4, 2, 0, (2,), 1, family=EXACT)
+    ref = oracle_stage(net, dtype, 0, 2, got["xv"], got["G"], family=EXACT, certify=True)
+    check_stage(got, ref, dtype, f"bias sums c={c} {h}x{w}", EXACT)
+    got["sess"].close()
+
+
+@pytest.mark.parametrize("c,h,w", [(192, 14, 14), (64, 9, 7), (48, 11, 5)])
+def test_masked_depthwise_gradient_past_the_last_column(c, h, w):
+    """Two cells whose depthwise data gradient stores the ReLU backward of the
+    1x1 layer below with blocks that end past the image."""
+    net = specs.amoeba_cells(2, c, 8)
+    net = Net("cells", net.layers, c, h, w)
+    got = gpu_stage(net, BF16, 4, 2, 0, (4,), 1, family=EXACT)
+    ref = oracle_stage(net, BF16, 0, 4, got["xv"], got["G"], family=EXACT, certify=True)
+    check_stage(got, ref, BF16, f"cells c={c} {h}x{w}", EXACT)
+    got["sess"].close()
