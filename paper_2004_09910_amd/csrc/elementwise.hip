@@ -1,5 +1,5 @@
-// Non-MFMA kernels: direct convolutions for float32 runs and for shapes the
-// MFMA tiles do not cover (e.g. a 1-channel head), depthwise 3x3, ReLU
+// Non-MFMA kernels: 1x1 convolutions with few outputs (e.g. a 1-channel head),
+// depthwise 3x3, ReLU
 // backward, bias gradient, max-pool, upsample-concat, MSE and gradient
 // accumulation.  All reductions run in a fixed order (per-thread serial sums,
 // fixed LDS trees, fixed split order), so results are bit-reproducible.
@@ -64,84 +64,7 @@ template <> struct Pk<float> {
 template <typename T> __device__ __forceinline__ uint4 ld16(const T* p) { return *(const uint4*)p; }
 template <typename T> __device__ __forceinline__ void st16(T* p, uint4 v) { *(uint4*)p = v; }
 
-// ---------------------------------------------------------------- direct conv
-
-template <typename T>
-__global__ __launch_bounds__(256) void conv_fwd_direct(const T* __restrict__ x,
-                                                       const T* __restrict__ w,
-                                                       const float* __restrict__ b,
-                                                       T* __restrict__ y, long P, int H, int W,
-                                                       int Cin, int Cout, int taps, int relu) {
-  long e = (long)blockIdx.x * 256 + threadIdx.x;
-  if (e >= P * Cout) return;
-  int co = e % Cout;
-  long p = e / Cout;
-  int HW = H * W;
-  int rem = p % HW, h = rem / W, wq = rem - h * W;
-  float acc = 0.f;
-  for (int t = 0; t < taps; ++t) {
-    int dr = taps == 9 ? t / 3 - 1 : 0, dc = taps == 9 ? t % 3 - 1 : 0;
-    int hh = h + dr, ww = wq + dc;
-    if ((unsigned)hh >= (unsigned)H || (unsigned)ww >= (unsigned)W) continue;
-    const T* xr = x + (p + (long)dr * W + dc) * Cin;
-    const T* wr = w + ((long)co * taps + t) * Cin;
-    for (int ci = 0; ci < Cin; ++ci) acc += Elt<T>::ld(xr + ci) * Elt<T>::ld(wr + ci);
-  }
-  if (b) acc += b[co];
-  if (relu) acc = fmaxf(acc, 0.f);
-  Elt<T>::st(y + e, acc);
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void conv_dgrad_direct(const T* __restrict__ dz,
-                                                         const T* __restrict__ w,
-                                                         T* __restrict__ dx, long P, int H,
-                                                         int W, int Cin, int Cout, int taps) {
-  long e = (long)blockIdx.x * 256 + threadIdx.x;
-  if (e >= P * Cin) return;
-  int ci = e % Cin;
-  long p = e / Cin;
-  int HW = H * W;
-  int rem = p % HW, h = rem / W, wq = rem - h * W;
-  float acc = 0.f;
-  for (int t = 0; t < taps; ++t) {
-    int dr = taps == 9 ? t / 3 - 1 : 0, dc = taps == 9 ? t % 3 - 1 : 0;
-    // output pixel (h - dr, w - dc) read input pixel (h, w) through tap t
-    int hh = h - dr, ww = wq - dc;
-    if ((unsigned)hh >= (unsigned)H || (unsigned)ww >= (unsigned)W) continue;
-    const T* dr_ = dz + (p - (long)dr * W - dc) * Cout;
-    for (int co = 0; co < Cout; ++co)
-      acc += Elt<T>::ld(dr_ + co) * Elt<T>::ld(w + ((long)co * taps + t) * Cin + ci);
-  }
-  Elt<T>::st(dx + e, acc);
-}
-
-// partial[s][co][tap][ci] = sum over pixels of split s of dz[p][co] * x[p+off][ci]
-template <typename T>
-__global__ __launch_bounds__(256) void conv_wgrad_direct(const T* __restrict__ x,
-                                                         const T* __restrict__ dz,
-                                                         float* __restrict__ part, long P,
-                                                         int H, int W, int Cin, int Cout,
-                                                         int taps, long pps) {
-  long E = (long)Cout * taps * Cin;
-  long e = (long)blockIdx.x * 256 + threadIdx.x;
-  if (e >= E) return;
-  int ci = e % Cin;
-  long r = e / Cin;
-  int t = r % taps;
-  int co = r / taps;
-  int dr = taps == 9 ? t / 3 - 1 : 0, dc = taps == 9 ? t % 3 - 1 : 0;
-  long ps = (long)blockIdx.y * pps, pe = ps + pps < P ? ps + pps : P;
-  int HW = H * W;
-  float acc = 0.f;
-  for (long p = ps; p < pe; ++p) {
-    int rem = p % HW, h = rem / W, wq = rem - h * W;
-    int hh = h + dr, ww = wq + dc;
-    if ((unsigned)hh >= (unsigned)H || (unsigned)ww >= (unsigned)W) continue;
-    acc += Elt<T>::ld(dz + p * Cout + co) * Elt<T>::ld(x + (p + (long)dr * W + dc) * Cin + ci);
-  }
-  part[(long)blockIdx.y * E + e] = acc;
-}
+// ---------------------------------------------------------------- few-output 1x1
 
 // 1x1 convolution with at most kSmallCo output channels (the network head):
 // one thread per pixel reads its channels in 16-byte packs.
@@ -923,17 +846,38 @@ __global__ __launch_bounds__(256) void upcat_bwd_skip_k(const T* __restrict__ dc
 
 // ---------------------------------------------------------------- loss / accumulate
 
+// Squared differences of one micro-batch and its loss gradient: block b takes
+// the packs of 16 bytes b 256 + t, + gridDim.x 256, .. (one element at a time
+// where the tensors are not aligned to packs), adds them per thread in order and
+// over the block in a tree.
 template <typename T>
 __global__ __launch_bounds__(256) void mse_k(const T* __restrict__ y, const T* __restrict__ t,
                                              T* __restrict__ dy, float* __restrict__ part, long n,
-                                             float inv_numel, long per_block) {
+                                             float inv_numel, int vec) {
+  constexpr int N = Pk<T>::N;
   __shared__ float red[256];
-  long b0 = (long)blockIdx.x * per_block, b1 = b0 + per_block < n ? b0 + per_block : n;
   float s = 0.f;
-  for (long e = b0 + threadIdx.x; e < b1; e += 256) {
-    float d = Elt<T>::ld(y + e) - Elt<T>::ld(t + e);
-    s += d * d;
-    Elt<T>::st(dy + e, 2.0f * d * inv_numel);
+  const long n8 = (n + N - 1) / N;
+  for (long q = (long)blockIdx.x * 256 + threadIdx.x; q < n8; q += (long)gridDim.x * 256) {
+    const long e0 = q * N;
+    if (vec && e0 + N <= n) {
+      float a[N], b[N];
+      Pk<T>::un(ld16(y + e0), a);
+      Pk<T>::un(ld16(t + e0), b);
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const float d = a[i] - b[i];
+        s += d * d;
+        a[i] = 2.0f * d * inv_numel;
+      }
+      st16(dy + e0, Pk<T>::pk(a));
+    } else {
+      for (long e = e0; e < n && e < e0 + N; ++e) {
+        const float d = Elt<T>::ld(y + e) - Elt<T>::ld(t + e);
+        s += d * d;
+        Elt<T>::st(dy + e, 2.0f * d * inv_numel);
+      }
+    }
   }
   red[threadIdx.x] = s;
   __syncthreads();
@@ -944,12 +888,20 @@ __global__ __launch_bounds__(256) void mse_k(const T* __restrict__ y, const T* _
   if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-__global__ void serial_sum_k(const float* __restrict__ a, int n, float scale,
-                             float* __restrict__ out) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// *out = scale sum of n partial sums: thread t adds t, t + 256, .. in order,
+// the threads meet in a tree.
+__global__ __launch_bounds__(256) void loss_sum_k(const float* __restrict__ a, int n, float scale,
+                                                  float* __restrict__ out) {
+  __shared__ float red[256];
   float s = 0.f;
-  for (int i = 0; i < n; ++i) s += a[i];
-  *out = s * scale;
+  for (int i = threadIdx.x; i < n; i += 256) s += a[i];
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (int k = 128; k > 0; k >>= 1) {
+    if (threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *out = red[0] * scale;
 }
 
 __global__ __launch_bounds__(256) void accumulate_k(float* __restrict__ acc, const float* __restrict__ g,
@@ -1100,18 +1052,7 @@ hipError_t conv_forward(int dt, const void* x, const void* w, const float* b, vo
                  (const float*)x, (const float*)w, b, (float*)y, P, s.cin, s.cout, relu);
     return launch_status();
   }
-  long P = s.pixels();
-  dim3 g(cdiv(P * s.cout, 256));
-  int esz = dt == 0 ? 2 : 4;
-  ProfScope ps("conv_fwd_direct", 2.0 * P * s.cout * s.taps * s.cin,
-               (double)esz * (P * s.cin + (double)s.cout * s.taps * s.cin + P * s.cout), st);
-  if (dt == 0)
-    TGP_LAUNCH(ps, conv_fwd_direct<bf16_t>, g, dim3(256), 0, st, (const bf16_t*)x,
-                       (const bf16_t*)w, b, (bf16_t*)y, P, s.H, s.W, s.cin, s.cout, s.taps, relu);
-  else
-    TGP_LAUNCH(ps, conv_fwd_direct<float>, g, dim3(256), 0, st, (const float*)x,
-                       (const float*)w, b, (float*)y, P, s.H, s.W, s.cin, s.cout, s.taps, relu);
-  return launch_status();
+  return conv_gen_forward(dt, 1, &x, w, b, &y, s, relu, false, st);
 }
 
 bool conv_dgrad_uses_wt(int dt, const ConvShape& s) {
@@ -1129,29 +1070,18 @@ hipError_t conv_dgrad(int dt, const void* dz, const void* w, const void* wt, voi
     t_in_dgrad = 0;
     return e;
   }
-  long P = s.pixels();
-  dim3 g(cdiv(P * s.cin, 256));
-  int esz = dt == 0 ? 2 : 4;
-  ProfScope ps("conv_dgrad_direct", 2.0 * P * s.cout * s.taps * s.cin,
-               (double)esz * (P * s.cin + (double)s.cout * s.taps * s.cin + P * s.cout), st);
-  if (dt == 0)
-    TGP_LAUNCH(ps, conv_dgrad_direct<bf16_t>, g, dim3(256), 0, st, (const bf16_t*)dz,
-                       (const bf16_t*)w, (bf16_t*)dx, P, s.H, s.W, s.cin, s.cout, s.taps);
-  else
-    TGP_LAUNCH(ps, conv_dgrad_direct<float>, g, dim3(256), 0, st, (const float*)dz,
-                       (const float*)w, (float*)dx, P, s.H, s.W, s.cin, s.cout, s.taps);
-  return launch_status();
+  return conv_gen_forward(dt, 1, &dz, w, nullptr, &dx, t, 0, true, st);
 }
 
 size_t conv_wgrad_partial_floats(int dt, const ConvShape& s) {
   if (mfma_wgrad_ok(dt, s)) return wgrad_mfma_partial_floats(s);
   const int N = dt == 0 ? 8 : 4;
   if (small1x1_ok(dt, s, (const void*)16)) {   // (alignment is checked per call)
-    const size_t direct = (size_t)direct_wgrad_splits(s.pixels()) * s.cout * s.taps * s.cin;
+    const size_t direct = conv_gen_wgrad_partial_floats(s);
     const size_t small = (size_t)cdiv(s.pixels(), relu_bias_rows(s.pixels(), s.cin, N, 1024)) * s.cout * s.cin;
     return direct > small ? direct : small;
   }
-  return (size_t)direct_wgrad_splits(s.pixels()) * s.cout * s.taps * s.cin;
+  return conv_gen_wgrad_partial_floats(s);
 }
 
 hipError_t conv_wgrad(int dt, const void* x, const void* dz, float* dw, float* partial,
@@ -1182,28 +1112,12 @@ hipError_t conv_wgrad(int dt, const void* x, const void* dz, float* dw, float* p
     }
     return splitk_reduce_launch(partial, dw, E, nbk, st, extra);
   }
-  long P = s.pixels();
-  long E = (long)s.cout * s.taps * s.cin;
-  long pps = direct_wgrad_pps(P);
-  int S = direct_wgrad_splits(P);
-  dim3 g(cdiv(E, 256), S);
-  {
-  int esz = dt == 0 ? 2 : 4;
-  ProfScope ps("conv_wgrad_direct", 2.0 * P * E, (double)esz * P * (s.cin + s.cout) + 4.0 * S * E, st);
-  if (dt == 0)
-    TGP_LAUNCH(ps, conv_wgrad_direct<bf16_t>, g, dim3(256), 0, st, (const bf16_t*)x,
-                       (const bf16_t*)dz, partial, P, s.H, s.W, s.cin, s.cout, s.taps, pps);
-  else
-    TGP_LAUNCH(ps, conv_wgrad_direct<float>, g, dim3(256), 0, st, (const float*)x,
-                       (const float*)dz, partial, P, s.H, s.W, s.cin, s.cout, s.taps, pps);
-  }
-  hipError_t e = launch_status();
-  if (e != hipSuccess) return e;
-  if (defer) {
-    *defer = ReduceJob{partial, dw, E, S};
-    return hipSuccess;
-  }
-  return splitk_reduce_launch(partial, dw, E, S, st, extra);
+  ReduceJob job;
+  ReduceJob* const jp = defer ? defer : &job;
+  const hipError_t e = conv_gen_wgrad_launch(dt, 1, &x, &dz, &dw, &partial, s, st, &jp);
+  if (e != hipSuccess || defer) return e;
+  if (job.S > 1) return splitk_reduce_launch(job.part, dw, job.E, job.S, st, extra);
+  return extra ? splitk_reduce_launch(extra->part, extra->out, extra->E, extra->S, st) : hipSuccess;
 }
 
 hipError_t conv_forward_n(int dt, int n, const void* const* x, const void* w, const float* b,
@@ -1212,6 +1126,9 @@ hipError_t conv_forward_n(int dt, int n, const void* const* x, const void* w, co
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
   if (mfma_fwd_ok(dt, s))
     return conv_forward_mfma_n(n, x, w, b, y, s, relu, part, part_cap, st);
+  bool small = false;
+  for (int k = 0; k < n; ++k) small = small || small1x1_ok(dt, s, x[k]);
+  if (!small) return conv_gen_forward(dt, n, x, w, b, y, s, relu, false, st);
   for (int k = 0; k < n; ++k) {
     const hipError_t e = conv_forward(dt, x[k], w, b, y[k], s, relu, part[k], part_cap, st);
     if (e != hipSuccess) return e;
@@ -1231,11 +1148,7 @@ hipError_t conv_dgrad_n(int dt, int n, const void* const* dz, const void* w, con
     t_in_dgrad = 0;
     return e;
   }
-  for (int k = 0; k < n; ++k) {
-    const hipError_t e = conv_dgrad(dt, dz[k], w, wt, dx[k], s, part[k], part_cap, st);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  return conv_gen_forward(dt, n, dz, w, nullptr, dx, t, 0, true, st);
 }
 
 hipError_t conv_wgrad_n(int dt, int n, const void* const* x, const void* const* dz,
@@ -1245,6 +1158,9 @@ hipError_t conv_wgrad_n(int dt, int n, const void* const* x, const void* const* 
   for (int k = 0; k < n; ++k)
     if (!defer[k]) return hipErrorInvalidValue;
   if (mfma_wgrad_ok(dt, s)) return conv_wgrad_mfma_n(n, x, dz, dw, part, s, st, defer);
+  bool small = false;
+  for (int k = 0; k < n; ++k) small = small || small1x1_ok(dt, s, x[k]);
+  if (!small) return conv_gen_wgrad_launch(dt, n, x, dz, dw, part, s, st, defer);
   for (int k = 0; k < n; ++k) {
     const hipError_t e = conv_wgrad(dt, x[k], dz[k], dw[k], part[k], s, st, nullptr, defer[k]);
     if (e != hipSuccess) return e;
@@ -1680,33 +1596,30 @@ hipError_t upcat_backward(int dt, const void* dcat, void* dprev, void* dskip, in
   return launch_status();
 }
 
-static long mse_per_block(long n) { return n < 4096 ? 4096 : 16384; }
-size_t mse_partial_floats(long n) { return (size_t)cdiv(n, mse_per_block(n)); }
+// Blocks of one micro-batch's loss: one per 2048 elements, up to 64.  (16384 elements a block and one thread adding the blocks up took 18 us
+// for 32768 elements and 32 us for 147456.)
+int mse_blocks(long n) {
+  const long b = cdiv(n, 2048);
+  return (int)(b < 64 ? b : 64);
+}
 
-hipError_t mse_forward_backward(int dt, const void* y, const void* t, void* dy,
-                                float* loss_part, float* partial, long n, float inv_numel,
-                                hipStream_t st) {
-  long pb = mse_per_block(n);
-  int nb = cdiv(n, pb);
-  {
+hipError_t mse_forward_backward(int dt, const void* y, const void* t, void* dy, float* partial,
+                                long n, float inv_numel, hipStream_t st) {
+  const int vec = al16(y) && al16(t) && al16(dy) ? 1 : 0;
   ProfScope ps("mse", 3.0 * n, (dt == 0 ? 6.0 : 12.0) * n, st);
   if (dt == 0)
-    TGP_LAUNCH(ps, mse_k<bf16_t>, dim3(nb), dim3(256), 0, st, (const bf16_t*)y,
-                       (const bf16_t*)t, (bf16_t*)dy, partial, n, inv_numel, pb);
+    TGP_LAUNCH(ps, mse_k<bf16_t>, dim3(mse_blocks(n)), dim3(256), 0, st, (const bf16_t*)y,
+               (const bf16_t*)t, (bf16_t*)dy, partial, n, inv_numel, vec);
   else
-    TGP_LAUNCH(ps, mse_k<float>, dim3(nb), dim3(256), 0, st, (const float*)y,
-                       (const float*)t, (float*)dy, partial, n, inv_numel, pb);
-  }
-  hipError_t e = launch_status();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(serial_sum_k, dim3(1), dim3(64), 0, st, (const float*)partial, nb, 1.0f,
-                     loss_part);
+    TGP_LAUNCH(ps, mse_k<float>, dim3(mse_blocks(n)), dim3(256), 0, st, (const float*)y,
+               (const float*)t, (float*)dy, partial, n, inv_numel, vec);
   return launch_status();
 }
 
-hipError_t loss_finalize(const float* parts, int m, float inv_numel, float* loss,
+hipError_t loss_finalize(const float* parts, int n, float inv_numel, float* loss,
                          hipStream_t st) {
-  hipLaunchKernelGGL(serial_sum_k, dim3(1), dim3(64), 0, st, parts, m, inv_numel, loss);
+  ProfScope ps("loss_sum", (double)n, 4.0 * n, st);
+  TGP_LAUNCH(ps, loss_sum_k, dim3(1), dim3(256), 0, st, parts, n, inv_numel, loss);
   return launch_status();
 }
 

@@ -50,6 +50,12 @@ hipError_t conv_forward_tile(int n, const void* const* x, const void* w, const f
                              void* const* y, const ConvShape& s, int relu, bool dg,
                              hipStream_t st);
 extern int g_tile_cfg;
+// 3x3 and 1x1 convolutions of n micro-batches on float32 MFMA, any shape and
+// storage type (dg: the data gradient, as above); and the weight gradient's
+// partial slices and launch, each sum left pending in *defer[k].
+hipError_t conv_gen_forward(int dt, int n, const void* const* x, const void* w, const float* b,
+                            void* const* y, const ConvShape& s, int relu, bool dg,
+                            hipStream_t st);
 extern int g_rows32_cfg;
 extern int g_rows32_ch;
 extern int g_wgrad_ks;
@@ -82,6 +88,10 @@ hipError_t conv_wgrad_rows_launch_n(int n, const void* const* x, const void* con
                                     hipStream_t st, ReduceJob* const* defer);
 // The same weight gradient for any image size and channel counts that are
 // multiples of 8, same contracts.
+size_t conv_gen_wgrad_partial_floats(const ConvShape& s);
+hipError_t conv_gen_wgrad_launch(int dt, int n, const void* const* x, const void* const* dz,
+                                 float* const* dw, float* const* partial, const ConvShape& s,
+                                 hipStream_t st, ReduceJob* const* defer);
 bool wgrad_tile_ok(const ConvShape& s);
 int wgrad_general_splits(const ConvShape& s);
 int direct_wgrad_splits(long P);   // of P pixels, the per-element kernels
@@ -192,14 +202,13 @@ hipError_t upcat_forward(int dt, const void* prev, const void* skip, void* out, 
 hipError_t upcat_backward(int dt, const void* dcat, void* dprev, void* dskip, int nb, int H,
                           int W, int C1, int C2, hipStream_t st);
 
-// Squared-error part of one micro-batch: *loss_part = sum (y-t)^2 and
-// dy = 2 (y-t) * inv_numel, fixed-order reduction.
-size_t mse_partial_floats(long n);
-hipError_t mse_forward_backward(int dt, const void* y, const void* t, void* dy,
-                                float* loss_part, float* partial, long n, float inv_numel,
-                                hipStream_t st);
-// *loss = (sum_{i<m} parts[i]) * inv_numel, in order.
-hipError_t loss_finalize(const float* parts, int m, float inv_numel, float* loss,
+// Squared-error part of one micro-batch of n elements: mse_blocks(n) partial
+// sums of (y-t)^2 and dy = 2 (y-t) * inv_numel, fixed-order reduction.
+int mse_blocks(long n);
+hipError_t mse_forward_backward(int dt, const void* y, const void* t, void* dy, float* partial,
+                                long n, float inv_numel, hipStream_t st);
+// *loss = (sum of the step's n partial sums) * inv_numel, in a fixed order.
+hipError_t loss_finalize(const float* parts, int n, float inv_numel, float* loss,
                          hipStream_t st);
 
 // acc = g (overwrite) or acc + g, float32.

@@ -111,7 +111,7 @@ struct tgp_net {
   int nsets = 0;
   std::map<int, size_t> o_stash, o_stash_grad;  // offsets for micro-batch 1
   size_t stash_stride = 0;                      // bytes per micro-batch of stash area
-  size_t o_g0 = 0, o_g1 = 0, o_dinp = 0, o_dz = 0, o_part = 0, o_colpart = 0, o_msepart = 0,
+  size_t o_g0 = 0, o_g1 = 0, o_dinp = 0, o_dz = 0, o_part = 0, o_colpart = 0,
          o_loss = 0, o_fpart = 0, fpart_floats = 0;
   std::vector<size_t> o_bnd, o_gbnd;  // per (i, j) pipeline boundaries, [i*n + j]
   size_t o_out = 0, o_dy = 0, out_bytes_mb = 0;
@@ -929,9 +929,8 @@ struct GpuExec : Exec {
     long numel = n_mb * N->m;
     HIPCHK(tgpk::mse_forward_backward(N->dt, bnd(i, N->n),
                                       target + (size_t)(i - 1) * out_mb_bytes, gbnd(i, N->n),
-                                      (float*)W_(N, N->o_loss) + (i - 1),
-                                      (float*)T_(N, i, N->o_msepart), n_mb, 1.0f / (float)numel,
-                                      on(i)),
+                                      (float*)W_(N, N->o_loss) + (long)(i - 1) * tgpk::mse_blocks(n_mb),
+                                      n_mb, 1.0f / (float)numel, on(i)),
            "mse_forward_backward");
     return TGP_OK;
   }
@@ -1214,7 +1213,6 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
   // per-micro-batch gradients g_i and transformed weights
   size_t max_part = 0, max_col = 0;
   for (auto& Lr : N->L) {
-    Lr.o_gb = Lr.d.bias ? takeG(Lr.d.cout * 4) : 0;
     tgpk::ConvShape s{N->b, Lr.H, Lr.W, Lr.d.cin, Lr.d.cout, Lr.taps};
     Lr.has_wt = Lr.d.kind != TGP_DWCONV3X3 && tgpk::conv_dgrad_uses_wt(N->dt, s);
     Lr.o_wt = Lr.has_wt ? takeL(Lr.w_elems * N->esz) : 0;
@@ -1285,7 +1283,9 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
       if (li + 1 < N->L.size() && N->L[li + 1].mask_below && !Lr.defer_b)
         N->L[li + 1].mask_below = false;   // its sums need the slot
     }
-    Lr.o_gcol = Lr.defer_b ? takeG(Lr.o_gcol_floats * 4) : 0;
+    // the bias gradient itself, where a call reduces it at once, or its sums
+    Lr.o_gb = Lr.d.bias ? takeG(std::max<size_t>(Lr.defer_b ? Lr.o_gcol_floats : 0, Lr.d.cout) * 4) : 0;
+    Lr.o_gcol = Lr.o_gb;
     if (Lr.o_gcol_floats && !Lr.defer_b && (packs == 0 || 256 % packs == 0))
       max_col = std::max(max_col, Lr.o_gcol_floats);
     if (Lr.d.bias) max_col = std::max(max_col, tgpk::colsum_partial_floats(P, Lr.d.cout));
@@ -1318,8 +1318,7 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
   const LayerRt& last = N->L.back();
   long out_mb = (long)N->b * last.H * last.W * last.d.cout;
   N->out_bytes_mb = out_mb * N->esz;
-  N->o_msepart = takeL(tgpk::mse_partial_floats(out_mb) * 4);
-  N->o_loss = take(m * 4);
+  N->o_loss = take((size_t)m * tgpk::mse_blocks(out_mb) * 4);   // partial sums of the loss
   // pipeline boundaries
   N->o_bnd.assign((size_t)m * n + n, 0);
   N->o_gbnd.assign((size_t)m * n + n, 0);
@@ -1753,7 +1752,9 @@ tgp_status tgp_pipeline_step(tgp_net* N, const void* x, const void* target, int 
   if (r != TGP_OK) return r;
   const LayerRt& last = N->L.back();
   long numel = (long)N->B * last.H * last.W * last.d.cout;
-  HIPCHK(tgpk::loss_finalize((const float*)W_(N, N->o_loss), m, 1.0f / (float)numel, loss_dev,
+  HIPCHK(tgpk::loss_finalize((const float*)W_(N, N->o_loss),
+                             m * tgpk::mse_blocks((long)N->b * last.H * last.W * last.d.cout),
+                             1.0f / (float)numel, loss_dev,
                              S(stream)),
          "loss_finalize");
   return TGP_OK;

@@ -7,10 +7,12 @@ import pytest
 import torch
 
 import paper_2004_09910_amd as tgp
-from gpu_util import check_stage, gpu_stage, oracle_stage, say
+from gpu_util import (check_network, check_stage, gpu_network, gpu_stage, oracle_network,
+                      oracle_stage, say)
 from paper_2004_09910_amd.harness import Session
 from workloads import specs
-from workloads.specs import BF16, CONV3X3, DWCONV3X3, FP32, PRO_MAXPOOL2, Layer, Net
+from workloads.specs import (BF16, CONV1X1, CONV3X3, DWCONV3X3, FP32, PRO_MAXPOOL2, Layer,
+                             Net)
 from workloads.synth import EXACT, NORMAL
 
 pytestmark = pytest.mark.gpu
@@ -130,4 +132,45 @@ def test_masked_depthwise_gradient_past_the_last_column(c, h, w):
     got = gpu_stage(net, BF16, 4, 2, 0, (4,), 1, family=EXACT)
     ref = oracle_stage(net, BF16, 0, 4, got["xv"], got["G"], family=EXACT, certify=True)
     check_stage(got, ref, BF16, f"cells c={c} {h}x{w}", EXACT)
+    got["sess"].close()
+
+
+@pytest.mark.parametrize("dtype,kind,cin,cout,h,w,B,m", [
+    (FP32, CONV3X3, 1, 1, 1, 1, 1, 1),
+    (FP32, CONV3X3, 3, 5, 7, 9, 4, 2),          # K = 27, scalar loads
+    (FP32, CONV3X3, 16, 16, 32, 32, 4, 2),      # the K step split over four waves
+    (FP32, CONV3X3, 72, 100, 40, 36, 2, 1),     # 64 x 32 and 64 x 64 tiles, ragged channels
+    (FP32, CONV3X3, 20, 68, 90, 61, 4, 2),
+    (FP32, CONV1X1, 130, 70, 11, 13, 2, 1),
+    (FP32, CONV1X1, 8, 24, 100, 90, 2, 2),      # 32 x 128 tiles
+    (BF16, CONV3X3, 3, 64, 33, 29, 4, 2),       # an image layer
+    (BF16, CONV3X3, 64, 3, 20, 12, 2, 1),
+    (BF16, CONV3X3, 5, 7, 9, 11, 2, 2),
+    (BF16, CONV3X3, 12, 20, 17, 5, 2, 1),       # multiples of 4, not of 8
+    (BF16, CONV1X1, 1, 1, 5, 3, 2, 1),
+    (BF16, CONV1X1, 36, 28, 19, 21, 4, 2),
+])
+def test_float32_matrix_convolutions(dtype, kind, cin, cout, h, w, B, m):
+    run_and_check(Layer(kind, cin, cout), h, w, dtype, B, m,
+                  f"{'fp32' if dtype == FP32 else 'bf16'} kind {kind} {cin}->{cout} @{h}x{w}")
+
+
+def test_float32_matrix_convolutions_groups_are_bitwise():
+    net = one_layer(Layer(CONV3X3, 12, 36), 19, 23)
+    one = gpu_stage(net, FP32, 6, 6, 0, (1,), 1)
+    grp = gpu_stage(net, FP32, 6, 6, 0, (1,), 1, lanes=6, group=6, serial=True)
+    assert torch.equal(one["y"], grp["y"]) and torch.equal(one["dx"], grp["dx"])
+    for a, b in zip(one["grads"][0], grp["grads"][0]):
+        np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("dtype,h,w,B,m", [(BF16, 3, 5, 6, 3), (BF16, 40, 60, 2, 1),
+                                           (FP32, 130, 90, 2, 2)])
+def test_loss_of_odd_sizes(dtype, h, w, B, m):
+    """One-channel outputs whose micro-batch slices are not 16-byte aligned,
+    and more elements than one round of the loss's blocks."""
+    cin = 64 if dtype == BF16 else 4
+    net = one_layer(Layer(CONV1X1, cin, 1, relu=False), h, w)
+    got = gpu_network(net, dtype, B, m, 1, 0)
+    check_network(got, oracle_network(net, dtype, B), dtype, f"loss {h}x{w} B={B} m={m}")
     got["sess"].close()
