@@ -356,7 +356,8 @@ tgp_status tgp_profile_clear(void);
  * automatic per-shape plan; 1..7 row-stage tiles; 100..102 per-tap tiles;
  * 201..207 persistent row-stage tiles; 300 the 16x16x32 row-tiled kernel
  * (301 + i its configuration i); 400 the nine-tap whole-row kernel (401 + i
- * its configuration i).  A forced choice that does not fit a shape falls
+ * its configuration i); 500 the rectangular-tile 3x3 kernel (501 + i); 600
+ * the tiled 1x1 kernel (601 + i).  A forced choice that does not fit a shape falls
  * back to the per-tap kernel.
  *
  * tgp_debug_set_rowtile_mask(m) enables kernel families in the automatic

@@ -1256,10 +1256,10 @@ WgradPlan wgrad_plan(long P, int tiles, long E) {
 bool mfma_conv_ok(int dt, int cin, int cout) {
   return dt == 0 && cin % 64 == 0 && cout % 64 == 0;
 }
-// Shapes conv_forward_mfma takes: those, and 3x3 layers of the
-// rectangular-tile kernel.
+// Shapes conv_forward_mfma takes: those, and the layers of the kernels for
+// any multiple of 8 channels.
 bool mfma_fwd_ok(int dt, const ConvShape& s) {
-  return mfma_conv_ok(dt, s.cin, s.cout) || (dt == 0 && conv_tile_ok(s));
+  return mfma_conv_ok(dt, s.cin, s.cout) || (dt == 0 && (conv_tile_ok(s) || conv1x1_tile_ok(s)));
 }
 
 // Forward tile configurations.  A configuration is chosen per shape by
@@ -1461,9 +1461,9 @@ PersTile pers_tile(int cfg) {
 FwdPlan fwd_plan(const ConvShape& s) {
   const long P = 4L * s.H * s.W;
   FwdPlan pl{0, 1};
-  if (s.cin % 64 || s.cout % 64) {   // the kernel that takes any multiple of 8
-    pl.cfg = 500;
-    if (g_fwd_variant >= 500) pl.cfg = g_fwd_variant;
+  if (s.cin % 64 || s.cout % 64) {   // the kernels that take any multiple of 8
+    pl.cfg = s.taps == 9 ? 500 : 600;
+    if (g_fwd_variant >= pl.cfg && g_fwd_variant < pl.cfg + 100) pl.cfg = g_fwd_variant;
     return pl;
   }
   // Measured per shape (3x3, kernel time in a step): the nine-tap
@@ -1489,13 +1489,15 @@ FwdPlan fwd_plan(const ConvShape& s) {
     pl.cfg = 150;  // 1x1, all weights resident in LDS
   } else if (conv_tile_ok(s)) {
     pl.cfg = 500;  // rectangular tiles
+  } else if (conv1x1_tile_ok(s)) {
+    pl.cfg = 600;  // 1x1 tiles
   } else {
     pl.cfg = 100;
   }
   if (g_fwd_variant > 0) pl.cfg = g_fwd_variant;
   if (pl.cfg == 150 && !conv1x1_res_ok(s)) pl.cfg = 100;
   if (pl.cfg >= 500) {
-    if (!conv_tile_ok(s)) pl.cfg = 100;
+    if (pl.cfg >= 600 ? !conv1x1_tile_ok(s) : !conv_tile_ok(s)) pl.cfg = 100;
     return pl;
   }
   if (pl.cfg >= 400) {
@@ -1540,20 +1542,26 @@ FwdPlan fwd_plan(const ConvShape& s) {
   return pl;
 }
 
-// The rectangular-tile kernel, in the configuration a forced plan names.
+// The rectangular-tile kernel (500 ..) or the 1x1 tile kernel (600 ..), in the
+// configuration a forced plan names.
 static hipError_t launch_tile_cfg(int cfg, int n, const void* const* x, const void* w,
                                   const float* b, void* const* y, const ConvShape& s, int relu,
                                   bool dg, hipStream_t st) {
+  if (s.taps == 1) {
+    g_1x1_cfg = cfg >= 601 ? cfg - 601 : -1;
+    const hipError_t e = conv_forward_1x1(n, x, w, b, y, s, relu, dg, st);
+    g_1x1_cfg = -1;
+    return e;
+  }
   g_tile_cfg = cfg >= 501 ? cfg - 501 : -1;
   const hipError_t e = conv_forward_tile(n, x, w, b, y, s, relu, dg, st);
   g_tile_cfg = -1;
   return e;
 }
 
-// Whether a shape's data gradient (t: its transposed shape) runs on the
-// rectangular-tile kernel, which reads the forward weights, and that launch
-// (also where a forced plan names another kernel but no transformed weights
-// were planned for).
+// Whether a shape's data gradient (t: its transposed shape) runs on a kernel
+// that reads the forward weights, and that launch (also where a forced plan
+// names another kernel but no transformed weights were planned for).
 bool conv_dgrad_tile_planned(const ConvShape& t) {
   t_in_dgrad = 1;
   const bool r = fwd_plan(t).cfg >= 500;
@@ -1562,8 +1570,9 @@ bool conv_dgrad_tile_planned(const ConvShape& t) {
 }
 hipError_t conv_dgrad_tile(int n, const void* const* dz, const void* w, void* const* dx,
                            const ConvShape& t, hipStream_t st) {
-  return launch_tile_cfg(g_fwd_variant >= 500 ? g_fwd_variant : 500, n, dz, w, nullptr, dx, t, 0,
-                         true, st);
+  const int base = t.taps == 9 ? 500 : 600;
+  const bool forced = g_fwd_variant >= base && g_fwd_variant < base + 100;
+  return launch_tile_cfg(forced ? g_fwd_variant : base, n, dz, w, nullptr, dx, t, 0, true, st);
 }
 
 size_t conv_forward_partial_floats(int dt, const ConvShape& s) {
@@ -1676,12 +1685,13 @@ static bool use_wgrad_tile(const ConvShape& s) {
 }
 // Shapes conv_wgrad_mfma takes.
 bool mfma_wgrad_ok(int dt, const ConvShape& s) {
-  return mfma_conv_ok(dt, s.cin, s.cout) || (dt == 0 && wgrad_tile_ok(s));
+  return mfma_conv_ok(dt, s.cin, s.cout) || (dt == 0 && (wgrad_tile_ok(s) || wgrad1x1_tile_ok(s)));
 }
 
 size_t wgrad_mfma_partial_floats(const ConvShape& s) {
   if (use_wgrad_rows(s)) return wgrad_rows_partial_floats(s);
   if (use_wgrad_tile(s)) return wgrad_tile_partial_floats(s);
+  if (wgrad1x1_tile_ok(s)) return wgrad1x1_tile_partial_floats(s);
   int tiles = s.taps * (s.cin / 64) * (s.cout / 64);
   if (s.cin % 128 == 0 && s.cout % 128 == 0) tiles = s.taps * (s.cin / 128) * (s.cout / 128);
   long E = (long)s.cout * s.taps * s.cin;
@@ -1740,10 +1750,11 @@ hipError_t conv_wgrad_mfma(const void* x, const void* dz, float* dw, float* part
                            ReduceJob* defer) {
   if (use_wgrad_rows(s)) return conv_wgrad_rows_launch(x, dz, dw, partial, s, st, extra, defer);
   long E = (long)s.cout * s.taps * s.cin;
-  if (use_wgrad_tile(s)) {
+  if (use_wgrad_tile(s) || wgrad1x1_tile_ok(s)) {
     ReduceJob job;
     ReduceJob* const jp = defer ? defer : &job;
-    const hipError_t e = conv_wgrad_tile_launch(1, &x, &dz, &dw, &partial, s, st, &jp);
+    const hipError_t e = s.taps == 1 ? wgrad1x1_tile_launch(1, &x, &dz, &dw, &partial, s, st, &jp)
+                                     : conv_wgrad_tile_launch(1, &x, &dz, &dw, &partial, s, st, &jp);
     if (e != hipSuccess) return e;
     if (defer) return extra ? hipErrorInvalidValue : hipSuccess;
     if (job.S > 1) return splitk_reduce_launch(job.part, dw, E, job.S, st, extra);
@@ -1857,6 +1868,7 @@ hipError_t conv_wgrad_mfma_n(int n, const void* const* x, const void* const* dz,
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
   if (use_wgrad_rows(s)) return conv_wgrad_rows_launch_n(n, x, dz, dw, part, s, st, defer);
   if (use_wgrad_tile(s)) return conv_wgrad_tile_launch(n, x, dz, dw, part, s, st, defer);
+  if (wgrad1x1_tile_ok(s)) return wgrad1x1_tile_launch(n, x, dz, dw, part, s, st, defer);
   const long E = (long)s.cout * s.taps * s.cin;
   WgradPlan pl;
   float* pp[kMaxGroup];

@@ -18,6 +18,16 @@ struct ConvShape {
   long pixels() const { return (long)nb * H * W; }
 };
 
+// out[e] = sum_{k < S} part[k E + e] in a fixed order that depends only on
+// (E, S); `extra`, if given, is a second independent sum of the same kind run
+// in the same launch (its order then also depends on the first sum's S).
+struct ReduceJob {
+  const float* part;
+  float* out;
+  long E;
+  int S;
+};
+
 // y = act(conv(x, w) + b); w is KRSC [cout][taps][cin].  Deep shapes split
 // the K loop; their fp32 partials go to `part` (conv_forward_partial_floats
 // floats; part_cap is the space available).
@@ -50,6 +60,18 @@ hipError_t conv_forward_tile(int n, const void* const* x, const void* w, const f
                              void* const* y, const ConvShape& s, int relu, bool dg,
                              hipStream_t st);
 extern int g_tile_cfg;
+// The same for 1x1 layers (bf16; Cin and Cout multiples of 8), and their
+// weight gradient, each sum left pending in *defer[k].
+bool conv1x1_tile_ok(const ConvShape& s);
+hipError_t conv_forward_1x1(int n, const void* const* x, const void* w, const float* b,
+                            void* const* y, const ConvShape& s, int relu, bool dg,
+                            hipStream_t st);
+bool wgrad1x1_tile_ok(const ConvShape& s);
+size_t wgrad1x1_tile_partial_floats(const ConvShape& s);
+hipError_t wgrad1x1_tile_launch(int n, const void* const* x, const void* const* dz,
+                                float* const* dw, float* const* partial, const ConvShape& s,
+                                hipStream_t st, ReduceJob* const* defer);
+extern int g_1x1_cfg;
 // 3x3 and 1x1 convolutions of n micro-batches on float32 MFMA, any shape and
 // storage type (dg: the data gradient, as above); and the weight gradient's
 // partial slices and launch, each sum left pending in *defer[k].
@@ -65,15 +87,6 @@ extern thread_local int t_in_dgrad;
 // (bf16; W in {48, 96, 192}, Cin and Cout multiples of 64): whether it
 // supports a shape, the fp32 partial-slice scratch it needs, and the launch
 // (dw = sum over pixels, summed over its K ranges in a fixed order).
-// out[e] = sum_{k < S} part[k E + e] in a fixed order that depends only on
-// (E, S); `extra`, if given, is a second independent sum of the same kind run
-// in the same launch (its order then also depends on the first sum's S).
-struct ReduceJob {
-  const float* part;
-  float* out;
-  long E;
-  int S;
-};
 hipError_t splitk_reduce_launch(const float* part, float* out, long E, int S, hipStream_t st,
                                const ReduceJob* extra = nullptr);
 bool wgrad_rows_ok(const ConvShape& s);

@@ -174,3 +174,30 @@ def test_loss_of_odd_sizes(dtype, h, w, B, m):
     got = gpu_network(net, dtype, B, m, 1, 0)
     check_network(got, oracle_network(net, dtype, B), dtype, f"loss {h}x{w} B={B} m={m}")
     got["sess"].close()
+
+
+@pytest.mark.parametrize("cin,cout,h,w,B,m", [
+    (8, 8, 1, 1, 1, 1),
+    (24, 40, 17, 33, 4, 2),       # one partial stage
+    (72, 200, 13, 9, 2, 1),       # a second stage of 8 channels, ragged channel tiles
+    (264, 64, 7, 7, 2, 2),        # the deep ring
+    (64, 32, 40, 30, 4, 2),       # 32-channel tiles
+    (192, 136, 60, 50, 4, 1),     # 128 x 128 tiles
+])
+def test_conv1x1_any_channels(cin, cout, h, w, B, m):
+    run_and_check(Layer(CONV1X1, cin, cout), h, w, BF16, B, m,
+                  f"conv1x1 {cin}->{cout} @{h}x{w} B={B} m={m}")
+
+
+@pytest.mark.parametrize("cfg", range(5))
+def test_conv1x1_tile_configurations(cfg):
+    """Each tile of the 1x1 kernel, forced, with ragged tiles on both sides;
+    the sums run in one order, so their bits agree, in groups too."""
+    net = one_layer(Layer(CONV1X1, 72, 136), 11, 17)
+    base = gpu_stage(net, BF16, 3, 3, 0, (1,), 1, lanes=3, group=3, serial=True)
+    tgp.debug_set_fwd_variant(601 + cfg)
+    try:
+        got = run_and_check(Layer(CONV1X1, 72, 136), 11, 17, BF16, 3, 3, f"1x1 tile cfg {cfg}")
+    finally:
+        tgp.debug_set_fwd_variant(0)
+    assert torch.equal(got["y"], base["y"]) and torch.equal(got["dx"], base["dx"])
