@@ -99,6 +99,56 @@ __global__ __launch_bounds__(256) void conv1x1_small_fwd_k(const T* __restrict__
   }
 }
 
+// Its data gradient dx[p][ci] = sum_co dz[p][co] w[co][ci]: a thread keeps one
+// channel pack's weights and takes kSmallPix pixels, so that a block writes
+// whole rows; bound by that write (64 -> 1 at 192 x 192 x 4: 29 us on the
+// float32 matrix unit, 8.6 here).  blockIdx.y is the micro-batch.  Needs
+// 256 % (Cin / pack) == 0.
+constexpr int kSmallPix = 4;
+template <typename T>
+struct SmallDg {
+  const T* dz[kMaxGroup];
+  T* dx[kMaxGroup];
+};
+template <typename T>
+__global__ __launch_bounds__(256) void dgrad1x1_small_k(SmallDg<T> io, const T* __restrict__ w,
+                                                        long P, int Cin, int Cout) {
+  constexpr int N = Pk<T>::N;
+  const int CP = Cin / N, cp = threadIdx.x % CP, nl = 256 / CP;
+  const T* __restrict__ dz = pickg(io.dz, blockIdx.y);
+  T* __restrict__ dx = pickg(io.dx, blockIdx.y);
+  float wv[kSmallCo][N];
+#pragma unroll
+  for (int co = 0; co < kSmallCo; ++co)
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      wv[co][i] = co < Cout ? Elt<T>::ld(w + (long)co * Cin + cp * N + i) : 0.f;
+  const long p0 = (long)blockIdx.x * nl * kSmallPix + threadIdx.x / CP;
+  float g[kSmallPix][kSmallCo];
+#pragma unroll
+  for (int u = 0; u < kSmallPix; ++u)
+#pragma unroll
+    for (int co = 0; co < kSmallCo; ++co) {   // past the end: the last pixel, unused
+      const long p = p0 + (long)u * nl < P ? p0 + (long)u * nl : P - 1;
+      g[u][co] = Elt<T>::ld(dz + p * Cout + (co < Cout ? co : 0));
+    }
+#pragma unroll
+  for (int u = 0; u < kSmallPix; ++u) {
+    const long p = p0 + (long)u * nl;
+    if (p >= P) break;
+    float acc[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) acc[i] = 0.f;
+#pragma unroll
+    for (int co = 0; co < kSmallCo; ++co) {
+      if (co >= Cout) break;
+#pragma unroll
+      for (int i = 0; i < N; ++i) acc[i] += g[u][co] * wv[co][i];
+    }
+    st16(dx + p * Cin + cp * N, Pk<T>::pk(acc));
+  }
+}
+
 // Its weight gradient dW[co][ci] = sum_p dz[p][co] x[p][ci]: block b covers
 // pixels [b*rows, (b+1)*rows); thread t takes channel pack t % CP of pixels
 // t / CP, t / CP + 256 / CP, ... in order; row lanes are then added in order
@@ -666,23 +716,31 @@ __global__ __launch_bounds__(256) void pool_relu_bwd_bias_k(RbGroup<T> ga, int r
 }
 
 // Column sums of a P x C matrix: block (cg, pb) sums rows [pb*rows, ...) for
-// channels cg*64 .. +63; 4 row lanes, combined in fixed order.
+// channels cg*64 .. +63, 256 / (channels) row lanes, combined in fixed order (a
+// one-channel head then has 256 lanes at work: 4 of them took 25 us for 147456
+// rows, 3.9 now).
 template <typename T>
 __global__ __launch_bounds__(256) void colsum_k(const T* __restrict__ a, float* __restrict__ part,
                                                 long P, int C, long rows) {
-  __shared__ float red[4][64];
-  int c = blockIdx.x * 64 + (threadIdx.x & 63);
-  int lane = threadIdx.x >> 6;
-  long p0 = (long)blockIdx.y * rows, p1 = p0 + rows < P ? p0 + rows : P;
+  __shared__ float red[256];
+  const int c0 = blockIdx.x * 64, nc = C - c0 < 64 ? C - c0 : 64;
+  const int nl = 256 / nc, col = threadIdx.x % nc, lane = threadIdx.x / nc;
+  const long p0 = (long)blockIdx.y * rows, p1 = p0 + rows < P ? p0 + rows : P;
   float s = 0.f;
-  if (c < C)
-    for (long p = p0 + lane; p < p1; p += 4) s += Elt<T>::ld(a + p * C + c);
-  red[lane][threadIdx.x & 63] = s;
-  __syncthreads();
-  if (lane == 0 && c < C) {
-    int k = threadIdx.x & 63;
-    part[(long)blockIdx.y * C + c] = ((red[0][k] + red[1][k]) + red[2][k]) + red[3][k];
+  if (lane < nl) {
+#pragma unroll 4
+    for (long p = p0 + lane; p < p1; p += nl) s += Elt<T>::ld(a + p * C + c0 + col);
   }
+  red[threadIdx.x] = s;
+  __syncthreads();
+  int n = nl;
+  while (n > 1) {                                               // block-uniform
+    const int h = (n + 1) / 2;
+    if (lane < n - h) red[threadIdx.x] += red[threadIdx.x + h * nc];
+    __syncthreads();
+    n = h;
+  }
+  if (lane == 0) part[(long)blockIdx.y * C + c0 + col] = red[threadIdx.x];
 }
 
 // depthwise wgrad partials: thread (c, tap) of split s
@@ -937,6 +995,24 @@ __host__ __device__ __forceinline__ int acc_c4(int S) {
   return c;
 }
 
+// Columns e .. e + 3 of a row of E floats; one by one where the rows' 16-byte
+// packs are not aligned (E % 4, tile-uniform).
+__device__ __forceinline__ float4 ld_cols(const float* row, long e, long E) {
+  if (E % 4 == 0) return *(const float4*)(row + e);
+  return make_float4(row[e], e + 1 < E ? row[e + 1] : 0.f, e + 2 < E ? row[e + 2] : 0.f,
+                     e + 3 < E ? row[e + 3] : 0.f);
+}
+__device__ __forceinline__ void st_cols(float* row, long e, long E, float4 v) {
+  if (E % 4 == 0) {
+    *(float4*)(row + e) = v;
+    return;
+  }
+  row[e] = v.x;
+  if (e + 1 < E) row[e + 1] = v.y;
+  if (e + 2 < E) row[e + 2] = v.z;
+  if (e + 3 < E) row[e + 3] = v.w;
+}
+
 // NG: micro-batches per entry as a template constant (1) or b.ng (0).
 template <int NG>
 __global__ __launch_bounds__(1024) void reduce_accumulate_k(AccBatch b, int overwrite,
@@ -952,20 +1028,6 @@ __global__ __launch_bounds__(1024) void reduce_accumulate_k(AccBatch b, int over
     const long E = b.n[k];
     const int S = b.S[k];
     float* __restrict__ acc = b.acc[k];
-    if (E % 4) {   // tile-uniform
-      const long e = bx * 1024 + threadIdx.x;
-      if (e < E) {
-        float cur = 0.f;
-        for (int q = 0; q < ng; ++q) {
-          const float* __restrict__ part = b.g[k] + q * b.gstride[k];
-          float r = 0.f;
-          for (int s = 0; s < S; ++s) r += part[(long)s * E + e];
-          cur = q > 0 ? cur + r : overwrite ? r : acc[e] + r;
-        }
-        acc[e] = cur;
-      }
-      continue;
-    }
     const int C4 = acc_c4(S), LANES = 1024 / C4;
     const int col = threadIdx.x % C4, lane = threadIdx.x / C4;
     const long e4 = (bx * C4 + col) * 4;
@@ -979,7 +1041,7 @@ __global__ __launch_bounds__(1024) void reduce_accumulate_k(AccBatch b, int over
           float4 t[8];
 #pragma unroll
           for (int u = 0; u < 8; ++u)
-            t[u] = s + u * LANES < S ? *(const float4*)(part + (long)(s + u * LANES) * E + e4)
+            t[u] = s + u * LANES < S ? ld_cols(part + (long)(s + u * LANES) * E, e4, E)
                                      : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
           for (int u = 0; u < 8; ++u) {
@@ -1007,12 +1069,12 @@ __global__ __launch_bounds__(1024) void reduce_accumulate_k(AccBatch b, int over
         } else if (overwrite) {
           cur = r;
         } else {
-          const float4 o = *(const float4*)(acc + e4);
+          const float4 o = ld_cols(acc, e4, E);
           cur.x = o.x + r.x; cur.y = o.y + r.y; cur.z = o.z + r.z; cur.w = o.w + r.w;
         }
       }
     }
-    if (lane == 0 && e4 < E) *(float4*)(acc + e4) = cur;
+    if (lane == 0 && e4 < E) st_cols(acc, e4, E, cur);
     if (NG == 1 && LANES > 1) __syncthreads();   // red is rewritten by the next tile
   }
 }
@@ -1035,6 +1097,28 @@ static bool small1x1_ok(int dt, const ConvShape& s, const void* x) {
   return CP <= 256 && 256 % CP == 0;
 }
 
+template <typename T>
+static hipError_t launch_dgrad_small(int n, const void* const* dz, const void* w, void* const* dx,
+                                     const ConvShape& s, hipStream_t st) {
+  SmallDg<T> io;
+  for (int k = 0; k < kMaxGroup; ++k) {   // unused entries repeat the first
+    io.dz[k] = (const T*)dz[k < n ? k : 0];
+    io.dx[k] = (T*)dx[k < n ? k : 0];
+  }
+  const long P = s.pixels(), per = 256 / (s.cin / Pk<T>::N) * kSmallPix;
+  if (P == 0) return hipSuccess;
+  ProfScope ps("dgrad1x1_small", 2.0 * n * P * s.cout * s.cin,
+               (double)sizeof(T) * n * P * (s.cin + s.cout), st);
+  TGP_LAUNCH(ps, dgrad1x1_small_k<T>, dim3(cdiv(P, per), n), dim3(256), 0, st, io, (const T*)w, P,
+             s.cin, s.cout);
+  return launch_status();
+}
+static hipError_t dgrad1x1_small(int dt, int n, const void* const* dz, const void* w,
+                                 void* const* dx, const ConvShape& s, hipStream_t st) {
+  return dt == 0 ? launch_dgrad_small<bf16_t>(n, dz, w, dx, s, st)
+                 : launch_dgrad_small<float>(n, dz, w, dx, s, st);
+}
+
 hipError_t conv_forward(int dt, const void* x, const void* w, const float* b, void* y,
                         const ConvShape& s, int relu, float* part, size_t part_cap,
                         hipStream_t st) {
@@ -1052,6 +1136,7 @@ hipError_t conv_forward(int dt, const void* x, const void* w, const float* b, vo
                  (const float*)x, (const float*)w, b, (float*)y, P, s.cin, s.cout, relu);
     return launch_status();
   }
+  if (conv_stem_ok(dt, s)) return conv_stem_forward(1, &x, w, b, &y, s, relu, st);
   return conv_gen_forward(dt, 1, &x, w, b, &y, s, relu, false, st);
 }
 
@@ -1070,6 +1155,7 @@ hipError_t conv_dgrad(int dt, const void* dz, const void* w, const void* wt, voi
     t_in_dgrad = 0;
     return e;
   }
+  if (small1x1_ok(dt, s, dx)) return dgrad1x1_small(dt, 1, &dz, w, &dx, s, st);
   return conv_gen_forward(dt, 1, &dz, w, nullptr, &dx, t, 0, true, st);
 }
 
@@ -1081,7 +1167,7 @@ size_t conv_wgrad_partial_floats(int dt, const ConvShape& s) {
     const size_t small = (size_t)cdiv(s.pixels(), relu_bias_rows(s.pixels(), s.cin, N, 1024)) * s.cout * s.cin;
     return direct > small ? direct : small;
   }
-  return conv_gen_wgrad_partial_floats(s);
+  return conv_stem_ok(dt, s) ? conv_stem_wgrad_partial_floats(s) : conv_gen_wgrad_partial_floats(s);
 }
 
 hipError_t conv_wgrad(int dt, const void* x, const void* dz, float* dw, float* partial,
@@ -1114,7 +1200,9 @@ hipError_t conv_wgrad(int dt, const void* x, const void* dz, float* dw, float* p
   }
   ReduceJob job;
   ReduceJob* const jp = defer ? defer : &job;
-  const hipError_t e = conv_gen_wgrad_launch(dt, 1, &x, &dz, &dw, &partial, s, st, &jp);
+  const hipError_t e = conv_stem_ok(dt, s)
+                           ? conv_stem_wgrad_launch(1, &x, &dz, &dw, &partial, s, st, &jp)
+                           : conv_gen_wgrad_launch(dt, 1, &x, &dz, &dw, &partial, s, st, &jp);
   if (e != hipSuccess || defer) return e;
   if (job.S > 1) return splitk_reduce_launch(job.part, dw, job.E, job.S, st, extra);
   return extra ? splitk_reduce_launch(extra->part, extra->out, extra->E, extra->S, st) : hipSuccess;
@@ -1126,6 +1214,7 @@ hipError_t conv_forward_n(int dt, int n, const void* const* x, const void* w, co
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
   if (mfma_fwd_ok(dt, s))
     return conv_forward_mfma_n(n, x, w, b, y, s, relu, part, part_cap, st);
+  if (conv_stem_ok(dt, s)) return conv_stem_forward(n, x, w, b, y, s, relu, st);
   bool small = false;
   for (int k = 0; k < n; ++k) small = small || small1x1_ok(dt, s, x[k]);
   if (!small) return conv_gen_forward(dt, n, x, w, b, y, s, relu, false, st);
@@ -1148,6 +1237,9 @@ hipError_t conv_dgrad_n(int dt, int n, const void* const* dz, const void* w, con
     t_in_dgrad = 0;
     return e;
   }
+  bool small = true;
+  for (int k = 0; k < n; ++k) small = small && small1x1_ok(dt, s, dx[k]);
+  if (small) return dgrad1x1_small(dt, n, dz, w, dx, s, st);
   return conv_gen_forward(dt, n, dz, w, nullptr, dx, t, 0, true, st);
 }
 
@@ -1158,6 +1250,7 @@ hipError_t conv_wgrad_n(int dt, int n, const void* const* x, const void* const* 
   for (int k = 0; k < n; ++k)
     if (!defer[k]) return hipErrorInvalidValue;
   if (mfma_wgrad_ok(dt, s)) return conv_wgrad_mfma_n(n, x, dz, dw, part, s, st, defer);
+  if (conv_stem_ok(dt, s)) return conv_stem_wgrad_launch(n, x, dz, dw, part, s, st, defer);
   bool small = false;
   for (int k = 0; k < n; ++k) small = small || small1x1_ok(dt, s, x[k]);
   if (!small) return conv_gen_wgrad_launch(dt, n, x, dz, dw, part, s, st, defer);
@@ -1634,7 +1727,7 @@ hipError_t grad_accumulate_batch(AccBatch b, int overwrite, hipStream_t st) {
     b.n[used] = b.n[k]; b.S[used] = b.S[k];
     b.blk0[used] = (int)blocks;
     const int C4 = acc_c4(b.S[k]);
-    blocks += b.n[k] % 4 ? cdiv(b.n[k], 1024L) : cdiv(b.n[k], 4L * C4);
+    blocks += cdiv(b.n[k], 4L * C4);
     bytes += 4.0 * b.n[k] * ((double)b.S[k] * b.ng + (overwrite ? 1 : 2));
     ++used;
   }

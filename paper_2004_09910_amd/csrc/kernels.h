@@ -28,6 +28,15 @@ struct ReduceJob {
   int S;
 };
 
+// bf16 3x3 convolutions of 1 .. 7 input channels (conv_stem.hip).
+bool conv_stem_ok(int dt, const ConvShape& s);
+hipError_t conv_stem_forward(int n, const void* const* x, const void* w, const float* b,
+                             void* const* y, const ConvShape& s, int relu, hipStream_t st);
+size_t conv_stem_wgrad_partial_floats(const ConvShape& s);
+hipError_t conv_stem_wgrad_launch(int n, const void* const* x, const void* const* dz,
+                                  float* const* dw, float* const* partial, const ConvShape& s,
+                                  hipStream_t st, ReduceJob* const* defer);
+
 // y = act(conv(x, w) + b); w is KRSC [cout][taps][cin].  Deep shapes split
 // the K loop; their fp32 partials go to `part` (conv_forward_partial_floats
 // floats; part_cap is the space available).

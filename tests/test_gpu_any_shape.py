@@ -201,3 +201,27 @@ def test_conv1x1_tile_configurations(cfg):
     finally:
         tgp.debug_set_fwd_variant(0)
     assert torch.equal(got["y"], base["y"]) and torch.equal(got["dx"], base["dx"])
+
+
+@pytest.mark.parametrize("cin,cout,h,w,B,m", [
+    (1, 8, 1, 1, 1, 1),
+    (1, 72, 9, 5, 2, 2),          # one block of 16 terms, a second channel tile
+    (3, 64, 33, 47, 6, 2),        # two blocks; rows no multiple of a tile
+    (4, 24, 130, 70, 2, 1),       # three blocks, two tiles of terms; several ranges
+    (7, 136, 31, 3, 15, 3),       # all 63 terms
+])
+def test_conv3x3_few_input_channels(cin, cout, h, w, B, m):
+    run_and_check(Layer(CONV3X3, cin, cout), h, w, BF16, B, m,
+                  f"conv3x3 {cin}->{cout} @{h}x{w} B={B} m={m}")
+
+
+@pytest.mark.parametrize("dt", [BF16, FP32])
+@pytest.mark.parametrize("cin,cout,h,w,B,m", [
+    (8, 1, 1, 1, 1, 1),
+    (64, 1, 29, 31, 6, 2),
+    (256, 3, 17, 40, 6, 3),       # bias sums of rows of three
+    (16, 4, 70, 66, 4, 1),
+])
+def test_conv1x1_few_output_channels(dt, cin, cout, h, w, B, m):
+    run_and_check(Layer(CONV1X1, cin, cout, relu=False), h, w, dt, B, m,
+                  f"conv1x1 {cin}->{cout} @{h}x{w} B={B} m={m}")
