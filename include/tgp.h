@@ -284,15 +284,17 @@ tgp_status tgp_grad_accumulate_n(tgp_net* net, int j, int i0, int count, int ove
  * F'_{i,j} (if checkpointed) + B_{i,j} + grad accumulate.  Writes the loss
  * (float32) to *loss_dev and the network output to y_out (may be NULL).
  * B, m, n and ckpt_mode must match tgp_plan and tgp_set_partition.
- * With more than one lane (tgp_set_lanes) the step forks from `stream`
- * onto library-owned streams (default priority), micro-batch i's tasks on
- * lane (i - 1) % lanes and the accumulations, in schedule order, on one
- * more stream that waits for each B_{i,j}, and joins back into `stream`
- * before the loss; the results are bit-identical to one lane.  The streams
- * are created on first use (on the current device) and destroyed with the
- * net; the fork and join are events, so the step can be captured into a
- * HIP graph from `stream`.  If a task fails (TGP_EHIP) the step is
- * abandoned: the lanes are still joined into `stream`, every task returns to
+ * With more than one lane (tgp_set_lanes) the schedule's tasks are groups
+ * of `lanes` consecutive micro-batches, whose layers' launches take the
+ * whole group (tgp_stage_forward_n, tgp_stage_backward_recompute_n) on
+ * `stream`, and the accumulations run, in schedule order, on a
+ * library-owned stream (default priority) that waits for each group's
+ * backward and joins back into `stream` before the loss; the results are
+ * bit-identical to one lane.  The stream is created on first use (on the
+ * current device) and destroyed with the net; the fork and join are events,
+ * so the step can be captured into a HIP graph from `stream`.  If a task
+ * fails (TGP_EHIP) the step is abandoned: the accumulations are still joined
+ * into `stream`, every task returns to
  * its idle state, and the next tgp_pipeline_step (or stage call) starts a
  * fresh step; the work already enqueued still runs and the outputs and
  * accumulators hold partial results. */

@@ -1200,10 +1200,14 @@ __global__ __launch_bounds__(1024) void splitk_reduce(const float* __restrict__ 
 // The same sum for E not a multiple of 4 (e.g. the bias of a one-channel
 // head): a block takes C = 2^lc columns (up to 64), 256 / C split lanes added
 // in a fixed tree (one thread a column took 10.7 us for 144 splits of one, this 4.0).
-__global__ __launch_bounds__(256) void splitk_reduce_scalar(const float* __restrict__ part,
-                                                            float* __restrict__ out, long E,
-                                                            int S, int lc) {
+struct SumGroup {
+  const float* part[kMaxGroup];
+  float* out[kMaxGroup];
+};
+__global__ __launch_bounds__(256) void splitk_reduce_scalar(SumGroup io, long E, int S, int lc) {
   __shared__ float red[256];
+  const float* __restrict__ part = pickg(io.part, blockIdx.y);
+  float* __restrict__ out = pickg(io.out, blockIdx.y);
   const int C = 1 << lc, col = threadIdx.x & (C - 1), lane = threadIdx.x >> lc;
   const long e = (long)blockIdx.x * C + col;
   float acc = 0.f;
@@ -1781,6 +1785,21 @@ hipError_t conv_wgrad_mfma(const void* x, const void* dz, float* dw, float* part
   return splitk_reduce_launch(partial, dw, E, pl.S, st, extra);
 }
 
+hipError_t splitk_reduce_n(int n, const float* const* part, float* const* out, long E, int S,
+                           hipStream_t st) {
+  if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
+  SumGroup io;
+  for (int k = 0; k < kMaxGroup; ++k) {   // unused entries repeat the first
+    io.part[k] = part[k < n ? k : 0];
+    io.out[k] = out[k < n ? k : 0];
+  }
+  int lc = 0;
+  while (lc < 6 && (1L << lc) < E) ++lc;
+  ProfScope ps("splitk_reduce", 0.0, 4.0 * n * E * (S + 1), st);
+  TGP_LAUNCH(ps, splitk_reduce_scalar, dim3(cdiv(E, 1L << lc), n), dim3(256), 0, st, io, E, S, lc);
+  return launch_status();
+}
+
 hipError_t splitk_reduce_launch(const float* part, float* out, long E, int S, hipStream_t st,
                                const ReduceJob* extra) {
   if (extra && (E % 4 || extra->E % 4)) {   // scalar sums run on their own
@@ -1788,15 +1807,9 @@ hipError_t splitk_reduce_launch(const float* part, float* out, long E, int S, hi
     if (e != hipSuccess) return e;
     extra = nullptr;
   }
+  if (E % 4) return splitk_reduce_n(1, &part, &out, E, S, st);
   ProfScope ps("splitk_reduce", 0.0,
                4.0 * E * (S + 1) + (extra ? 4.0 * extra->E * (extra->S + 1) : 0.0), st);
-  if (E % 4) {
-    int lc = 0;
-    while (lc < 6 && (1L << lc) < E) ++lc;
-    TGP_LAUNCH(ps, splitk_reduce_scalar, dim3(cdiv(E, 1L << lc)), dim3(256), 0, st, part, out, E, S,
-               lc);
-    return launch_status();
-  }
   // many splits of few columns: 16 columns x 64 split lanes; few splits:
   // 256 columns x 4 lanes (chosen by the first sum's S; the second, if any,
   // uses the same layout)

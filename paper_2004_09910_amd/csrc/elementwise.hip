@@ -64,6 +64,27 @@ template <> struct Pk<float> {
 template <typename T> __device__ __forceinline__ uint4 ld16(const T* p) { return *(const uint4*)p; }
 template <typename T> __device__ __forceinline__ void st16(T* p, uint4 v) { *(uint4*)p = v; }
 
+// Up to four tensors of each of a launch's n (1 .. kMaxGroup) micro-batches;
+// blockIdx.y (or .z) selects one.  Unused entries repeat the first.
+struct Group {
+  const void* a[kMaxGroup];
+  const void* b[kMaxGroup];
+  const void* c[kMaxGroup];
+  void* y[kMaxGroup];
+};
+Group make_group(int n, void* const* y, const void* const* a, const void* const* b = nullptr,
+                 const void* const* c = nullptr) {
+  Group g{};
+  for (int k = 0; k < kMaxGroup; ++k) {
+    const int q = k < n ? k : 0;
+    g.y[k] = y[q];
+    if (a) g.a[k] = a[q];
+    if (b) g.b[k] = b[q];
+    if (c) g.c[k] = c[q];
+  }
+  return g;
+}
+
 // ---------------------------------------------------------------- few-output 1x1
 
 // 1x1 convolution with at most kSmallCo output channels (the network head):
@@ -71,12 +92,12 @@ template <typename T> __device__ __forceinline__ void st16(T* p, uint4 v) { *(ui
 constexpr int kSmallCo = 4;
 
 template <typename T>
-__global__ __launch_bounds__(256) void conv1x1_small_fwd_k(const T* __restrict__ x,
-                                                           const T* __restrict__ w,
-                                                           const float* __restrict__ b,
-                                                           T* __restrict__ y, long P, int Cin,
-                                                           int Cout, int relu) {
+__global__ __launch_bounds__(256) void conv1x1_small_fwd_k(Group io, const T* __restrict__ w,
+                                                           const float* __restrict__ b, long P,
+                                                           int Cin, int Cout, int relu) {
   constexpr int N = Pk<T>::N;
+  const T* __restrict__ x = (const T*)pickg(io.a, blockIdx.y);
+  T* __restrict__ y = (T*)pickg(io.y, blockIdx.y);
   const long p = (long)blockIdx.x * 256 + threadIdx.x;
   if (p >= P) return;
   float acc[kSmallCo];
@@ -106,17 +127,12 @@ __global__ __launch_bounds__(256) void conv1x1_small_fwd_k(const T* __restrict__
 // 256 % (Cin / pack) == 0.
 constexpr int kSmallPix = 4;
 template <typename T>
-struct SmallDg {
-  const T* dz[kMaxGroup];
-  T* dx[kMaxGroup];
-};
-template <typename T>
-__global__ __launch_bounds__(256) void dgrad1x1_small_k(SmallDg<T> io, const T* __restrict__ w,
+__global__ __launch_bounds__(256) void dgrad1x1_small_k(Group io, const T* __restrict__ w,
                                                         long P, int Cin, int Cout) {
   constexpr int N = Pk<T>::N;
   const int CP = Cin / N, cp = threadIdx.x % CP, nl = 256 / CP;
-  const T* __restrict__ dz = pickg(io.dz, blockIdx.y);
-  T* __restrict__ dx = pickg(io.dx, blockIdx.y);
+  const T* __restrict__ dz = (const T*)pickg(io.a, blockIdx.y);
+  T* __restrict__ dx = (T*)pickg(io.y, blockIdx.y);
   float wv[kSmallCo][N];
 #pragma unroll
   for (int co = 0; co < kSmallCo; ++co)
@@ -154,11 +170,12 @@ __global__ __launch_bounds__(256) void dgrad1x1_small_k(SmallDg<T> io, const T* 
 // t / CP, t / CP + 256 / CP, ... in order; row lanes are then added in order
 // in LDS and part[b][co][ci] is written.  Needs 256 % CP == 0 (CP = Cin / pack).
 template <typename T>
-__global__ __launch_bounds__(256) void wgrad1x1_small_k(const T* __restrict__ x,
-                                                        const T* __restrict__ dz,
-                                                        float* __restrict__ part, long P,
-                                                        int Cin, int Cout, long rows) {
+__global__ __launch_bounds__(256) void wgrad1x1_small_k(Group io, long P, int Cin, int Cout,
+                                                        long rows) {
   constexpr int N = Pk<T>::N;
+  const T* __restrict__ x = (const T*)pickg(io.a, blockIdx.y);
+  const T* __restrict__ dz = (const T*)pickg(io.b, blockIdx.y);
+  float* __restrict__ part = (float*)pickg(io.y, blockIdx.y);
   __shared__ float red[256 * N];
   const int CP = Cin / N;
   const int cp = threadIdx.x % CP, rl = threadIdx.x / CP, nl = 256 / CP;
@@ -526,10 +543,12 @@ static int dw3_wgrad_blocks(int nb, int H, int W, int C) {
 // ---------------------------------------------------------------- elementwise
 
 template <typename T>
-__global__ __launch_bounds__(256) void relu_bwd_k(const T* __restrict__ dy, const T* __restrict__ ds,
-                                                  const T* __restrict__ y, T* __restrict__ dz,
-                                                  int relu, long n, int vec) {
+__global__ __launch_bounds__(256) void relu_bwd_k(Group io, int relu, long n, int vec) {
   constexpr int N = Pk<T>::N;
+  const T* __restrict__ dy = (const T*)pickg(io.a, blockIdx.y);
+  const T* __restrict__ ds = (const T*)pickg(io.b, blockIdx.y);
+  const T* __restrict__ y = (const T*)pickg(io.c, blockIdx.y);
+  T* __restrict__ dz = (T*)pickg(io.y, blockIdx.y);
   long e0 = ((long)blockIdx.x * 256 + threadIdx.x) * N;
   if (e0 >= n) return;
   if (vec && e0 + N <= n) {
@@ -720,9 +739,10 @@ __global__ __launch_bounds__(256) void pool_relu_bwd_bias_k(RbGroup<T> ga, int r
 // one-channel head then has 256 lanes at work: 4 of them took 25 us for 147456
 // rows, 3.9 now).
 template <typename T>
-__global__ __launch_bounds__(256) void colsum_k(const T* __restrict__ a, float* __restrict__ part,
-                                                long P, int C, long rows) {
+__global__ __launch_bounds__(256) void colsum_k(Group io, long P, int C, long rows) {
   __shared__ float red[256];
+  const T* __restrict__ a = (const T*)pickg(io.a, blockIdx.z);
+  float* __restrict__ part = (float*)pickg(io.y, blockIdx.z);
   const int c0 = blockIdx.x * 64, nc = C - c0 < 64 ? C - c0 : 64;
   const int nl = 256 / nc, col = threadIdx.x % nc, lane = threadIdx.x / nc;
   const long p0 = (long)blockIdx.y * rows, p1 = p0 + rows < P ? p0 + rows : P;
@@ -767,29 +787,28 @@ __global__ __launch_bounds__(256) void dw_wgrad_k(const T* __restrict__ x, const
 
 // ---------------------------------------------------------------- pool
 
-// 2x2/2 max pool of gridDim.y (1 .. kMaxGroup) micro-batches (blockIdx.y
-// selects x[k] / y[k]).
-template <typename T>
-struct PoolGroup {
-  const T* x[kMaxGroup];
-  T* y[kMaxGroup];
+// The pool and upsample kernels move every byte once and are bound by that; a
+// thread takes one channel pack of a 2 x 2 block of pixels, indexed in 32 bits
+// (a 64-bit division by each of three sizes took as long as the loads: 64 + 64
+// channels at 192 x 192 x 4 upsampled in 13.7 us, 10.9 now).
+struct Quad {
+  int cp, w2, h2, n;
 };
+__device__ __forceinline__ Quad quad_of(unsigned e, unsigned CP, unsigned W2, unsigned H2) {
+  const unsigned r = e / CP, q = r / W2, n = q / H2;
+  return {(int)(e - r * CP), (int)(r - q * W2), (int)(q - n * H2), (int)n};
+}
+
+// 2x2/2 max pool of gridDim.y micro-batches.
 template <typename T>
-__global__ __launch_bounds__(256) void maxpool_fwd_k(PoolGroup<T> pg, int nb, int H, int W, int C) {
-  const T* __restrict__ x = pickg(pg.x, blockIdx.y);
-  T* __restrict__ y = pickg(pg.y, blockIdx.y);
+__global__ __launch_bounds__(256) void maxpool_fwd_k(Group io, unsigned total, int H, int W, int C) {
   constexpr int N = Pk<T>::N;
-  int CP = C / N, H2 = H / 2, W2 = W / 2;
-  long e = (long)blockIdx.x * 256 + threadIdx.x;
-  long total = (long)nb * H2 * W2 * CP;
+  const T* __restrict__ x = (const T*)pickg(io.a, blockIdx.y);
+  T* __restrict__ y = (T*)pickg(io.y, blockIdx.y);
+  const unsigned e = blockIdx.x * 256 + threadIdx.x;
   if (e >= total) return;
-  int cp = e % CP;
-  long r = e / CP;
-  int w2 = r % W2;
-  r /= W2;
-  int h2 = r % H2;
-  int n = r / H2;
-  const T* base = x + (((long)n * H + 2 * h2) * W + 2 * w2) * C + cp * N;
+  const Quad q = quad_of(e, C / N, W / 2, H / 2);
+  const T* base = x + (((long)q.n * H + 2 * q.h2) * W + 2 * q.w2) * C + q.cp * N;
   float m[N], v[N];
   Pk<T>::un(ld16(base), m);
   const long off[3] = {C, (long)W * C, (long)W * C + C};
@@ -799,29 +818,24 @@ __global__ __launch_bounds__(256) void maxpool_fwd_k(PoolGroup<T> pg, int nb, in
 #pragma unroll
     for (int i = 0; i < N; ++i) m[i] = v[i] > m[i] ? v[i] : m[i];
   }
-  st16(y + e * N, Pk<T>::pk(m));
+  st16(y + (long)e * N, Pk<T>::pk(m));
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void maxpool_bwd_k(const T* __restrict__ x, const T* __restrict__ dy,
-                                                     T* __restrict__ dx, int nb, int H, int W, int C) {
+__global__ __launch_bounds__(256) void maxpool_bwd_k(Group io, unsigned total, int H, int W, int C) {
   constexpr int N = Pk<T>::N;
-  int CP = C / N, H2 = H / 2, W2 = W / 2;
-  long e = (long)blockIdx.x * 256 + threadIdx.x;
-  long total = (long)nb * H2 * W2 * CP;
+  const T* __restrict__ x = (const T*)pickg(io.a, blockIdx.y);
+  const T* __restrict__ dy = (const T*)pickg(io.b, blockIdx.y);
+  T* __restrict__ dx = (T*)pickg(io.y, blockIdx.y);
+  const unsigned e = blockIdx.x * 256 + threadIdx.x;
   if (e >= total) return;
-  int cp = e % CP;
-  long r = e / CP;
-  int w2 = r % W2;
-  r /= W2;
-  int h2 = r % H2;
-  int n = r / H2;
-  long o = (((long)n * H + 2 * h2) * W + 2 * w2) * C + cp * N;
+  const Quad q = quad_of(e, C / N, W / 2, H / 2);
+  const long o = (((long)q.n * H + 2 * q.h2) * W + 2 * q.w2) * C + q.cp * N;
   const long off[4] = {0, C, (long)W * C, (long)W * C + C};
   float v[4][N], g[N];
 #pragma unroll
   for (int k = 0; k < 4; ++k) Pk<T>::un(ld16(x + o + off[k]), v[k]);
-  Pk<T>::un(ld16(dy + e * N), g);
+  Pk<T>::un(ld16(dy + (long)e * N), g);
   float out[4][N];
 #pragma unroll
   for (int i = 0; i < N; ++i) {
@@ -839,80 +853,81 @@ __global__ __launch_bounds__(256) void maxpool_bwd_k(const T* __restrict__ x, co
 
 // ---------------------------------------------------------------- upsample-concat
 
+// io.a: prev, io.b: skip, io.y: the concatenation.
 template <typename T>
-__global__ __launch_bounds__(256) void upcat_fwd_k(const T* __restrict__ prev, const T* __restrict__ skip,
-                                                   T* __restrict__ out, int nb, int H, int W, int C1,
+__global__ __launch_bounds__(256) void upcat_fwd_k(Group io, unsigned total, int H, int W, int C1,
                                                    int C2) {
   constexpr int N = Pk<T>::N;
-  int C = C1 + C2, CP = C / N;
-  long e = (long)blockIdx.x * 256 + threadIdx.x;
-  long total = (long)nb * H * W * CP;
+  const T* __restrict__ prev = (const T*)pickg(io.a, blockIdx.y);
+  const T* __restrict__ skip = (const T*)pickg(io.b, blockIdx.y);
+  T* __restrict__ out = (T*)pickg(io.y, blockIdx.y);
+  const unsigned e = blockIdx.x * 256 + threadIdx.x;
   if (e >= total) return;
-  int cp = e % CP;
-  long p = e / CP;
-  int w = p % W;
-  long r = p / W;
-  int h = r % H;
-  int n = r / H;
-  int c = cp * N;
-  uint4 v;
-  if (c < C1)
-    v = ld16(prev + (((long)n * (H / 2) + h / 2) * (W / 2) + w / 2) * C1 + c);
-  else
-    v = ld16(skip + p * C2 + (c - C1));
-  st16(out + p * C + c, v);
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void upcat_bwd_prev_k(const T* __restrict__ dcat, T* __restrict__ dprev,
-                                                        int nb, int H, int W, int C1, int C2) {
-  constexpr int N = Pk<T>::N;
-  int C = C1 + C2, CP = C1 / N, H2 = H / 2, W2 = W / 2;
-  long e = (long)blockIdx.x * 256 + threadIdx.x;
-  long total = (long)nb * H2 * W2 * CP;
-  if (e >= total) return;
-  int cp = e % CP;
-  long r = e / CP;
-  int w2 = r % W2;
-  r /= W2;
-  int h2 = r % H2;
-  int n = r / H2;
-  long o = (((long)n * H + 2 * h2) * W + 2 * w2) * C + cp * N;
-  const long off[4] = {0, C, (long)W * C, (long)W * C + C};
-  float s[N], v[N];
-  Pk<T>::un(ld16(dcat + o), s);
+  const int C = C1 + C2;
+  const Quad q = quad_of(e, C / N, W / 2, H / 2);
+  const int c = q.cp * N;
+  const long p0 = ((long)q.n * H + 2 * q.h2) * W + 2 * q.w2;
+  const long off[4] = {0, 1, W, (long)W + 1};
+  uint4 v[4];
+  if (c < C1) {
+    v[0] = ld16(prev + (((long)q.n * (H / 2) + q.h2) * (W / 2) + q.w2) * C1 + c);
+    v[1] = v[2] = v[3] = v[0];
+  } else {
 #pragma unroll
-  for (int k = 1; k < 4; ++k) {
-    Pk<T>::un(ld16(dcat + o + off[k]), v);
-#pragma unroll
-    for (int i = 0; i < N; ++i) s[i] += v[i];
+    for (int k = 0; k < 4; ++k) v[k] = ld16(skip + (p0 + off[k]) * C2 + (c - C1));
   }
-  st16(dprev + e * N, Pk<T>::pk(s));
+#pragma unroll
+  for (int k = 0; k < 4; ++k) st16(out + (p0 + off[k]) * C + c, v[k]);
 }
 
+// io.a: dcat, io.y: dprev (sums of the 2 x 2 blocks), io.b: dskip (written).
 template <typename T>
-__global__ __launch_bounds__(256) void upcat_bwd_skip_k(const T* __restrict__ dcat, T* __restrict__ dskip,
-                                                        long P, int C1, int C2) {
+__global__ __launch_bounds__(256) void upcat_bwd_k(Group io, unsigned total, int H, int W, int C1,
+                                                   int C2) {
   constexpr int N = Pk<T>::N;
-  int CP = C2 / N;
-  long e = (long)blockIdx.x * 256 + threadIdx.x;
-  if (e >= P * CP) return;
-  int cp = e % CP;
-  long p = e / CP;
-  st16(dskip + p * C2 + cp * N, ld16(dcat + p * (C1 + C2) + C1 + cp * N));
+  const T* __restrict__ dcat = (const T*)pickg(io.a, blockIdx.y);
+  T* __restrict__ dprev = (T*)pickg(io.y, blockIdx.y);
+  T* __restrict__ dskip = (T*)const_cast<void*>(pickg(io.b, blockIdx.y));
+  const unsigned e = blockIdx.x * 256 + threadIdx.x;
+  if (e >= total) return;
+  const int C = C1 + C2;
+  const Quad q = quad_of(e, C / N, W / 2, H / 2);
+  const int c = q.cp * N;
+  const long p0 = ((long)q.n * H + 2 * q.h2) * W + 2 * q.w2;
+  const long off[4] = {0, 1, W, (long)W + 1};
+  uint4 v[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v[k] = ld16(dcat + (p0 + off[k]) * C + c);
+  if (c < C1) {
+    float sum[N], t[N];
+    Pk<T>::un(v[0], sum);
+#pragma unroll
+    for (int k = 1; k < 4; ++k) {
+      Pk<T>::un(v[k], t);
+#pragma unroll
+      for (int i = 0; i < N; ++i) sum[i] += t[i];
+    }
+    st16(dprev + (((long)q.n * (H / 2) + q.h2) * (W / 2) + q.w2) * C1 + c, Pk<T>::pk(sum));
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) st16(dskip + (p0 + off[k]) * C2 + (c - C1), v[k]);
+  }
 }
 
 // ---------------------------------------------------------------- loss / accumulate
 
-// Squared differences of one micro-batch and its loss gradient: block b takes
+// Squared differences of micro-batch blockIdx.y (io.a, io.b) and its loss
+// gradient (io.y): block b takes
 // the packs of 16 bytes b 256 + t, + gridDim.x 256, .. (one element at a time
 // where the tensors are not aligned to packs), adds them per thread in order and
 // over the block in a tree.
 template <typename T>
-__global__ __launch_bounds__(256) void mse_k(const T* __restrict__ y, const T* __restrict__ t,
-                                             T* __restrict__ dy, float* __restrict__ part, long n,
+__global__ __launch_bounds__(256) void mse_k(Group io, float* __restrict__ part, long n,
                                              float inv_numel, int vec) {
   constexpr int N = Pk<T>::N;
+  const T* __restrict__ y = (const T*)pickg(io.a, blockIdx.y);
+  const T* __restrict__ t = (const T*)pickg(io.b, blockIdx.y);
+  T* __restrict__ dy = (T*)pickg(io.y, blockIdx.y);
   __shared__ float red[256];
   float s = 0.f;
   const long n8 = (n + N - 1) / N;
@@ -943,7 +958,7 @@ __global__ __launch_bounds__(256) void mse_k(const T* __restrict__ y, const T* _
     if (threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
     __syncthreads();
   }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+  if (threadIdx.x == 0) part[blockIdx.y * gridDim.x + blockIdx.x] = red[0];
 }
 
 // *out = scale sum of n partial sums: thread t adds t, t + 256, .. in order,
@@ -1100,11 +1115,7 @@ static bool small1x1_ok(int dt, const ConvShape& s, const void* x) {
 template <typename T>
 static hipError_t launch_dgrad_small(int n, const void* const* dz, const void* w, void* const* dx,
                                      const ConvShape& s, hipStream_t st) {
-  SmallDg<T> io;
-  for (int k = 0; k < kMaxGroup; ++k) {   // unused entries repeat the first
-    io.dz[k] = (const T*)dz[k < n ? k : 0];
-    io.dx[k] = (T*)dx[k < n ? k : 0];
-  }
+  const Group io = make_group(n, dx, dz);
   const long P = s.pixels(), per = 256 / (s.cin / Pk<T>::N) * kSmallPix;
   if (P == 0) return hipSuccess;
   ProfScope ps("dgrad1x1_small", 2.0 * n * P * s.cout * s.cin,
@@ -1113,6 +1124,45 @@ static hipError_t launch_dgrad_small(int n, const void* const* dz, const void* w
              s.cin, s.cout);
   return launch_status();
 }
+static hipError_t conv1x1_small(int dt, int n, const void* const* x, const void* w, const float* b,
+                                void* const* y, const ConvShape& s, int relu, hipStream_t st) {
+  const long P = s.pixels();
+  const Group io = make_group(n, y, x);
+  ProfScope ps("conv1x1_small_fwd", 2.0 * n * P * s.cout * s.cin,
+               (dt == 0 ? 2.0 : 4.0) * n * P * (s.cin + s.cout), st);
+  if (dt == 0)
+    TGP_LAUNCH(ps, conv1x1_small_fwd_k<bf16_t>, dim3(cdiv(P, 256), n), dim3(256), 0, st, io,
+               (const bf16_t*)w, b, P, s.cin, s.cout, relu);
+  else
+    TGP_LAUNCH(ps, conv1x1_small_fwd_k<float>, dim3(cdiv(P, 256), n), dim3(256), 0, st, io,
+               (const float*)w, b, P, s.cin, s.cout, relu);
+  return launch_status();
+}
+
+// The weight gradient's sums of n micro-batches, left pending in defer[k].
+static hipError_t wgrad1x1_small(int dt, int n, const void* const* x, const void* const* dz,
+                                 float* const* dw, float* const* part, const ConvShape& s,
+                                 hipStream_t st, ReduceJob* const* defer) {
+  const long P = s.pixels(), E = (long)s.cout * s.cin;
+  const long rows = relu_bias_rows(P, s.cin, dt == 0 ? 8 : 4, 1024);
+  const int nbk = cdiv(P, rows);
+  const Group io = make_group(n, (void* const*)part, x, dz);
+  {
+    ProfScope ps("wgrad1x1_small", 2.0 * n * P * E,
+                 n * ((dt == 0 ? 2.0 : 4.0) * P * (s.cin + s.cout) + 4.0 * nbk * E), st);
+    if (dt == 0)
+      TGP_LAUNCH(ps, wgrad1x1_small_k<bf16_t>, dim3(nbk, n), dim3(256), 0, st, io, P, s.cin, s.cout,
+                 rows);
+    else
+      TGP_LAUNCH(ps, wgrad1x1_small_k<float>, dim3(nbk, n), dim3(256), 0, st, io, P, s.cin, s.cout,
+                 rows);
+  }
+  const hipError_t e = launch_status();
+  if (e != hipSuccess) return e;
+  for (int k = 0; k < n; ++k) *defer[k] = ReduceJob{part[k], dw[k], E, nbk};
+  return hipSuccess;
+}
+
 static hipError_t dgrad1x1_small(int dt, int n, const void* const* dz, const void* w,
                                  void* const* dx, const ConvShape& s, hipStream_t st) {
   return dt == 0 ? launch_dgrad_small<bf16_t>(n, dz, w, dx, s, st)
@@ -1124,18 +1174,7 @@ hipError_t conv_forward(int dt, const void* x, const void* w, const float* b, vo
                         hipStream_t st) {
   if (mfma_fwd_ok(dt, s))
     return conv_forward_mfma(x, w, b, y, s, relu, part, part_cap, st);
-  if (small1x1_ok(dt, s, x)) {
-    const long P = s.pixels();
-    ProfScope ps("conv1x1_small_fwd", 2.0 * P * s.cout * s.cin,
-                 (dt == 0 ? 2.0 : 4.0) * P * (s.cin + s.cout), st);
-    if (dt == 0)
-      TGP_LAUNCH(ps, conv1x1_small_fwd_k<bf16_t>, dim3(cdiv(P, 256)), dim3(256), 0, st,
-                 (const bf16_t*)x, (const bf16_t*)w, b, (bf16_t*)y, P, s.cin, s.cout, relu);
-    else
-      TGP_LAUNCH(ps, conv1x1_small_fwd_k<float>, dim3(cdiv(P, 256)), dim3(256), 0, st,
-                 (const float*)x, (const float*)w, b, (float*)y, P, s.cin, s.cout, relu);
-    return launch_status();
-  }
+  if (small1x1_ok(dt, s, x)) return conv1x1_small(dt, 1, &x, w, b, &y, s, relu, st);
   if (conv_stem_ok(dt, s)) return conv_stem_forward(1, &x, w, b, &y, s, relu, st);
   return conv_gen_forward(dt, 1, &x, w, b, &y, s, relu, false, st);
 }
@@ -1176,31 +1215,11 @@ hipError_t conv_wgrad(int dt, const void* x, const void* dz, float* dw, float* p
   if (defer && extra) return hipErrorInvalidValue;
   if (mfma_wgrad_ok(dt, s))
     return conv_wgrad_mfma(x, dz, dw, partial, s, st, extra, defer);
-  if (small1x1_ok(dt, s, x)) {
-    const long P = s.pixels(), E = (long)s.cout * s.cin;
-    const long rows = relu_bias_rows(P, s.cin, dt == 0 ? 8 : 4, 1024);
-    const int nbk = cdiv(P, rows);
-    {
-      ProfScope ps("wgrad1x1_small", 2.0 * P * E,
-                   (dt == 0 ? 2.0 : 4.0) * P * (s.cin + s.cout) + 4.0 * nbk * E, st);
-      if (dt == 0)
-        TGP_LAUNCH(ps, wgrad1x1_small_k<bf16_t>, dim3(nbk), dim3(256), 0, st, (const bf16_t*)x,
-                   (const bf16_t*)dz, partial, P, s.cin, s.cout, rows);
-      else
-        TGP_LAUNCH(ps, wgrad1x1_small_k<float>, dim3(nbk), dim3(256), 0, st, (const float*)x,
-                   (const float*)dz, partial, P, s.cin, s.cout, rows);
-    }
-    const hipError_t e = launch_status();
-    if (e != hipSuccess) return e;
-    if (defer) {
-      *defer = ReduceJob{partial, dw, E, nbk};
-      return hipSuccess;
-    }
-    return splitk_reduce_launch(partial, dw, E, nbk, st, extra);
-  }
   ReduceJob job;
   ReduceJob* const jp = defer ? defer : &job;
-  const hipError_t e = conv_stem_ok(dt, s)
+  const hipError_t e = small1x1_ok(dt, s, x)
+                           ? wgrad1x1_small(dt, 1, &x, &dz, &dw, &partial, s, st, &jp)
+                       : conv_stem_ok(dt, s)
                            ? conv_stem_wgrad_launch(1, &x, &dz, &dw, &partial, s, st, &jp)
                            : conv_gen_wgrad_launch(dt, 1, &x, &dz, &dw, &partial, s, st, &jp);
   if (e != hipSuccess || defer) return e;
@@ -1218,6 +1237,9 @@ hipError_t conv_forward_n(int dt, int n, const void* const* x, const void* w, co
   bool small = false;
   for (int k = 0; k < n; ++k) small = small || small1x1_ok(dt, s, x[k]);
   if (!small) return conv_gen_forward(dt, n, x, w, b, y, s, relu, false, st);
+  bool all = true;
+  for (int k = 0; k < n; ++k) all = all && small1x1_ok(dt, s, x[k]);
+  if (all) return conv1x1_small(dt, n, x, w, b, y, s, relu, st);
   for (int k = 0; k < n; ++k) {
     const hipError_t e = conv_forward(dt, x[k], w, b, y[k], s, relu, part[k], part_cap, st);
     if (e != hipSuccess) return e;
@@ -1254,6 +1276,9 @@ hipError_t conv_wgrad_n(int dt, int n, const void* const* x, const void* const* 
   bool small = false;
   for (int k = 0; k < n; ++k) small = small || small1x1_ok(dt, s, x[k]);
   if (!small) return conv_gen_wgrad_launch(dt, n, x, dz, dw, part, s, st, defer);
+  bool all = true;
+  for (int k = 0; k < n; ++k) all = all && small1x1_ok(dt, s, x[k]);
+  if (all) return wgrad1x1_small(dt, n, x, dz, dw, part, s, st, defer);
   for (int k = 0; k < n; ++k) {
     const hipError_t e = conv_wgrad(dt, x[k], dz[k], dw[k], part[k], s, st, nullptr, defer[k]);
     if (e != hipSuccess) return e;
@@ -1433,18 +1458,23 @@ hipError_t dw_wgrad(int dt, const void* x, const void* dz, float* dw, float* par
   return splitk_reduce_launch(partial, dw, E, S, st);
 }
 
-hipError_t relu_backward(int dt, const void* dy, const void* dskip, const void* y, void* dz,
-                         int relu, long n, hipStream_t st) {
-  int N = dt == 0 ? 8 : 4;
-  int vec = al16(dy) && al16(dz) && (!dskip || al16(dskip)) && (!relu || al16(y)) ? 1 : 0;
-  dim3 g(cdiv(n, 256L * N));
-  ProfScope ps("relu_backward", 0.0, (dt == 0 ? 2.0 : 4.0) * n * (3 + (dskip ? 1 : 0) - (relu ? 0 : 1)), st);
+hipError_t relu_backward_n(int dt, int n, const void* const* dy, const void* const* dskip,
+                           const void* const* y, void* const* dz, int relu, long numel,
+                           hipStream_t st) {
+  if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
+  const int N = dt == 0 ? 8 : 4;
+  int vec = 1, skips = 0;
+  for (int k = 0; k < n; ++k) {
+    if (!al16(dy[k]) || !al16(dz[k]) || !al16(dskip[k]) || (relu && !al16(y[k]))) vec = 0;
+    skips += dskip[k] != nullptr;
+  }
+  const Group io = make_group(n, dz, dy, dskip, y);
+  const dim3 g(cdiv(numel, 256L * N), n);
+  ProfScope ps("relu_backward", 0.0, (dt == 0 ? 2.0 : 4.0) * numel * (n * (relu ? 3 : 2) + skips), st);
   if (dt == 0)
-    TGP_LAUNCH(ps, relu_bwd_k<bf16_t>, g, dim3(256), 0, st, (const bf16_t*)dy,
-                       (const bf16_t*)dskip, (const bf16_t*)y, (bf16_t*)dz, relu, n, vec);
+    TGP_LAUNCH(ps, relu_bwd_k<bf16_t>, g, dim3(256), 0, st, io, relu, numel, vec);
   else
-    TGP_LAUNCH(ps, relu_bwd_k<float>, g, dim3(256), 0, st, (const float*)dy,
-                       (const float*)dskip, (const float*)y, (float*)dz, relu, n, vec);
+    TGP_LAUNCH(ps, relu_bwd_k<float>, g, dim3(256), 0, st, io, relu, numel, vec);
   return launch_status();
 }
 
@@ -1589,31 +1619,30 @@ hipError_t pool_relu_backward_bias(int dt, const void* dp, const void* dskip, co
   return pool_relu_backward_bias_n(dt, 1, &a, relu, nb, H, W, C, cap, st);
 }
 
-hipError_t bias_grad(int dt, const void* dz, float* db, float* partial, long P, int C,
-                     hipStream_t st) {
-  long rows = colsum_rows(P);
-  int nb = cdiv(P, rows);
-  dim3 g(cdiv(C, 64), nb);
+hipError_t bias_grad_n(int dt, int n, const void* const* dz, float* const* db,
+                       float* const* partial, long P, int C, hipStream_t st) {
+  if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
+  const long rows = colsum_rows(P);
+  const int nb = cdiv(P, rows);
+  const dim3 g(cdiv(C, 64), nb, n);
   {
-  ProfScope ps("bias_colsum", 0.0, (dt == 0 ? 2.0 : 4.0) * P * C + 4.0 * nb * C, st);
-  if (dt == 0)
-    TGP_LAUNCH(ps, colsum_k<bf16_t>, g, dim3(256), 0, st, (const bf16_t*)dz, partial, P, C, rows);
-  else
-    TGP_LAUNCH(ps, colsum_k<float>, g, dim3(256), 0, st, (const float*)dz, partial, P, C, rows);
+    const Group io = make_group(n, (void* const*)partial, dz);
+    ProfScope ps("bias_colsum", 0.0, n * ((dt == 0 ? 2.0 : 4.0) * P * C + 4.0 * nb * C), st);
+    if (dt == 0)
+      TGP_LAUNCH(ps, colsum_k<bf16_t>, g, dim3(256), 0, st, io, P, C, rows);
+    else
+      TGP_LAUNCH(ps, colsum_k<float>, g, dim3(256), 0, st, io, P, C, rows);
   }
   hipError_t e = launch_status();
   if (e != hipSuccess) return e;
-  return splitk_reduce_launch(partial, db, C, nb, st);
+  return splitk_reduce_n(n, partial, db, C, nb, st);
 }
 
-template <typename T>
-static PoolGroup<T> pool_group(int n, const void* const* x, void* const* y) {
-  PoolGroup<T> g;
-  for (int k = 0; k < kMaxGroup; ++k) {   // unused entries repeat the first
-    g.x[k] = (const T*)x[k < n ? k : 0];
-    g.y[k] = (T*)y[k < n ? k : 0];
-  }
-  return g;
+// Packs of the 2 x 2 blocks of nb images; 0 where a 32-bit index does not reach
+// (tensors past the card's memory).
+static unsigned quad_total(int nb, int H, int W, int CP) {
+  const long t = (long)nb * (H / 2) * (W / 2) * CP;
+  return t < (1L << 32) - 256 ? (unsigned)t : 0u;
 }
 
 hipError_t maxpool_forward_n(int dt, int n, const void* const* x, void* const* y, int nb, int H,
@@ -1621,71 +1650,62 @@ hipError_t maxpool_forward_n(int dt, int n, const void* const* x, void* const* y
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
   for (int k = 0; k < n; ++k)
     if (!x[k] || !y[k]) return hipErrorInvalidValue;
-  int N = dt == 0 ? 8 : 4;
-  long total = (long)nb * (H / 2) * (W / 2) * (C / N);
-  dim3 g(cdiv(total, 256), n);
+  const unsigned total = quad_total(nb, H, W, C / (dt == 0 ? 8 : 4));
+  if (!total) return hipErrorInvalidValue;
+  const dim3 g(cdiv(total, 256L), n);
+  const Group io = make_group(n, y, x);
   ProfScope ps("maxpool_forward", 0.0, n * (dt == 0 ? 2.0 : 4.0) * nb * H * W * C * 1.25, st);
   if (dt == 0)
-    TGP_LAUNCH(ps, maxpool_fwd_k<bf16_t>, g, dim3(256), 0, st, pool_group<bf16_t>(n, x, y), nb, H,
-               W, C);
+    TGP_LAUNCH(ps, maxpool_fwd_k<bf16_t>, g, dim3(256), 0, st, io, total, H, W, C);
   else
-    TGP_LAUNCH(ps, maxpool_fwd_k<float>, g, dim3(256), 0, st, pool_group<float>(n, x, y), nb, H,
-               W, C);
+    TGP_LAUNCH(ps, maxpool_fwd_k<float>, g, dim3(256), 0, st, io, total, H, W, C);
   return launch_status();
 }
 
-hipError_t maxpool_forward(int dt, const void* x, void* y, int nb, int H, int W, int C,
+hipError_t maxpool_backward_n(int dt, int n, const void* const* x, const void* const* dy,
+                              void* const* dx, int nb, int H, int W, int C, hipStream_t st) {
+  if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
+  const unsigned total = quad_total(nb, H, W, C / (dt == 0 ? 8 : 4));
+  if (!total) return hipErrorInvalidValue;
+  const dim3 g(cdiv(total, 256L), n);
+  const Group io = make_group(n, dx, x, dy);
+  ProfScope ps("maxpool_backward", 0.0, n * (dt == 0 ? 2.0 : 4.0) * nb * H * W * C * 2.25, st);
+  if (dt == 0)
+    TGP_LAUNCH(ps, maxpool_bwd_k<bf16_t>, g, dim3(256), 0, st, io, total, H, W, C);
+  else
+    TGP_LAUNCH(ps, maxpool_bwd_k<float>, g, dim3(256), 0, st, io, total, H, W, C);
+  return launch_status();
+}
+
+hipError_t upcat_forward_n(int dt, int n, const void* const* prev, const void* const* skip,
+                           void* const* out, int nb, int H, int W, int C1, int C2,
                            hipStream_t st) {
-  return maxpool_forward_n(dt, 1, &x, &y, nb, H, W, C, st);
-}
-
-hipError_t maxpool_backward(int dt, const void* x, const void* dy, void* dx, int nb, int H,
-                            int W, int C, hipStream_t st) {
-  int N = dt == 0 ? 8 : 4;
-  long total = (long)nb * (H / 2) * (W / 2) * (C / N);
-  dim3 g(cdiv(total, 256));
-  ProfScope ps("maxpool_backward", 0.0, (dt == 0 ? 2.0 : 4.0) * nb * H * W * C * 2.25, st);
+  if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
+  const unsigned total = quad_total(nb, H, W, (C1 + C2) / (dt == 0 ? 8 : 4));
+  if (!total) return hipErrorInvalidValue;
+  const dim3 g(cdiv(total, 256L), n);
+  const Group io = make_group(n, out, prev, skip);
+  ProfScope ps("upcat_forward", 0.0, n * (dt == 0 ? 2.0 : 4.0) * nb * H * W * (1.25 * C1 + 2.0 * C2), st);
   if (dt == 0)
-    TGP_LAUNCH(ps, maxpool_bwd_k<bf16_t>, g, dim3(256), 0, st, (const bf16_t*)x,
-                       (const bf16_t*)dy, (bf16_t*)dx, nb, H, W, C);
+    TGP_LAUNCH(ps, upcat_fwd_k<bf16_t>, g, dim3(256), 0, st, io, total, H, W, C1, C2);
   else
-    TGP_LAUNCH(ps, maxpool_bwd_k<float>, g, dim3(256), 0, st, (const float*)x,
-                       (const float*)dy, (float*)dx, nb, H, W, C);
+    TGP_LAUNCH(ps, upcat_fwd_k<float>, g, dim3(256), 0, st, io, total, H, W, C1, C2);
   return launch_status();
 }
 
-hipError_t upcat_forward(int dt, const void* prev, const void* skip, void* out, int nb, int H,
-                         int W, int C1, int C2, hipStream_t st) {
-  int N = dt == 0 ? 8 : 4;
-  long total = (long)nb * H * W * ((C1 + C2) / N);
-  dim3 g(cdiv(total, 256));
-  ProfScope ps("upcat_forward", 0.0, (dt == 0 ? 2.0 : 4.0) * nb * H * W * (0.25 * C1 + C2 + C1 + C2), st);
+hipError_t upcat_backward_n(int dt, int n, const void* const* dcat, void* const* dprev,
+                            void* const* dskip, int nb, int H, int W, int C1, int C2,
+                            hipStream_t st) {
+  if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
+  const unsigned total = quad_total(nb, H, W, (C1 + C2) / (dt == 0 ? 8 : 4));
+  if (!total) return hipErrorInvalidValue;
+  const dim3 g(cdiv(total, 256L), n);
+  const Group io = make_group(n, dprev, dcat, (const void* const*)dskip);
+  ProfScope ps("upcat_backward", 0.0, n * (dt == 0 ? 2.0 : 4.0) * nb * H * W * (1.25 * C1 + 2.0 * C2), st);
   if (dt == 0)
-    TGP_LAUNCH(ps, upcat_fwd_k<bf16_t>, g, dim3(256), 0, st, (const bf16_t*)prev,
-                       (const bf16_t*)skip, (bf16_t*)out, nb, H, W, C1, C2);
+    TGP_LAUNCH(ps, upcat_bwd_k<bf16_t>, g, dim3(256), 0, st, io, total, H, W, C1, C2);
   else
-    TGP_LAUNCH(ps, upcat_fwd_k<float>, g, dim3(256), 0, st, (const float*)prev,
-                       (const float*)skip, (float*)out, nb, H, W, C1, C2);
-  return launch_status();
-}
-
-hipError_t upcat_backward(int dt, const void* dcat, void* dprev, void* dskip, int nb, int H,
-                          int W, int C1, int C2, hipStream_t st) {
-  int N = dt == 0 ? 8 : 4;
-  long t1 = (long)nb * (H / 2) * (W / 2) * (C1 / N);
-  long P = (long)nb * H * W;
-  ProfScope ps("upcat_backward", 0.0, (dt == 0 ? 2.0 : 4.0) * P * (C1 + 0.25 * C1 + 2.0 * C2), st);
-  if (dt == 0) {
-    TGP_LAUNCH(ps, upcat_bwd_prev_k<bf16_t>, dim3(cdiv(t1, 256)), dim3(256), 0, st,
-                       (const bf16_t*)dcat, (bf16_t*)dprev, nb, H, W, C1, C2);
-    TGP_LAUNCH(ps, upcat_bwd_skip_k<bf16_t>, dim3(cdiv(P * (C2 / N), 256)), dim3(256), 0, st,
-                       (const bf16_t*)dcat, (bf16_t*)dskip, P, C1, C2);
-  } else {
-    TGP_LAUNCH(ps, upcat_bwd_prev_k<float>, dim3(cdiv(t1, 256)), dim3(256), 0, st,
-                       (const float*)dcat, (float*)dprev, nb, H, W, C1, C2);
-    TGP_LAUNCH(ps, upcat_bwd_skip_k<float>, dim3(cdiv(P * (C2 / N), 256)), dim3(256), 0, st,
-                       (const float*)dcat, (float*)dskip, P, C1, C2);
-  }
+    TGP_LAUNCH(ps, upcat_bwd_k<float>, g, dim3(256), 0, st, io, total, H, W, C1, C2);
   return launch_status();
 }
 
@@ -1696,16 +1716,20 @@ int mse_blocks(long n) {
   return (int)(b < 64 ? b : 64);
 }
 
-hipError_t mse_forward_backward(int dt, const void* y, const void* t, void* dy, float* partial,
-                                long n, float inv_numel, hipStream_t st) {
-  const int vec = al16(y) && al16(t) && al16(dy) ? 1 : 0;
-  ProfScope ps("mse", 3.0 * n, (dt == 0 ? 6.0 : 12.0) * n, st);
+hipError_t mse_forward_backward_n(int dt, int n, const void* const* y, const void* const* t,
+                                  void* const* dy, float* partial, long numel, float inv_numel,
+                                  hipStream_t st) {
+  if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
+  int vec = 1;
+  for (int k = 0; k < n; ++k)
+    if (!al16(y[k]) || !al16(t[k]) || !al16(dy[k])) vec = 0;
+  const Group io = make_group(n, dy, y, t);
+  const dim3 g(mse_blocks(numel), n);
+  ProfScope ps("mse", 3.0 * n * numel, n * (dt == 0 ? 6.0 : 12.0) * numel, st);
   if (dt == 0)
-    TGP_LAUNCH(ps, mse_k<bf16_t>, dim3(mse_blocks(n)), dim3(256), 0, st, (const bf16_t*)y,
-               (const bf16_t*)t, (bf16_t*)dy, partial, n, inv_numel, vec);
+    TGP_LAUNCH(ps, mse_k<bf16_t>, g, dim3(256), 0, st, io, partial, numel, inv_numel, vec);
   else
-    TGP_LAUNCH(ps, mse_k<float>, dim3(mse_blocks(n)), dim3(256), 0, st, (const float*)y,
-               (const float*)t, (float*)dy, partial, n, inv_numel, vec);
+    TGP_LAUNCH(ps, mse_k<float>, g, dim3(256), 0, st, io, partial, numel, inv_numel, vec);
   return launch_status();
 }
 

@@ -98,6 +98,9 @@ extern thread_local int t_in_dgrad;
 // (dw = sum over pixels, summed over its K ranges in a fixed order).
 hipError_t splitk_reduce_launch(const float* part, float* out, long E, int S, hipStream_t st,
                                const ReduceJob* extra = nullptr);
+// out[k][e] = sum_s part[k][s E + e], n sums of one shape in one launch.
+hipError_t splitk_reduce_n(int n, const float* const* part, float* const* out, long E, int S,
+                           hipStream_t st);
 bool wgrad_rows_ok(const ConvShape& s);
 size_t wgrad_rows_partial_floats(const ConvShape& s);
 hipError_t conv_wgrad_rows_launch(const void* x, const void* dz, float* dw, float* partial,
@@ -200,35 +203,37 @@ hipError_t dw_wgrad(int dt, const void* x, const void* dz, float* dw, float* par
                     int H, int W, int C, hipStream_t st);
 
 // dz = (dy [+ dskip]) * [y > 0] (mask only when relu), stored in dt.
-hipError_t relu_backward(int dt, const void* dy, const void* dskip, const void* y, void* dz,
-                         int relu, long n, hipStream_t st);
+// Here and below, _n kernels take n (1 .. kMaxGroup) micro-batches in one launch.
+hipError_t relu_backward_n(int dt, int n, const void* const* dy, const void* const* dskip,
+                           const void* const* y, void* const* dz, int relu, long numel,
+                           hipStream_t st);
 // db[c] = sum_p dz[p][c] over P rows, fixed-order two-stage reduction.
 size_t colsum_partial_floats(long P, int C);
-hipError_t bias_grad(int dt, const void* dz, float* db, float* partial, long P, int C,
-                     hipStream_t st);
+hipError_t bias_grad_n(int dt, int n, const void* const* dz, float* const* db,
+                       float* const* partial, long P, int C, hipStream_t st);
 
 // 2x2/2 max-pool of x (nb x H x W x C) into y; backward routes dy to the first
 // maximal element of each window (row-major).
 // n (1 .. kMaxGroup) micro-batches x[k] -> y[k] in one launch.
 hipError_t maxpool_forward_n(int dt, int n, const void* const* x, void* const* y, int nb, int H,
                              int W, int C, hipStream_t st);
-hipError_t maxpool_forward(int dt, const void* x, void* y, int nb, int H, int W, int C,
-                           hipStream_t st);
-hipError_t maxpool_backward(int dt, const void* x, const void* dy, void* dx, int nb, int H,
-                            int W, int C, hipStream_t st);
+hipError_t maxpool_backward_n(int dt, int n, const void* const* x, const void* const* dy,
+                              void* const* dx, int nb, int H, int W, int C, hipStream_t st);
 
 // out (nb x H x W x (C1+C2)) = [nearest 2x upsample of prev (H/2 x W/2 x C1), skip].
-hipError_t upcat_forward(int dt, const void* prev, const void* skip, void* out, int nb, int H,
-                         int W, int C1, int C2, hipStream_t st);
+hipError_t upcat_forward_n(int dt, int n, const void* const* prev, const void* const* skip,
+                           void* const* out, int nb, int H, int W, int C1, int C2, hipStream_t st);
 // dprev = sum of 2x2 blocks of dcat[..., :C1]; dskip = dcat[..., C1:].
-hipError_t upcat_backward(int dt, const void* dcat, void* dprev, void* dskip, int nb, int H,
-                          int W, int C1, int C2, hipStream_t st);
+hipError_t upcat_backward_n(int dt, int n, const void* const* dcat, void* const* dprev,
+                            void* const* dskip, int nb, int H, int W, int C1, int C2,
+                            hipStream_t st);
 
 // Squared-error part of one micro-batch of n elements: mse_blocks(n) partial
 // sums of (y-t)^2 and dy = 2 (y-t) * inv_numel, fixed-order reduction.
 int mse_blocks(long n);
-hipError_t mse_forward_backward(int dt, const void* y, const void* t, void* dy, float* partial,
-                                long n, float inv_numel, hipStream_t st);
+hipError_t mse_forward_backward_n(int dt, int n, const void* const* y, const void* const* t,
+                                  void* const* dy, float* partial, long numel, float inv_numel,
+                                  hipStream_t st);
 // *loss = (sum of the step's n partial sums) * inv_numel, in a fixed order.
 hipError_t loss_finalize(const float* parts, int n, float inv_numel, float* loss,
                          hipStream_t st);

@@ -134,15 +134,15 @@ struct tgp_net {
   // not refreshed at its first backward of this step (a paired backward
   // reads only its first micro-batch's lane); refreshed before a later use
   std::vector<char> wt_stale;
-  // Streams and events tgp_pipeline_step forks onto with several lanes (one
-  // per lane plus one for the accumulations), created on first use on the
+  // The accumulation stream tgp_pipeline_step forks onto with several lanes
+  // and its events (group backward, fork, join), created on first use on the
   // device current then; default priority.
-  std::vector<hipStream_t> lane_streams;
-  std::vector<hipEvent_t> lane_events;
-  int lane_device = -1;
+  hipStream_t acc_stream = nullptr;
+  std::vector<hipEvent_t> acc_events;
+  int acc_device = -1;
   ~tgp_net() {
-    for (auto e : lane_events) (void)hipEventDestroy(e);
-    for (auto st : lane_streams) (void)hipStreamDestroy(st);
+    for (auto e : acc_events) (void)hipEventDestroy(e);
+    if (acc_stream) (void)hipStreamDestroy(acc_stream);
   }
   // Per-layer timing plan (tgp_layer_times_plan): one-layer partitions,
   // m = 1, plus four activation buffers from o_lt on; the caller's
@@ -280,6 +280,7 @@ tgp_status run_forward_g(tgp_net* N, int j, int cnt, const int* iv, const int* p
     void* out[MG];
     const void* cin_ptr[MG];
     void* pro_ptr[MG];
+    const void* skips[MG];
     float* fpart[MG];
     for (int k = 0; k < cnt; ++k) {
       const int i = iv[k];
@@ -291,20 +292,19 @@ tgp_status run_forward_g(tgp_net* N, int j, int cnt, const int* iv, const int* p
       cin_ptr[k] = src[k];
       if (d.prologue != TGP_PRO_NONE) {
         void* pro = (phase[k] == 1) ? W_(N, Lr.o_sto_pro[set[k]]) : T_(N, i, Lr.o_scr_pro);
-        if (d.prologue == TGP_PRO_UPCAT2) {
-          const LayerRt& sl = N->L[N->stash_layer.at(d.pop_id)];
-          HIPCHK(tgpk::upcat_forward(N->dt, src[k], W_(N, stash_off(N, i, d.pop_id, false)), pro,
-                                     N->b, Lr.H, Lr.W, Lr.inC, sl.d.cout, st),
-                 "upcat_forward");
-        }
+        if (d.prologue == TGP_PRO_UPCAT2) skips[k] = W_(N, stash_off(N, i, d.pop_id, false));
         cin_ptr[k] = pro;
         pro_ptr[k] = pro;
       }
       fpart[k] = (float*)T_(N, i, N->o_fpart);
     }
-    if (d.prologue == TGP_PRO_MAXPOOL2)   // the group's pools in one launch
+    if (d.prologue == TGP_PRO_MAXPOOL2)   // the group's prologues in one launch
       HIPCHK(tgpk::maxpool_forward_n(N->dt, cnt, src, pro_ptr, N->b, Lr.inH, Lr.inW, Lr.inC, st),
              "maxpool_forward");
+    else if (d.prologue == TGP_PRO_UPCAT2)
+      HIPCHK(tgpk::upcat_forward_n(N->dt, cnt, src, skips, pro_ptr, N->b, Lr.H, Lr.W, Lr.inC,
+                                   N->L[N->stash_layer.at(d.pop_id)].d.cout, st),
+             "upcat_forward");
     if (d.kind == TGP_DWCONV3X3) {
       // the row-window depthwise kernel takes the whole group in one launch
       bool rows = cnt > 1;
@@ -541,6 +541,11 @@ tgp_status run_backward_g(tgp_net* N, int j, int cnt, const int* iv,
         M[k].dy_pool = nullptr;
       }
     }
+    // micro-batches whose pool the fused kernel does not take, in one launch
+    const void* pool_x[MG];
+    const void* pool_dy[MG];
+    void* pool_dx[MG];
+    int pools = 0;
     for (int k = 0; k < cnt; ++k) {
       BwdMb& B = M[k];
       if (B.dy_pool && d.bias && Lr.o_gcol_floats &&
@@ -553,12 +558,16 @@ tgp_status run_backward_g(tgp_net* N, int j, int cnt, const int* iv,
         ran(k);
         B.dy_pool = nullptr;
       } else if (B.dy_pool) {
-        HIPCHK(tgpk::maxpool_backward(N->dt, yk[k], B.dy_pool, (void*)B.dy, N->b, Lr.H, Lr.W,
-                                      d.cout, st),
-               "maxpool_backward");
+        pool_x[pools] = yk[k];
+        pool_dy[pools] = B.dy_pool;
+        pool_dx[pools++] = (void*)B.dy;
         B.dy_pool = nullptr;
       }
     }
+    if (pools)
+      HIPCHK(tgpk::maxpool_backward_n(N->dt, pools, pool_x, pool_dy, pool_dx, N->b, Lr.H, Lr.W,
+                                      d.cout, st),
+             "maxpool_backward");
     bool all_rb = cnt > 0;
     for (int k = 0; k < cnt; ++k)
       all_rb = all_rb && (*pjs[k])[1].S == 0 && d.bias && Lr.o_gcol_floats &&
@@ -571,6 +580,15 @@ tgp_status run_backward_g(tgp_net* N, int j, int cnt, const int* iv,
              "relu_backward_bias");
       for (int k = 0; k < cnt; ++k) ran(k);
     }
+    // and those whose ReLU (and bias sums) it does not
+    const void* rl_dy[MG];
+    const void* rl_skip[MG];
+    const void* rl_y[MG];
+    void* rl_dz[MG];
+    const void* rl_dzc[MG];
+    float* rl_db[MG];
+    float* rl_col[MG];
+    int relus = 0;
     for (int k = 0; k < cnt; ++k) {
       BwdMb& B = M[k];
       std::array<tgpk::ReduceJob, 2>& pj = *pjs[k];
@@ -586,14 +604,22 @@ tgp_status run_backward_g(tgp_net* N, int j, int cnt, const int* iv,
         dzk[k] = B.dy;
         pj[1].S = 1;
       } else if (pj[1].S == 0) {
-        HIPCHK(tgpk::relu_backward(N->dt, B.dy, dskipk[k], yk[k], B.dz, d.relu, nout, st),
-               "relu_backward");
-        if (d.bias)
-          HIPCHK(tgpk::bias_grad(N->dt, B.dz, gbk[k], B.colpart, P, d.cout, st), "bias_grad");
+        rl_dy[relus] = B.dy;
+        rl_skip[relus] = dskipk[k];
+        rl_y[relus] = yk[k];
+        rl_dzc[relus] = rl_dz[relus] = B.dz;
+        rl_db[relus] = gbk[k];
+        rl_col[relus++] = B.colpart;
         pj[1].S = 1;
       }
       float* gw = (float*)G_(N, B.i, Lr.o_gw);
       pj[0] = tgpk::ReduceJob{gw, gw, Lr.w_elems, 1};
+    }
+    if (relus) {
+      HIPCHK(tgpk::relu_backward_n(N->dt, relus, rl_dy, rl_skip, rl_y, rl_dz, d.relu, nout, st),
+             "relu_backward");
+      if (d.bias)
+        HIPCHK(tgpk::bias_grad_n(N->dt, relus, rl_dzc, rl_db, rl_col, P, d.cout, st), "bias_grad");
     }
     // weight gradient
     tgpk::ConvShape s{N->b, Lr.H, Lr.W, d.cin, d.cout, Lr.taps};
@@ -694,24 +720,27 @@ tgp_status run_backward_g(tgp_net* N, int j, int cnt, const int* iv,
                               N->fpart_floats, st),
              "conv_dgrad");
     }
+    const void* dinps[MG];
+    void* dskips[MG];
     for (int k = 0; k < cnt; ++k) {
       BwdMb& B = M[k];
       if (d.prologue == TGP_PRO_MAXPOOL2 && l > lo) {
         B.dy_pool = B.dinp;   // routed by layer l - 1's ReLU backward
-      } else if (d.prologue == TGP_PRO_MAXPOOL2) {
-        HIPCHK(tgpk::maxpool_backward(N->dt, src[k], B.dinp, dest_prev[k], N->b, Lr.inH, Lr.inW,
-                                      Lr.inC, st),
-               "maxpool_backward");
-      } else if (d.prologue == TGP_PRO_UPCAT2) {
-        const LayerRt& sl = N->L[N->stash_layer.at(d.pop_id)];
-        HIPCHK(tgpk::upcat_backward(N->dt, B.dinp, dest_prev[k],
-                                    W_(N, stash_off(N, B.i, d.pop_id, true)), N->b, Lr.H, Lr.W,
-                                    Lr.inC, sl.d.cout, st),
-               "upcat_backward");
+      } else if (d.prologue != TGP_PRO_NONE) {
+        dinps[k] = B.dinp;
+        if (d.prologue == TGP_PRO_UPCAT2) dskips[k] = W_(N, stash_off(N, B.i, d.pop_id, true));
       }
       B.dy = B.gnext;
       std::swap(B.gcur, B.gnext);
     }
+    if (d.prologue == TGP_PRO_MAXPOOL2 && l == lo)
+      HIPCHK(tgpk::maxpool_backward_n(N->dt, cnt, src, dinps, dest_prev, N->b, Lr.inH, Lr.inW,
+                                      Lr.inC, st),
+             "maxpool_backward");
+    else if (d.prologue == TGP_PRO_UPCAT2)
+      HIPCHK(tgpk::upcat_backward_n(N->dt, cnt, dinps, dest_prev, dskips, N->b, Lr.H, Lr.W, Lr.inC,
+                                    N->L[N->stash_layer.at(d.pop_id)].d.cout, st),
+             "upcat_backward");
   }
   return TGP_OK;
 }
@@ -900,15 +929,20 @@ struct GpuExec : Exec {
   char* y_out;
   hipStream_t st;
   size_t in_mb_bytes, out_mb_bytes;
-  // With K > 1 lanes, micro-batch i's tasks run on lane[(i - 1) % K] and the
-  // accumulations, in schedule order, on acc, which waits for each B_{i,j}
-  // through its lane's event (every cross-stream edge points from a lane to
-  // acc, never back).  K = 1: everything on st.
+  // With K > 1 lanes, a task of the schedule is a group of K consecutive
+  // micro-batches ((g - 1) K + 1 .. g K, the last group what is left): each
+  // layer's kernels take the whole group in one launch on st, and the
+  // accumulations run in schedule order on acc, which waits for each group's
+  // backward (every edge points from st to acc, never back).  A launch of two
+  // micro-batches takes about as long as one of one where either leaves CUs
+  // idle (weight gradients at 96 x 96 x 128, four samples: 38 us for one, 42
+  // for two), so this is faster than a stream per lane.  K = 1: single
+  // micro-batches, everything on st.
   int K = 1;
-  hipStream_t lane[TGP_MAX_LANES] = {};
-  hipEvent_t lane_ev[TGP_MAX_LANES] = {};
+  hipEvent_t bwd_ev = nullptr;
   hipStream_t acc = nullptr;
-  hipStream_t on(int i) const { return K > 1 ? lane[(i - 1) % K] : st; }
+  int first(int g) const { return (g - 1) * K + 1; }
+  int last(int g) const { return std::min(g * K, N->m); }
   const void* bnd(int i, int j) {  // output of partition j for micro-batch i (j = 0: input)
     if (j == 0) return x + (size_t)(i - 1) * in_mb_bytes;
     if (j == N->n) return y_out ? (const void*)(y_out + (size_t)(i - 1) * out_mb_bytes)
@@ -919,47 +953,69 @@ struct GpuExec : Exec {
     if (j == N->n) return W_(N, N->o_dy + (size_t)(i - 1) * al256(out_mb_bytes));
     return W_(N, N->o_gbnd[(i - 1) * N->n + j]);
   }
-  tgp_status forward(int i, int j, bool ckpt) override {
-    return tgp_stage_forward(N, j, i, ckpt ? 1 : 0, bnd(i, j - 1), (void*)bnd(i, j), on(i));
+  tgp_status forward(int g, int j, bool ckpt) override {
+    if (K == 1) return tgp_stage_forward(N, j, g, ckpt ? 1 : 0, bnd(g, j - 1), (void*)bnd(g, j), st);
+    int ck[MG];
+    const void* xs[MG];
+    void* ys[MG];
+    int cnt = 0;
+    for (int i = first(g); i <= last(g); ++i, ++cnt) {
+      ck[cnt] = ckpt_of(N->mode, i, N->m) ? 1 : 0;
+      xs[cnt] = bnd(i, j - 1);
+      ys[cnt] = (void*)bnd(i, j);
+    }
+    return tgp_stage_forward_n(N, j, first(g), cnt, ck, xs, ys, st);
   }
-  tgp_status loss(int i) override {
-    Range rg("LOSS", i, 0);
-    const LayerRt& last = N->L.back();
-    long n_mb = (long)N->b * last.H * last.W * last.d.cout;
-    long numel = n_mb * N->m;
-    HIPCHK(tgpk::mse_forward_backward(N->dt, bnd(i, N->n),
-                                      target + (size_t)(i - 1) * out_mb_bytes, gbnd(i, N->n),
-                                      (float*)W_(N, N->o_loss) + (long)(i - 1) * tgpk::mse_blocks(n_mb),
-                                      n_mb, 1.0f / (float)numel, on(i)),
+  tgp_status loss(int g) override {
+    const LayerRt& out = N->L.back();
+    const long n_mb = (long)N->b * out.H * out.W * out.d.cout;
+    const long numel = n_mb * N->m;
+    Range rg("LOSS", first(g), 0);
+    const void* ys[MG];
+    const void* ts[MG];
+    void* dys[MG];
+    int cnt = 0;
+    for (int i = first(g); i <= last(g); ++i, ++cnt) {
+      ys[cnt] = bnd(i, N->n);
+      ts[cnt] = target + (size_t)(i - 1) * out_mb_bytes;
+      dys[cnt] = gbnd(i, N->n);
+    }
+    HIPCHK(tgpk::mse_forward_backward_n(
+               N->dt, cnt, ys, ts, dys,
+               (float*)W_(N, N->o_loss) + (long)(first(g) - 1) * tgpk::mse_blocks(n_mb), n_mb,
+               1.0f / (float)numel, st),
            "mse_forward_backward");
     return TGP_OK;
   }
-  tgp_status backward(int i, int j, bool) override {
-    tgp_status r = tgp_stage_backward_recompute(N, j, i, gbnd(i, j),
-                                                j > 1 ? gbnd(i, j - 1) : nullptr, on(i));
-    if (r != TGP_OK || K == 1) return r;
-    const int k = (i - 1) % K;
-    HIPCHK(hipEventRecord(lane_ev[k], lane[k]), "hipEventRecord");
-    HIPCHK(hipStreamWaitEvent(acc, lane_ev[k], 0), "hipStreamWaitEvent");
+  tgp_status backward(int g, int j, bool) override {
+    if (K == 1)
+      return tgp_stage_backward_recompute(N, j, g, gbnd(g, j), j > 1 ? gbnd(g, j - 1) : nullptr, st);
+    const void* dys[MG];
+    void* dxs[MG];
+    int cnt = 0;
+    for (int i = last(g); i >= first(g); --i, ++cnt) {
+      dys[cnt] = gbnd(i, j);
+      dxs[cnt] = j > 1 ? gbnd(i, j - 1) : nullptr;
+    }
+    tgp_status r = tgp_stage_backward_recompute_n(N, j, last(g), cnt, dys, dxs, st);
+    if (r != TGP_OK) return r;
+    HIPCHK(hipEventRecord(bwd_ev, st), "hipEventRecord");
+    HIPCHK(hipStreamWaitEvent(acc, bwd_ev, 0), "hipStreamWaitEvent");
     return TGP_OK;
   }
-  // With a gradient slot per micro-batch (K > 1), the accumulations of
-  // partition j are issued in groups of up to kAccGroup consecutive
-  // micro-batches (i0 down to i0 - count + 1, the schedule's order), one
-  // launch each: every g^j is read and written once per group, with the
-  // values of one accumulation per micro-batch.
+  // With K > 1 (a gradient slot per micro-batch), the accumulations of
+  // partition j are issued over as many whole groups as fit in kAccGroup
+  // consecutive micro-batches (the schedule's order), one launch each: every
+  // g^j is read and written once per launch, with the values of one
+  // accumulation per micro-batch.
   static constexpr int kAccGroup = 8;
-  std::vector<int> acc_top, acc_cnt;
-  tgp_status accumulate(int i, int j, bool ow) override {
-    if (K == 1 || N->gslots < N->m) return tgp_grad_accumulate(N, j, i, ow ? 1 : 0, K > 1 ? acc : st);
-    if (acc_cnt.size() < (size_t)N->n + 1) {
-      acc_top.assign(N->n + 1, 0);
-      acc_cnt.assign(N->n + 1, 0);
-    }
-    if (acc_cnt[j] == 0) acc_top[j] = i;
-    ++acc_cnt[j];
-    if (acc_cnt[j] < kAccGroup && i > 1) return TGP_OK;
-    const int top = acc_top[j], cnt = acc_cnt[j];
+  std::vector<int> acc_cnt;
+  tgp_status accumulate(int g, int j, bool ow) override {
+    if (K == 1) return tgp_grad_accumulate(N, j, g, ow ? 1 : 0, st);
+    if (acc_cnt.size() < (size_t)N->n + 1) acc_cnt.assign(N->n + 1, 0);
+    acc_cnt[j] += last(g) - first(g) + 1;
+    if (acc_cnt[j] + K <= kAccGroup && g > 1) return TGP_OK;
+    const int cnt = acc_cnt[j], top = first(g) + cnt - 1;
     acc_cnt[j] = 0;
     return tgp_grad_accumulate_n(N, j, top, cnt, top == N->m ? 1 : 0, acc);
   }
@@ -1663,27 +1719,24 @@ tgp_status tgp_grad_accumulate_n(tgp_net* N, int j, int i0, int count, int overw
   return TGP_OK;
 }
 
-// Streams (count) and events (2 count) for tgp_pipeline_step's lanes, on the
-// current device; recreated if the device changed.
-static tgp_status lane_streams_ready(tgp_net* N, int count) {
+// The accumulation stream and the three events of tgp_pipeline_step with
+// several lanes, on the current device; recreated if the device changed.
+static tgp_status acc_stream_ready(tgp_net* N) {
   int dev = 0;
   HIPCHK(hipGetDevice(&dev), "hipGetDevice");
-  if (N->lane_device != dev) {
-    for (auto e : N->lane_events) (void)hipEventDestroy(e);
-    for (auto st : N->lane_streams) (void)hipStreamDestroy(st);
-    N->lane_events.clear();
-    N->lane_streams.clear();
-    N->lane_device = dev;
+  if (N->acc_device != dev) {
+    for (auto e : N->acc_events) (void)hipEventDestroy(e);
+    if (N->acc_stream) (void)hipStreamDestroy(N->acc_stream);
+    N->acc_events.clear();
+    N->acc_stream = nullptr;
+    N->acc_device = dev;
   }
-  while ((int)N->lane_streams.size() < count) {
-    hipStream_t st = nullptr;
-    HIPCHK(hipStreamCreateWithFlags(&st, hipStreamNonBlocking), "hipStreamCreateWithFlags");
-    N->lane_streams.push_back(st);
-  }
-  while ((int)N->lane_events.size() < 2 * count) {
+  if (!N->acc_stream)
+    HIPCHK(hipStreamCreateWithFlags(&N->acc_stream, hipStreamNonBlocking), "hipStreamCreateWithFlags");
+  while (N->acc_events.size() < 3) {
     hipEvent_t e = nullptr;
     HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming), "hipEventCreateWithFlags");
-    N->lane_events.push_back(e);
+    N->acc_events.push_back(e);
   }
   return TGP_OK;
 }
@@ -1714,20 +1767,15 @@ tgp_status tgp_pipeline_step(tgp_net* N, const void* x, const void* target, int 
   ex.out_mb_bytes = N->out_bytes_mb;
   ex.K = std::min(N->lanes, m);
   if (ex.K > 1) {
-    // fork: lanes + the accumulation stream wait for the caller's stream
-    r = lane_streams_ready(N, ex.K + 1);
+    // fork: the accumulation stream waits for the caller's stream
+    r = acc_stream_ready(N);
     if (r != TGP_OK) return r;
-    for (int k = 0; k < ex.K; ++k) {
-      ex.lane[k] = N->lane_streams[k];
-      ex.lane_ev[k] = N->lane_events[k];
-    }
-    ex.acc = N->lane_streams[ex.K];
-    hipEvent_t fork = N->lane_events[ex.K];
-    HIPCHK(hipEventRecord(fork, ex.st), "hipEventRecord");
-    for (int k = 0; k <= ex.K; ++k)
-      HIPCHK(hipStreamWaitEvent(N->lane_streams[k], fork, 0), "hipStreamWaitEvent");
+    ex.acc = N->acc_stream;
+    ex.bwd_ev = N->acc_events[0];
+    HIPCHK(hipEventRecord(N->acc_events[1], ex.st), "hipEventRecord");
+    HIPCHK(hipStreamWaitEvent(ex.acc, N->acc_events[1], 0), "hipStreamWaitEvent");
   }
-  r = run_schedule(m, n, mode, ex);
+  r = run_schedule((m + ex.K - 1) / ex.K, n, mode, ex);
   if (r != TGP_OK) {
     // a task failed part way: the step is abandoned, so every task of it
     // returns to idle and the next step (or stage call) starts afresh
@@ -1737,17 +1785,12 @@ tgp_status tgp_pipeline_step(tgp_net* N, const void* x, const void* target, int 
     g_err = msg;
   }
   if (ex.K > 1) {
-    // join every lane, also after an error, so that no fork is left open in
-    // a capture; the first failure is the one reported
-    tgp_status rj = TGP_OK;
-    for (int k = 0; k <= ex.K; ++k) {
-      hipEvent_t e = N->lane_events[ex.K + 1 + k];
-      hipError_t he = hipEventRecord(e, N->lane_streams[k]);
-      if (he == hipSuccess) he = hipStreamWaitEvent(ex.st, e, 0);
-      if (he != hipSuccess && rj == TGP_OK && r == TGP_OK)
-        rj = fail(TGP_EHIP, "lane join: %s", hipGetErrorString(he));
-    }
-    if (r == TGP_OK) r = rj;
+    // join, also after an error, so that no fork is left open in a capture;
+    // the first failure is the one reported
+    hipError_t he = hipEventRecord(N->acc_events[2], ex.acc);
+    if (he == hipSuccess) he = hipStreamWaitEvent(ex.st, N->acc_events[2], 0);
+    if (he != hipSuccess && r == TGP_OK)
+      r = fail(TGP_EHIP, "accumulation join: %s", hipGetErrorString(he));
   }
   if (r != TGP_OK) return r;
   const LayerRt& last = N->L.back();
