@@ -355,17 +355,15 @@ tgp_status tgp_profile_clear(void);
  * tgp_debug_set_fwd_variant(v) forces the kernel family and tile
  * configuration of every bf16 convolution launch that goes through the
  * forward-convolution path (forward, recompute and data gradient): 0 is the
- * automatic per-shape plan; 1..7 row-stage tiles; 100..102 per-tap tiles;
- * 201..207 persistent row-stage tiles; 300 the 16x16x32 row-tiled kernel
- * (301 + i its configuration i); 400 the nine-tap whole-row kernel (401 + i
- * its configuration i); 500 the rectangular-tile 3x3 kernel (501 + i); 600
- * the tiled 1x1 kernel (601 + i).  A forced choice that does not fit a shape falls
- * back to the per-tap kernel.
+ * automatic per-shape plan; 100..102 per-tap tiles; 300 the 16x16x32
+ * row-tiled kernel (301 + i its configuration i); 400 the nine-tap whole-row
+ * kernel (401 + i its configuration i); 500 the rectangular-tile 3x3 kernel
+ * (501 + i); 600 the tiled 1x1 kernel (601 + i).  A forced choice that does
+ * not fit a shape, or names no kernel, falls back to the per-tap kernel.
  *
  * tgp_debug_set_rowtile_mask(m) enables kernel families in the automatic
- * plan: bit 0 the row-tiled kernel for forward calls, bit 1 for data-gradient
- * calls, bit 2 the row-blocked weight gradient, bit 3 the nine-tap whole-row
- * kernel (default: bits 0-3 set); bit 4 restricts the nine-tap kernel to
+ * plan: bit 2 the row-blocked weight gradient, bit 3 the nine-tap whole-row
+ * kernel (default: bits 0-3 set; 0 and 1 have no effect); bit 4 restricts the nine-tap kernel to
  * its four-wave layouts (by default it picks among four- and eight-wave
  * ones), bit 5 makes the row-blocked weight gradient use its four-wave
  * layout at every width, bit 6 keeps it at one filter row per work item

@@ -28,156 +28,6 @@ namespace {
 // written at the same chunk, hit distinct banks.
 __device__ __forceinline__ int swz(int row, int q) { return q ^ ((row ^ (row >> 3)) & 7); }
 
-// Global -> register prefetch of one 64-wide K step of the forward GEMM:
-// A = weight rows (16-byte chunk q of each of A_CH rows), B = im2col rows
-// (the pixel's neighbour at this step's tap, zero outside the image).
-template <int A_CH, int B_CH, int TAPS>
-__device__ __forceinline__ void fwd_gload(u32x4 (&ra)[A_CH], u32x4 (&rb)[B_CH], int ks, int cpt,
-                                          int Cin, int K, int W, int H,
-                                          const bf16_t* __restrict__ wbase,
-                                          const bf16_t* __restrict__ xbase,
-                                          const int (&ph)[B_CH], const int (&pw)[B_CH],
-                                          const bool (&pok)[B_CH]) {
-  const int tap = ks / cpt;
-  const int c0 = (ks - tap * cpt) * 64;
-  const int dr = (TAPS == 9) ? tap / 3 - 1 : 0;
-  const int dc = (TAPS == 9) ? tap % 3 - 1 : 0;
-#pragma unroll
-  for (int u = 0; u < A_CH; ++u)
-    ra[u] = *(const u32x4*)(wbase + (long)32 * u * K + tap * Cin + c0);
-  const long shift = ((long)dr * W + dc) * Cin + c0;
-#pragma unroll
-  for (int u = 0; u < B_CH; ++u) {
-    const int hh = ph[u] + dr, ww = pw[u] + dc;
-    const bool ok = pok[u] && (unsigned)hh < (unsigned)H && (unsigned)ww < (unsigned)W;
-    u32x4 v = u32x4{0, 0, 0, 0};
-    if (ok) v = *(const u32x4*)(xbase + (long)32 * u * Cin + shift);
-    rb[u] = v;
-  }
-}
-
-template <int A_CH, int B_CH>
-__device__ __forceinline__ void fwd_lstore(const u32x4 (&ra)[A_CH], const u32x4 (&rb)[B_CH],
-                                           u32x4* As, u32x4* Bs, int tid, int q) {
-#pragma unroll
-  for (int u = 0; u < A_CH; ++u) {
-    const int row = (tid >> 3) + 32 * u;
-    As[row * 8 + swz(row, q)] = ra[u];
-  }
-#pragma unroll
-  for (int u = 0; u < B_CH; ++u) {
-    const int row = (tid >> 3) + 32 * u;
-    Bs[row * 8 + swz(row, q)] = rb[u];
-  }
-}
-
-// ---------------------------------------------------------------- forward
-
-// WCO x WP waves; each wave owns TM x TN MFMA tiles of 32 x 32.
-template <int WCO, int WP, int TM, int TN, int TAPS>
-__global__ __launch_bounds__(256) void conv_fwd_mfma(
-    const bf16_t* __restrict__ X, const bf16_t* __restrict__ Wt,
-    const float* __restrict__ bias, bf16_t* __restrict__ Y, int P, int H, int W, int Cin,
-    int Cout, int relu) {
-  static_assert(WCO * WP == 4, "4 waves");
-  constexpr int BN = WCO * TM * 32;  // output channels per block
-  constexpr int BM = WP * TN * 32;   // pixels per block
-  constexpr int BK = 64;
-  constexpr int A_CH = BN * 8 / 256;  // 16-byte chunks per thread per K step
-  constexpr int B_CH = BM * 8 / 256;
-  static_assert(A_CH >= 1 && B_CH >= 1, "tile too small");
-  __shared__ u32x4 smem[2][(BN + BM) * 8];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wco = wave / WP, wp = wave % WP;
-  const int p0 = blockIdx.x * BM, co0 = blockIdx.y * BN;
-  const int K = TAPS * Cin;
-  const int cpt = Cin / BK;
-  const int nk = TAPS * cpt;
-  const int q = tid & 7;
-  const int HW = H * W;
-
-  int ph[B_CH], pw[B_CH];
-  bool pok[B_CH];
-#pragma unroll
-  for (int u = 0; u < B_CH; ++u) {
-    int p = p0 + (tid >> 3) + 32 * u;
-    pok[u] = p < P;
-    int pp = pok[u] ? p : 0;
-    int rem = pp % HW;
-    ph[u] = rem / W;
-    pw[u] = rem - ph[u] * W;
-  }
-  const bf16_t* xbase = X + (long)(p0 + (tid >> 3)) * Cin + q * 8;
-  const bf16_t* wbase = Wt + (long)(co0 + (tid >> 3)) * K + q * 8;
-
-  u32x4 ra[A_CH], rb[B_CH];
-  f32x16_t acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = f32x16_t{};
-
-  fwd_gload<A_CH, B_CH, TAPS>(ra, rb, 0, cpt, Cin, K, W, H, wbase, xbase, ph, pw, pok);
-  fwd_lstore<A_CH, B_CH>(ra, rb, smem[0], smem[0] + BN * 8, tid, q);
-  __syncthreads();
-  for (int ks = 0; ks < nk; ++ks) {
-    const int buf = ks & 1;
-    if (ks + 1 < nk)
-      fwd_gload<A_CH, B_CH, TAPS>(ra, rb, ks + 1, cpt, Cin, K, W, H, wbase, xbase, ph, pw, pok);
-    const u32x4* As = smem[buf];
-    const u32x4* Bs = smem[buf] + BN * 8;
-#pragma unroll
-    for (int kk = 0; kk < BK / 16; ++kk) {
-      const int qq = 2 * kk + (lane >> 5);
-      bf16x8_t a[TM], b[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        int row = wco * TM * 32 + i * 32 + (lane & 31);
-        a[i] = as_bf16x8(As[row * 8 + swz(row, qq)]);
-      }
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        int row = wp * TN * 32 + j * 32 + (lane & 31);
-        b[j] = as_bf16x8(Bs[row * 8 + swz(row, qq)]);
-      }
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = mfma32(a[i], b[j], acc[i][j]);
-    }
-    if (ks + 1 < nk) fwd_lstore<A_CH, B_CH>(ra, rb, smem[buf ^ 1], smem[buf ^ 1] + BN * 8, tid, q);
-    __syncthreads();
-  }
-
-  // Epilogue: lane holds pixel (lane & 31) of each 32x32 tile and, per group
-  // g, four consecutive channels 8g + 4*(lane>>5) + 0..3.
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      int p = p0 + wp * TN * 32 + j * 32 + (lane & 31);
-      if (p >= P) continue;
-      bf16_t* yrow = Y + (long)p * Cout;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        int co = co0 + wco * TM * 32 + i * 32 + 8 * g + 4 * (lane >> 5);
-        float v[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          v[t] = acc[i][j][4 * g + t];
-          if (bias) v[t] += bias[co + t];
-          if (relu) v[t] = fmaxf(v[t], 0.0f);
-        }
-        uint2 o;
-        o.x = f2bf(v[0]) | (f2bf(v[1]) << 16);
-        o.y = f2bf(v[2]) | (f2bf(v[3]) << 16);
-        *(uint2*)(yrow + co) = o;
-      }
-    }
-  }
-}
-
 // ---------------------------------------------------------------- forward (LDS DMA)
 
 // Sixteen zero bytes in device memory: the source of every im2col chunk that
@@ -369,238 +219,6 @@ __global__ __launch_bounds__(WCO * WP * 64) void conv_fwd_dma(
   }
 }
 
-// ---------------------------------------------------------------- forward, row-stage 3x3
-
-// 3x3 implicit GEMM whose K loop runs over stages (64-channel chunk c, filter
-// row r).  A stage holds, for a block of BM consecutive output pixels
-// [p0, p0 + BM), the BM + 2 input pixel rows q = p0 + (r-1) W - 1 + j
-// (j = 0 .. BM+1) and the weights of the three taps (r, 0..2); the three
-// column taps then read the pixel rows at offsets 0, 1, 2 from LDS, so each
-// input row is fetched once per filter row instead of once per tap.  A B
-// fragment whose source pixel (h + r - 1, w + s - 1) lies outside the image
-// is zeroed after the LDS read (that covers the left / right padding and the
-// rows that belong to the neighbouring sample).  K order (chunk, r, s,
-// channel) is fixed by the shape, so recomputation is bit-identical.
-//
-// SPLIT: the stages are divided over gridDim.x / tiles splits; each split
-// writes fp32 partials part[split][p][co] and conv_rows_epilogue sums them
-// in split order and applies bias, ReLU and the bf16 rounding.
-template <int WCO, int WP, int TM, int TN, int NS, bool SPLIT>
-__global__ __launch_bounds__(WCO * WP * 64) void conv_fwd_rows(
-    const bf16_t* __restrict__ X, const bf16_t* __restrict__ Wt,
-    const float* __restrict__ bias, bf16_t* __restrict__ Y, float* __restrict__ part, int P,
-    int H, int W, int Cin, int Cout, int relu, int co_major, int tiles, int st_per_split) {
-  constexpr int NW = WCO * WP;
-  constexpr int BN = WCO * TM * 32;
-  constexpr int BM = WP * TN * 32;
-  constexpr int RA = 3 * BN;                               // weight rows per stage
-  constexpr int ROWS = (RA + BM + 2 + 8 * NW - 1) / (8 * NW) * (8 * NW);
-  constexpr int LPS = ROWS / (8 * NW);                     // DMA instructions per wave per stage
-  static_assert(BN % 64 == 0, "weight rows must keep the swizzle phase");
-  __shared__ u32x4 smem[NS][ROWS * 8];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wco = wave / WP, wp = wave % WP;
-  const int nct = Cout / BN;
-  const int npt = tiles / nct;
-  int lb = xcd_remap(blockIdx.x, gridDim.x);
-  const int split = lb / tiles;
-  lb -= split * tiles;
-  const int p0 = (co_major ? lb % npt : lb / nct) * BM;
-  const int co0 = (co_major ? lb / npt : lb % nct) * BN;
-  const int nst = 3 * (Cin / 64);
-  const int s_begin = SPLIT ? split * st_per_split : 0;
-  const int s_end = SPLIT ? min(nst, s_begin + st_per_split) : nst;
-  const int HW = H * W;
-
-  // DMA sources: row rr of the stage (A: weight row of tap (r, rr / BN),
-  // B: input pixel row rr - RA); logical chunk from the swizzle.
-  const bf16_t* abase[LPS];
-  int brow[LPS];
-#pragma unroll
-  for (int u = 0; u < LPS; ++u) {
-    const int r = (wave + NW * u) * 8 + (lane >> 3);
-    const int c = (lane & 7) ^ ((r ^ (r >> 3)) & 7);
-    if ((wave + NW * u) * 8 < RA) {
-      const int t3 = r / BN, co = co0 + r % BN;
-      abase[u] = Wt + ((long)co * 9 + t3) * Cin + c * 8;   // + 3 * rfilt * Cin + c0
-      brow[u] = 0;
-    } else {
-      abase[u] = X + c * 8;
-      brow[u] = r - RA;                                   // j
-    }
-  }
-  const bf16_t* zero = (const bf16_t*)g_zero16;
-
-  // Validity of the B fragment of tile j for filter row rf, column tap t3.
-  unsigned vmask[TN];
-#pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const int p = p0 + wp * TN * 32 + j * 32 + (lane & 31);
-    unsigned m = 0;
-    if (p < P) {
-      const int rem = p % HW, h = rem / W, w = rem - (rem / W) * W;
-#pragma unroll
-      for (int rf = 0; rf < 3; ++rf)
-#pragma unroll
-        for (int t3 = 0; t3 < 3; ++t3)
-          if ((unsigned)(h + rf - 1) < (unsigned)H && (unsigned)(w + t3 - 1) < (unsigned)W)
-            m |= 1u << (rf * 3 + t3);
-    }
-    vmask[j] = m;
-  }
-
-  auto issue = [&](int st, int slot) __attribute__((always_inline)) {
-    const int chunk = st / 3, rf = st - chunk * 3;
-    const int c0 = chunk * 64;
-    const long qbase = (long)p0 + (long)(rf - 1) * W - 1;
-#pragma unroll
-    for (int u = 0; u < LPS; ++u) {
-      const bf16_t* g;
-      if ((wave + NW * u) * 8 < RA) {
-        g = abase[u] + (long)rf * 3 * Cin + c0;
-      } else {
-        const long q = qbase + brow[u];
-        const bool ok = brow[u] < BM + 2 && q >= 0 && q < P;
-        g = ok ? abase[u] + q * Cin + c0 : zero;
-      }
-      __builtin_amdgcn_global_load_lds((const void*)g,
-                                       TGP_LDS(&smem[slot][(wave + NW * u) * 64]), 16, 0, 0);
-    }
-  };
-
-  f32x16_t acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = f32x16_t{};
-  // this lane's bias values for the epilogue, loaded up front (channels
-  // co0 + wco TM 32 + 32 i + 8 g + 4 (lane / 32) + t)
-  f32x4_t bv[TM][4];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-      bv[i][g] = (!SPLIT && bias) ? *(const f32x4_t*)(bias + co0 + wco * TM * 32 + i * 32 +
-                                                     8 * g + 4 * (lane >> 5))
-                                  : f32x4_t{};
-
-  const int n = s_end - s_begin;
-#pragma unroll
-  for (int k = 0; k < NS - 1; ++k)
-    if (k < n) issue(s_begin + k, k);
-  for (int k = 0; k < n; ++k) {
-    const int ahead = min(NS - 2, n - 1 - k);
-    wait_stages<NS, LPS>(ahead);
-    ring_barrier();
-    if (k + NS - 1 < n) issue(s_begin + k + NS - 1, (k + NS - 1) % NS);
-    const int st = s_begin + k;
-    const int rf = st % 3;
-    const u32x4* As = smem[k % NS];
-    const u32x4* Bs = smem[k % NS] + RA * 8;
-    // 12 steps (3 column taps x 4 K sub-steps); the fragments of step t + 1
-    // are read from LDS while the MFMAs of step t run.
-    bf16x8_t fa[2][TM];
-    u32x4 fb[2][TN];
-    auto load = [&](int t, int buf) __attribute__((always_inline)) {
-      const int t3 = t >> 2, kk = t & 3;
-      const int qq = 2 * kk + (lane >> 5);
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int row = t3 * BN + wco * TM * 32 + i * 32 + (lane & 31);
-        fa[buf][i] = as_bf16x8(As[row * 8 + swz(row, qq)]);
-      }
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int row = wp * TN * 32 + j * 32 + (lane & 31) + t3;
-        fb[buf][j] = Bs[row * 8 + swz(row, qq)];
-      }
-    };
-    load(0, 0);
-#pragma unroll
-    for (int t = 0; t < 12; ++t) {
-      const int cur = t & 1;
-      // the B rows of a column tap that falls outside the image are zeroed
-      // here, at use, so that the wait for the LDS read sits after the
-      // previous step's MFMAs
-      bf16x8_t bm[TN];
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const bool ok = (vmask[j] >> (rf * 3 + (t >> 2))) & 1u;
-        bm[j] = as_bf16x8(ok ? fb[cur][j] : u32x4{0, 0, 0, 0});
-      }
-      if (t + 1 < 12) load(t + 1, cur ^ 1);
-      // fence: the reads above are issued before the MFMAs below, which
-      // then cover their latency
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = mfma32(fa[cur][i], bm[j], acc[i][j]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int p = p0 + wp * TN * 32 + j * 32 + (lane & 31);
-      if (p >= P) continue;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int co = co0 + wco * TM * 32 + i * 32 + 8 * g + 4 * (lane >> 5);
-        if constexpr (SPLIT) {
-          float4 o = make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2],
-                                 acc[i][j][4 * g + 3]);
-          *(float4*)(part + ((long)split * P + p) * Cout + co) = o;
-        } else {
-          float v[4];
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            v[t] = acc[i][j][4 * g + t] + bv[i][g][t];
-            if (relu) v[t] = fmaxf(v[t], 0.0f);
-          }
-          uint2 o;
-          o.x = f2bf(v[0]) | (f2bf(v[1]) << 16);
-          o.y = f2bf(v[2]) | (f2bf(v[3]) << 16);
-          *(uint2*)(Y + (long)p * Cout + co) = o;
-        }
-      }
-    }
-  }
-}
-
-// y[p][co] = bf16(act(sum_{s < S} part[s][p][co] + b[co])), s ascending.
-__global__ __launch_bounds__(256) void conv_rows_epilogue(const float* __restrict__ part,
-                                                          const float* __restrict__ bias,
-                                                          bf16_t* __restrict__ Y, long P,
-                                                          int Cout, int S, int relu) {
-  const long e = ((long)blockIdx.x * 256 + threadIdx.x) * 8;
-  const long n = P * Cout;
-  if (e >= n) return;
-  float v[8];
-  const float4 a0 = *(const float4*)(part + e), a1 = *(const float4*)(part + e + 4);
-  v[0] = a0.x; v[1] = a0.y; v[2] = a0.z; v[3] = a0.w;
-  v[4] = a1.x; v[5] = a1.y; v[6] = a1.z; v[7] = a1.w;
-  for (int s = 1; s < S; ++s) {
-    const float4 b0 = *(const float4*)(part + (long)s * n + e);
-    const float4 b1 = *(const float4*)(part + (long)s * n + e + 4);
-    v[0] += b0.x; v[1] += b0.y; v[2] += b0.z; v[3] += b0.w;
-    v[4] += b1.x; v[5] += b1.y; v[6] += b1.z; v[7] += b1.w;
-  }
-  const int co = e % Cout;
-  u32x4 o;
-#pragma unroll
-  for (int t = 0; t < 8; t += 2) {
-    float x0 = v[t], x1 = v[t + 1];
-    if (bias) { x0 += bias[co + t]; x1 += bias[co + t + 1]; }
-    if (relu) { x0 = fmaxf(x0, 0.f); x1 = fmaxf(x1, 0.f); }
-    o[t / 2] = f2bf(x0) | (f2bf(x1) << 16);
-  }
-  *(u32x4*)(Y + e) = o;
-}
-
 // ---------------------------------------------------------------- 1x1, resident weights
 
 // 1x1 convolution y[p][co] = act(sum_ci x[p][ci] w[co][ci] + b[co]) with
@@ -738,242 +356,6 @@ __global__ __launch_bounds__(512) void conv1x1_res(Mb1x1 io, int ng,
         if (p < P)
           *(u32x4*)(Y + (long)p * COUT + 32 * wave + 16 * h + 8 * (lane >> 5)) =
               u32x4{pk[2 * h][0], pk[2 * h][1], pk[2 * h + 1][0], pk[2 * h + 1][1]};
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------- forward, persistent row-stage 3x3
-
-// XOR swizzle of the four 16-byte chunks of a 64-byte LDS row: eight
-// consecutive rows read at one logical chunk land on eight distinct 16-byte
-// slots of a 128-byte bank cycle.
-__device__ __forceinline__ int swz4(int row, int q) { return q ^ ((row >> 1) & 3); }
-
-// Persistent 3x3 implicit GEMM.  The K loop of an output tile (BN channels x
-// BM consecutive pixels) runs over stages (32-channel chunk c, filter row r):
-// a stage holds the weights of taps (r, 0..2) for the tile's channels and the
-// BM + 2 input pixel rows q = p0 + (r - 1) W - 1 + j, so each input row is
-// fetched once per filter row and read by the three column taps at row
-// offsets 0, 1, 2.  A B fragment whose source pixel lies outside the image
-// (left / right padding, or a row of the neighbouring sample) is zeroed at
-// use.  Work items are (split, pixel tile, channel tile); block lb of G takes
-// items lb, lb + G, ... and streams all their stages through one NS-deep LDS
-// ring, so the next item's loads are in flight while the current item
-// finishes and writes its tile.  Each wave owns TM x TN MFMA tiles of 32 x 32.
-// The K order (chunk, r, s, channel) is fixed by the shape and the split
-// count, so a recomputation is bit-identical.
-//
-// SPLIT: item split s covers stages [s * nk, (s + 1) * nk) and writes fp32
-// partials part[s][p][co]; conv_rows_epilogue sums them in split order.
-template <int WCO, int WP, int TM, int TN, int NS, bool SPLIT>
-__global__ __launch_bounds__(WCO * WP * 64) void conv_rows_pers(
-    const bf16_t* __restrict__ X, const bf16_t* __restrict__ Wt,
-    const float* __restrict__ bias, bf16_t* __restrict__ Y, float* __restrict__ part, int P,
-    int H, int W, int Cin, int Cout, int relu, int co_major, int npt, int S) {
-  constexpr int NW = WCO * WP;
-  constexpr int BN = WCO * TM * 32;                        // output channels per tile
-  constexpr int BM = WP * TN * 32;                         // output pixels per tile
-  constexpr int RA = 3 * BN;                               // weight rows per stage
-  constexpr int RB = BM + 2;                               // input pixel rows per stage
-  constexpr int RPI = 16 * NW;                             // LDS rows per DMA round
-  constexpr int ROWS = (RA + RB + RPI - 1) / RPI * RPI;
-  constexpr int L = ROWS / RPI;                            // DMA instructions per wave per stage
-  constexpr int LA = RA / RPI;                             // ... of which weight rows
-  static_assert(RA % RPI == 0, "weight rows must fill whole DMA rounds");
-  __shared__ u32x4 smem[NS][ROWS * 4];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wco = wave / WP, wp = wave % WP;
-  const int wcu = __builtin_amdgcn_readfirstlane(wco);
-  const int nct = Cout / BN;
-  const int tiles = npt * nct;
-  const int G = gridDim.x;
-  const int lb = xcd_remap(blockIdx.x, G);
-  const int items = tiles * S;
-  const int n_items = lb < items ? (items - lb + G - 1) / G : 0;
-  const int nk = 3 * (Cin / 32) / S;                       // stages per item
-  const int total = n_items * nk;
-  const int HW = H * W;
-
-  // Buffer descriptors: a byte offset at or past the end (or negative, read
-  // as unsigned) returns zeros, which is the zero padding of pixels outside
-  // [0, P).  Sizes are below 2^31 (checked by the launcher).
-  const u32x4 rx = make_rsrc(X, P * Cin * 2);
-  const u32x4 rw = make_rsrc(Wt, Cout * 9 * Cin * 2);
-
-  // Per-lane byte offsets of the rows this lane fills (loop invariant).
-  // Weight row of instruction u < LA: channel co (within the tile), column
-  // tap t3; pixel row of instruction u >= LA: j (0 .. BM + 1, or padding).
-  int aoff[LA], boff[L - LA];
-#pragma unroll
-  for (int u = 0; u < L; ++u) {
-    const int row = (wave + NW * u) * 16 + (lane >> 2);
-    const int c = (lane & 3) ^ ((row >> 1) & 3);
-    if (u < LA) {
-      const int t3 = row / BN, co = row - t3 * BN;
-      aoff[u < LA ? u : 0] = ((co * 9 + t3) * Cin + c * 8) * 2;
-    } else {
-      boff[u < LA ? 0 : u - LA] = ((row - RA) * Cin + c * 8) * 2;
-    }
-  }
-
-  auto coords = [&](int it, int& split, int& p0, int& co0) __attribute__((always_inline)) {
-    const int item = lb + it * G;
-    split = item / tiles;
-    const int t = item - split * tiles;
-    p0 = (co_major ? t % npt : t / nct) * BM;
-    co0 = (co_major ? t / npt : t % nct) * BN;
-  };
-
-  // issue side: the item whose stage is loaded next
-  int i_it = 0, i_ks = 0, i_split = 0, i_p0 = 0, i_co0 = 0;
-  if (total > 0) coords(0, i_split, i_p0, i_co0);
-  auto issue = [&](int slot) __attribute__((always_inline)) {
-    const int stg = i_split * nk + i_ks;
-    const int chunk = stg / 3, rf = stg - 3 * chunk;
-    const int c0 = chunk * 32;
-    const int soff_a = ((i_co0 * 9 + 3 * rf) * Cin + c0) * 2;
-    const int base_b = ((i_p0 + (rf - 1) * W - 1) * Cin + c0) * 2;
-#pragma unroll
-    for (int u = 0; u < L; ++u) {
-      auto* dst = TGP_LDS(&smem[slot][(wave + NW * u) * 64]);
-      if (u < LA)
-        dma16(rw, dst, aoff[u < LA ? u : 0], soff_a);
-      else
-        dma16(rx, dst, base_b + boff[u < LA ? 0 : u - LA], 0);
-    }
-    if (++i_ks == nk) {
-      i_ks = 0;
-      if (++i_it < n_items) coords(i_it, i_split, i_p0, i_co0);
-    }
-  };
-
-#pragma unroll
-  for (int k = 0; k < NS - 1; ++k)
-    if (k < total) issue(k);
-
-  // compute side: one item at a time, its stages streamed through the ring
-  int idx = 0;
-  for (int c_it = 0; c_it < n_items; ++c_it) {
-    int c_split, c_p0, c_co0;
-    coords(c_it, c_split, c_p0, c_co0);
-    unsigned vmask[TN];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int p = c_p0 + wp * TN * 32 + j * 32 + (lane & 31);
-      unsigned m = 0;
-      if (p < P) {
-        const int rem = p % HW, h = rem / W, w = rem - (rem / W) * W;
-#pragma unroll
-        for (int rf = 0; rf < 3; ++rf)
-#pragma unroll
-          for (int t3 = 0; t3 < 3; ++t3)
-            if ((unsigned)(h + rf - 1) < (unsigned)H && (unsigned)(w + t3 - 1) < (unsigned)W)
-              m |= 1u << (rf * 3 + t3);
-      }
-      vmask[j] = m;
-    }
-
-    f32x16_t acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] = f32x16_t{};
-
-    for (int c_ks = 0; c_ks < nk; ++c_ks, ++idx) {
-      // Loads complete in order, so stage idx is in when at most the stages
-      // issued after it are pending (stores of a tile epilogue only make
-      // this wait longer).
-      wait_stages<NS, L>(min(NS - 2, total - 1 - idx));
-      ring_barrier();
-      if (idx + NS - 1 < total) issue((idx + NS - 1) % NS);
-      const int rf = (c_split * nk + c_ks) % 3;
-      const u32x4* As = smem[idx % NS];
-      const u32x4* Bs = smem[idx % NS] + RA * 4;
-      // 6 steps (3 column taps x 2 K sub-steps of 16 channels).  Step t + 1's
-      // fragments are read while step t's MFMAs run, and its B fragments
-      // are masked between them.
-      bf16x8_t fa[2][TM], bm[2][TN];
-      u32x4 fb[TN];
-      auto load = [&](int t, int buf) __attribute__((always_inline)) {
-        const int t3 = t >> 1, kk = t & 1;
-        const int qq = 2 * kk + (lane >> 5);
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const int row = t3 * BN + wco * TM * 32 + i * 32 + (lane & 31);
-          fa[buf][i] = as_bf16x8(As[row * 4 + swz4(row, qq)]);
-        }
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int row = wp * TN * 32 + j * 32 + (lane & 31) + t3;
-          fb[j] = Bs[row * 4 + swz4(row + RA, qq)];
-        }
-      };
-      auto mask = [&](int t, int buf) __attribute__((always_inline)) {
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const bool ok = (vmask[j] >> (rf * 3 + (t >> 1))) & 1u;
-          bm[buf][j] = as_bf16x8(ok ? fb[j] : u32x4{0, 0, 0, 0});
-        }
-      };
-      load(0, 0);
-      mask(0, 0);
-#pragma unroll
-      for (int t = 0; t < 6; ++t) {
-        const int cur = t & 1;
-        if (t + 1 < 6) load(t + 1, cur ^ 1);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j) acc[i][j] = mfma32(fa[cur][i], bm[cur][j], acc[i][j]);
-        if (t + 1 < 6) {
-          mask(t + 1, cur ^ 1);
-          // reads first, half the MFMAs (covering the read latency), the
-          // masking, then the other half
-          __builtin_amdgcn_sched_group_barrier(0x100, TM + TN, 0);
-          __builtin_amdgcn_sched_group_barrier(0x008, (TM * TN + 1) / 2, 0);
-          __builtin_amdgcn_sched_group_barrier(0x002, 4 * TN + 8, 0);
-          __builtin_amdgcn_sched_group_barrier(0x008, TM * TN / 2, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-
-    // tile epilogue; the bias goes through the constant address space so its
-    // (wave-uniform) loads are scalar and do not wait on the DMA ring
-    const __attribute__((address_space(4))) float* cbias =
-        (const __attribute__((address_space(4))) float*)bias;
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int p = c_p0 + wp * TN * 32 + j * 32 + (lane & 31);
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int cob = c_co0 + wcu * TM * 32 + i * 32 + 8 * g;
-          const int co = cob + 4 * (lane >> 5);
-          if constexpr (SPLIT) {
-            const float4 o = make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1],
-                                         acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
-            if (p < P) *(float4*)(part + ((long)c_split * P + p) * Cout + co) = o;
-          } else {
-            float v[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              v[e] = acc[i][j][4 * g + e];
-              if (bias) {
-                const float b0 = cbias[cob + e], b1 = cbias[cob + 4 + e];
-                v[e] += (lane >> 5) ? b1 : b0;
-              }
-              if (relu) v[e] = fmaxf(v[e], 0.0f);
-            }
-            uint2 o;
-            o.x = f2bf(v[0]) | (f2bf(v[1]) << 16);
-            o.y = f2bf(v[2]) | (f2bf(v[3]) << 16);
-            if (p < P) *(uint2*)(Y + (long)p * Cout + co) = o;
-          }
-        }
       }
     }
   }
@@ -1313,119 +695,15 @@ hipError_t launch_fwd_dma(const char* name9, const char* name1, const bf16_t* X,
 // Row-stage forward launches.  S > 1 splits the stages over S blocks per
 // tile; the partials live in `part` (capacity part_cap floats; S is reduced
 // to fit, which only happens under measurement overrides).
-template <int WCO, int WP, int TM, int TN, int NS>
-hipError_t launch_fwd_rows(const char* name_f, const char* name_t, const bf16_t* X,
-                           const bf16_t* Wt, const float* b,
-                           bf16_t* Y, float* part, size_t part_cap, long P, const ConvShape& s,
-                           int relu, int S, hipStream_t st) {
-  constexpr int BN = WCO * TM * 32, BM = WP * TN * 32;
-  if (s.cout % BN || s.cin % 64 || s.taps != 9) return hipErrorInvalidValue;
-  const int tiles = cdiv(P, BM) * (s.cout / BN);
-  const int nst = 3 * (s.cin / 64);
-  if (S > nst) S = nst;
-  while (S > 1 && (size_t)S * P * s.cout > part_cap) --S;
-  const int sps = cdiv(nst, S > 1 ? S : 1);
-  S = cdiv(nst, sps);
-  const double flops = 2.0 * P * s.cout * 9 * s.cin;
-  const double xbytes = 2.0 * P * s.cin, wbytes = 2.0 * s.cout * 9 * s.cin;
-  const int co_major = g_fwd_order >= 0 ? g_fwd_order : (wbytes > xbytes ? 1 : 0);
-  dim3 grid(tiles * S), block(WCO * WP * 64);
-  if (S == 1) {
-    ProfScope ps(name_f, flops, xbytes + wbytes + 2.0 * P * s.cout, st);
-    TGP_LAUNCH(ps, (conv_fwd_rows<WCO, WP, TM, TN, NS, false>), grid, block, 0, st, X, Wt, b,
-                       Y, part, (int)P, s.H, s.W, s.cin, s.cout, relu, co_major, tiles, sps);
-    return launch_status();
-  }
-  {
-    ProfScope ps(name_t, flops, xbytes + wbytes + 4.0 * S * P * s.cout, st);
-    TGP_LAUNCH(ps, (conv_fwd_rows<WCO, WP, TM, TN, NS, true>), grid, block, 0, st, X, Wt, b,
-                       Y, part, (int)P, s.H, s.W, s.cin, s.cout, relu, co_major, tiles, sps);
-  }
-  hipError_t e = launch_status();
-  if (e != hipSuccess) return e;
-  ProfScope ps2("conv_rows_epilogue", 0.0, 4.0 * S * P * s.cout + 2.0 * P * s.cout, st);
-  TGP_LAUNCH(ps2, conv_rows_epilogue, dim3(cdiv(P * s.cout, 2048)), dim3(256), 0, st, part, b,
-                     Y, P, s.cout, S, relu);
-  return launch_status();
-}
-
-#define TGP_ROWS_CFG(WCO, WP, TM, TN, NS, S)                                                   \
-  launch_fwd_rows<WCO, WP, TM, TN, NS>(                                                        \
-      "conv_fwd_rows<" #WCO "," #WP "," #TM "," #TN "," #NS ",false>",                          \
-      "conv_fwd_rows<" #WCO "," #WP "," #TM "," #TN "," #NS ",true>", X, Wt, b, Y, part, part_cap, \
-      P, s, relu, S, st)
-
-// Persistent row-stage launches.  S (a divisor of the 3 * Cin / 32 stages,
-// reduced to fit part_cap) splits every tile's K range; the grid is the
-// number of blocks that fit on the chip at once, capped by the item count.
-constexpr int rows_pers_lds(int WCO, int WP, int TM, int TN, int NS) {
-  return NS * ((3 * WCO * TM * 32 + WP * TN * 32 + 2 + 16 * WCO * WP - 1) / (16 * WCO * WP) *
-               (16 * WCO * WP)) * 64;
-}
-
-template <int WCO, int WP, int TM, int TN, int NS>
-hipError_t launch_rows_pers(const char* name_f, const char* name_t, const bf16_t* X,
-                            const bf16_t* Wt, const float* b,
-                            bf16_t* Y, float* part, size_t part_cap, long P, const ConvShape& s,
-                            int relu, int S, hipStream_t st) {
-  constexpr int BN = WCO * TM * 32, BM = WP * TN * 32, NW = WCO * WP;
-  constexpr int LDS = rows_pers_lds(WCO, WP, TM, TN, NS);
-  static_assert(LDS <= 160 * 1024, "LDS ring too large");
-  if (s.cout % BN || s.cin % 32 || s.taps != 9) return hipErrorInvalidValue;
-  // byte offsets into X and W are 32-bit, negative ones must read as out of range
-  if ((double)(P + BM + 2L * s.W + 2) * s.cin * 2 >= 2147483648.0 ||
-      (double)s.cout * 9 * s.cin * 2 >= 2147483648.0)
-    return hipErrorInvalidValue;
-  const int nst = 3 * (s.cin / 32);
-  if (S < 1) S = 1;
-  if (S > nst) S = nst;
-  while (S > 1 && (nst % S || (size_t)S * P * s.cout > part_cap)) --S;
-  const int npt = cdiv(P, BM);
-  const long items = (long)npt * (s.cout / BN) * S;
-  int occ = (160 * 1024) / LDS;
-  if (occ * NW > 16) occ = 16 / NW;
-  if (occ < 1) occ = 1;
-  const int G = (int)(items < 256L * occ ? items : 256L * occ);
-  const double flops = 2.0 * P * s.cout * 9 * s.cin;
-  const double xbytes = 2.0 * P * s.cin, wbytes = 2.0 * s.cout * 9 * s.cin;
-  const int co_major = g_fwd_order >= 0 ? g_fwd_order : (wbytes > xbytes ? 1 : 0);
-  if (G == 0) return hipSuccess;
-  if (S == 1) {
-    ProfScope ps(name_f, flops, xbytes + wbytes + 2.0 * P * s.cout, st);
-    TGP_LAUNCH(ps, (conv_rows_pers<WCO, WP, TM, TN, NS, false>), dim3(G), dim3(NW * 64), 0, st,
-                       X, Wt, b, Y, part, (int)P, s.H, s.W, s.cin, s.cout, relu, co_major, npt, 1);
-    return launch_status();
-  }
-  {
-    ProfScope ps(name_t, flops, xbytes + wbytes + 4.0 * S * P * s.cout, st);
-    TGP_LAUNCH(ps, (conv_rows_pers<WCO, WP, TM, TN, NS, true>), dim3(G), dim3(NW * 64), 0, st,
-                       X, Wt, b, Y, part, (int)P, s.H, s.W, s.cin, s.cout, relu, co_major, npt, S);
-  }
-  hipError_t e = launch_status();
-  if (e != hipSuccess) return e;
-  ProfScope ps2("conv_rows_epilogue", 0.0, 4.0 * S * P * s.cout + 2.0 * P * s.cout, st);
-  TGP_LAUNCH(ps2, conv_rows_epilogue, dim3(cdiv(P * s.cout, 2048)), dim3(256), 0, st, part, b,
-                     Y, P, s.cout, S, relu);
-  return launch_status();
-}
-
-#define TGP_PERS_CFG(WCO, WP, TM, TN, NS, S)                                                    \
-  launch_rows_pers<WCO, WP, TM, TN, NS>(                                                        \
-      "conv_rows_pers<" #WCO "," #WP "," #TM "," #TN "," #NS ",false>",                          \
-      "conv_rows_pers<" #WCO "," #WP "," #TM "," #TN "," #NS ",true>", X, Wt, b, Y, part, part_cap, \
-      P, s, relu, S, st)
-
 int g_fwd_split = 0;   // > 0 forces the split count (measurement only)
-// Measurement only: bit 0 allows the row-tiled kernel for forward calls, bit
-// 1 for data-gradient calls, bit 2 the row-blocked weight gradient, bit 3
-// the nine-tap row kernel.
+// Measurement only: bit 2 allows the row-blocked weight gradient, bit 3 the
+// nine-tap row kernel.
 int g_rowtile_mask = 15;
-thread_local int t_in_dgrad = 0;
 
 struct FwdPlan {
-  int cfg;   // 1..: row-stage configurations; 100+: per-tap (150: 1x1 with resident
-             // weights); 200+: persistent row-stage
-  int S;
+  int cfg;   // 100+: per-tap (150: 1x1 with resident weights); 300+: row-tiled; 400+:
+             // whole-row; 500+: rectangular tiles; 600+: 1x1 tiles
+  int S;     // shares of the sum (500)
 };
 
 // The resident-weight 1x1 kernel's shapes (its static LDS holds 256 x 256
@@ -1453,51 +731,29 @@ static hipError_t launch_1x1_res(int n, const void* const* x, const bf16_t* Wt, 
   return launch_status();
 }
 
-struct PersTile { int BN, BM; };
-PersTile pers_tile(int cfg) {
-  switch (cfg) {
-    case 202: return {128, 256};
-    case 203: return {64, 256};
-    case 204: return {128, 128};
-    case 205: return {64, 640};
-    case 206: return {128, 256};
-    case 207: return {128, 256};
-    default: return {64, 512};
-  }
-}
-
 // Pure function of the per-sample shape (H, W, Cin, Cout, taps), plus the
 // measurement overrides: the kernel family and the split count fix the K
 // summation order, so keeping them independent of the number of samples
 // keeps every sample's output bit-identical whatever the micro-batch size.
 // The tile-count heuristics use a nominal micro-batch of 4 samples.
 FwdPlan fwd_plan(const ConvShape& s) {
-  const long P = 4L * s.H * s.W;
   FwdPlan pl{0, 1};
   if (s.cin % 64 || s.cout % 64) {   // the kernels that take any multiple of 8
     pl.cfg = s.taps == 9 ? 500 : 600;
     if (g_fwd_variant >= pl.cfg && g_fwd_variant < pl.cfg + 100) pl.cfg = g_fwd_variant;
     return pl;
   }
-  // Measured per shape (3x3, kernel time in a step): the nine-tap
-  // whole-row kernel is fastest on images of 48 x 48 and up, and from 24 x 24
-  // where one micro-batch gives it at least 48 tiles (at 24 x 24 a paired
-  // launch of it takes 27 us where the split-K row-stage kernel and its
-  // epilogue take 40; with fewer tiles, as at one or two samples, most CUs
-  // idle); the persistent row-stage kernel with split K on the other small,
-  // deep layers (few pixel tiles, long K); the per-tap kernel for the rest.
-  const bool k3 = s.taps == 9 && s.cin % 64 == 0;
+  // The nine-tap whole-row kernel on images of 48 x 48 and up of the widths it
+  // is built for, and from 24 x 24 where one micro-batch gives it at least 48
+  // tiles; the rectangular tiles for every other 3x3 layer (us, forward + data
+  // gradient with the transform of its weights, against the kernels these
+  // shapes had: 64 at 224 x 224 x 1 22 / 44, x 16 185 / 285; 256 at 56 x 56 x 8 75
+  // / 141, x 1 29 / 61; 256 at 28 x 28 x 32 79 / 237; 64 at 14 x 14 x 2 12 / 44).
+  const bool k3 = s.taps == 9;
   const long hw = (long)s.H * s.W;
   if (k3 && (hw >= 48 * 48 || (hw >= 24 * 24 && conv_rows32_tiles(s) >= 48)) &&
       (g_rowtile_mask >> 3 & 1) && conv_rows32_ok(s)) {
     pl.cfg = 400;  // whole-row tiles, nine taps per stage, 32x32x16
-  } else if (k3 && (long)s.H * s.W >= 96 * 96 && conv_rowtile_ok(s) &&
-      (g_rowtile_mask >> (t_in_dgrad ? 1 : 0) & 1)) {
-    pl.cfg = 300;  // row-tiled 16x16x32
-  } else if (k3 && P <= 4096) {
-    pl.cfg = 203;  // persistent row-stage, 64 x 256
-  } else if (k3 && P <= 16384 && s.cin >= 256 && s.cout % 128 == 0) {
-    pl.cfg = 207;  // persistent row-stage, 128 x 256, 8 waves
   } else if (conv1x1_res_ok(s)) {
     pl.cfg = 150;  // 1x1, all weights resident in LDS
   } else if (conv_tile_ok(s)) {
@@ -1511,6 +767,8 @@ FwdPlan fwd_plan(const ConvShape& s) {
   if (pl.cfg == 150 && !conv1x1_res_ok(s)) pl.cfg = 100;
   if (pl.cfg >= 500) {
     if (pl.cfg >= 600 ? !conv1x1_tile_ok(s) : !conv_tile_ok(s)) pl.cfg = 100;
+    if (pl.cfg < 600)
+      pl.S = g_fwd_split > 0 && s.cin / 16 % g_fwd_split == 0 ? g_fwd_split : conv_tile_split(s);
     return pl;
   }
   if (pl.cfg >= 400) {
@@ -1523,43 +781,26 @@ FwdPlan fwd_plan(const ConvShape& s) {
     if (!conv_rowtile_ok(s)) pl.cfg = 100;
     return pl;
   }
-  if ((pl.cfg == 2 || pl.cfg == 5) && s.cout % 128) pl.cfg = pl.cfg == 2 ? 1 : 3;  // 128-wide tiles need cout % 128 == 0
-  if (pl.cfg >= 200) {
-    if (s.taps != 9 || s.cin % 32) { pl.cfg = 100; return pl; }
-    const PersTile t = pers_tile(pl.cfg);
-    if (s.cout % t.BN) pl.cfg = 201;                   // 64-channel tiles fit every shape here
-    const PersTile u = pers_tile(pl.cfg);
-    const long tiles = cdiv(P, u.BM) * (long)(s.cout / u.BN);
-    const int nst = 3 * (s.cin / 32);
-    int S = 1;
-    // split K only when the tiles alone leave most of the chip idle
-    while (tiles * S < 192 && S < 8) {
-      int n = S + 1;
-      while (n <= nst && nst % n) ++n;
-      if (n > nst) break;
-      S = n;
-    }
-    pl.S = g_fwd_split > 0 ? g_fwd_split : S;
-    return pl;
-  }
-  if (pl.cfg < 100) {
-    const int BN = (pl.cfg == 2 || pl.cfg == 5) ? 128 : 64;
-    const int BM = (pl.cfg == 2 || pl.cfg == 5 || pl.cfg == 6 || pl.cfg == 7) ? 128 : 256;
-    const long tiles = cdiv(P, BM) * (s.cout / BN);
-    const int nst = 3 * (s.cin / 64);
-    int S = tiles > 0 ? (int)cdiv(512, tiles) : 1;
-    if (S > nst / 3) S = nst / 3 > 0 ? nst / 3 : 1;   // at least one channel chunk per split
-    if (S < 1) S = 1;
-    pl.S = g_fwd_split > 0 ? g_fwd_split : S;
-  }
+  if (pl.cfg < 100 || (pl.cfg >= 200 && pl.cfg < 300)) pl.cfg = 100;   // no such kernel
   return pl;
+}
+
+// A launch of the whole-row kernel's shapes that is too small for it: its tiles
+// are whole rows, so few samples leave CUs idle, where the rectangular tiles can
+// be smaller.  Both sum over (chunk, tap, channel), so the choice does not
+// change a bit.  (us, forward, rectangular / rows: 128 at 96 x 96 x 1 10.4 /
+// 15.5, 64 at 192 x 192 x 1 11.1 / 14.9, 256 at 48 x 48 x 4 22.9 / 22.1, 128 at
+// 96 x 96 x 4 22.3 / 19.8.)
+static bool tile_instead(const FwdPlan& pl, const ConvShape& s, int n) {
+  return pl.cfg == 400 && g_fwd_variant == 0 && n * s.pixels() * s.cout < 2359296 && conv_tile_ok(s);
 }
 
 // The rectangular-tile kernel (500 ..) or the 1x1 tile kernel (600 ..), in the
 // configuration a forced plan names.
-static hipError_t launch_tile_cfg(int cfg, int n, const void* const* x, const void* w,
+static hipError_t launch_tile_cfg(const FwdPlan& pl, int n, const void* const* x, const void* w,
                                   const float* b, void* const* y, const ConvShape& s, int relu,
-                                  bool dg, hipStream_t st) {
+                                  bool dg, float* const* part, size_t part_cap, hipStream_t st) {
+  const int cfg = pl.cfg;
   if (s.taps == 1) {
     g_1x1_cfg = cfg >= 601 ? cfg - 601 : -1;
     const hipError_t e = conv_forward_1x1(n, x, w, b, y, s, relu, dg, st);
@@ -1567,7 +808,8 @@ static hipError_t launch_tile_cfg(int cfg, int n, const void* const* x, const vo
     return e;
   }
   g_tile_cfg = cfg >= 501 ? cfg - 501 : -1;
-  const hipError_t e = conv_forward_tile(n, x, w, b, y, s, relu, dg, st);
+  if (pl.S > 1 && (size_t)pl.S * s.pixels() * s.cout > part_cap) return hipErrorInvalidValue;
+  const hipError_t e = conv_forward_tile(n, x, w, b, y, s, relu, dg, pl.S, part, st);
   g_tile_cfg = -1;
   return e;
 }
@@ -1576,23 +818,24 @@ static hipError_t launch_tile_cfg(int cfg, int n, const void* const* x, const vo
 // that reads the forward weights, and that launch (also where a forced plan
 // names another kernel but no transformed weights were planned for).
 bool conv_dgrad_tile_planned(const ConvShape& t) {
-  t_in_dgrad = 1;
-  const bool r = fwd_plan(t).cfg >= 500;
-  t_in_dgrad = 0;
-  return r;
+  return fwd_plan(t).cfg >= 500;
+}
+bool conv_dgrad_tile_now(const ConvShape& t, int n) {
+  const FwdPlan pl = fwd_plan(t);
+  return pl.cfg >= 500 || tile_instead(pl, t, n);
 }
 hipError_t conv_dgrad_tile(int n, const void* const* dz, const void* w, void* const* dx,
-                           const ConvShape& t, hipStream_t st) {
-  const int base = t.taps == 9 ? 500 : 600;
-  const bool forced = g_fwd_variant >= base && g_fwd_variant < base + 100;
-  return launch_tile_cfg(forced ? g_fwd_variant : base, n, dz, w, nullptr, dx, t, 0, true, st);
+                           const ConvShape& t, float* const* part, size_t part_cap,
+                           hipStream_t st) {
+  FwdPlan pl = fwd_plan(t);
+  if (pl.cfg < 500) pl = FwdPlan{t.taps == 9 ? 500 : 600, 1};
+  return launch_tile_cfg(pl, n, dz, w, nullptr, dx, t, 0, true, part, part_cap, st);
 }
 
 size_t conv_forward_partial_floats(int dt, const ConvShape& s) {
   if (!mfma_fwd_ok(dt, s)) return 0;
   FwdPlan pl = fwd_plan(s);
-  const bool splits = pl.cfg < 100 || (pl.cfg >= 200 && pl.cfg < 300);   // per-tap and row-tiled never split
-  return splits && pl.S > 1 ? (size_t)pl.S * s.pixels() * s.cout : 0;
+  return pl.S > 1 ? (size_t)pl.S * s.pixels() * s.cout : 0;
 }
 
 hipError_t conv_forward_mfma(const void* x, const void* w, const float* b, void* y,
@@ -1605,9 +848,11 @@ hipError_t conv_forward_mfma(const void* x, const void* w, const float* b, void*
   const bf16_t* X2 = nullptr;   // per-tap configurations: one micro-batch
   bf16_t* Y2 = nullptr;
   const FwdPlan pl = fwd_plan(s);
-  const bool wide = s.cout % 128 == 0;
   if (pl.cfg == 150) return launch_1x1_res(1, &x, Wt, b, &y, s, relu, st);
-  if (pl.cfg >= 500) return launch_tile_cfg(pl.cfg, 1, &x, w, b, &y, s, relu, false, st);
+  if (tile_instead(pl, s, 1))
+    return launch_tile_cfg(FwdPlan{500, 1}, 1, &x, w, b, &y, s, relu, false, nullptr, 0, st);
+  if (pl.cfg >= 500)
+    return launch_tile_cfg(pl, 1, &x, w, b, &y, s, relu, false, &part, part_cap, st);
   if (pl.cfg >= 400) {
     g_rows32_cfg = pl.cfg >= 401 ? pl.cfg - 401 : -1;
     const hipError_t e = conv_forward_rows32(1, &x, w, b, &y, s, relu, st);
@@ -1619,25 +864,6 @@ hipError_t conv_forward_mfma(const void* x, const void* w, const float* b, void*
     const hipError_t e = conv_forward_rowtile(x, w, b, y, s, relu, st);
     g_rowtile_cfg = -1;
     return e;
-  }
-  switch (pl.cfg) {
-    case 1: return TGP_ROWS_CFG(1, 4, 2, 2, 2, pl.S);                 // 64 x 256, 4 waves
-    case 2: return wide ? TGP_ROWS_CFG(2, 2, 2, 2, 2, pl.S)           // 128 x 128, 4 waves
-                        : TGP_ROWS_CFG(1, 4, 2, 2, 2, pl.S);
-    case 3: return TGP_ROWS_CFG(1, 8, 2, 1, 2, pl.S);                 // 64 x 256, 8 waves
-    case 4: return TGP_ROWS_CFG(2, 4, 1, 2, 2, pl.S);                 // 64 x 256, 8 waves
-    case 5: return wide ? TGP_ROWS_CFG(2, 4, 2, 1, 2, pl.S)           // 128 x 128, 8 waves
-                        : TGP_ROWS_CFG(1, 8, 2, 1, 2, pl.S);
-    case 6: return TGP_ROWS_CFG(1, 4, 2, 1, 2, pl.S);                 // 64 x 128, 4 waves
-    case 7: return TGP_ROWS_CFG(1, 4, 2, 1, 3, pl.S);                 // 64 x 128, 4 waves, 3 stages
-    case 201: return TGP_PERS_CFG(1, 4, 2, 4, 3, pl.S);               // 64 x 512
-    case 202: return TGP_PERS_CFG(2, 2, 2, 4, 3, pl.S);               // 128 x 256
-    case 203: return TGP_PERS_CFG(1, 4, 2, 2, 4, pl.S);               // 64 x 256
-    case 204: return TGP_PERS_CFG(2, 2, 2, 2, 4, pl.S);               // 128 x 128
-    case 205: return TGP_PERS_CFG(1, 4, 2, 5, 2, pl.S);               // 64 x 640
-    case 206: return TGP_PERS_CFG(2, 2, 2, 4, 2, pl.S);               // 128 x 256, 2 stages
-    case 207: return TGP_PERS_CFG(2, 4, 2, 2, 3, pl.S);               // 128 x 256, 8 waves
-    default: break;
   }
   // per-tap kernel (1x1 convolutions, and reference configurations)
   const int v = pl.cfg >= 100 ? pl.cfg - 100 : 0;
@@ -1868,7 +1094,10 @@ hipError_t conv_forward_mfma_n(int n, const void* const* x, const void* w, const
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
   const FwdPlan pl = fwd_plan(s);
   if (pl.cfg == 150) return launch_1x1_res(n, x, (const bf16_t*)w, b, y, s, relu, st);
-  if (pl.cfg >= 500) return launch_tile_cfg(pl.cfg, n, x, w, b, y, s, relu, false, st);
+  if (tile_instead(pl, s, n))
+    return launch_tile_cfg(FwdPlan{500, 1}, n, x, w, b, y, s, relu, false, nullptr, 0, st);
+  if (pl.cfg >= 500)
+    return launch_tile_cfg(pl, n, x, w, b, y, s, relu, false, part, part_cap, st);
   if (pl.cfg >= 400) {
     g_rows32_cfg = pl.cfg >= 401 ? pl.cfg - 401 : -1;
     const hipError_t e = conv_forward_rows32(n, x, w, b, y, s, relu, st);

@@ -59,6 +59,7 @@ constexpr int kTileGroup = 8;
 struct TileIo {
   const bf16_t* x[kTileGroup];
   bf16_t* y[kTileGroup];
+  float* part[kTileGroup];   // split K: S sums of every output
 };
 // How an image is cut: R rows x TW columns a tile, BWP LDS rows per input
 // row, nrb row blocks and ns column strips; inv = ceil(2^20 / TW), invB =
@@ -70,11 +71,15 @@ struct TileCut {
 // WC x WP waves; a wave covers MT 32-channel tiles x FW pixel fragments.  LW
 // is the DMA instructions of a wave per stage (1 KiB each), which fixes the
 // slot size; chunks past the stage's rows read zeros.
-template <int MT, int WC, int WP, int FW, int LW, int NS, bool DG>
+// With SPLIT an item is a tile's share of the sum, 1 / S of its stages, whose
+// float32 sums go to part; the items of one share of one channel tile are
+// neighbours, so that an XCD reads its weights once.
+template <int MT, int WC, int WP, int FW, int LW, int NS, bool DG, bool SPLIT>
 __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
     TileIo io, int ng, const bf16_t* __restrict__ Wt, const float* __restrict__ bias, int nb,
-    int H, int W, int Cin, int Cout, int relu, TileCut cut) {
+    int H, int W, int Cin, int Cout, int relu, int S, TileCut cut) {
   constexpr int NW = WC * WP;
+  constexpr int NQ = MT * FW;                                   // MFMAs per tap
   constexpr int BN = 32 * MT * WC;
   constexpr int AR = 9 * BN;                                    // weight rows per stage
   constexpr int ACH = AR / 32;                                  // ... in 1 KiB chunks
@@ -90,11 +95,11 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
   const int R = cut.R, TW = cut.TW, BWP = cut.BWP;
   const int nct = (Cout + BN - 1) / BN;
   const int per_n = cut.nrb * cut.ns * nct;                     // tiles per sample
-  const int items = ng * nb * per_n;
+  const int items = ng * nb * per_n * (SPLIT ? S : 1);
   const int G = gridDim.x;
   const int lb = xcd_remap(blockIdx.x, G);
   const int n_items = lb < items ? (items - lb + G - 1) / G : 0;
-  const int nk = (Cin + 15) / 16;                               // stages per tile
+  const int nk = (Cin + 15) / 16 / (SPLIT ? S : 1);             // stages per item (S divides)
   const int total = n_items * nk;
 
   const int xbytes = nb * H * W * Cin * 2;                      // one micro-batch's input
@@ -167,13 +172,26 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
 
   // item -> micro-batch gi, its sample n, first row h0 and column w0, first
   // output channel co0
-  auto coords = [&](int it, int& gi, int& n, int& h0, int& w0, int& co0)
+  // (SPLIT: and its share sk of the sum)
+  auto coords = [&](int it, int& gi, int& n, int& h0, int& w0, int& co0, int& sk)
       __attribute__((always_inline)) {
     const int item = lb + it * G;
-    const int smp = item / per_n;
-    int t = item - smp * per_n;
-    const int ct = t % nct;
-    t /= nct;
+    int smp, t, ct;
+    if constexpr (SPLIT) {
+      const int px = cut.nrb * cut.ns, npx = ng * nb * px;
+      const int sc = item / npx;
+      sk = sc / nct;
+      ct = sc - sk * nct;
+      t = item - sc * npx;
+      smp = t / px;
+      t -= smp * px;
+    } else {
+      sk = 0;
+      smp = item / per_n;
+      t = item - smp * per_n;
+      ct = t % nct;
+      t /= nct;
+    }
     const int sx = t % cut.ns;
     gi = smp / nb;
     n = smp - gi * nb;
@@ -182,11 +200,11 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
     co0 = ct * BN;
   };
 
-  int i_it = 0, i_ks = 0, i_gi = 0, i_n = 0, i_h0 = 0, i_w0 = 0, i_co0 = 0;
-  if (total > 0) coords(0, i_gi, i_n, i_h0, i_w0, i_co0);
+  int i_it = 0, i_ks = 0, i_gi = 0, i_n = 0, i_h0 = 0, i_w0 = 0, i_co0 = 0, i_sk = 0;
+  if (total > 0) coords(0, i_gi, i_n, i_h0, i_w0, i_co0, i_sk);
   u32x4 rxg = make_rsrc(pickg(io.x, i_gi), xbytes);            // the issuing item's input
   auto issue_part = [&](int slot, int u0, int u1) __attribute__((always_inline)) {
-    const int c0 = i_ks * 16;
+    const int c0 = (i_sk * nk + i_ks) * 16;
     const int soff_a = DG ? (c0 * 9 * Cout + i_co0) * 2 : (i_co0 * 9 * Cin + c0) * 2;
     const int hb = i_h0 - 1;                                    // input row of block row 0
     const int base_b = (((i_n * H + hb) * W + i_w0) * Cin + c0) * 2;   // negative for hb = -1
@@ -194,7 +212,7 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
     // the tile's bias values, ahead of its first stage (whose wait covers
     // them): a load in the epilogue would wait for the DMA in flight, and
     // held in registers they spill the widest configuration
-    if (u0 == 0 && i_ks == 0 && wave == 0)
+    if (!SPLIT && u0 == 0 && i_ks == 0 && wave == 0)
       dma16(rbias, TGP_LDS(bslots + (i_it % (NS + 1)) * 1024),
             lane < BN / 4 ? (i_co0 + 4 * lane) * 4 : CT_OOB, 0);
 #pragma unroll
@@ -217,7 +235,7 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
     if (++i_ks == nk) {
       i_ks = 0;
       if (++i_it < n_items) {
-        coords(i_it, i_gi, i_n, i_h0, i_w0, i_co0);
+        coords(i_it, i_gi, i_n, i_h0, i_w0, i_co0, i_sk);
         rxg = make_rsrc(pickg(io.x, i_gi), xbytes);
       }
     }
@@ -232,8 +250,8 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
 
   int idx = 0;
   for (int c_it = 0; c_it < n_items; ++c_it) {
-    int gi, n, h0, w0, co0;
-    coords(c_it, gi, n, h0, w0, co0);
+    int gi, n, h0, w0, co0, sk;
+    coords(c_it, gi, n, h0, w0, co0, sk);
     f32x16_t acc[MT][FW];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -266,7 +284,6 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
           fb[buf][j] = as_bf16x8(*(const u32x4*)(st + bq[j][s] + r * BWP * 32));
       };
       load(0, 0);
-      constexpr int NQ = MT * FW;                               // MFMAs per tap
 #pragma unroll
       for (int t = 0; t < 9; ++t) {
         // reads for tap t + 1, half of tap t's MFMAs, this tap's share of the
@@ -289,6 +306,26 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
       if (fill) issue_done();
     }
 
+    if constexpr (SPLIT) {
+      float* const pt = pickg(io.part, gi) + (long)sk * nb * H * W * Cout;
+#pragma unroll
+      for (int j = 0; j < FW; ++j) {
+        const int tp = (pg * FW + j) * 32 + (lane & 31);
+        const int rho = (tp * cut.inv) >> 20, w = tp - rho * TW;
+        if (rho >= R || h0 + rho >= H || w0 + w >= W) continue;
+        float* const row = pt + ((long)(n * H + h0 + rho) * W + w0 + w) * Cout;
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const int co = co0 + (wc * MT + i) * 32 + 8 * g + 4 * (lane >> 5);
+            if (co < Cout)
+              *(float4*)(row + co) = make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1],
+                                                 acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
+          }
+      }
+      continue;
+    }
     // Epilogue, staged through LDS so that every store writes whole runs of
     // one pixel's channels.  The slot of the stage just consumed is free once
     // every wave is past its last reads; its refill is issued only after the
@@ -338,6 +375,35 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
   }
 }
 
+// y[p][co] = bf16(act(sum_{s < S} part[s][p][co] + b[co])), s ascending, of
+// micro-batch blockIdx.y.
+__global__ __launch_bounds__(256) void split_epilogue(TileIo io, const float* __restrict__ bias,
+                                                      long n, int Cout, int S, int relu) {
+  const long e = ((long)blockIdx.x * 256 + threadIdx.x) * 8;
+  if (e >= n) return;
+  const float* __restrict__ part = pickg(io.part, blockIdx.y);
+  float v[8];
+  const float4 a0 = *(const float4*)(part + e), a1 = *(const float4*)(part + e + 4);
+  v[0] = a0.x; v[1] = a0.y; v[2] = a0.z; v[3] = a0.w;
+  v[4] = a1.x; v[5] = a1.y; v[6] = a1.z; v[7] = a1.w;
+  for (int s = 1; s < S; ++s) {
+    const float4 b0 = *(const float4*)(part + (long)s * n + e);
+    const float4 b1 = *(const float4*)(part + (long)s * n + e + 4);
+    v[0] += b0.x; v[1] += b0.y; v[2] += b0.z; v[3] += b0.w;
+    v[4] += b1.x; v[5] += b1.y; v[6] += b1.z; v[7] += b1.w;
+  }
+  const int co = e % Cout;
+  u32x4 o;
+#pragma unroll
+  for (int t = 0; t < 8; t += 2) {
+    float x0 = v[t], x1 = v[t + 1];
+    if (bias) { x0 += bias[co + t]; x1 += bias[co + t + 1]; }
+    if (relu) { x0 = fmaxf(x0, 0.f); x1 = fmaxf(x1, 0.f); }
+    o[t / 2] = pack2_ct(x0, x1);
+  }
+  *(u32x4*)(pickg(io.y, blockIdx.y) + e) = o;
+}
+
 // Configurations, with what one round of blocks costs (measured in us: `a`
 // per tile and `b` per 16-channel stage; 128 channels at 56 x 56 and 256 at
 // 28 x 28, 32 samples).
@@ -345,7 +411,7 @@ struct TileCfg { int MT, WC, WP, FW, LW, NS; double a, b; };
 constexpr TileCfg kTileCfgs[] = {
     {2, 2, 4, 2, 7, 2, 4.8, 2.0},    // 128 channels x 256 pixels
     {1, 2, 4, 4, 5, 3, 4.0, 1.94},   // 64 x 512
-    {1, 2, 4, 2, 4, 4, 1.5, 1.2},    // 64 x 256
+    {1, 2, 4, 2, 4, 4, 3.0, 1.2},    // 64 x 256
     {1, 2, 4, 1, 4, 4, 2.0, 0.8},    // 64 x 128
     {1, 1, 8, 2, 4, 4, 2.4, 1.07},   // 32 x 512
     {1, 1, 8, 1, 3, 4, 1.8, 0.69},   // 32 x 256
@@ -386,19 +452,23 @@ bool tile_cut(int H, int W, int px, int rows, TileCut& c) {
 
 int g_tile_cfg = -1;   // >= 0 forces a configuration (tests and measurement)
 
+// Configurations that have a split-K form.
+constexpr bool tile_splits(int c) { return c == 0 || c == 2 || c == 3; }
+
 // Configuration for ng micro-batches of a shape: the least estimated time,
 // rounds of blocks times what a round costs.
-static int tile_pick(const ConvShape& s, int ng, TileCut& cut) {
+static int tile_pick(const ConvShape& s, int ng, int S, TileCut& cut) {
   int best = -1;
   double best_cost = 0;
-  const int nk = (s.cin + 15) / 16;
+  const int nk = (s.cin + 15) / 16 / S;
   for (int c = 0; c < kTileN; ++c) {
     const TileCfg k = kTileCfgs[c];
     if (g_tile_cfg >= 0 && g_tile_cfg != c) continue;
+    if (S > 1 && !tile_splits(c)) continue;
     const int NW = k.WC * k.WP, BN = 32 * k.MT * k.WC;
     TileCut t;
     if (!tile_cut(s.H, s.W, 32 * k.WP * k.FW, k.LW * NW * 32 - 9 * BN, t)) continue;
-    const long items = (long)ng * s.nb * t.nrb * t.ns * ((s.cout + BN - 1) / BN);
+    const long items = (long)ng * s.nb * t.nrb * t.ns * ((s.cout + BN - 1) / BN) * S;
     const long rounds = (items + 255) / 256;
     const double cost = rounds * (k.a + nk * k.b) / (rounds > 1 && tile_occ(k) > 1 ? 1.4 : 1.0);
     if (best < 0 || cost < best_cost) {
@@ -410,60 +480,99 @@ static int tile_pick(const ConvShape& s, int ng, TileCut& cut) {
   return best;
 }
 
+// Shares of a split sum, a function of the per-sample shape (so that every
+// sample's sums keep their order whatever the micro-batch): two or four where
+// four samples give few tiles of 64 x 256 and a share keeps 16 stages.  The
+// shares' sums cost a write, a read and a launch (4 us).  Forward, us: 2048 at 16
+// x 16 x 4: one share 155, two 131, four 92 (the split row kernel, two
+// micro-batches apart: 198); 1024 at 14 x 14 x 1: 42, 32, 21 (38); x 16: 80, 79,
+// 86 (154); 512 at 14 x 14 x 1: 23, 20, 15 (17), x 16: 29, 31; 256 at 16 x 16 x
+// 1: 13, 14 (13).
+int conv_tile_split(const ConvShape& s) {
+  const long P = 4L * s.H * s.W, nk = s.cin / 16;
+  if (P > 4096 || s.cin % 64 || s.cout % 64) return 1;
+  const long tiles = (P + 255) / 256 * (s.cout / 64);
+  int S = 1;
+  while (S < 4 && tiles * S < 256 && nk / (2 * S) >= 16 && nk % (2 * S) == 0) S *= 2;
+  return S;
+}
+
 bool conv_tile_ok(const ConvShape& s) {
   return s.taps == 9 && s.cin % 8 == 0 && s.cout % 8 == 0 && s.pixels() > 0 &&
          (double)s.pixels() * s.cin * 2 < 2147483648.0 &&
          (double)s.cout * 9 * s.cin * 2 < 2147483648.0;
 }
 
-template <int MT, int WC, int WP, int FW, int LW, int NS, bool DG>
+template <int MT, int WC, int WP, int FW, int LW, int NS, bool DG, bool SPLIT>
 static hipError_t launch_tile(const TileIo& io, int ng, const bf16_t* Wt, const float* b,
-                              const ConvShape& s, int relu, const TileCut& cut, hipStream_t st) {
+                              const ConvShape& s, int relu, int S, const TileCut& cut,
+                              hipStream_t st) {
   static char name[64];
-  if (!name[0]) snprintf(name, sizeof name, "conv3x3_tile<%d,%d,%d,%d,%d,%d%s>", MT, WC, WP, FW, LW, NS, DG ? ",dg" : "");
+  if (!name[0])
+    snprintf(name, sizeof name, "conv3x3_tile<%d,%d,%d,%d,%d,%d%s%s>", MT, WC, WP, FW, LW, NS,
+             DG ? ",dg" : "", SPLIT ? ",split" : "");
   constexpr int BN = 32 * MT * WC, NW = WC * WP;
-  const long items = (long)ng * s.nb * cut.nrb * cut.ns * ((s.cout + BN - 1) / BN);
+  const long items = (long)ng * s.nb * cut.nrb * cut.ns * ((s.cout + BN - 1) / BN) * S;
   constexpr int occ = tile_occ(TileCfg{MT, WC, WP, FW, LW, NS, 0, 0});
   const int G = (int)(items < 256 * occ ? items : 256 * occ);
   const long P = (long)ng * s.pixels();
   ProfScope ps(name, 2.0 * P * s.cout * 9 * s.cin,
                2.0 * ((double)P * s.cin + 9.0 * s.cin * s.cout + (double)P * s.cout), st);
-  TGP_LAUNCH(ps, (conv3x3_tile<MT, WC, WP, FW, LW, NS, DG>), dim3(G), dim3(NW * 64), 0, st, io, ng, Wt,
-             b, s.nb, s.H, s.W, s.cin, s.cout, relu, cut);
+  TGP_LAUNCH(ps, (conv3x3_tile<MT, WC, WP, FW, LW, NS, DG, SPLIT>), dim3(G), dim3(NW * 64), 0, st,
+             io, ng, Wt, b, s.nb, s.H, s.W, s.cin, s.cout, relu, S, cut);
   return launch_status();
 }
 
 // y = act(conv(x, w) + b), or with dg the data gradient: x = dz, s the
 // transposed shape (cin: its sum channels, the forward layer's outputs), and w
-// the forward layer's weights.
+// the forward layer's weights.  With S > 1 (conv_tile_split) part[k] holds S
+// nb H W Cout floats.
 hipError_t conv_forward_tile(int n, const void* const* x, const void* w, const float* b,
-                             void* const* y, const ConvShape& s, int relu, bool dg,
-                             hipStream_t st) {
-  if (n < 1 || n > kMaxGroup || !conv_tile_ok(s) || !w) return hipErrorInvalidValue;
+                             void* const* y, const ConvShape& s, int relu, bool dg, int S,
+                             float* const* part, hipStream_t st) {
+  if (n < 1 || n > kMaxGroup || !conv_tile_ok(s) || !w || S < 1 || (S > 1 && !part))
+    return hipErrorInvalidValue;
   if (n > kTileGroup) {
     for (int k0 = 0; k0 < n; k0 += kTileGroup) {
       const int c = n - k0 < kTileGroup ? n - k0 : kTileGroup;
-      const hipError_t e = conv_forward_tile(c, x + k0, w, b, y + k0, s, relu, dg, st);
+      const hipError_t e =
+          conv_forward_tile(c, x + k0, w, b, y + k0, s, relu, dg, S, S > 1 ? part + k0 : nullptr, st);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
   }
   TileCut cut{};
-  const int c = tile_pick(s, n, cut);
+  const int c = tile_pick(s, n, S, cut);
   if (c < 0) return hipErrorInvalidValue;
   TileIo io{};
   for (int k = 0; k < kTileGroup; ++k) {   // unused entries repeat micro-batch 0
     io.x[k] = (const bf16_t*)x[k < n ? k : 0];
     io.y[k] = (bf16_t*)y[k < n ? k : 0];
-    if (!io.x[k] || !io.y[k]) return hipErrorInvalidValue;
+    io.part[k] = S > 1 ? part[k < n ? k : 0] : nullptr;
+    if (!io.x[k] || !io.y[k] || (S > 1 && !io.part[k])) return hipErrorInvalidValue;
   }
   const bf16_t* Wt = (const bf16_t*)w;
-  switch (c) {
-#define CT_GO(i, D)                                                                         \
+#define CT_GO(i, D, SP)                                                                     \
   launch_tile<kTileCfgs[i].MT, kTileCfgs[i].WC, kTileCfgs[i].WP, kTileCfgs[i].FW,           \
-              kTileCfgs[i].LW, kTileCfgs[i].NS, D>(io, n, Wt, b, s, relu, cut, st)
+              kTileCfgs[i].LW, kTileCfgs[i].NS, D, SP>(io, n, Wt, b, s, relu, S, cut, st)
+  if (S > 1) {
+    hipError_t e = hipErrorInvalidValue;
+    switch (c) {
 #define CT_CASE(i) \
-  case i: return dg ? CT_GO(i, true) : CT_GO(i, false);
+  case i: e = dg ? CT_GO(i, true, true) : CT_GO(i, false, true); break;
+      CT_CASE(0) CT_CASE(2) CT_CASE(3)
+#undef CT_CASE
+    }
+    if (e != hipSuccess) return e;
+    const long numel = s.pixels() * s.cout;
+    ProfScope ps("split_epilogue", 0.0, n * numel * (4.0 * S + 2.0), st);
+    TGP_LAUNCH(ps, split_epilogue, dim3((unsigned)((numel / 8 + 255) / 256), n), dim3(256), 0, st,
+               io, b, numel, s.cout, S, relu);
+    return launch_status();
+  }
+  switch (c) {
+#define CT_CASE(i) \
+  case i: return dg ? CT_GO(i, true, false) : CT_GO(i, false, false);
     CT_CASE(0) CT_CASE(1) CT_CASE(2) CT_CASE(3) CT_CASE(4) CT_CASE(5) CT_CASE(6)
 #undef CT_CASE
 #undef CT_GO

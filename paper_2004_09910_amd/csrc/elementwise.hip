@@ -12,8 +12,10 @@ namespace tgpk {
 bool mfma_fwd_ok(int dt, const ConvShape& s);
 bool mfma_wgrad_ok(int dt, const ConvShape& s);
 bool conv_dgrad_tile_planned(const ConvShape& t);
+bool conv_dgrad_tile_now(const ConvShape& t, int n);
 hipError_t conv_dgrad_tile(int n, const void* const* dz, const void* w, void* const* dx,
-                           const ConvShape& t, hipStream_t st);
+                           const ConvShape& t, float* const* part, size_t part_cap,
+                           hipStream_t st);
 hipError_t conv_forward_mfma(const void* x, const void* w, const float* b, void* y,
                              const ConvShape& s, int relu, float* part, size_t part_cap,
                              hipStream_t st);
@@ -1188,11 +1190,9 @@ hipError_t conv_dgrad(int dt, const void* dz, const void* w, const void* wt, voi
                       const ConvShape& s, float* part, size_t part_cap, hipStream_t st) {
   const ConvShape t{s.nb, s.H, s.W, s.cout, s.cin, s.taps};
   if (mfma_fwd_ok(dt, t)) {
-    if (!wt || conv_dgrad_tile_planned(t)) return conv_dgrad_tile(1, &dz, w, &dx, t, st);
-    t_in_dgrad = 1;
-    const hipError_t e = conv_forward_mfma(dz, wt, nullptr, dx, t, 0, part, part_cap, st);
-    t_in_dgrad = 0;
-    return e;
+    if (!wt || conv_dgrad_tile_now(t, 1))
+      return conv_dgrad_tile(1, &dz, w, &dx, t, &part, part_cap, st);
+    return conv_forward_mfma(dz, wt, nullptr, dx, t, 0, part, part_cap, st);
   }
   if (small1x1_ok(dt, s, dx)) return dgrad1x1_small(dt, 1, &dz, w, &dx, s, st);
   return conv_gen_forward(dt, 1, &dz, w, nullptr, &dx, t, 0, true, st);
@@ -1253,11 +1253,9 @@ hipError_t conv_dgrad_n(int dt, int n, const void* const* dz, const void* w, con
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
   const ConvShape t{s.nb, s.H, s.W, s.cout, s.cin, s.taps};
   if (mfma_fwd_ok(dt, t)) {
-    if (!wt || conv_dgrad_tile_planned(t)) return conv_dgrad_tile(n, dz, w, dx, t, st);
-    t_in_dgrad = 1;
-    const hipError_t e = conv_forward_mfma_n(n, dz, wt, nullptr, dx, t, 0, part, part_cap, st);
-    t_in_dgrad = 0;
-    return e;
+    if (!wt || conv_dgrad_tile_now(t, n))
+      return conv_dgrad_tile(n, dz, w, dx, t, part, part_cap, st);
+    return conv_forward_mfma_n(n, dz, wt, nullptr, dx, t, 0, part, part_cap, st);
   }
   bool small = true;
   for (int k = 0; k < n; ++k) small = small && small1x1_ok(dt, s, dx[k]);

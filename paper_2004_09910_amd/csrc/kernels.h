@@ -66,8 +66,9 @@ hipError_t conv_forward_rows32(int n, const void* const* x, const void* w, const
 // the forward weights w = [cin][taps][cout], s being the transposed shape.
 bool conv_tile_ok(const ConvShape& s);
 hipError_t conv_forward_tile(int n, const void* const* x, const void* w, const float* b,
-                             void* const* y, const ConvShape& s, int relu, bool dg,
-                             hipStream_t st);
+                             void* const* y, const ConvShape& s, int relu, bool dg, int S,
+                             float* const* part, hipStream_t st);
+int conv_tile_split(const ConvShape& s);
 extern int g_tile_cfg;
 // The same for 1x1 layers (bf16; Cin and Cout multiples of 8), and their
 // weight gradient, each sum left pending in *defer[k].
@@ -91,7 +92,6 @@ extern int g_rows32_cfg;
 extern int g_rows32_ch;
 extern int g_wgrad_ks;
 extern int g_rowtile_mask;
-extern thread_local int t_in_dgrad;
 // Row-blocked 3x3 weight gradient on 32x32x16 MFMA with transpose LDS reads
 // (bf16; W in {48, 96, 192}, Cin and Cout multiples of 64): whether it
 // supports a shape, the fp32 partial-slice scratch it needs, and the launch

@@ -225,3 +225,25 @@ def test_conv3x3_few_input_channels(cin, cout, h, w, B, m):
 def test_conv1x1_few_output_channels(dt, cin, cout, h, w, B, m):
     run_and_check(Layer(CONV1X1, cin, cout, relu=False), h, w, dt, B, m,
                   f"conv1x1 {cin}->{cout} @{h}x{w} B={B} m={m}")
+
+
+@pytest.mark.parametrize("cin,cout,h,w", [(512, 64, 13, 11), (1024, 192, 5, 7), (2048, 64, 16, 16)])
+def test_conv3x3_shares_of_a_long_sum(cin, cout, h, w):
+    """Layers of long sums and few pixels, whose sums are split over blocks, and
+    their data gradients (sums over 64 and 192: not split): against the oracle,
+    and the same bits in a group as one by one."""
+    net = one_layer(Layer(CONV3X3, cin, cout), h, w)
+    got = run_and_check(Layer(CONV3X3, cin, cout), h, w, BF16, 3, 3, f"conv3x3 {cin}->{cout} @{h}x{w}")
+    grp = gpu_stage(net, BF16, 3, 3, 0, (1,), 1, lanes=3, group=3, serial=True)
+    assert torch.equal(got["y"], grp["y"]) and torch.equal(got["dx"], grp["dx"])
+    back = run_and_check(Layer(CONV3X3, cout, cin), h, w, BF16, 2, 1, f"conv3x3 {cout}->{cin} @{h}x{w}")
+    back["sess"].close()
+
+
+def test_conv3x3_small_and_large_launches_agree():
+    """The whole-row kernel's widths: a launch of few samples takes the
+    rectangular tiles, one of many the whole rows, with the same bits."""
+    net = one_layer(Layer(CONV3X3, 64, 64), 96, 96)
+    one = gpu_stage(net, BF16, 6, 6, 0, (1,), 1, lanes=6)
+    grp = gpu_stage(net, BF16, 6, 6, 0, (1,), 1, lanes=6, group=6, serial=True)
+    assert torch.equal(one["y"], grp["y"]) and torch.equal(one["dx"], grp["dx"])
