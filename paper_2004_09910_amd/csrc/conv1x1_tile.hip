@@ -462,17 +462,19 @@ hipError_t conv_forward_1x1(int n, const void* const* x, const void* w, const fl
   }
 }
 
-// K ranges of one micro-batch: about 256 items, one stage of 64 pixels or
-// more each, at most 8 MB of slices and no more than the general kernels'.
-struct Plan1x1 { int MC, nK, spk; };
+// K ranges of one micro-batch: twelve stages of 64 pixels each, since a range's
+// sums are written and read once more (256 x 256, 12544 pixels, sixteen
+// micro-batches: 32 ranges 68 us, 16 58), but at least 128 items of 64 x 64 and
+// at most 512; at most 8 MB of slices and no more than the general kernels'.
+struct Plan1x1 { int nK, spk; };
 static Plan1x1 wg1x1_plan(const ConvShape& s) {
-  const int MC = s.cin > 64 && s.cout > 64 ? 2 : 1;
-  const long per_k = (long)((s.cout + 64 * MC - 1) / (64 * MC)) * ((s.cin + 64 * MC - 1) / (64 * MC));
+  const long t64 = (long)((s.cout + 63) / 64) * ((s.cin + 63) / 64);
   const long T = (s.pixels() + 63) / 64, E = (long)s.cout * s.cin;
-  const long nK = std::max(1L, std::min({T, (256 + per_k - 1) / per_k, std::max(1L, (8L << 20) / (4 * E)),
+  const long want = std::min((512 + t64 - 1) / t64, std::max(T / 12, (128 + t64 - 1) / t64));
+  const long nK = std::max(1L, std::min({T, want, std::max(1L, (8L << 20) / (4 * E)),
                                          (long)wgrad_general_splits(s)}));
   const int spk = (int)((T + nK - 1) / nK);
-  return {MC, (int)((T + spk - 1) / spk), spk};
+  return {(int)((T + spk - 1) / spk), spk};
 }
 
 bool wgrad1x1_tile_ok(const ConvShape& s) {
@@ -496,12 +498,15 @@ hipError_t wgrad1x1_tile_launch(int n, const void* const* x, const void* const* 
     io.out[k] = p.nK > 1 ? partial[q] : dw[q];
   }
   const long E = (long)s.cout * s.cin;
-  const long items = (long)n * p.nK * ((s.cout + 64 * p.MC - 1) / (64 * p.MC)) *
-                     ((s.cin + 64 * p.MC - 1) / (64 * p.MC));
+  // 128 x 128 items where they give every CU one (the sums of an element run
+  // over the same pixels in the same order either way)
+  const long big = (long)n * p.nK * ((s.cout + 127) / 128) * ((s.cin + 127) / 128);
+  const int MC = s.cin > 64 && s.cout > 64 && big >= 256 ? 2 : 1;
+  const long items = MC == 2 ? big : (long)n * p.nK * ((s.cout + 63) / 64) * ((s.cin + 63) / 64);
   {
-    ProfScope ps(p.MC == 2 ? "wgrad1x1_tile<2,2>" : "wgrad1x1_tile<1,1>", 2.0 * n * s.pixels() * E,
+    ProfScope ps(MC == 2 ? "wgrad1x1_tile<2,2>" : "wgrad1x1_tile<1,1>", 2.0 * n * s.pixels() * E,
                  n * (2.0 * s.pixels() * (s.cin + s.cout) + 4.0 * p.nK * E), st);
-    if (p.MC == 2) {
+    if (MC == 2) {
       const int G = (int)(items < 512 ? items : 512);
       TGP_LAUNCH(ps, (wgrad1x1_tile<2, 2, 2>), dim3(G), dim3(256), 0, st, io, n, (int)s.pixels(),
                  s.cin, s.cout, p.nK, p.spk);

@@ -1001,8 +1001,7 @@ __global__ __launch_bounds__(256) void accumulate_k(float* __restrict__ acc, con
 // split lanes; lane l sums s = l, l + LANES, .. in ascending order, then the
 // lanes are added pairwise in LDS (lane l takes lane l + h for h = LANES / 2,
 // .., 1), with (C4, LANES) a function of S only, so the sum is fixed by the
-// shape.  An entry with n not a multiple of 4 takes one element per thread,
-// s ascending.
+// shape.
 __host__ __device__ __forceinline__ int acc_c4(int S) {
   // about four slices per split lane: C4 = 4096 / S rounded down to a power
   // of two, within 1 .. 1024 (a bias gradient's hundreds of block sums then
@@ -1030,14 +1029,18 @@ __device__ __forceinline__ void st_cols(float* row, long e, long E, float4 v) {
   if (e + 3 < E) row[e + 3] = v.w;
 }
 
-// NG: micro-batches per entry as a template constant (1) or b.ng (0).
-template <int NG>
+// QB micro-batches at a time: their slices are loaded together and their lanes
+// meet in one tree, instead of sixteen chains of loads and barriers one after
+// the other (256 x 256 weights in 16 slices and a bias of 784 block sums, sixteen
+// micro-batches: 70 us one at a time, 58 four at a time, 37 with half the block
+// sums; 30 without the bias).
+template <int QB>
 __global__ __launch_bounds__(1024) void reduce_accumulate_k(AccBatch b, int overwrite,
                                                             int ntiles) {
   // blocks are persistent over tiles (tile = the block of the layout above),
   // so the entry lookup and the block start are paid once per block
-  __shared__ float4 red[1024];
-  const int ng = NG ? NG : b.ng;
+  __shared__ float4 red[QB][1024];
+  const int ng = b.ng;
   int k = 0;   // entry of the current tile (tiles only increase)
   for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     while (k + 1 < b.count && tile >= b.blk0[k + 1]) ++k;
@@ -1048,51 +1051,63 @@ __global__ __launch_bounds__(1024) void reduce_accumulate_k(AccBatch b, int over
     const int C4 = acc_c4(S), LANES = 1024 / C4;
     const int col = threadIdx.x % C4, lane = threadIdx.x / C4;
     const long e4 = (bx * C4 + col) * 4;
-    float4 cur = make_float4(0.f, 0.f, 0.f, 0.f);   // the running sum (lane 0)
-    for (int q = 0; q < ng; ++q) {
-      const float* __restrict__ part = b.g[k] + q * b.gstride[k];
-      float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+    const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 cur = zero;   // the running sum (lane 0)
+    for (int q0 = 0; q0 < ng; q0 += QB) {
+      float4 r[QB];
+#pragma unroll
+      for (int q = 0; q < QB; ++q) r[q] = zero;
       if (e4 < E) {
-        // up to eight loads in flight per step; slices past S add zeros
-        for (int s = lane; s < S; s += 8 * LANES) {
-          float4 t[8];
+        // four slices of each in flight per step; those past S add zeros
+        for (int s = lane; s < S; s += 4 * LANES) {
+          float4 t[QB][4];
 #pragma unroll
-          for (int u = 0; u < 8; ++u)
-            t[u] = s + u * LANES < S ? ld_cols(part + (long)(s + u * LANES) * E, e4, E)
-                                     : make_float4(0.f, 0.f, 0.f, 0.f);
+          for (int q = 0; q < QB; ++q)
 #pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            a.x += t[u].x; a.y += t[u].y; a.z += t[u].z; a.w += t[u].w;
-          }
+            for (int u = 0; u < 4; ++u)
+              t[q][u] = s + u * LANES < S && q0 + q < ng
+                            ? ld_cols(b.g[k] + (q0 + q) * b.gstride[k] + (long)(s + u * LANES) * E, e4, E)
+                            : zero;
+#pragma unroll
+          for (int q = 0; q < QB; ++q)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              r[q].x += t[q][u].x; r[q].y += t[q][u].y; r[q].z += t[q][u].z; r[q].w += t[q][u].w;
+            }
         }
       }
-      float4 r = a;
       if (LANES > 1) {   // tile-uniform
-        red[lane * C4 + col] = a;
+#pragma unroll
+        for (int q = 0; q < QB; ++q) red[q][lane * C4 + col] = r[q];
         __syncthreads();
         for (int h = LANES >> 1; h > 0; h >>= 1) {
           if (lane < h) {
-            const float4 t = red[(lane + h) * C4 + col];
-            r.x += t.x; r.y += t.y; r.z += t.z; r.w += t.w;
-            red[lane * C4 + col] = r;
+#pragma unroll
+            for (int q = 0; q < QB; ++q) {
+              const float4 t = red[q][(lane + h) * C4 + col];
+              r[q].x += t.x; r[q].y += t.y; r[q].z += t.z; r[q].w += t.w;
+              red[q][lane * C4 + col] = r[q];
+            }
           }
-          __syncthreads();
+          __syncthreads();   // (the last one also frees red for the next round)
         }
-        if (NG != 1) __syncthreads();   // red is rewritten by the next micro-batch
       }
       if (lane == 0 && e4 < E) {
-        if (q > 0) {
-          cur.x = cur.x + r.x; cur.y = cur.y + r.y; cur.z = cur.z + r.z; cur.w = cur.w + r.w;
-        } else if (overwrite) {
-          cur = r;
-        } else {
-          const float4 o = ld_cols(acc, e4, E);
-          cur.x = o.x + r.x; cur.y = o.y + r.y; cur.z = o.z + r.z; cur.w = o.w + r.w;
+#pragma unroll
+        for (int q = 0; q < QB; ++q) {
+          if (q0 + q >= ng) break;
+          if (q0 + q > 0) {
+            cur.x = cur.x + r[q].x; cur.y = cur.y + r[q].y; cur.z = cur.z + r[q].z; cur.w = cur.w + r[q].w;
+          } else if (overwrite) {
+            cur = r[q];
+          } else {
+            const float4 o = ld_cols(acc, e4, E);
+            cur.x = o.x + r[q].x; cur.y = o.y + r[q].y; cur.z = o.z + r[q].z; cur.w = o.w + r[q].w;
+          }
         }
       }
     }
     if (lane == 0 && e4 < E) st_cols(acc, e4, E, cur);
-    if (NG == 1 && LANES > 1) __syncthreads();   // red is rewritten by the next tile
   }
 }
 
@@ -1483,14 +1498,17 @@ size_t colsum_partial_floats(long P, int C) {
 
 // Threads of a block over CP channel packs: whole rows of packs.
 static int pack_threads(int CP) { return 256 / CP * CP; }
-// Rows per block of the fused ReLU-backward / bias kernel: about 1024 blocks
+// Rows per block of the fused ReLU-backward / bias kernel: about 512 blocks
 // (a multiple of the block's row lanes), so deep layers with few pixels and
 // many channels still fill the chip.  Where the pack count divides no
 // 256-thread block (192 channels: 24 packs), at most `cap` blocks, which the
 // plan sets so that their sums fit the room it already had.
 static long relu_bias_rows(long P, int C, int N, int cap) {
   const int CP = C / N, nl = 256 / CP;
-  const long blocks = 256 % CP ? cap : 1024;
+  // 512 blocks: with 1024 a pass of one micro-batch is no faster (14.1 and 14.2
+  // us at 56 x 56 x 256, four samples x 4), and the accumulation reads twice the
+  // block sums, its longest chain; with 256 the pass is slower (17 us for 14 in a U-Net of two micro-batches)
+  const long blocks = 256 % CP ? cap : 512;
   long r = (P + blocks - 1) / blocks;
   r = (r + nl - 1) / nl * nl;
   return r < nl ? nl : r;
@@ -1762,7 +1780,7 @@ hipError_t grad_accumulate_batch(AccBatch b, int overwrite, hipStream_t st) {
     TGP_LAUNCH(ps, reduce_accumulate_k<1>, dim3(grid), dim3(1024), 0, st, b, overwrite,
                (int)blocks);
   else
-    TGP_LAUNCH(ps, reduce_accumulate_k<0>, dim3(grid), dim3(1024), 0, st, b, overwrite,
+    TGP_LAUNCH(ps, reduce_accumulate_k<4>, dim3(grid), dim3(1024), 0, st, b, overwrite,
                (int)blocks);
   return launch_status();
 }
