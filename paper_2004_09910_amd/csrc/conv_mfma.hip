@@ -222,108 +222,105 @@ __global__ __launch_bounds__(WCO * WP * 64) void conv_fwd_dma(
 // ---------------------------------------------------------------- 1x1, resident weights
 
 // 1x1 convolution y[p][co] = act(sum_ci x[p][ci] w[co][ci] + b[co]) with
-// Cout = 256 and Cin a multiple of 64 up to 256 (the depthwise/pointwise
-// cells): a GEMM whose K is short, so a block with a tile of weights has
-// little work per byte of weights it loads.  Here each block loads the
-// whole weight matrix into LDS once (256 rows of Cin channels, in the
-// 64-channel stage blocks and 16-byte-chunk swizzle of conv_fwd_dma) and
-// then streams tiles of 64 pixels through an NS-deep ring of 64-channel
-// stages.  Wave w computes output channels 32 w .. 32 w + 31 of the tile's
-// 64 pixels (two 32 x 32 MFMA tiles), so every pixel row is read once.
-// The K order (64-channel stages, 16-channel MFMA steps, increasing
-// channel) is conv_fwd_dma's, so both kernels give the same bits.  Blocks
-// are persistent over the tiles of all ng micro-batches of the launch (each
-// of P pixels, micro-batch k's tiles after those of k - 1).
+// Cout = 256 and Cin = 64 NKS up to 256 (the depthwise/pointwise cells): its K
+// is so short that it is bound by reading x and writing y.  So each wave keeps
+// its 32 output channels' weights in registers (16 VGPRs per 64 channels), and
+// all of LDS is a ring of NS stages of 64 pixels x Cin, three of them in flight:
+// 96 KiB a CU.  The loads are issued from inline assembly (the compiler would
+// wait for all of them before every LDS read), and in the steady state the wait
+// counts the stores of the tiles between, so that it does not wait for those
+// either.  Measured at 256 -> 256, 56 x 56 x 4, sixteen micro-batches: weights
+// in LDS and four stages of 64 pixels x 64 channels 61 us, this 48.  Wave w
+// computes output channels 32 w .. 32 w + 31 of the tile's 64 pixels (two 32 x
+// 32 MFMA tiles), so every pixel row is read once.  The K order (16-channel MFMA
+// steps, increasing channel) is the other 1x1 kernels', so they give the same
+// bits.  Blocks are persistent over the tiles of all ng micro-batches of the
+// launch (each of P pixels, micro-batch k's tiles after those of k - 1).
 struct Mb1x1 {
   const bf16_t* x[kMaxGroup];
   bf16_t* y[kMaxGroup];
 };
-template <int NS>
+template <int NKS, int NS>
 __global__ __launch_bounds__(512) void conv1x1_res(Mb1x1 io, int ng,
                                                    const bf16_t* __restrict__ Wt,
-                                                   const float* __restrict__ bias, int P, int Cin,
-                                                   int relu) {
-  constexpr int COUT = 256, BM = 64, NW = 8;
-  __shared__ u32x4 smem[(4 * COUT + NS * BM) * 8];             // weights, then the ring
-  u32x4* const ring = smem + 4 * COUT * 8;
+                                                   const float* __restrict__ bias, int P, int relu) {
+  constexpr int COUT = 256, BM = 64, CIN = 64 * NKS;
+  constexpr int SB = BM * CIN * 2;                              // stage bytes
+  static_assert(NS * SB <= 160 * 1024, "LDS ring");
+  __shared__ __attribute__((aligned(16))) unsigned char ring[NS * SB];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int nks = Cin / 64;                                     // stages per tile
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int T1 = (P + BM - 1) / BM;                             // tiles per micro-batch
   const int T = ng * T1;
   const int G = gridDim.x;
   const int lb = xcd_remap(blockIdx.x, G);
   const int n_mine = lb < T ? (T - lb + G - 1) / G : 0;
-  const int total = n_mine * nks;
 
-  // DMA: one wave instruction fills 8 rows of 128 bytes; lane l the 16
-  // bytes of physical chunk l & 7 of row l >> 3, holding logical chunk c.
-  const int rsub = lane >> 3;
-  // weights: row R = 256 s + co of stage block s
-  for (int u = 0; u < nks * COUT / 8 / NW; ++u) {
-    const int R = (wave + NW * u) * 8 + rsub;
-    const int sblk = R / COUT, co = R - sblk * COUT;
-    const int c = (lane & 7) ^ ((R ^ (R >> 3)) & 7);
-    __builtin_amdgcn_global_load_lds((const void*)(Wt + (long)co * Cin + sblk * 64 + c * 8),
-                                     TGP_LDS(&smem[(wave + NW * u) * 64]), 16, 0, 0);
-  }
-  // the X ring: stage idx of this block is tile lb + (idx / nks) G, stage
-  // idx % nks; row r = wave * 8 + rsub of the slot is pixel p0 + r
-  const int xr = wave * 8 + rsub;
-  const int xc = (lane & 7) ^ ((xr ^ (xr >> 3)) & 7);
-  auto issue = [&](int idx) __attribute__((always_inline)) {
-    const int tt = lb + (idx / nks) * G, ks = idx - (idx / nks) * nks;
-    const int gi = tt / T1;                                     // micro-batch (uniform)
-    const bf16_t* X = pickg(io.x, gi);
-    const int p = min((tt - gi * T1) * BM + xr, P - 1);         // rows past P: any pixel
-    __builtin_amdgcn_global_load_lds((const void*)(X + (long)p * Cin + ks * 64 + xc * 8),
-                                     TGP_LDS(&ring[(idx % NS) * BM * 8 + wave * 64]), 16, 0, 0);
-  };
+  // This wave's weights: fragment k holds channels 16 k + 8 (lane / 32) .. + 7.
+  bf16x8_t wf[4 * NKS];
 #pragma unroll
-  for (int k = 0; k < NS - 1; ++k)
-    if (k < total) issue(k);
-
-  // this lane's bias values (channels 32 wave + 8 g + 4 (lane / 32) + t)
+  for (int k = 0; k < 4 * NKS; ++k)
+    wf[k] = as_bf16x8(
+        *(const u32x4*)(Wt + (long)(32 * wave + (lane & 31)) * CIN + 16 * k + 8 * (lane >> 5)));
+  // and bias values (channels 32 wave + 8 g + 4 (lane / 32) + t)
   f32x4_t bv[4];
 #pragma unroll
   for (int g = 0; g < 4; ++g)
     bv[g] = bias ? *(const f32x4_t*)(bias + 32 * wave + 8 * g + 4 * (lane >> 5)) : f32x4_t{};
 
-  int idx = 0;
+  // DMA: instruction u of this wave fills rows 8 wave .. + 7 (128 bytes, chunks
+  // XOR-swizzled) of the stage's 64-channel block u; pixels past P read zeros.
+  const int xr = wave * 8 + (lane >> 3);
+  const int xoff = xr * CIN * 2 + (((lane & 7) ^ ((xr ^ (xr >> 3)) & 7)) << 4);
+  auto issue = [&](int it) __attribute__((always_inline)) {
+    const int tt = lb + it * G;
+    const int gi = tt / T1;                                     // micro-batch (uniform)
+    const u32x4 rx = make_rsrc(pickg(io.x, gi), P * CIN * 2);
+    const int p0 = (tt - gi * T1) * BM;
+#pragma unroll
+    for (int u = 0; u < NKS; ++u)
+      dma16(rx, TGP_LDS(ring + (it % NS) * SB + u * BM * 128 + wave * 1024), xoff + u * 128,
+            p0 * CIN * 2);
+  };
+#pragma unroll
+  for (int k = 0; k < NS - 1; ++k)
+    if (k < n_mine) issue(k);
+
+  const bool whole = P % BM == 0;                               // every tile stores 4 times a wave
   for (int it = 0; it < n_mine; ++it) {
     const int tt = lb + it * G;
     const int gi = tt / T1;
     bf16_t* __restrict__ Y = pickg(io.y, gi);
     const int p0 = (tt - gi * T1) * BM;
     f32x16_t acc[2] = {f32x16_t{}, f32x16_t{}};
-    for (int ks = 0; ks < nks; ++ks, ++idx) {
-      // loads complete in order (the weights first); epilogue stores only
-      // lengthen this wait
-      wait_stages<NS, 1>(min(NS - 2, total - 1 - idx));
-      ring_barrier();
-      if (idx + NS - 1 < total) issue(idx + NS - 1);
-      const u32x4* As = smem + ks * COUT * 8;
-      const u32x4* Bs = ring + (idx % NS) * BM * 8;
-      bf16x8_t a[2], b[2][2];
-      auto load = [&](int kk, int buf) __attribute__((always_inline)) {
-        const int qq = 2 * kk + (lane >> 5);
-        const int ra = 32 * wave + (lane & 31);
-        a[buf] = as_bf16x8(As[ra * 8 + swz(ra, qq)]);
+    // Stage `it` is in once at most what was issued after it is pending: the
+    // NS - 2 stages after it and, from the NS - 1st tile on, the stores of the
+    // NS - 1 tiles before this one.
+    if (whole && it >= NS - 1 && it + NS - 2 < n_mine)
+      wait_vmcnt<(NS - 2) * NKS + (NS - 1) * 4>();
+    else
+      wait_stages<NS, NKS>(min(NS - 2, n_mine - 1 - it));
+    ring_barrier();
+    if (it + NS - 1 < n_mine) issue(it + NS - 1);
+    const u32x4* Bs = (const u32x4*)(ring + (it % NS) * SB);
+    bf16x8_t b[2][2];
+    auto load = [&](int k, int buf) __attribute__((always_inline)) {
+      const int qq = 2 * (k & 3) + (lane >> 5);
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int rb = 32 * j + (lane & 31);
-          b[buf][j] = as_bf16x8(Bs[rb * 8 + swz(rb, qq)]);
-        }
-      };
-      load(0, 0);
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        if (kk + 1 < 4) load(kk + 1, (kk + 1) & 1);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[j] = mfma32(a[kk & 1], b[kk & 1][j], acc[j]);
-        __builtin_amdgcn_sched_barrier(0);
+      for (int j = 0; j < 2; ++j) {
+        const int rb = 32 * j + (lane & 31);
+        b[buf][j] = as_bf16x8(Bs[(k >> 2) * BM * 8 + rb * 8 + swz(rb, qq)]);
       }
+    };
+    load(0, 0);
+#pragma unroll
+    for (int k = 0; k < 4 * NKS; ++k) {
+      if (k + 1 < 4 * NKS) load(k + 1, (k + 1) & 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[j] = mfma32(wf[k], b[k & 1][j], acc[j]);
+      __builtin_amdgcn_sched_barrier(0);
     }
     // Epilogue: lanes l and l + 32 hold channels 8 g + 0..3 and 8 g + 4..7
     // of pixel l % 32; swapping the halves of groups 2 h and 2 h + 1 across
@@ -706,10 +703,9 @@ struct FwdPlan {
   int S;     // shares of the sum (500)
 };
 
-// The resident-weight 1x1 kernel's shapes (its static LDS holds 256 x 256
-// weights) and its launch.
+// The resident-weight 1x1 kernel's shapes and its launch.
 static bool conv1x1_res_ok(const ConvShape& s) {
-  return s.taps == 1 && s.cout == 256 && s.cin % 64 == 0 && s.cin <= 256 && s.pixels() > 0;
+  return s.cout == 256 && s.cin % 64 == 0 && s.cin <= 256 && conv1x1_tile_ok(s);
 }
 
 // n micro-batches x[k] -> y[k] in one launch.
@@ -727,7 +723,12 @@ static hipError_t launch_1x1_res(int n, const void* const* x, const bf16_t* Wt, 
   const int G = (int)(T < 256 ? T : 256);
   ProfScope ps("conv1x1_res", 2.0 * n * P * s.cout * s.cin,
                2.0 * ((double)n * P * (s.cin + s.cout) + (double)s.cout * s.cin), st);
-  TGP_LAUNCH(ps, conv1x1_res<4>, dim3(G), dim3(512), 0, st, io, n, Wt, b, (int)P, s.cin, relu);
+  switch (s.cin / 64) {
+    case 1: TGP_LAUNCH(ps, (conv1x1_res<1, 8>), dim3(G), dim3(512), 0, st, io, n, Wt, b, (int)P, relu); break;
+    case 2: TGP_LAUNCH(ps, (conv1x1_res<2, 8>), dim3(G), dim3(512), 0, st, io, n, Wt, b, (int)P, relu); break;
+    case 3: TGP_LAUNCH(ps, (conv1x1_res<3, 5>), dim3(G), dim3(512), 0, st, io, n, Wt, b, (int)P, relu); break;
+    default: TGP_LAUNCH(ps, (conv1x1_res<4, 4>), dim3(G), dim3(512), 0, st, io, n, Wt, b, (int)P, relu);
+  }
   return launch_status();
 }
 
@@ -791,7 +792,11 @@ FwdPlan fwd_plan(const ConvShape& s) {
 // change a bit.  (us, forward, rectangular / rows: 128 at 96 x 96 x 1 10.4 /
 // 15.5, 64 at 192 x 192 x 1 11.1 / 14.9, 256 at 48 x 48 x 4 22.9 / 22.1, 128 at
 // 96 x 96 x 4 22.3 / 19.8.)
+// Likewise the resident-weight 1x1 kernel, which needs a tile of 64 pixels for
+// each of 256 blocks to be worth its weights (256 -> 256 at 14 x 14 x 1 7.6, tiles
+// 5.9; 196 tiles 8.8 and 8.8; 3136 50 and 72).
 static bool tile_instead(const FwdPlan& pl, const ConvShape& s, int n) {
+  if (pl.cfg == 150) return g_fwd_variant == 0 && n * ((s.pixels() + 63) / 64) < 256;
   return pl.cfg == 400 && g_fwd_variant == 0 && n * s.pixels() * s.cout < 2359296 && conv_tile_ok(s);
 }
 
@@ -848,9 +853,10 @@ hipError_t conv_forward_mfma(const void* x, const void* w, const float* b, void*
   const bf16_t* X2 = nullptr;   // per-tap configurations: one micro-batch
   bf16_t* Y2 = nullptr;
   const FwdPlan pl = fwd_plan(s);
-  if (pl.cfg == 150) return launch_1x1_res(1, &x, Wt, b, &y, s, relu, st);
   if (tile_instead(pl, s, 1))
-    return launch_tile_cfg(FwdPlan{500, 1}, 1, &x, w, b, &y, s, relu, false, nullptr, 0, st);
+    return launch_tile_cfg(FwdPlan{s.taps == 9 ? 500 : 600, 1}, 1, &x, w, b, &y, s, relu, false,
+                           nullptr, 0, st);
+  if (pl.cfg == 150) return launch_1x1_res(1, &x, Wt, b, &y, s, relu, st);
   if (pl.cfg >= 500)
     return launch_tile_cfg(pl, 1, &x, w, b, &y, s, relu, false, &part, part_cap, st);
   if (pl.cfg >= 400) {
@@ -1093,9 +1099,10 @@ hipError_t conv_forward_mfma_n(int n, const void* const* x, const void* w, const
                                size_t part_cap, hipStream_t st) {
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
   const FwdPlan pl = fwd_plan(s);
-  if (pl.cfg == 150) return launch_1x1_res(n, x, (const bf16_t*)w, b, y, s, relu, st);
   if (tile_instead(pl, s, n))
-    return launch_tile_cfg(FwdPlan{500, 1}, n, x, w, b, y, s, relu, false, nullptr, 0, st);
+    return launch_tile_cfg(FwdPlan{s.taps == 9 ? 500 : 600, 1}, n, x, w, b, y, s, relu, false,
+                           nullptr, 0, st);
+  if (pl.cfg == 150) return launch_1x1_res(n, x, (const bf16_t*)w, b, y, s, relu, st);
   if (pl.cfg >= 500)
     return launch_tile_cfg(pl, n, x, w, b, y, s, relu, false, part, part_cap, st);
   if (pl.cfg >= 400) {

@@ -247,3 +247,14 @@ def test_conv3x3_small_and_large_launches_agree():
     one = gpu_stage(net, BF16, 6, 6, 0, (1,), 1, lanes=6)
     grp = gpu_stage(net, BF16, 6, 6, 0, (1,), 1, lanes=6, group=6, serial=True)
     assert torch.equal(one["y"], grp["y"]) and torch.equal(one["dx"], grp["dx"])
+
+
+@pytest.mark.parametrize("cin,h,w", [(64, 40, 33), (128, 47, 31), (192, 64, 32), (256, 37, 45)])
+def test_conv1x1_resident_weights(cin, h, w):
+    """Launches of one micro-batch (the 1x1 tiles) and of a group (the kernel
+    with its weights in registers, with and without a ragged last tile): each
+    against the oracle and the same bits."""
+    one = run_and_check(Layer(CONV1X1, cin, 256), h, w, BF16, 14, 14, f"conv1x1 {cin}->256 one by one")
+    grp = run_and_check(Layer(CONV1X1, cin, 256), h, w, BF16, 14, 14, f"conv1x1 {cin}->256 group",
+                        lanes=14, group=14, serial=True)
+    assert torch.equal(one["y"], grp["y"]) and torch.equal(one["dx"], grp["dx"])
