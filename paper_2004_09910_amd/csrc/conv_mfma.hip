@@ -792,11 +792,7 @@ FwdPlan fwd_plan(const ConvShape& s) {
 // change a bit.  (us, forward, rectangular / rows: 128 at 96 x 96 x 1 10.4 /
 // 15.5, 64 at 192 x 192 x 1 11.1 / 14.9, 256 at 48 x 48 x 4 22.9 / 22.1, 128 at
 // 96 x 96 x 4 22.3 / 19.8.)
-// Likewise the resident-weight 1x1 kernel, which needs a tile of 64 pixels for
-// each of 256 blocks to be worth its weights (256 -> 256 at 14 x 14 x 1 7.6, tiles
-// 5.9; 196 tiles 8.8 and 8.8; 3136 50 and 72).
 static bool tile_instead(const FwdPlan& pl, const ConvShape& s, int n) {
-  if (pl.cfg == 150) return g_fwd_variant == 0 && n * ((s.pixels() + 63) / 64) < 256;
   return pl.cfg == 400 && g_fwd_variant == 0 && n * s.pixels() * s.cout < 2359296 && conv_tile_ok(s);
 }
 
@@ -854,8 +850,7 @@ hipError_t conv_forward_mfma(const void* x, const void* w, const float* b, void*
   bf16_t* Y2 = nullptr;
   const FwdPlan pl = fwd_plan(s);
   if (tile_instead(pl, s, 1))
-    return launch_tile_cfg(FwdPlan{s.taps == 9 ? 500 : 600, 1}, 1, &x, w, b, &y, s, relu, false,
-                           nullptr, 0, st);
+    return launch_tile_cfg(FwdPlan{500, 1}, 1, &x, w, b, &y, s, relu, false, nullptr, 0, st);
   if (pl.cfg == 150) return launch_1x1_res(1, &x, Wt, b, &y, s, relu, st);
   if (pl.cfg >= 500)
     return launch_tile_cfg(pl, 1, &x, w, b, &y, s, relu, false, &part, part_cap, st);
@@ -907,8 +902,8 @@ static bool use_wgrad_rows(const ConvShape& s) {
   return (g_rowtile_mask >> 2 & 1) && wgrad_rows_ok(s);
 }
 
-// Split count of the general weight gradients (per-tap, or direct where the
-// channels are no multiples of 64): what a plan's slices may take.
+// Split count of the general weight gradients (per-tap, or the pixel ranges of
+// channels that are no multiples of 64): what a plan's slices may take.
 int wgrad_general_splits(const ConvShape& s) {
   if (s.cin % 64 || s.cout % 64) return direct_wgrad_splits(s.pixels());
   const int t = s.cin % 128 == 0 && s.cout % 128 == 0 ? 128 : 64;
@@ -1100,8 +1095,7 @@ hipError_t conv_forward_mfma_n(int n, const void* const* x, const void* w, const
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
   const FwdPlan pl = fwd_plan(s);
   if (tile_instead(pl, s, n))
-    return launch_tile_cfg(FwdPlan{s.taps == 9 ? 500 : 600, 1}, n, x, w, b, y, s, relu, false,
-                           nullptr, 0, st);
+    return launch_tile_cfg(FwdPlan{500, 1}, n, x, w, b, y, s, relu, false, nullptr, 0, st);
   if (pl.cfg == 150) return launch_1x1_res(n, x, (const bf16_t*)w, b, y, s, relu, st);
   if (pl.cfg >= 500)
     return launch_tile_cfg(pl, n, x, w, b, y, s, relu, false, part, part_cap, st);

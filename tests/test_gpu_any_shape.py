@@ -250,10 +250,10 @@ def test_conv3x3_small_and_large_launches_agree():
 
 
 @pytest.mark.parametrize("cin,h,w", [(64, 40, 33), (128, 47, 31), (192, 64, 32), (256, 37, 45)])
-def test_conv1x1_resident_weights(cin, h, w):
-    """Launches of one micro-batch (the 1x1 tiles) and of a group (the kernel
-    with its weights in registers, with and without a ragged last tile): each
-    against the oracle and the same bits."""
+def test_conv1x1_register_weights(cin, h, w):
+    """The 1x1 kernel with its weights in registers, with and without a ragged
+    last tile, one micro-batch a launch and a group (several tiles a block):
+    each against the oracle and the same bits."""
     one = run_and_check(Layer(CONV1X1, cin, 256), h, w, BF16, 14, 14, f"conv1x1 {cin}->256 one by one")
     grp = run_and_check(Layer(CONV1X1, cin, 256), h, w, BF16, 14, 14, f"conv1x1 {cin}->256 group",
                         lanes=14, group=14, serial=True)
