@@ -21,9 +21,10 @@
 // units of 8 pixels, each within one image row, so the half-waves take their
 // own row's offset.  Pixels outside the image, channels past Cin or Cout and
 // the padding are buffer reads at out-of-range offsets (zeros); the input of
-// a unit's padding pixels is also cleared in registers, since it may be a
-// real pixel that no output pairs with that tap, or unset LDS, and 0 x Inf is
-// not 0.  Rows past the image are not summed at all.
+// a unit's padding pixels (past the strip's real width, which for the last
+// strip may end in any unit of a row) is also cleared in registers, since it
+// may be a real pixel that no output pairs with that tap, or unset LDS, and 0 x
+// Inf is not 0.  Rows past the image are not summed at all.
 //
 // Each item writes its fp32 slice for its K range; the slices are summed in
 // K-range order.
@@ -229,8 +230,10 @@ __global__ __launch_bounds__(64 * kWtNW) void conv_wgrad_tile(WtIo io, int ng, i
       const int w0 = (col - (col / cut.ns) * cut.ns) * cut.TW;
       const int U = min(cut.RPS, H - h) * n8;   // units of this stage
       const int KT = (U + 1) / 2;
-      const int rem = min(cut.TW, W - w0) - 8 * (n8 - 1);     // pixels of a row's last unit
-      const bool ragged = rem < 8 || (U & 1);   // some unit has padding pixels
+      const int tw = min(cut.TW, W - w0);       // pixels of a row
+      const int ul = (tw - 1) >> 3;             // unit that holds its last one, as pixel rem - 1
+      const int rem = tw - 8 * ul;
+      const bool ragged = tw < TWP || (U & 1);  // some unit has padding pixels
       unsigned mrem[4];                         // rem pixels of a fragment's 8
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -246,13 +249,13 @@ __global__ __launch_bounds__(64 * kWtNW) void conv_wgrad_tile(WtIo io, int ng, i
         for (int i = 0; i < 2; ++i) a[i] = frag(sp + fa[i] + ka);
 #pragma unroll
         for (int s = 0; s < 3; ++s) b[s] = frag(sp + fb[s] + ka + ue);
-        // a unit with padding pixels: a row's last one (rem pixels), or past an
-        // odd count (none); skipped by the waves that have none
-        const bool pad = 2 * t + half >= U;
-        if (ragged && __any(pad || uc == n8 - 1)) {
+        // units with padding pixels: unit ul of a row (rem real ones), and past
+        // it or past an odd count (none); skipped by the waves that have none
+        const bool pad = 2 * t + half >= U || uc > ul;
+        if (ragged && __any(pad || uc == ul)) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const unsigned m = pad ? 0u : uc == n8 - 1 ? mrem[e] : ~0u;
+            const unsigned m = pad ? 0u : uc == ul ? mrem[e] : ~0u;
 #pragma unroll
             for (int s = 0; s < 3; ++s) b[s][e] &= m;
           }

@@ -97,6 +97,55 @@ def test_wgrad_padding_keeps_infinities_apart(h, w):
     sess.close()
 
 
+def kernels_of(call):
+    """Names of the kernels that `call` launches."""
+    tgp.profile_enable(True)
+    try:
+        tgp.profile_read()
+        call()
+        torch.cuda.synchronize()
+        return {k["name"] for k in tgp.profile_read()}
+    finally:
+        tgp.profile_enable(False)
+
+
+@pytest.mark.parametrize("cin,cout,h,w,b", [
+    (128, 128, 100, 100, 4),     # 24-pixel strips, 4 pixels in the last: its first unit is ragged
+    (64, 72, 40, 52, 2),         # the same, two strips of channels
+    (48, 48, 86, 86, 2),         # a last strip of 6 pixels
+    (64, 64, 49, 49, 21),        # a last strip of one pixel
+    (40, 24, 5, 9, 3),           # two units a row, the second of one pixel
+])
+def test_wgrad_tile_clears_the_padding_of_every_unit(cin, cout, h, w, b):
+    """The rectangular-stage weight gradient: the last column's input pixels
+    pair with no output at column tap 0, nor the last row's at row tap 0, so an
+    infinity there must not reach those taps, whatever unit of a strip the
+    image ends in."""
+    net = one_layer(Layer(CONV3X3, cin, cout, relu=False), h, w)
+    sess = Session(net, BF16)
+    sess.plan(b, 1, specs.CKPT_NEVER)
+    torch.manual_seed(3)
+    x = torch.randn(b, h, w, cin, device="cuda").bfloat16()
+    dy = torch.randn(b, h, w, cout, device="cuda").bfloat16()
+    y = torch.empty_like(dy)
+
+    def step(xs):
+        names = kernels_of(lambda: sess.stage_step(1, xs, y, dy, None,
+                                                   torch.cuda.current_stream().cuda_stream))
+        assert "conv_wgrad_tile" in names, names
+        return sess.params[0]["dw"].clone()                   # cout, kh, kw, cin
+
+    for edge, tap in ((np.s_[:, :, -1, 5], np.s_[:, :, 0, 5]), (np.s_[:, -1, :, 5], np.s_[:, 0, :, 5])):
+        x0, x1 = x.clone(), x.clone()
+        x0[edge] = 0.0
+        x1[edge] = float("inf")
+        d0, d1 = step(x0), step(x1)
+        assert torch.equal(d0[tap], d1[tap])
+        assert torch.equal(d0[..., :5], d1[..., :5]) and torch.equal(d0[..., 6:], d1[..., 6:])
+        assert not torch.isfinite(d1[:, 1, 1, 5]).any()
+    sess.close()
+
+
 @pytest.mark.parametrize("c,h,w,relu,bias", [
     (24, 9, 13, True, True),       # 3 packs: 255 threads, partly filled rows
     (192, 28, 28, True, True),     # 24 packs, several strips and chunks
