@@ -84,9 +84,13 @@ __global__ __launch_bounds__(64 * kWtNW) void conv_wgrad_tile(WtIo io, int ng, i
                                                               int Cin, int Cout, WtCut cut) {
   constexpr int NW = kWtNW;
   constexpr int SB = LW * NW * 1024;            // slot bytes
-  static_assert(NS * SB <= 160 * 1024, "LDS ring");
+  // The last k step of an odd count of units reads its second unit from the
+  // rows after the stage's input (and clears it): up to the first 8 pixels and
+  // 2 column taps of the next row, which may lie past the last slot.
+  constexpr int TAIL = (8 + 2) * 128;
+  static_assert(NS * SB + TAIL <= 160 * 1024, "LDS ring");
   static_assert(6 * 12 * 1024 <= SB, "exchange of the phases' sums fits a slot");
-  __shared__ __attribute__((aligned(16))) unsigned char smem[NS * SB];
+  __shared__ __attribute__((aligned(16))) unsigned char smem[NS * SB + TAIL];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -41,6 +41,7 @@ def run_and_check(L, h, w, dtype, B, m, what, **kw):
     (64, 64, 57, 56, 4, 2),      # 64-multiples at a width of no table
     (64, 192, 40, 61, 12, 2),    # the rectangular-stage weight gradient, odd units
     (264, 16, 7, 7, 2, 2),       # many chunks, few pixels
+    (64, 72, 27, 8, 64, 1),      # a full slot of 27 one-unit rows in the weight gradient
 ])
 def test_conv3x3_any_shape(cin, cout, h, w, B, m):
     run_and_check(Layer(CONV3X3, cin, cout), h, w, BF16, B, m,
@@ -110,10 +111,10 @@ def kernels_of(call):
 
 
 @pytest.mark.parametrize("cin,cout,h,w,b", [
-    (128, 128, 100, 100, 4),     # 24-pixel strips, 4 pixels in the last: its first unit is ragged
-    (64, 72, 40, 52, 2),         # the same, two strips of channels
-    (48, 48, 86, 86, 2),         # a last strip of 6 pixels
-    (64, 64, 49, 49, 21),        # a last strip of one pixel
+    (128, 128, 100, 100, 4),     # strips of 24 pixels, the last of 4
+    (64, 72, 40, 52, 2),         # of 16, the last of 4; a second channel item of 8
+    (48, 48, 86, 86, 2),         # of 32, the last of 22
+    (64, 64, 49, 49, 21),        # of 32, the last of 17
     (40, 24, 5, 9, 3),           # two units a row, the second of one pixel
 ])
 def test_wgrad_tile_clears_the_padding_of_every_unit(cin, cout, h, w, b):
