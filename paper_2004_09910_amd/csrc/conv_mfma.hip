@@ -815,12 +815,10 @@ static hipError_t launch_tile_cfg(const FwdPlan& pl, int n, const void* const* x
   return e;
 }
 
-// Whether a shape's data gradient (t: its transposed shape) runs on a kernel
-// that reads the forward weights, and that launch (also where a forced plan
-// names another kernel but no transformed weights were planned for).
-bool conv_dgrad_tile_planned(const ConvShape& t) {
-  return fwd_plan(t).cfg >= 500;
-}
+// Whether a shape's data gradient (t: its transposed shape) over n micro-batches
+// (and then over any fewer) runs on a kernel that reads the forward weights, and
+// that launch (also where a forced plan names another kernel but no transformed
+// weights were planned for).
 bool conv_dgrad_tile_now(const ConvShape& t, int n) {
   const FwdPlan pl = fwd_plan(t);
   return pl.cfg >= 500 || tile_instead(pl, t, n);

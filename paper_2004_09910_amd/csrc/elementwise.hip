@@ -11,7 +11,6 @@ namespace tgpk {
 
 bool mfma_fwd_ok(int dt, const ConvShape& s);
 bool mfma_wgrad_ok(int dt, const ConvShape& s);
-bool conv_dgrad_tile_planned(const ConvShape& t);
 bool conv_dgrad_tile_now(const ConvShape& t, int n);
 hipError_t conv_dgrad_tile(int n, const void* const* dz, const void* w, void* const* dx,
                            const ConvShape& t, float* const* part, size_t part_cap,
@@ -1196,9 +1195,9 @@ hipError_t conv_forward(int dt, const void* x, const void* w, const float* b, vo
   return conv_gen_forward(dt, 1, &x, w, b, &y, s, relu, false, st);
 }
 
-bool conv_dgrad_uses_wt(int dt, const ConvShape& s) {
+bool conv_dgrad_uses_wt(int dt, const ConvShape& s, int n_max) {
   const ConvShape t{s.nb, s.H, s.W, s.cout, s.cin, s.taps};
-  return mfma_fwd_ok(dt, t) && !conv_dgrad_tile_planned(t);
+  return mfma_fwd_ok(dt, t) && !conv_dgrad_tile_now(t, n_max);
 }
 
 hipError_t conv_dgrad(int dt, const void* dz, const void* w, const void* wt, void* dx,

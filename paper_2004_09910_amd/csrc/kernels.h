@@ -125,9 +125,10 @@ hipError_t conv_wgrad_tile_launch(int n, const void* const* x, const void* const
                                   float* const* dw, float* const* partial, const ConvShape& s,
                                   hipStream_t st, ReduceJob* const* defer);
 
-// Whether the data-gradient kernel planned for this shape reads the
-// transformed weight wt = [cin][taps][cout] (taps rotated by 180 degrees).
-bool conv_dgrad_uses_wt(int dt, const ConvShape& s);
+// Whether a data gradient of this shape over at most n_max micro-batches a
+// launch reads the transformed weight wt = [cin][taps][cout] (taps rotated by
+// 180 degrees).
+bool conv_dgrad_uses_wt(int dt, const ConvShape& s, int n_max);
 // Builds those transformed weights, wt[ci][tap'][co] = w[co][taps-1-tap'][ci],
 // for up to kMaxWt tensors in one launch (passed by value).
 constexpr int kMaxWt = 32;

@@ -1270,7 +1270,9 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
   size_t max_part = 0, max_col = 0;
   for (auto& Lr : N->L) {
     tgpk::ConvShape s{N->b, Lr.H, Lr.W, Lr.d.cin, Lr.d.cout, Lr.taps};
-    Lr.has_wt = Lr.d.kind != TGP_DWCONV3X3 && tgpk::conv_dgrad_uses_wt(N->dt, s);
+    // (a launch covers at most one micro-batch of every lane)
+    Lr.has_wt = Lr.d.kind != TGP_DWCONV3X3 &&
+                tgpk::conv_dgrad_uses_wt(N->dt, s, std::min(N->lanes, N->m));
     Lr.o_wt = Lr.has_wt ? takeL(Lr.w_elems * N->esz) : 0;
     // Split-K partials stay in the slot for the accumulation to sum when a
     // layer's are at most kDeferBytes per micro-batch; larger ones (deep,

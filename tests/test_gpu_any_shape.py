@@ -299,6 +299,19 @@ def test_conv3x3_small_and_large_launches_agree():
     assert torch.equal(one["y"], grp["y"]) and torch.equal(one["dx"], grp["dx"])
 
 
+@pytest.mark.parametrize("c,hw,b,m,lanes,wt", [
+    (128, 96, 1, 2, 1, False),   # every launch of the plan is small: the forward weights serve
+    (128, 96, 1, 4, 4, True),    # a launch of all four lanes takes the whole rows
+    (64, 96, 8, 1, 1, True),
+])
+def test_transposed_weights_only_where_a_launch_reads_them(c, hw, b, m, lanes, wt):
+    net = one_layer(Layer(CONV3X3, c, c), hw, hw)
+    what = f"conv3x3 {c} @{hw}x{hw}x{b} m={m}"
+    names = kernels_of(lambda: run_and_check(net.layers[0], hw, hw, BF16, b * m, m, what,
+                                             lanes=lanes, group=lanes, serial=True))
+    assert ("wtransform" in names) == wt, names
+
+
 @pytest.mark.parametrize("cin,h,w", [(64, 40, 33), (128, 47, 31), (192, 64, 32), (256, 37, 45)])
 def test_conv1x1_register_weights(cin, h, w):
     """The 1x1 kernel with its weights in registers, with and without a ragged
