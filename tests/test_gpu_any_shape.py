@@ -301,6 +301,7 @@ def test_conv3x3_small_and_large_launches_agree():
 
 @pytest.mark.parametrize("c,hw,b,m,lanes,wt", [
     (128, 96, 1, 2, 1, False),   # every launch of the plan is small: the forward weights serve
+    (128, 96, 1, 2, 2, False),   # the largest small launch
     (128, 96, 1, 4, 4, True),    # a launch of all four lanes takes the whole rows
     (64, 96, 8, 1, 1, True),
 ])
