@@ -745,7 +745,7 @@ FwdPlan fwd_plan(const ConvShape& s) {
     return pl;
   }
   // The nine-tap whole-row kernel on images of 48 x 48 and up of the widths it
-  // is built for, and from 24 x 24 where four samples give it at least 48
+  // is built for, and from 24 x 24 where one micro-batch gives it at least 48
   // tiles; the rectangular tiles for every other 3x3 layer (us, forward + data
   // gradient with the transform of its weights, against the kernels these
   // shapes had: 64 at 224 x 224 x 1 22 / 44, x 16 185 / 285; 256 at 56 x 56 x 8 75
