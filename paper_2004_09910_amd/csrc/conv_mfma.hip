@@ -732,11 +732,17 @@ static hipError_t launch_1x1_res(int n, const void* const* x, const bf16_t* Wt, 
   return launch_status();
 }
 
-// Pure function of the per-sample shape (H, W, Cin, Cout, taps), plus the
-// measurement overrides: the kernel family and the split count fix the K
-// summation order, so keeping them independent of the number of samples
-// keeps every sample's output bit-identical whatever the micro-batch size.
-// The tile-count heuristics use a nominal micro-batch of 4 samples.
+// Pure function of one micro-batch's shape, plus the measurement overrides: the
+// kernel family and the split count fix the K summation order, so a
+// recomputation and a launch over several micro-batches give the same bits.
+// Both depend on the per-sample shape alone (split counts use a nominal
+// micro-batch of 4 samples), which keeps a sample's output bit-identical
+// whatever the micro-batch size, with one exception: images from 24 x 24 to below
+// 48 x 48 of the whole-row kernel's widths, where that kernel needs 48 tiles of
+// the micro-batch and adds each sum in one chain, while the rectangular tiles
+// that run otherwise split deep sums (512 channels at 24 x 24: one sample in
+// shares, two or more in one chain).  Making that choice per sample cost single
+// samples up to 19% (896 -> 256 at 24 x 24) or groups of them the whole rows.
 FwdPlan fwd_plan(const ConvShape& s) {
   FwdPlan pl{0, 1};
   if (s.cin % 64 || s.cout % 64) {   // the kernels that take any multiple of 8

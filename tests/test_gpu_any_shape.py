@@ -290,6 +290,27 @@ def test_conv3x3_shares_of_a_long_sum(cin, cout, h, w):
     back["sess"].close()
 
 
+@pytest.mark.parametrize("dtype,kind,cin,cout,h,w", [
+    (BF16, CONV3X3, 512, 128, 20, 20),    # shares of the sum
+    (BF16, CONV3X3, 1024, 256, 14, 14),
+    (BF16, CONV3X3, 128, 128, 48, 48),    # whole rows or rectangles, by the launch
+    (BF16, CONV3X3, 64, 192, 45, 61),
+    (BF16, CONV3X3, 40, 72, 21, 37),
+    (BF16, CONV3X3, 3, 64, 33, 29),
+    (BF16, CONV1X1, 256, 256, 28, 28),
+    (BF16, CONV1X1, 192, 136, 30, 25),
+    (BF16, DWCONV3X3, 192, 192, 14, 14),
+    (FP32, CONV3X3, 16, 40, 32, 32),
+])
+def test_outputs_do_not_depend_on_the_micro_batch_size(dtype, kind, cin, cout, h, w):
+    """A sample's output and input gradient have the same bits alone and among
+    four samples: the order of every sum is fixed by the per-sample shape."""
+    net = one_layer(Layer(kind, cin, cout), h, w)
+    one = gpu_stage(net, dtype, 4, 4, 0, (1,), 1)
+    four = gpu_stage(net, dtype, 4, 1, 0, (1,), 1)
+    assert torch.equal(one["y"], four["y"]) and torch.equal(one["dx"], four["dx"])
+
+
 def test_conv3x3_small_and_large_launches_agree():
     """The whole-row kernel's widths: a launch of few samples takes the
     rectangular tiles, one of many the whole rows, with the same bits."""
