@@ -482,18 +482,23 @@ static int tile_pick(const ConvShape& s, int ng, int S, TileCut& cut) {
 
 // Shares of a split sum, a function of the per-sample shape (so that every
 // sample's sums keep their order whatever the micro-batch): two or four where
-// four samples give few tiles of 64 x 256 and a share keeps 16 stages.  The
-// shares' sums cost a write, a read and a launch (4 us).  Forward, us: 2048 at 16
-// x 16 x 4: one share 155, two 131, four 92 (the split row kernel, two
-// micro-batches apart: 198); 1024 at 14 x 14 x 1: 42, 32, 21 (38); x 16: 80, 79,
-// 86 (154); 512 at 14 x 14 x 1: 23, 20, 15 (17), x 16: 29, 31; 256 at 16 x 16 x
-// 1: 13, 14 (13).
+// four samples give few tiles of 64 x 256 and a share keeps 16 stages, of four 12.
+// The shares' sums cost a write, a read and a launch (4 us), and more the more
+// samples a launch has.  Forward with its epilogue, us, for 1, 2, 4 shares: 1024 at
+// 14 x 14 x 1: 42, 32, 21; x 16: 80, 79, 86; 512 at 14 x 14 x 1: 23, 20, 15; 896 ->
+// 192 at 7 x 7 x 1: 36, 26, 17; 896 -> 128 at 9 x 9 x 4: 37, 27, 18; 768 -> 128 at
+// 17 x 17 x 32: 37, 39, 42; 256 at 16 x 16 x 1: 13, 14.  Images past 4096 pixels in
+// four samples gain only with the longest sums (2048 -> 128 at 36 x 36 x 1: 80, 52;
+// x 16: 101, 140).  Shares stop at 192 tiles, which bounds the room their sums
+// take in a plan.
 int conv_tile_split(const ConvShape& s) {
   const long P = 4L * s.H * s.W, nk = s.cin / 16;
-  if (P > 4096 || s.cin % 64 || s.cout % 64) return 1;
+  if (s.cin % 64 || s.cout % 64) return 1;
   const long tiles = (P + 255) / 256 * (s.cout / 64);
+  if (P > 4096)
+    return P <= 8192 && tiles <= 64 && s.cout % 128 == 0 && nk % 2 == 0 && nk / 2 >= 48 ? 2 : 1;
   int S = 1;
-  while (S < 4 && tiles * S < 256 && nk / (2 * S) >= 16 && nk % (2 * S) == 0) S *= 2;
+  while (S < 4 && tiles * S < 192 && nk / (2 * S) >= (S == 1 ? 16 : 12) && nk % (2 * S) == 0) S *= 2;
   return S;
 }
 

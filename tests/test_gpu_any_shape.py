@@ -320,6 +320,25 @@ def test_conv3x3_small_and_large_launches_agree():
     assert torch.equal(one["y"], grp["y"]) and torch.equal(one["dx"], grp["dx"])
 
 
+@pytest.mark.parametrize("cin,cout,h,w,split", [
+    (768, 64, 10, 10, True),      # four shares of 12 stages
+    (512, 192, 5, 9, True),       # two of 16
+    (448, 64, 9, 10, False),      # two would have 14
+    (2048, 128, 34, 36, True),    # past 1024 pixels: the longest sums only
+    (1408, 128, 34, 36, False),
+])
+def test_conv3x3_where_a_sum_is_split(cin, cout, h, w, split):
+    """Both sides of the lines for split sums: against the oracle, one by one and
+    as a group of two with the same bits."""
+    layer = Layer(CONV3X3, cin, cout)
+    what = f"conv3x3 {cin}->{cout} @{h}x{w}"
+    out = []
+    names = kernels_of(lambda: out.append(run_and_check(layer, h, w, BF16, 2, 2, what)))
+    assert any(n.startswith("conv3x3_tile") and n.endswith("4,split>") for n in names) == split, names
+    grp = gpu_stage(one_layer(layer, h, w), BF16, 2, 2, 0, (1,), 1, lanes=2, group=2, serial=True)
+    assert torch.equal(out[0]["y"], grp["y"]) and torch.equal(out[0]["dx"], grp["dx"])
+
+
 @pytest.mark.parametrize("c,hw,b,m,lanes,wt", [
     (128, 96, 1, 2, 1, False),   # every launch of the plan is small: the forward weights serve
     (128, 96, 1, 2, 2, False),   # the largest small launch
