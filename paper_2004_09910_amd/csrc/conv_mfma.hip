@@ -796,14 +796,14 @@ FwdPlan fwd_plan(const ConvShape& s) {
 // are whole rows, so few samples leave CUs idle, where the rectangular tiles can
 // be smaller.  Both sum over (chunk, tap, channel), so the choice does not
 // change a bit.  The line is where a launch has 2304 tiles of 32 pixels x 32
-// channels.  At it (us, forward, rectangular / rows): 128 at 96 x 96 x 2 13.6 /
-// 15.9, 64 at 192 x 192 x 1 10.2 / 14.2, 256 at 48 x 48 x 4 20.4 / 20.2, 512 at 24
-// x 24 x 8 37.1 / 34.6, 256 -> 64 at 96 x 96 x 4 30.3 / 23.2 (the worst seen);
-// the data gradient of the square ones also saves the weights' transform, 4 to
-// 11.  Past it: 128 at 96 x 96 x 4 22.3 / 19.8.
+// channels: up to and at it with up to 128 input channels, below it with more,
+// whose stages are many.  At it (us, forward, rectangular / rows): 128 at 96 x 96 x
+// 2 13.6 / 15.9, 64 at 192 x 192 x 1 10.2 / 14.2; 256 at 48 x 48 x 4 20.4 / 20.2, 512
+// at 24 x 24 x 8 37.1 / 34.6, 256 -> 64 at 96 x 96 x 4 30.3 / 23.2, 2048 -> 256 at 24
+// x 24 x 16 138 / 123.  Past it: 128 at 96 x 96 x 4 22.3 / 19.8.
 static bool tile_instead(const FwdPlan& pl, const ConvShape& s, int n) {
-  return pl.cfg == 400 && g_fwd_variant == 0 && n * s.pixels() * s.cout <= 2304L * 1024 &&
-         conv_tile_ok(s);
+  return pl.cfg == 400 && g_fwd_variant == 0 &&
+         n * s.pixels() * s.cout < 2304L * 1024 + (s.cin <= 128 ? 1 : 0) && conv_tile_ok(s);
 }
 
 // The rectangular-tile kernel (500 ..) or the 1x1 tile kernel (600 ..), in the
