@@ -920,16 +920,24 @@ int wgrad_general_splits(const ConvShape& s) {
 }
 
 // 3x3 layers of no fixed width: the rectangular-stage kernel.  Where the
-// per-tap kernel can run too (channels in multiples of 64), small layers stay
-// with it: its many short blocks start and end sooner.  Measured, four or two
-// micro-batches a launch / one: 128 -> 128 at 56 x 56 x 8 52 / 45 us against
-// 65 / 45, 512 -> 512 at 14 x 14 x 4 31 / 28 against 49 / 25, 128 -> 192 at 45
-// x 61 x 3 29 / 29 against 32 / 26; 64 -> 64 at 56 x 56 x 4 20 (one) against
-// 12, x 1 15 against 8.  The line lies at 48 thousand pixel x item products.
+// per-tap kernel can run too (channels in multiples of 64), small layers and
+// those whose rows fill the stages badly stay with it.
+//  - Its many short blocks start and end sooner, so the lines for one micro-batch
+//    a launch and for several lie apart, and one has to serve both (a group gives
+//    the bits of single launches): 48 thousand pixel x item products.  Rectangular /
+//    per-tap, us with the sum, for one, two and four micro-batches a launch: 128 at
+//    56 x 56 x 4 33 / 29, 37 / 33, 39 / 45; 128 -> 192 at 45 x 61 x 3 31 / 28, 35 / 35,
+//    40 / 69; x 6 47 / 45, 50 / 55, 55 / 110; 64 at 56 x 56 x 4 23 / 17, 26 / 19, 29 / 30.
+//  - A stage's rows are padded to 8 pixels and its k steps to 16: where more than
+//    35% of what is multiplied is padding the per-tap kernel wins (384 -> 512 at 15
+//    x 10 x 16 96 / 57, 512 -> 256 at 100 x 4 x 4 75 / 43).
+// Over 700 random shapes (8 to 500 thousand products) the choice is 3.2%, 1.7% and
+// 3.9% from the faster of the two for one, two and four micro-batches a launch;
+// the per-tap kernel alone is 4%, 8% and 40% from it.
 static bool use_wgrad_tile(const ConvShape& s) {
   if (!wgrad_tile_ok(s)) return false;
   return s.cin % 64 || s.cout % 64 ||
-         s.pixels() * (s.cin / 64) * (s.cout / 64) >= 48 * 1024;
+         (s.pixels() * (s.cin / 64) * (s.cout / 64) >= 48 * 1024 && wgrad_tile_fill(s) >= 0.65);
 }
 // Shapes conv_wgrad_mfma takes.
 bool mfma_wgrad_ok(int dt, const ConvShape& s) {

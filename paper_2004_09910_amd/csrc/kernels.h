@@ -118,6 +118,7 @@ hipError_t conv_gen_wgrad_launch(int dt, int n, const void* const* x, const void
                                  float* const* dw, float* const* partial, const ConvShape& s,
                                  hipStream_t st, ReduceJob* const* defer);
 bool wgrad_tile_ok(const ConvShape& s);
+double wgrad_tile_fill(const ConvShape& s);   // share of what it multiplies that is pixels
 int wgrad_general_splits(const ConvShape& s);
 int direct_wgrad_splits(long P);   // of P pixels, the per-element kernels
 size_t wgrad_tile_partial_floats(const ConvShape& s);

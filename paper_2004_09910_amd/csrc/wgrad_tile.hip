@@ -374,6 +374,11 @@ bool wgrad_tile_ok(const ConvShape& s) {
          (double)s.pixels() * (s.cin > s.cout ? s.cin : s.cout) * 2 < 2147483648.0;
 }
 
+double wgrad_tile_fill(const ConvShape& s) {
+  const WtCut c = wt_cut(s);
+  return (double)s.pixels() / ((double)c.T * c.AROWS);
+}
+
 size_t wgrad_tile_partial_floats(const ConvShape& s) {
   const int S = wt_cut(s).nK;
   return S > 1 ? (size_t)S * s.cout * 9 * s.cin : 0;

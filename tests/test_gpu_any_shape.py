@@ -39,7 +39,7 @@ def run_and_check(L, h, w, dtype, B, m, what, **kw):
     (16, 8, 3, 130, 2, 2),       # column strips
     (40, 64, 2, 600, 1, 1),      # many strips, two rows
     (64, 64, 57, 56, 4, 2),      # 64-multiples at a width of no table
-    (64, 192, 40, 61, 12, 2),    # the rectangular-stage weight gradient, odd units
+    (64, 192, 40, 61, 14, 2),    # the rectangular-stage weight gradient, odd units
     (264, 16, 7, 7, 2, 2),       # many chunks, few pixels
     (64, 72, 27, 8, 64, 1),      # a full slot of 27 one-unit rows in the weight gradient
 ])
@@ -108,6 +108,18 @@ def kernels_of(call):
         return {k["name"] for k in tgp.profile_read()}
     finally:
         tgp.profile_enable(False)
+
+
+@pytest.mark.parametrize("cin,cout,h,w,b,tile", [
+    (64, 192, 40, 61, 7, True),
+    (64, 192, 40, 61, 6, False),      # few products
+    (128, 512, 15, 10, 24, False),    # rows of 10 pixels in units of 8
+    (128, 512, 15, 14, 16, True),
+])
+def test_wgrad_kernel_of_a_shape(cin, cout, h, w, b, tile):
+    names = kernels_of(lambda: run_and_check(Layer(CONV3X3, cin, cout), h, w, BF16, 2 * b, 2,
+                                             f"wgrad {cin}->{cout} @{h}x{w}x{b}"))
+    assert ("conv_wgrad_tile" in names) == tile, names
 
 
 @pytest.mark.parametrize("cin,cout,h,w,b", [
