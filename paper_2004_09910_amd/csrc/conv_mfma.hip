@@ -919,6 +919,13 @@ int wgrad_general_splits(const ConvShape& s) {
                           (long)s.cout * s.taps * s.cin).S;
 }
 
+int wgrad_room_splits(int dt, const ConvShape& s) {
+  if (dt != 0 || s.cin % 64 || s.cout % 64) return direct_wgrad_splits(s.pixels());
+  if (!use_wgrad_rows(s)) return wgrad_general_splits(s);
+  const size_t S = wgrad_rows_partial_floats(s) / ((size_t)s.cout * s.taps * s.cin);
+  return S > 1 ? (int)S : 1;
+}
+
 // 3x3 layers of no fixed width: the rectangular-stage kernel.  Where the
 // per-tap kernel can run too (channels in multiples of 64), small layers and
 // those whose rows fill the stages badly stay with it.

@@ -121,6 +121,9 @@ bool wgrad_tile_ok(const ConvShape& s);
 double wgrad_tile_fill(const ConvShape& s);   // share of what it multiplies that is pixels
 int wgrad_general_splits(const ConvShape& s);
 int direct_wgrad_splits(long P);   // of P pixels, the per-element kernels
+// Slices of the weight gradient that a plan has room for (at least what the
+// kernel of the shape writes).
+int wgrad_room_splits(int dt, const ConvShape& s);
 size_t wgrad_tile_partial_floats(const ConvShape& s);
 hipError_t conv_wgrad_tile_launch(int n, const void* const* x, const void* const* dz,
                                   float* const* dw, float* const* partial, const ConvShape& s,

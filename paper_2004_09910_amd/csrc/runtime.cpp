@@ -633,16 +633,21 @@ tgp_status run_backward_g(tgp_net* N, int j, int cnt, const int* iv,
       dw_wrows = dw_wrows && tgpk::dw_wgrad_rows_ok(N->dt, N->b, Lr.H, Lr.W, d.cout, cin_ptr[k],
                                                     dzk[k], dw_parts[k]);
     }
-    if (d.kind != TGP_DWCONV3X3 && cnt > 1 && Lr.defer_w) {
+    if (d.kind != TGP_DWCONV3X3 && cnt > 1) {
       float* gws[MG];
       float* gps[MG];
+      tgpk::ReduceJob jobs[MG];   // the sums of slices that are reduced at once
       tgpk::ReduceJob* dfs[MG];
       for (int k = 0; k < cnt; ++k) {
         gws[k] = (float*)G_(N, M[k].i, Lr.o_gw);
-        gps[k] = (float*)G_(N, M[k].i, Lr.o_gpart);
-        dfs[k] = &(*pjs[k])[0];
+        gps[k] = Lr.defer_w ? (float*)G_(N, M[k].i, Lr.o_gpart) : M[k].part;
+        dfs[k] = Lr.defer_w ? &(*pjs[k])[0] : &jobs[k];
       }
       HIPCHK(tgpk::conv_wgrad_n(N->dt, cnt, cin_ptr, dzk, gws, gps, s, st, dfs), "conv_wgrad_n");
+      for (int k = 0; k < cnt && !Lr.defer_w; ++k)
+        if (jobs[k].S > 1)
+          HIPCHK(tgpk::splitk_reduce_launch(jobs[k].part, gws[k], jobs[k].E, jobs[k].S, st),
+                 "conv_wgrad");
     } else if (dw_wrows && (cnt > 1 || Lr.defer_w)) {
       float* gws[MG];
       tgpk::ReduceJob* dfs[MG];
@@ -1275,11 +1280,15 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
                 tgpk::conv_dgrad_uses_wt(N->dt, s, std::min(N->lanes, N->m));
     Lr.o_wt = Lr.has_wt ? takeL(Lr.w_elems * N->esz) : 0;
     // Split-K partials stay in the slot for the accumulation to sum when a
-    // layer's are at most kDeferBytes per micro-batch; larger ones (deep,
-    // wide layers) are reduced at once through a lane buffer, so the slots
-    // do not grow with the sum of every layer's partials.
+    // layer's slices are at most kDeferBytes per micro-batch (or it writes
+    // none); those of larger ones (deep, wide layers) are reduced at once
+    // through a lane buffer, so the slots do not grow with the sum of every
+    // layer's partials.  The slices counted are those the layer has room for,
+    // also where its kernel writes fewer.
     constexpr size_t kDeferBytes = 32u << 20;
     const long P = (long)N->b * Lr.H * Lr.W;
+    const long general = Lr.d.kind == TGP_DWCONV3X3 ? tgpk::direct_wgrad_splits(P)
+                                                    : tgpk::wgrad_room_splits(N->dt, s);
     Lr.defer_w = false;
     size_t pf = 0;   // floats of the weight gradient's partial slices
     if (Lr.d.kind == TGP_DWCONV3X3) {
@@ -1291,7 +1300,7 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
       max_part = std::max(max_part, pf);
     } else {
       pf = tgpk::conv_wgrad_partial_floats(N->dt, s);
-      Lr.defer_w = pf * 4 <= kDeferBytes;
+      Lr.defer_w = pf == 0 || std::max<size_t>(pf, general * Lr.w_elems) * 4 <= kDeferBytes;
       if (!Lr.defer_w) max_part = std::max(max_part, pf);
     }
     // The gradient itself and its partial slices share their place: where the
@@ -1303,8 +1312,6 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
     // take no more room than the gradient and the slices of the general
     // kernels, else reduced at once through the lane's temporaries (below).
     const long Ec = Lr.d.kind == TGP_DWCONV3X3 ? 9 : (long)Lr.d.cin * Lr.taps;   // weights per channel
-    const long general = Lr.d.kind == TGP_DWCONV3X3 ? tgpk::direct_wgrad_splits(P)
-                                                     : tgpk::wgrad_general_splits(s);
     const long spare = Lr.defer_w && (pf || general > 1)
                            ? general + 1 - std::max(1L, (long)(pf / Lr.w_elems)) : 0;
     Lr.rb_cap = spare > 0 ? (int)std::min(240L, Ec * spare) : 240;

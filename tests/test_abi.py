@@ -221,6 +221,37 @@ def test_lanes_replicate_only_the_transient_buffers():
     tgp.net_destroy(h)
 
 
+C3, C1 = (specs.CONV3X3, specs.CONV1X1)
+
+
+def _plan_bytes(layers, h, w, dtype, n, b, m, mode, lanes):
+    net = tgp.net_create(layers, layers[0][1], h, w, dtype)
+    try:
+        tgp.set_partition(net, n)
+        tgp.set_lanes(net, lanes)
+        return tgp.plan(net, b * m, m, mode)
+    finally:
+        tgp.net_destroy(net)
+
+
+@pytest.mark.parametrize("kind,cin,cout,count,h,w,dtype,n,b,m,mode,lanes,most", [
+    # slices of every float32 layer in every micro-batch's slot
+    (C3, 128, 128, 8, 40, 16, specs.FP32, 2, 1, 8, specs.CKPT_EXCEPT_LAST, 2, 135564032),
+    # shares of a split sum
+    (C3, 768, 896, 1, 13, 76, specs.BF16, 1, 8, 1, specs.CKPT_NEVER, 1, 146950400),
+    (C3, 1024, 512, 1, 24, 24, specs.BF16, 1, 1, 1, specs.CKPT_NEVER, 1, 37459200),
+    # block sums of the bias where the weight gradient has few slices
+    (C3, 256, 384, 1, 52, 48, specs.BF16, 1, 4, 3, specs.CKPT_NEVER, 1, 82004736),
+    (C1, 64, 384, 1, 82, 64, specs.FP32, 1, 8, 7, specs.CKPT_ALWAYS, 1, 1167233024),
+])
+def test_plans_need_no_more_room_than_programs_give_them(kind, cin, cout, count, h, w, dtype, n, b,
+                                                         m, mode, lanes, most):
+    """Workspace sizes that programs have planned with: a plan that has fitted
+    a fixed array (tgp_pipeline_step_static) has to fit it still."""
+    layers = [(kind, cin, cout, 1, 1, specs.PRO_NONE, -1, -1)] * count
+    assert _plan_bytes(layers, h, w, dtype, n, b, m, mode, lanes) <= most
+
+
 def test_stage_state_machine_rejects_out_of_order_calls():
     h, nbytes = _bound_net(mode=1, B=4, m=2, n=2)
     tgp.bind_workspace(h, FAKE, nbytes)

@@ -226,6 +226,18 @@ def test_float32_matrix_convolutions_groups_are_bitwise():
         np.testing.assert_array_equal(a, b)
 
 
+def test_slices_reduced_at_once_groups_are_bitwise():
+    """A float32 layer whose slices are too many to keep: they are summed after
+    the launch, for one micro-batch and for a group.  (No ReLU: among four
+    million outputs one lies within float32 rounding of zero.)"""
+    layer = Layer(CONV3X3, 128, 128, relu=False)
+    one = run_and_check(layer, 122, 120, FP32, 2, 2, "conv3x3 128 @122x120 fp32")
+    grp = gpu_stage(one_layer(layer, 122, 120), FP32, 2, 2, 0, (1,), 1, lanes=2, group=2, serial=True)
+    assert torch.equal(one["y"], grp["y"]) and torch.equal(one["dx"], grp["dx"])
+    for a, b in zip(one["grads"][0], grp["grads"][0]):
+        np.testing.assert_array_equal(a, b)
+
+
 @pytest.mark.parametrize("dtype,h,w,B,m", [(BF16, 3, 5, 6, 3), (BF16, 40, 60, 2, 1),
                                            (FP32, 130, 90, 2, 2)])
 def test_loss_of_odd_sizes(dtype, h, w, B, m):
