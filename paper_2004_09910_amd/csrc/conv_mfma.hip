@@ -576,8 +576,8 @@ __global__ __launch_bounds__(1024) void splitk_reduce(const float* __restrict__ 
   }
 }
 
-// The same sum for E not a multiple of 4 (e.g. the bias of a one-channel
-// head): a block takes C = 2^lc columns (up to 64), 256 / C split lanes added
+// The same sum of any E (the bias of a one-channel head, a group's bias
+// sums): a block takes C = 2^lc columns (up to 64), 256 / C split lanes added
 // in a fixed tree (one thread a column took 10.7 us for 144 splits of one, this 4.0).
 struct SumGroup {
   const float* part[kMaxGroup];
@@ -1036,7 +1036,7 @@ hipError_t conv_wgrad_mfma(const void* x, const void* dz, float* dw, float* part
 }
 
 hipError_t splitk_reduce_n(int n, const float* const* part, float* const* out, long E, int S,
-                           hipStream_t st) {
+                           hipStream_t st, int lc_max) {
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
   SumGroup io;
   for (int k = 0; k < kMaxGroup; ++k) {   // unused entries repeat the first
@@ -1044,7 +1044,7 @@ hipError_t splitk_reduce_n(int n, const float* const* part, float* const* out, l
     io.out[k] = out[k < n ? k : 0];
   }
   int lc = 0;
-  while (lc < 6 && (1L << lc) < E) ++lc;
+  while (lc < lc_max && (1L << lc) < E) ++lc;
   ProfScope ps("splitk_reduce", 0.0, 4.0 * n * E * (S + 1), st);
   TGP_LAUNCH(ps, splitk_reduce_scalar, dim3(cdiv(E, 1L << lc), n), dim3(256), 0, st, io, E, S, lc);
   return launch_status();

@@ -98,9 +98,10 @@ extern int g_rowtile_mask;
 // (dw = sum over pixels, summed over its K ranges in a fixed order).
 hipError_t splitk_reduce_launch(const float* part, float* out, long E, int S, hipStream_t st,
                                const ReduceJob* extra = nullptr);
-// out[k][e] = sum_s part[k][s E + e], n sums of one shape in one launch.
+// out[k][e] = sum_s part[k][s E + e], n sums of one shape in one launch; a block
+// takes at most 2^lc_max columns (which fixes the order of a sum).
 hipError_t splitk_reduce_n(int n, const float* const* part, float* const* out, long E, int S,
-                           hipStream_t st);
+                           hipStream_t st, int lc_max = 6);
 bool wgrad_rows_ok(const ConvShape& s);
 size_t wgrad_rows_partial_floats(const ConvShape& s);
 hipError_t conv_wgrad_rows_launch(const void* x, const void* dz, float* dw, float* partial,

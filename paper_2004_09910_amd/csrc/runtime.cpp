@@ -502,8 +502,9 @@ tgp_status run_backward_g(tgp_net* N, int j, int cnt, const int* iv,
       pjs[k] = &pj;
       gbk[k] = d.bias ? (float*)G_(N, i, Lr.o_gb) : nullptr;
       pj[1] = tgpk::ReduceJob{gbk[k], gbk[k], d.bias ? (long)d.cout : 0, 0};   // S = 0: not yet run
-      // column partials: kept in the slot, or (too large to keep) reduced at once
-      bpartk[k] = Lr.defer_b ? (float*)G_(N, i, Lr.o_gcol) : B.colpart;
+      // column partials: kept in the slot, or reduced at once through the buffer
+      // this layer's data gradient is written to later
+      bpartk[k] = (float*)(Lr.defer_b ? G_(N, i, Lr.o_gcol) : B.gnext);
       bdeferk[k] = Lr.defer_b ? &pj[1] : nullptr;
       if (B.dz_ready) {
         // layer l + 1's data gradient stored this layer's dz and its bias
@@ -1307,16 +1308,32 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
     // slices stay in the slot, the gradient is written only when it is whole.
     Lr.o_gw = takeG(std::max<size_t>(Lr.defer_w ? pf : 0, Lr.w_elems) * 4);
     Lr.o_gpart = Lr.o_gw;
-    // Blocks of the bias sums of a layer whose channels are no power of two
-    // (240 read at about 4 TB/s): kept in the slot where, with its slices, they
-    // take no more room than the gradient and the slices of the general
-    // kernels, else reduced at once through the lane's temporaries (below).
+    // Blocks of the bias sums.  Where the channel packs divide a 256-thread block
+    // the sums stay in the slot.  Elsewhere they do only if that room, which with
+    // the layer's slices is what the gradient and the slices of the general
+    // kernels take, gives a block about as few rows as a free choice: a
+    // thread's row takes 1.1 us, and sums not in the slot a launch of 4 us
+    // more.  Sums that do not go there are reduced at once, through the buffer that
+    // the layer's data gradient writes afterwards.  (64 -> 192 at 224 x 224 x 8, one
+    // micro-batch, where the slot has room for 64 blocks: pass 716 us in the slot,
+    // 138 at once, 189 as separate ReLU and column sums; 16 -> 24 at 224 x 224 x 8, 16
+    // blocks: 238, 21, 71.)
     const long Ec = Lr.d.kind == TGP_DWCONV3X3 ? 9 : (long)Lr.d.cin * Lr.taps;   // weights per channel
     const long spare = Lr.defer_w && (pf || general > 1)
                            ? general + 1 - std::max(1L, (long)(pf / Lr.w_elems)) : 0;
-    Lr.rb_cap = spare > 0 ? (int)std::min(240L, Ec * spare) : 240;
-    Lr.o_gcol_floats =
-        Lr.d.bias ? tgpk::relu_bias_partial_floats(N->dt, P, Lr.d.cout, Lr.rb_cap) : 0;
+    const int packs = Lr.d.cout / vecN(N->dt);
+    bool in_slot = true;
+    Lr.rb_cap = 0;
+    if (packs > 0 && 256 % packs) {
+      const long nl = std::max(1, 256 / packs);   // rows of a block at a time
+      const long slot = spare > 0 ? std::min(240L, Ec * spare) : 0;
+      const long free = std::min(512L, (long)(al256(max_act) / 4 / Lr.d.cout));
+      auto rows = [&](long blocks) { return (P + blocks * nl - 1) / (blocks * nl); };
+      in_slot = slot > 0 && (free < 1 || rows(slot) <= rows(free) + 5);
+      Lr.rb_cap = (int)(in_slot ? slot : free);
+    }
+    const bool fuse = Lr.d.bias && (packs == 0 || 256 % packs == 0 || Lr.rb_cap > 0);
+    Lr.o_gcol_floats = fuse ? tgpk::relu_bias_partial_floats(N->dt, P, Lr.d.cout, Lr.rb_cap) : 0;
     {
       // this layer's ReLU backward folded into the data gradient of a
       // depthwise layer above it in the partition (bf16, no prologue there,
@@ -1328,7 +1345,9 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
                        U.d.kind == TGP_DWCONV3X3 && U.d.prologue == TGP_PRO_NONE &&
                        Lr.d.relu && Lr.d.bias && Lr.d.stash_id < 0 && Lr.o_gcol_floats &&
                        U.H == Lr.H && U.W == Lr.W && U.d.cin == Lr.d.cout &&
-                       tgpk::dw_dgrad_mask_ok(N->b, U.H, U.W, U.d.cout);
+                       tgpk::dw_dgrad_mask_ok(N->b, U.H, U.W, U.d.cout) && in_slot &&
+                       (size_t)tgpk::dw_dgrad_mask_rows(N->b, U.H, U.W, U.d.cout) * Lr.d.cout * 4 <=
+                           kDeferBytes;
         // where a block's last column may be past the image, only if its sums
         // fit the room of the separate pass
         if (U.mask_below && (long)U.W * (U.d.cout / 8) % 256)
@@ -1340,19 +1359,10 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
               (size_t)tgpk::dw_dgrad_mask_rows(N->b, U.H, U.W, U.d.cout) * Lr.d.cout);
       }
     }
-    const int packs = Lr.d.cout / vecN(N->dt);
-    Lr.defer_b = Lr.o_gcol_floats && Lr.o_gcol_floats * 4 <= kDeferBytes &&
-                 (spare > 0 || packs == 0 || 256 % packs == 0);
-    {
-      const size_t li = (size_t)(&Lr - &N->L[0]);
-      if (li + 1 < N->L.size() && N->L[li + 1].mask_below && !Lr.defer_b)
-        N->L[li + 1].mask_below = false;   // its sums need the slot
-    }
+    Lr.defer_b = Lr.o_gcol_floats && in_slot;
     // the bias gradient itself, where a call reduces it at once, or its sums
     Lr.o_gb = Lr.d.bias ? takeG(std::max<size_t>(Lr.defer_b ? Lr.o_gcol_floats : 0, Lr.d.cout) * 4) : 0;
     Lr.o_gcol = Lr.o_gb;
-    if (Lr.o_gcol_floats && !Lr.defer_b && (packs == 0 || 256 % packs == 0))
-      max_col = std::max(max_col, Lr.o_gcol_floats);
     if (Lr.d.bias) max_col = std::max(max_col, tgpk::colsum_partial_floats(P, Lr.d.cout));
   }
   N->o_g0 = takeL(max_act);
@@ -1368,18 +1378,11 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
                           tgpk::conv_forward_partial_floats(N->dt, d)});
   }
   N->fpart_floats = max_fpart;
-  // split-K partials of a convolution, and weight and bias partials reduced at
-  // once: each is read back by the launch after the one that wrote it, so one
+  // split-K partials of a convolution, weight partials reduced at once and column
+  // sums: each is read back by the launch after the one that wrote it, so one
   // buffer serves them in turn
   const size_t tmp_floats = std::max({max_fpart, max_part, max_col, (size_t)4});
   N->o_fpart = N->o_part = N->o_colpart = takeL(tmp_floats * 4);
-  for (auto& Lr : N->L) {   // blocks of the bias sums reduced at once, in that room
-    const int packs = Lr.d.cout / vecN(N->dt);
-    if (!Lr.o_gcol_floats || Lr.defer_b || packs == 0 || 256 % packs == 0) continue;
-    Lr.rb_cap = (int)std::min<size_t>(240, std::max<size_t>(1, tmp_floats / Lr.d.cout));
-    Lr.o_gcol_floats = tgpk::relu_bias_partial_floats(N->dt, (long)N->b * Lr.H * Lr.W, Lr.d.cout,
-                                                      Lr.rb_cap);
-  }
   const LayerRt& last = N->L.back();
   long out_mb = (long)N->b * last.H * last.W * last.d.cout;
   N->out_bytes_mb = out_mb * N->esz;

@@ -185,6 +185,36 @@ def test_bias_sums_any_channels(dtype, c, h, w):
     got["sess"].close()
 
 
+@pytest.mark.parametrize("dtype,cin,c,h,w,pool,at_once", [
+    (BF16, 8, 24, 128, 80, False, True),     # room for 8 blocks of 85 rows
+    (BF16, 8, 24, 128, 80, True, True),
+    (BF16, 8, 24, 100, 110, False, False),   # for 56
+    (BF16, 8, 24, 20, 30, False, False),     # few rows a block also with 8
+    (BF16, 8, 2000, 4, 6, False, True),      # one row a block at a time, no room
+    (FP32, 8, 12, 128, 80, True, True),
+])
+def test_bias_sums_in_the_slot_or_at_once(dtype, cin, c, h, w, pool, at_once):
+    """Bias sums of channels that are no power of two, kept for the accumulation or
+    summed in the same pass where the layer's room is too small: exact inputs,
+    one micro-batch a launch and a group with the same bits."""
+    layers = (Layer(CONV1X1, cin, c),)
+    if pool:
+        layers += (Layer(CONV1X1, c, 8, prologue=PRO_MAXPOOL2),)
+    net = Net("bias", layers, cin, h, w)
+    out = []
+    names = kernels_of(lambda: out.append(gpu_stage(net, dtype, 4, 2, 0, (len(layers),), 1,
+                                                    family=EXACT)))
+    one = out[0]
+    assert ("pool_relu_backward_bias" if pool else "relu_backward_bias") in names, names
+    assert ("splitk_reduce" in names) == at_once, names
+    ref = oracle_stage(net, dtype, 0, len(layers), one["xv"], one["G"], family=EXACT, certify=True)
+    check_stage(one, ref, dtype, f"bias sums {cin}->{c} {h}x{w}", EXACT)
+    grp = gpu_stage(net, dtype, 4, 2, 0, (len(layers),), 1, lanes=2, group=2, serial=True,
+                    family=EXACT)
+    for a, b in zip(one["grads"][0], grp["grads"][0]):
+        np.testing.assert_array_equal(a, b)
+
+
 @pytest.mark.parametrize("c,h,w", [(192, 14, 14), (64, 9, 7), (48, 11, 5)])
 def test_masked_depthwise_gradient_past_the_last_column(c, h, w):
     """Two cells whose depthwise data gradient stores the ReLU backward of the
