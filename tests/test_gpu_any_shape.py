@@ -280,6 +280,19 @@ def test_loss_of_odd_sizes(dtype, h, w, B, m):
     got["sess"].close()
 
 
+@pytest.mark.parametrize("c,h,w,B,m,lanes", [
+    (64, 46, 50, 2, 2, 1),        # 72 blocks, the last one ragged
+    (128, 97, 96, 2, 2, 2),       # past 512 blocks of 2048: some take a second round
+])
+def test_loss_of_wide_outputs(c, h, w, B, m, lanes):
+    """The loss and its gradient where a micro-batch has many elements, alone
+    and in one launch of two."""
+    net = one_layer(Layer(CONV1X1, 8, c, relu=False), h, w)
+    got = gpu_network(net, BF16, B, m, 1, 0, lanes=lanes)
+    check_network(got, oracle_network(net, BF16, B), BF16, f"loss c={c} {h}x{w} B={B} m={m}")
+    got["sess"].close()
+
+
 @pytest.mark.parametrize("cin,cout,h,w,B,m", [
     (8, 8, 1, 1, 1, 1),
     (24, 40, 17, 33, 4, 2),       # one partial stage
