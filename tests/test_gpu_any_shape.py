@@ -429,3 +429,41 @@ def test_conv1x1_register_weights(cin, h, w):
     grp = run_and_check(Layer(CONV1X1, cin, 256), h, w, BF16, 14, 14, f"conv1x1 {cin}->256 group",
                         lanes=14, group=14, serial=True)
     assert torch.equal(one["y"], grp["y"]) and torch.equal(one["dx"], grp["dx"])
+
+
+@pytest.mark.parametrize("cin,h,w", [(64, 128, 128), (128, 128, 128), (192, 96, 96), (256, 96, 96),
+                                     (64, 127, 129), (256, 97, 95)])
+def test_conv1x1_register_weights_long_runs(cin, h, w):
+    """Launches of so many tiles that each block's ring reaches its steady state,
+    where the wait for a stage counts the stores of the tiles between (whole
+    64-pixel tiles), and ragged ones, where it does not: the bits of the tiled
+    1x1 kernel, which sums in the same order, and torch's values."""
+    m = 16
+    sess = Session(one_layer(Layer(CONV1X1, cin, 256), h, w), BF16, init="device")
+    sess.plan(m, m, specs.CKPT_NEVER, lanes=m)
+    torch.manual_seed(cin)
+    x = torch.randn(m, h, w, cin, device="cuda").bfloat16()
+
+    def forward():
+        y = torch.zeros(m, h, w, 256, dtype=torch.bfloat16, device="cuda")
+        sess.plan(m, m, specs.CKPT_NEVER, lanes=m)
+        names = kernels_of(lambda: tgp.stage_forward_n(
+            sess.h, 1, 1, [False] * m, [x[i].data_ptr() for i in range(m)],
+            [y[i].data_ptr() for i in range(m)], torch.cuda.current_stream().cuda_stream))
+        return y, names
+
+    got, names = forward()
+    assert names == {"conv1x1_res"}, names
+    tgp.debug_set_fwd_variant(601)
+    try:
+        ref, names = forward()
+    finally:
+        tgp.debug_set_fwd_variant(0)
+    assert all(n.startswith("conv1x1_tile") for n in names), names
+    assert torch.equal(got, ref)
+    # rounded to bf16: 2^-9 of the value; float32 sums of up to 256 terms of at most
+    # about 70 in all: 256 2^-24 70 = 1e-3
+    w = sess.params[0]["w"].reshape(256, cin).float()
+    want = (x.reshape(-1, cin).float() @ w.t()).relu()
+    assert torch.allclose(got.reshape(-1, 256).float(), want, rtol=2.0 ** -8, atol=1e-3)
+    sess.close()
