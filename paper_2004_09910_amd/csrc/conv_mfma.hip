@@ -941,14 +941,24 @@ int wgrad_room_splits(int dt, const ConvShape& s) {
 // Over 700 random shapes (8 to 500 thousand products) the choice is 3.2%, 1.7% and
 // 3.9% from the faster of the two for one, two and four micro-batches a launch;
 // the per-tap kernel alone is 4%, 8% and 40% from it.
+//  - Below 256 pixels a plan has room for one K range, so an item's stages, one or
+//    more a sample, run as a chain: three and more samples of channels that the
+//    per-tap kernel does not take go to the pixel-tiled kernel, except where many
+//    items multiply long enough for the faster unit to win (rectangular / pixel
+//    tiles, us: 24 -> 16 at 6 x 4 x 10 27 / 9; 552 -> 520 at 6 x 3 x 13 40 / 61).  Over
+//    250 shapes 1.5 times faster in the mean, three up to 1.19 times slower.
+static bool wgrad_chain(const ConvShape& s) {
+  return (s.cin % 64 || s.cout % 64) && s.pixels() < 256 && s.nb >= 3 &&
+         s.pixels() * ((s.cin + 63) / 64) * ((s.cout + 63) / 64) <= 4096;
+}
 static bool use_wgrad_tile(const ConvShape& s) {
-  if (!wgrad_tile_ok(s)) return false;
+  if (!wgrad_tile_ok(s) || wgrad_chain(s)) return false;
   return s.cin % 64 || s.cout % 64 ||
          (s.pixels() * (s.cin / 64) * (s.cout / 64) >= 48 * 1024 && wgrad_tile_fill(s) >= 0.65);
 }
 // Shapes conv_wgrad_mfma takes.
 bool mfma_wgrad_ok(int dt, const ConvShape& s) {
-  return mfma_conv_ok(dt, s.cin, s.cout) || (dt == 0 && (wgrad_tile_ok(s) || wgrad1x1_tile_ok(s)));
+  return mfma_conv_ok(dt, s.cin, s.cout) || (dt == 0 && ((wgrad_tile_ok(s) && !wgrad_chain(s)) || wgrad1x1_tile_ok(s)));
 }
 
 size_t wgrad_mfma_partial_floats(const ConvShape& s) {

@@ -327,7 +327,9 @@ constexpr int kWtRows = kWtLW * kWtNW * 8;      // LDS rows of a slot
 // The stage geometry of a micro-batch and its K ranges.
 //  - Strips and rows: the fewest 16-pixel k steps per image, a stage's fixed
 //    cost counting as kStageSteps of them; fewer rows where the micro-batch
-//    has too few stages for kItems items.
+//    has too few stages for kItems items, but not more than two stages for each
+//    range it may have (below 256 pixels that is one, and its stages a chain: 24
+//    -> 16 channels at 6 x 4, ten samples, stages of one row 62 us).
 //  - K ranges: about kItems items per micro-batch (a launch over four then
 //    fills two rounds of blocks; one micro-batch alone runs on half the CUs),
 //    at most 8 MB of slices (their write and re-read otherwise cost more than
@@ -338,13 +340,17 @@ constexpr double kStageSteps = 4.0;
 constexpr int kItems = 128;
 WtCut wt_cut(const ConvShape& s) {
   const long per_k = (long)((s.cout + 63) / 64) * ((s.cin + 63) / 64);
+  const long E = (long)s.cout * 9 * s.cin;
+  const long kmax = std::min({(kItems + per_k - 1) / per_k, std::max(1L, (8L << 20) / (4 * E)),
+                              (long)wgrad_general_splits(s)});
   WtCut best{};
   double best_cost = 0;
   for (int ns = 1; ns <= s.W; ++ns) {
     const int TW = ns == 1 ? s.W : ((s.W + ns - 1) / ns + 7) / 8 * 8, n8 = (TW + 7) / 8;
     if (ns > 1 && TW < 16) break;
     const int nst = (s.W + TW - 1) / TW;
-    const int maxr = std::max(1, (int)(s.nb * (long)nst * s.H * per_k / kItems));
+    const long rows = s.nb * (long)nst * s.H;
+    const int maxr = (int)std::min((long)s.H, std::max({1L, rows * per_k / kItems, rows / (2 * kmax)}));
     int RPS = 0;
     while (RPS < s.H && RPS < maxr &&
            (((RPS + 1) * n8 + 1) / 2) * 16 + (RPS + 3) * (8 * n8 + 4) <= kWtRows)
@@ -358,10 +364,7 @@ WtCut wt_cut(const ConvShape& s) {
     best = WtCut{RPS, TW, n8, ((RPS * n8 + 1) / 2) * 16, nrb, nst, s.nb * nst * nrb, 1, 0,
                  ((1 << 20) + 8 * n8 - 1) / (8 * n8), ((1 << 20) + 8 * n8 + 3) / (8 * n8 + 4)};
   }
-  const long E = (long)s.cout * 9 * s.cin;
-  long nK = (kItems + per_k - 1) / per_k;
-  nK = std::min(nK, std::max(1L, (8L << 20) / (4 * E)));
-  nK = std::min({nK, (long)best.T, (long)wgrad_general_splits(s)});
+  const long nK = std::min(kmax, (long)best.T);
   best.spk = (int)((best.T + nK - 1) / nK);
   best.nK = (best.T + best.spk - 1) / best.spk;
   return best;

@@ -110,6 +110,22 @@ def kernels_of(call):
         tgp.profile_enable(False)
 
 
+@pytest.mark.parametrize("cin,cout,h,w,b,name", [
+    (24, 16, 6, 4, 10, "conv_gen_wgrad<1,4>"),    # a chain of ten samples
+    (72, 40, 5, 17, 3, "conv_gen_wgrad<2,2>"),    # 255 pixels
+    (72, 40, 8, 16, 2, "conv_wgrad_tile"),        # two samples
+    (72, 40, 8, 8, 4, "conv_wgrad_tile"),         # 256 pixels
+    (520, 472, 4, 4, 4, "conv_wgrad_tile"),       # 72 items
+    (8, 16, 15, 16, 1, "conv_wgrad_tile"),        # one range: two stages of rows
+])
+def test_wgrad_of_few_pixels(cin, cout, h, w, b, name):
+    """Layers of fewer than 256 pixels, whose weight gradient has one K range:
+    both sides of the line, against the oracle."""
+    what = f"conv3x3 {cin}->{cout} @{h}x{w}x{b}"
+    names = kernels_of(lambda: run_and_check(Layer(CONV3X3, cin, cout), h, w, BF16, b, 1, what))
+    assert [n for n in names if "wgrad" in n] == [name], names
+
+
 @pytest.mark.parametrize("cin,cout,h,w,b,tile", [
     (64, 192, 40, 61, 7, True),
     (64, 192, 40, 61, 6, False),      # few products
@@ -127,7 +143,7 @@ def test_wgrad_kernel_of_a_shape(cin, cout, h, w, b, tile):
     (64, 72, 40, 52, 2),         # of 16, the last of 4; a second channel item of 8
     (48, 48, 86, 86, 2),         # of 32, the last of 22
     (64, 64, 49, 49, 21),        # of 32, the last of 17
-    (40, 24, 5, 9, 3),           # two units a row, the second of one pixel
+    (40, 24, 5, 9, 2),           # two units a row, the second of one pixel
 ])
 def test_wgrad_tile_clears_the_padding_of_every_unit(cin, cout, h, w, b):
     """The rectangular-stage weight gradient: the last column's input pixels
