@@ -342,6 +342,7 @@ def test_conv1x1_tile_configurations(cfg):
     (3, 64, 33, 47, 6, 2),        # two blocks; rows no multiple of a tile
     (4, 24, 130, 70, 2, 1),       # three blocks, two tiles of terms; several ranges
     (7, 136, 31, 3, 15, 3),       # all 63 terms
+    (3, 16, 150, 110, 2, 1),      # two items a wave
 ])
 def test_conv3x3_few_input_channels(cin, cout, h, w, B, m):
     run_and_check(Layer(CONV3X3, cin, cout), h, w, BF16, B, m,
