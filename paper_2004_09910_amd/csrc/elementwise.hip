@@ -1506,8 +1506,12 @@ static long relu_bias_rows(long P, int C, int N, int cap) {
   const int CP = C / N, nl = 256 / CP;
   // 512 blocks: with 1024 a pass of one micro-batch is no faster (14.1 and 14.2
   // us at 56 x 56 x 256, four samples x 4), and the accumulation reads twice the
-  // block sums, its longest chain; with 256 the pass is slower (17 us for 14 in a U-Net of two micro-batches)
-  const long blocks = 256 % CP ? cap : 512;
+  // block sums, its longest chain; with 256 the pass is slower (17 us for 14 in a U-Net of two micro-batches).
+  // 1024 where a thread would have more than ten rows, or (up to two packs) whole
+  // rounds of rows leave too few blocks: with the accumulation, 64 channels of 205821
+  // pixels 20.5 -> 18.9 us, 16 of 75645, groups of two 81 -> 73.
+  const bool more = CP <= 2 || P > 512L * 10 * nl;
+  const long blocks = 256 % CP ? cap : more ? 1024 : 512;
   long r = (P + blocks - 1) / blocks;
   r = (r + nl - 1) / nl * nl;
   return r < nl ? nl : r;

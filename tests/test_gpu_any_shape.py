@@ -201,6 +201,20 @@ def test_bias_sums_any_channels(dtype, c, h, w):
     got["sess"].close()
 
 
+@pytest.mark.parametrize("dtype,kind,c,h,w", [
+    (BF16, CONV1X1, 16, 130, 151),      # two packs: rounds of 128 rows
+    (BF16, CONV1X1, 2048, 72, 73),      # one row at a time, past ten
+    (FP32, CONV1X1, 1024, 50, 51),      # not past ten
+])
+def test_bias_sums_of_many_rows(dtype, kind, c, h, w):
+    """The block counts of the ReLU backward with its bias sums; exact inputs."""
+    net = one_layer(Layer(kind, 8, c), h, w)
+    got = gpu_stage(net, dtype, 2, 2, 0, (1,), 1, family=EXACT)
+    ref = oracle_stage(net, dtype, 0, 1, got["xv"], got["G"], family=EXACT, certify=True)
+    check_stage(got, ref, dtype, f"bias sums c={c} {h}x{w}", EXACT)
+    got["sess"].close()
+
+
 @pytest.mark.parametrize("dtype,cin,c,h,w,pool,at_once", [
     (BF16, 8, 24, 128, 80, False, True),     # room for 8 blocks of 85 rows
     (BF16, 8, 24, 128, 80, True, True),
