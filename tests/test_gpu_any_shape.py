@@ -181,6 +181,7 @@ def test_wgrad_tile_clears_the_padding_of_every_unit(cin, cout, h, w, b):
     (2000, 3, 5, False, True),     # 250 packs: one column a block
     (2056, 3, 5, True, True),      # past 256 packs: the per-element kernels
     (40, 40, 30, False, False),
+    (192, 100, 56, True, True),    # past 128 blocks of eight rows
 ])
 def test_depthwise_any_channels(c, h, w, relu, bias):
     run_and_check(Layer(DWCONV3X3, c, c, relu=relu, bias=bias), h, w, BF16, 4, 2,
