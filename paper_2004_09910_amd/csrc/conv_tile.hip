@@ -63,10 +63,12 @@ struct TileIo {
 };
 // How an image is cut: R rows x TW columns a tile, BWP LDS rows per input
 // row, nrb row blocks and ns column strips; inv = ceil(2^20 / TW), invB =
-// ceil(2^20 / BWP) (exact quotients for a tile's pixels and a slot's rows).
+// ceil(2^20 / BWP) (exact quotients for a tile's pixels and a slot's rows).  TALL:
+// hp is H + 1 and invH = ceil(2^20 / hp) (exact for kTallRows rows and a tile more).
 struct TileCut {
-  int R, TW, BWP, nrb, ns, inv, invB;
+  int R, TW, BWP, nrb, ns, inv, invB, hp, invH;
 };
+constexpr int kTallRows = 1024;
 
 // WC x WP waves; a wave covers MT 32-channel tiles x FW pixel fragments.  LW
 // is the DMA instructions of a wave per stage (1 KiB each), which fixes the
@@ -74,7 +76,10 @@ struct TileCut {
 // With SPLIT an item is a tile's share of the sum, 1 / S of its stages, whose
 // float32 sums go to part; the items of one share of one channel tile are
 // neighbours, so that an XCD reads its weights once.
-template <int MT, int WC, int WP, int FW, int LW, int NS, bool DG, bool SPLIT>
+// With TALL a tile spans samples: a micro-batch is one image of nb (H + 1) - 1 rows,
+// the row after each sample a zero row that is the halo of both its neighbours and
+// whose outputs are left out.
+template <int MT, int WC, int WP, int FW, int LW, int NS, bool DG, bool SPLIT, bool TALL>
 __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
     TileIo io, int ng, const bf16_t* __restrict__ Wt, const float* __restrict__ bias, int nb,
     int H, int W, int Cin, int Cout, int relu, int S, TileCut cut) {
@@ -95,7 +100,8 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
   const int R = cut.R, TW = cut.TW, BWP = cut.BWP;
   const int nct = (Cout + BN - 1) / BN;
   const int per_n = cut.nrb * cut.ns * nct;                     // tiles per sample
-  const int items = ng * nb * per_n * (SPLIT ? S : 1);
+  const int nbv = TALL ? 1 : nb, Hv = TALL ? nb * cut.hp - 1 : H;   // images and rows cut into tiles
+  const int items = ng * nbv * per_n * (SPLIT ? S : 1);
   const int G = gridDim.x;
   const int lb = xcd_remap(blockIdx.x, G);
   const int n_items = lb < items ? (items - lb + G - 1) / G : 0;
@@ -178,7 +184,7 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
     const int item = lb + it * G;
     int smp, t, ct;
     if constexpr (SPLIT) {
-      const int px = cut.nrb * cut.ns, npx = ng * nb * px;
+      const int px = cut.nrb * cut.ns, npx = ng * nbv * px;
       const int sc = item / npx;
       sk = sc / nct;
       ct = sc - sk * nct;
@@ -193,8 +199,8 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
       t /= nct;
     }
     const int sx = t % cut.ns;
-    gi = smp / nb;
-    n = smp - gi * nb;
+    gi = smp / nbv;
+    n = smp - gi * nbv;
     h0 = (t / cut.ns) * R;
     w0 = sx * TW;
     co0 = ct * BN;
@@ -225,9 +231,10 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
         dma16(rw, dst, wok ? doff[u] + soff_a : CT_OOB, 0);
       } else {
         const int rr = drc[u] & 0xffff, col = i_w0 + (drc[u] >> 16) - 1;
-        const bool ok = drc[u] >= 0 && cok && (unsigned)(hb + rr) < (unsigned)H &&
-                        (unsigned)col < (unsigned)W;
-        dma16(rxg, dst, ok ? base_b + doff[u] : CT_OOB, 0);
+        const int hv = hb + rr, nz = TALL ? (hv * cut.invH) >> 20 : 0;   // zero rows above hv
+        const bool ok = drc[u] >= 0 && cok && (unsigned)hv < (unsigned)Hv &&
+                        (unsigned)col < (unsigned)W && (!TALL || hv - nz * cut.hp < H);
+        dma16(rxg, dst, ok ? base_b + doff[u] - nz * W * Cin * 2 : CT_OOB, 0);
       }
     }
   };
@@ -312,8 +319,9 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
       for (int j = 0; j < FW; ++j) {
         const int tp = (pg * FW + j) * 32 + (lane & 31);
         const int rho = (tp * cut.inv) >> 20, w = tp - rho * TW;
-        if (rho >= R || h0 + rho >= H || w0 + w >= W) continue;
-        float* const row = pt + ((long)(n * H + h0 + rho) * W + w0 + w) * Cout;
+        const int hv = h0 + rho, nz = TALL ? (hv * cut.invH) >> 20 : 0;
+        if (rho >= R || hv >= Hv || w0 + w >= W || (TALL && hv - nz * cut.hp >= H)) continue;
+        float* const row = pt + ((long)(n * H + hv - nz) * W + w0 + w) * Cout;
 #pragma unroll
         for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -368,8 +376,9 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
         const int tp = (pg * FW + j) * 32 + p;
         const int rho = (tp * cut.inv) >> 20, w = tp - rho * TW;   // tp / TW (tp < 1024)
         const int co = co0 + wc * MT * 32 + 8 * c;
-        if (rho < R && h0 + rho < H && w0 + w < W && co < Cout)
-          *(u32x4*)(Yg + ((long)(n * H + h0 + rho) * W + w0 + w) * Cout + co) = val;
+        const int hv = h0 + rho, nz = TALL ? (hv * cut.invH) >> 20 : 0;
+        if (rho < R && hv < Hv && w0 + w < W && co < Cout && (!TALL || hv - nz * cut.hp < H))
+          *(u32x4*)(Yg + ((long)(n * H + hv - nz) * W + w0 + w) * Cout + co) = val;
       }
     }
   }
@@ -441,7 +450,7 @@ bool tile_cut(int H, int W, int px, int rows, TileCut& c) {
       best = tiles;
       R = (H + nrb - 1) / nrb;                    // even row blocks
       c = TileCut{R, TW, BWP, nrb, (W + TW - 1) / TW, ((1 << 20) + TW - 1) / TW,
-                  ((1 << 20) + BWP - 1) / BWP};
+                  ((1 << 20) + BWP - 1) / BWP, 0, 0};
     }
     if (TW <= 8) break;
   }
@@ -452,8 +461,17 @@ bool tile_cut(int H, int W, int px, int rows, TileCut& c) {
 
 int g_tile_cfg = -1;   // >= 0 forces a configuration (tests and measurement)
 
-// Configurations that have a split-K form.
+// Configurations that have a split-K form, and that have tiles across samples (for
+// a sum split or not).
 constexpr bool tile_splits(int c) { return c == 0 || c == 2 || c == 3; }
+constexpr bool tile_tall(int c, int S) { return c == 3 || (c == 6 && S == 1); }
+
+// Images of at most 64 pixels may share a tile: one sample to a tile of 128 leaves
+// most of it idle (768 -> 640 at 3 x 3 x 12, four micro-batches, split sums, forward
+// 86 -> 31 us; 576 -> 1152 at 2 x 2 x 13, two, 59 -> 19).
+static bool tall_ok(const ConvShape& s) {
+  return s.nb > 1 && s.H * s.W <= 64 && s.nb * (s.H + 1L) <= kTallRows;
+}
 
 // Configuration for ng micro-batches of a shape: the least estimated time,
 // rounds of blocks times what a round costs.
@@ -466,15 +484,24 @@ static int tile_pick(const ConvShape& s, int ng, int S, TileCut& cut) {
     if (g_tile_cfg >= 0 && g_tile_cfg != c) continue;
     if (S > 1 && !tile_splits(c)) continue;
     const int NW = k.WC * k.WP, BN = 32 * k.MT * k.WC;
-    TileCut t;
-    if (!tile_cut(s.H, s.W, 32 * k.WP * k.FW, k.LW * NW * 32 - 9 * BN, t)) continue;
-    const long items = (long)ng * s.nb * t.nrb * t.ns * ((s.cout + BN - 1) / BN) * S;
-    const long rounds = (items + 255) / 256;
-    const double cost = rounds * (k.a + nk * k.b) / (rounds > 1 && tile_occ(k) > 1 ? 1.4 : 1.0);
-    if (best < 0 || cost < best_cost) {
-      best = c;
-      best_cost = cost;
-      cut = t;
+    for (int tall = 0; tall < 2; ++tall) {
+      if (tall && !(tall_ok(s) && tile_tall(c, S))) continue;
+      TileCut t;
+      const int Hv = tall ? s.nb * (s.H + 1) - 1 : s.H;
+      if (!tile_cut(Hv, s.W, 32 * k.WP * k.FW, k.LW * NW * 32 - 9 * BN, t)) continue;
+      if (tall) {
+        t.hp = s.H + 1;
+        t.invH = ((1 << 20) + t.hp - 1) / t.hp;
+      }
+      const long items =
+          (long)ng * (tall ? 1 : s.nb) * t.nrb * t.ns * ((s.cout + BN - 1) / BN) * S;
+      const long rounds = (items + 255) / 256;
+      const double cost = rounds * (k.a + nk * k.b) / (rounds > 1 && tile_occ(k) > 1 ? 1.4 : 1.0);
+      if (best < 0 || cost < best_cost) {
+        best = c;
+        best_cost = cost;
+        cut = t;
+      }
     }
   }
   return best;
@@ -508,22 +535,22 @@ bool conv_tile_ok(const ConvShape& s) {
          (double)s.cout * 9 * s.cin * 2 < 2147483648.0;
 }
 
-template <int MT, int WC, int WP, int FW, int LW, int NS, bool DG, bool SPLIT>
+template <int MT, int WC, int WP, int FW, int LW, int NS, bool DG, bool SPLIT, bool TALL = false>
 static hipError_t launch_tile(const TileIo& io, int ng, const bf16_t* Wt, const float* b,
                               const ConvShape& s, int relu, int S, const TileCut& cut,
                               hipStream_t st) {
   static char name[64];
   if (!name[0])
-    snprintf(name, sizeof name, "conv3x3_tile<%d,%d,%d,%d,%d,%d%s%s>", MT, WC, WP, FW, LW, NS,
-             DG ? ",dg" : "", SPLIT ? ",split" : "");
+    snprintf(name, sizeof name, "conv3x3_tile<%d,%d,%d,%d,%d,%d%s%s%s>", MT, WC, WP, FW, LW, NS,
+             TALL ? ",tall" : "", DG ? ",dg" : "", SPLIT ? ",split" : "");
   constexpr int BN = 32 * MT * WC, NW = WC * WP;
-  const long items = (long)ng * s.nb * cut.nrb * cut.ns * ((s.cout + BN - 1) / BN) * S;
+  const long items = (long)ng * (TALL ? 1 : s.nb) * cut.nrb * cut.ns * ((s.cout + BN - 1) / BN) * S;
   constexpr int occ = tile_occ(TileCfg{MT, WC, WP, FW, LW, NS, 0, 0});
   const int G = (int)(items < 256 * occ ? items : 256 * occ);
   const long P = (long)ng * s.pixels();
   ProfScope ps(name, 2.0 * P * s.cout * 9 * s.cin,
                2.0 * ((double)P * s.cin + 9.0 * s.cin * s.cout + (double)P * s.cout), st);
-  TGP_LAUNCH(ps, (conv3x3_tile<MT, WC, WP, FW, LW, NS, DG, SPLIT>), dim3(G), dim3(NW * 64), 0, st,
+  TGP_LAUNCH(ps, (conv3x3_tile<MT, WC, WP, FW, LW, NS, DG, SPLIT, TALL>), dim3(G), dim3(NW * 64), 0, st,
              io, ng, Wt, b, s.nb, s.H, s.W, s.cin, s.cout, relu, S, cut);
   return launch_status();
 }
@@ -560,9 +587,14 @@ hipError_t conv_forward_tile(int n, const void* const* x, const void* w, const f
 #define CT_GO(i, D, SP)                                                                     \
   launch_tile<kTileCfgs[i].MT, kTileCfgs[i].WC, kTileCfgs[i].WP, kTileCfgs[i].FW,           \
               kTileCfgs[i].LW, kTileCfgs[i].NS, D, SP>(io, n, Wt, b, s, relu, S, cut, st)
+#define CT_TALL(i, D, SP)                                                                   \
+  launch_tile<kTileCfgs[i].MT, kTileCfgs[i].WC, kTileCfgs[i].WP, kTileCfgs[i].FW,           \
+              kTileCfgs[i].LW, kTileCfgs[i].NS, D, SP, true>(io, n, Wt, b, s, relu, S, cut, st)
   if (S > 1) {
     hipError_t e = hipErrorInvalidValue;
-    switch (c) {
+    if (cut.hp) {
+      if (c == 3) e = dg ? CT_TALL(3, true, true) : CT_TALL(3, false, true);
+    } else switch (c) {
 #define CT_CASE(i) \
   case i: e = dg ? CT_GO(i, true, true) : CT_GO(i, false, true); break;
       CT_CASE(0) CT_CASE(2) CT_CASE(3)
@@ -575,12 +607,18 @@ hipError_t conv_forward_tile(int n, const void* const* x, const void* w, const f
                io, b, numel, s.cout, S, relu);
     return launch_status();
   }
+  if (cut.hp) {
+    if (c == 3) return dg ? CT_TALL(3, true, false) : CT_TALL(3, false, false);
+    if (c == 6) return dg ? CT_TALL(6, true, false) : CT_TALL(6, false, false);
+    return hipErrorInvalidValue;
+  }
   switch (c) {
 #define CT_CASE(i) \
   case i: return dg ? CT_GO(i, true, false) : CT_GO(i, false, false);
     CT_CASE(0) CT_CASE(1) CT_CASE(2) CT_CASE(3) CT_CASE(4) CT_CASE(5) CT_CASE(6)
 #undef CT_CASE
 #undef CT_GO
+#undef CT_TALL
     default: return hipErrorInvalidValue;
   }
 }

@@ -499,3 +499,27 @@ def test_conv1x1_register_weights_long_runs(cin, h, w):
     want = (x.reshape(-1, cin).float() @ w.t()).relu()
     assert torch.allclose(got.reshape(-1, 256).float(), want, rtol=2.0 ** -8, atol=1e-3)
     sess.close()
+
+
+@pytest.mark.parametrize("cin,cout,h,w,b,other", [
+    (16, 520, 2, 2, 64, 1),       # 9 samples a tile, ragged channels
+    (40, 328, 5, 7, 37, 1),       # the last row block ends in a sample
+    (520, 24, 1, 8, 40, 1),       # one row a sample; its data gradient in few chunks
+    (512, 512, 4, 3, 41, 2),      # split sums
+    (24, 640, 8, 8, 30, 1),
+])
+def test_conv3x3_tiles_across_samples(cin, cout, h, w, b, other):
+    """Images of at most 64 pixels: a tile covers several samples with a zero row
+    between.  Against the oracle, and bit for bit the one-sample tiles (forced)."""
+    layer, net = Layer(CONV3X3, cin, cout), one_layer(Layer(CONV3X3, cin, cout), h, w)
+    out = []
+    names = kernels_of(lambda: out.append(run_and_check(layer, h, w, BF16, b, 1,
+                                                        f"conv3x3 {cin}->{cout} @{h}x{w}x{b}")))
+    assert any(",tall" in n for n in names), names
+    tgp.debug_set_fwd_variant(501 + other)
+    try:
+        names = kernels_of(lambda: out.append(gpu_stage(net, BF16, b, 1, 0, (1,), 1)))
+    finally:
+        tgp.debug_set_fwd_variant(0)
+    assert not any(",tall" in n for n in names), names
+    assert torch.equal(out[0]["y"], out[1]["y"]) and torch.equal(out[0]["dx"], out[1]["dx"])
