@@ -113,6 +113,7 @@ struct tgp_net {
   size_t stash_stride = 0;                      // bytes per micro-batch of stash area
   size_t o_g0 = 0, o_g1 = 0, o_dinp = 0, o_dz = 0, o_part = 0, o_colpart = 0,
          o_loss = 0, o_fpart = 0, fpart_floats = 0;
+  bool loss_in_g0 = false;   // the loss's partial sums are in the first lane's g0
   std::vector<size_t> o_bnd, o_gbnd;  // per (i, j) pipeline boundaries, [i*n + j]
   size_t o_out = 0, o_dy = 0, out_bytes_mb = 0;
   // Transient buffers (activations of checkpointed passes, per-micro-batch
@@ -976,6 +977,7 @@ struct GpuExec : Exec {
     const LayerRt& out = N->L.back();
     const long n_mb = (long)N->b * out.H * out.W * out.d.cout;
     const long numel = n_mb * N->m;
+    float* const parts = (float*)(N->loss_in_g0 ? T_(N, 1, N->o_g0) : W_(N, N->o_loss));
     Range rg("LOSS", first(g), 0);
     const void* ys[MG];
     const void* ts[MG];
@@ -988,9 +990,13 @@ struct GpuExec : Exec {
     }
     HIPCHK(tgpk::mse_forward_backward_n(
                N->dt, cnt, ys, ts, dys,
-               (float*)W_(N, N->o_loss) + (long)(first(g) - 1) * tgpk::mse_blocks(n_mb), n_mb,
-               1.0f / (float)numel, st),
+               parts + (long)(first(g) - 1) * tgpk::mse_blocks(n_mb), n_mb, 1.0f / (float)numel, st),
            "mse_forward_backward");
+    // every loss comes before the first backward
+    if (last(g) == N->m)
+      HIPCHK(tgpk::loss_finalize(parts, N->m * tgpk::mse_blocks(n_mb), 1.0f / (float)numel, loss_dev,
+                                 st),
+             "loss_finalize");
     return TGP_OK;
   }
   tgp_status backward(int g, int j, bool) override {
@@ -1386,7 +1392,10 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
   const LayerRt& last = N->L.back();
   long out_mb = (long)N->b * last.H * last.W * last.d.cout;
   N->out_bytes_mb = out_mb * N->esz;
-  N->o_loss = take((size_t)m * tgpk::mse_blocks(out_mb) * 4);   // partial sums of the loss
+  // partial sums of the loss: added up before the first backward writes g0
+  const size_t loss_bytes = (size_t)m * tgpk::mse_blocks(out_mb) * 4;
+  N->loss_in_g0 = loss_bytes <= al256(max_act);
+  N->o_loss = N->loss_in_g0 ? 0 : take(loss_bytes);
   // pipeline boundaries
   N->o_bnd.assign((size_t)m * n + n, 0);
   N->o_gbnd.assign((size_t)m * n + n, 0);
@@ -1804,15 +1813,7 @@ tgp_status tgp_pipeline_step(tgp_net* N, const void* x, const void* target, int 
     if (he != hipSuccess && r == TGP_OK)
       r = fail(TGP_EHIP, "accumulation join: %s", hipGetErrorString(he));
   }
-  if (r != TGP_OK) return r;
-  const LayerRt& last = N->L.back();
-  long numel = (long)N->B * last.H * last.W * last.d.cout;
-  HIPCHK(tgpk::loss_finalize((const float*)W_(N, N->o_loss),
-                             m * tgpk::mse_blocks((long)N->b * last.H * last.W * last.d.cout),
-                             1.0f / (float)numel, loss_dev,
-                             S(stream)),
-         "loss_finalize");
-  return TGP_OK;
+  return r;
 }
 
 // ------------------------------------------------------------ static scratch
