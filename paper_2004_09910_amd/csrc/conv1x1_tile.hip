@@ -30,22 +30,7 @@
 namespace tgpk {
 namespace {
 
-constexpr int C1_OOB = (int)0x80000000;
 
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-// Transpose read: within each group of 16 lanes, lane i receives element
-// i % 4 of the 8-byte blocks addressed by lanes 4 e + i / 4, e = 0..3.
-__device__ __forceinline__ uint2 tr16p(const unsigned char* p) {
-  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)TGP_LDS(p)));
-}
-// A fragment's 8 sum rows of `pitch` bytes from p on.
-__device__ __forceinline__ bf16x8_t frag_tr(const unsigned char* p, int pitch) {
-  const uint2 lo = tr16p(p), hi = tr16p(p + 4 * pitch);
-  return as_bf16x8(u32x4{lo.x, lo.y, hi.x, hi.y});
-}
-
-__device__ __forceinline__ int swz8(int row, int q) { return q ^ ((row ^ (row >> 3)) & 7); }
 
 struct Io1x1 {
   const bf16_t* x[kMaxGroup];
@@ -96,7 +81,7 @@ __global__ __launch_bounds__(WC * WP * 64) void conv1x1_tile(Io1x1 io, int ng,
       ak[u] = kk;
       ac[u] = 8 * c;
     } else {
-      const int row = k * 8 + r8, c = swz8(row, lane & 7);
+      const int row = k * 8 + r8, c = swz(row, lane & 7);
       aoff[u] = (row * Cin + 8 * c) * 2;
       ak[u] = 8 * c;
       ac[u] = row;
@@ -105,7 +90,7 @@ __global__ __launch_bounds__(WC * WP * 64) void conv1x1_tile(Io1x1 io, int ng,
 #pragma unroll
   for (int u = 0; u < LW - ACH / NW; ++u) {
     prow[u] = (NW * u + wave) * 8 + r8;
-    pc[u] = 8 * swz8(prow[u], lane & 7);
+    pc[u] = 8 * swz(prow[u], lane & 7);
   }
 
   auto coords = [&](int it, int& gi, int& p0, int& co0) __attribute__((always_inline)) {
@@ -124,14 +109,14 @@ __global__ __launch_bounds__(WC * WP * 64) void conv1x1_tile(Io1x1 io, int ng,
 #pragma unroll
     for (int u = 0; u < ACH / NW; ++u) {
       const bool ok = c0 + ak[u] < Cin && i_co0 + ac[u] < Cout;
-      dma16(rw, TGP_LDS(ring + slot * SB + (NW * u + wave) * 1024), ok ? aoff[u] + wo : C1_OOB, 0);
+      dma16(rw, TGP_LDS(ring + slot * SB + (NW * u + wave) * 1024), ok ? aoff[u] + wo : kOob, 0);
     }
 #pragma unroll
     for (int u = 0; u < LW - ACH / NW; ++u) {
       const int p = i_p0 + prow[u];
       const bool ok = p < P && c0 + pc[u] < Cin;
       dma16(rx, TGP_LDS(ring + slot * SB + (ACH + NW * u + wave) * 1024),
-            ok ? (p * Cin + c0 + pc[u]) * 2 : C1_OOB, 0);
+            ok ? (p * Cin + c0 + pc[u]) * 2 : kOob, 0);
     }
     if (++i_ks == nk) {
       i_ks = 0;
@@ -179,16 +164,16 @@ __global__ __launch_bounds__(WC * WP * 64) void conv1x1_tile(Io1x1 io, int ng,
         for (int i = 0; i < MT; ++i) {
           if constexpr (DG) {
             const int cb = ((wc * MT + i) * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
-            a[buf][i] = frag_tr(As + (16 * kk + kb) * RAB + (((cb >> 4) ^ wswz(kb)) << 4) + (cb & 15), RAB);
+            a[buf][i] = as_bf16x8(frag_tr(As + (16 * kk + kb) * RAB + (((cb >> 4) ^ wswz(kb)) << 4) + (cb & 15), RAB));
           } else {
             const int row = (wc * MT + i) * 32 + (lane & 31);
-            a[buf][i] = as_bf16x8(*(const u32x4*)(As + row * 128 + swz8(row, qq) * 16));
+            a[buf][i] = as_bf16x8(*(const u32x4*)(As + row * 128 + swz(row, qq) * 16));
           }
         }
 #pragma unroll
         for (int j = 0; j < FW; ++j) {
           const int row = (wp * FW + j) * 32 + (lane & 31);
-          b[buf][j] = as_bf16x8(*(const u32x4*)(Bs + row * 128 + swz8(row, qq) * 16));
+          b[buf][j] = as_bf16x8(*(const u32x4*)(Bs + row * 128 + swz(row, qq) * 16));
         }
       };
       // the fragments of K sub-step kk + 1 are read while the MFMAs of kk run;
@@ -311,10 +296,10 @@ __global__ __launch_bounds__(256) void wgrad1x1_tile(Wg1x1 io, int ng, int P, in
       auto* dst = TGP_LDS(ring + slot * SB + c * 1024);
       if (pl < MC) {
         const int ch = i_co0 + 64 * pl + 8 * lc;
-        dma16(rz, dst, p < P && ch < Cout ? (p * Cout + ch) * 2 : C1_OOB, 0);
+        dma16(rz, dst, p < P && ch < Cout ? (p * Cout + ch) * 2 : kOob, 0);
       } else {
         const int ch = i_ci0 + 64 * (pl - MC) + 8 * lc;
-        dma16(rx, dst, p < P && ch < Cin ? (p * Cin + ch) * 2 : C1_OOB, 0);
+        dma16(rx, dst, p < P && ch < Cin ? (p * Cin + ch) * 2 : kOob, 0);
       }
     }
     if (++i_st == i_n) {
@@ -359,9 +344,9 @@ __global__ __launch_bounds__(256) void wgrad1x1_tile(Wg1x1 io, int ng, int P, in
       for (int kk = 0; kk < 4; ++kk) {
         bf16x8_t a[MC], b[NC];
 #pragma unroll
-        for (int i = 0; i < MC; ++i) a[i] = frag_tr(sp + fa[i] + kk * 16 * 128, 128);
+        for (int i = 0; i < MC; ++i) a[i] = as_bf16x8(frag_tr(sp + fa[i] + kk * 16 * 128, 128));
 #pragma unroll
-        for (int j = 0; j < NC; ++j) b[j] = frag_tr(sp + fb[j] + kk * 16 * 128, 128);
+        for (int j = 0; j < NC; ++j) b[j] = as_bf16x8(frag_tr(sp + fb[j] + kk * 16 * 128, 128));
 #pragma unroll
         for (int i = 0; i < MC; ++i)
 #pragma unroll

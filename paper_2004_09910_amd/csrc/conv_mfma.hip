@@ -23,11 +23,6 @@
 namespace tgpk {
 namespace {
 
-// XOR swizzle of the eight 16-byte chunks of a 128-byte LDS row, so that
-// eight consecutive rows read at the same logical chunk, and rows eight apart
-// written at the same chunk, hit distinct banks.
-__device__ __forceinline__ int swz(int row, int q) { return q ^ ((row ^ (row >> 3)) & 7); }
-
 // ---------------------------------------------------------------- forward (LDS DMA)
 
 // Sixteen zero bytes in device memory: the source of every im2col chunk that
@@ -689,10 +684,7 @@ hipError_t launch_fwd_dma(const char* name9, const char* name1, const bf16_t* X,
                                       "conv_fwd_dma<" #WCO "," #WP "," #TM "," #TN ",1," #NS ">", \
                                       X, Wt, b, Y, P, s, relu, st, X2, Y2)
 
-// Row-stage forward launches.  S > 1 splits the stages over S blocks per
-// tile; the partials live in `part` (capacity part_cap floats; S is reduced
-// to fit, which only happens under measurement overrides).
-int g_fwd_split = 0;   // > 0 forces the split count (measurement only)
+int g_fwd_split = 0;   // > 0 forces the shares of a sum (measurement only)
 // Measurement only: bit 2 allows the row-blocked weight gradient, bit 3 the
 // nine-tap row kernel.
 int g_rowtile_mask = 15;
@@ -762,7 +754,7 @@ FwdPlan fwd_plan(const ConvShape& s) {
       (g_rowtile_mask >> 3 & 1) && conv_rows32_ok(s)) {
     pl.cfg = 400;  // whole-row tiles, nine taps per stage, 32x32x16
   } else if (conv1x1_res_ok(s)) {
-    pl.cfg = 150;  // 1x1, all weights resident in LDS
+    pl.cfg = 150;  // 1x1, weights in registers
   } else if (conv_tile_ok(s)) {
     pl.cfg = 500;  // rectangular tiles
   } else if (conv1x1_tile_ok(s)) {
@@ -1019,30 +1011,25 @@ static hipError_t launch_wgrad_mfma(int n, const void* const* x, const void* con
 }
 
 hipError_t conv_wgrad_mfma(const void* x, const void* dz, float* dw, float* partial,
-                           const ConvShape& s, hipStream_t st, const ReduceJob* extra,
-                           ReduceJob* defer) {
-  if (use_wgrad_rows(s)) return conv_wgrad_rows_launch(x, dz, dw, partial, s, st, extra, defer);
+                           const ConvShape& s, hipStream_t st, ReduceJob* defer) {
+  if (use_wgrad_rows(s)) return conv_wgrad_rows_launch(x, dz, dw, partial, s, st, defer);
   long E = (long)s.cout * s.taps * s.cin;
   if (use_wgrad_tile(s) || wgrad1x1_tile_ok(s)) {
     ReduceJob job;
     ReduceJob* const jp = defer ? defer : &job;
     const hipError_t e = s.taps == 1 ? wgrad1x1_tile_launch(1, &x, &dz, &dw, &partial, s, st, &jp)
                                      : conv_wgrad_tile_launch(1, &x, &dz, &dw, &partial, s, st, &jp);
-    if (e != hipSuccess) return e;
-    if (defer) return extra ? hipErrorInvalidValue : hipSuccess;
-    if (job.S > 1) return splitk_reduce_launch(job.part, dw, E, job.S, st, extra);
-    return extra ? splitk_reduce_launch(extra->part, extra->out, extra->E, extra->S, st) : hipSuccess;
+    if (e != hipSuccess || defer) return e;
+    return job.S > 1 ? splitk_reduce_launch(job.part, dw, E, job.S, st) : hipSuccess;
   }
   WgradPlan pl;
   hipError_t e = launch_wgrad_mfma(1, &x, &dz, &dw, &partial, s, pl, st);
   if (e != hipSuccess) return e;
   if (defer) {
     *defer = ReduceJob{partial, dw, E, pl.S};   // partial == dw when S == 1
-    return extra ? hipErrorInvalidValue : hipSuccess;
+    return hipSuccess;
   }
-  if (pl.S == 1)
-    return extra ? splitk_reduce_launch(extra->part, extra->out, extra->E, extra->S, st) : hipSuccess;
-  return splitk_reduce_launch(partial, dw, E, pl.S, st, extra);
+  return pl.S > 1 ? splitk_reduce_launch(partial, dw, E, pl.S, st) : hipSuccess;
 }
 
 hipError_t splitk_reduce_n(int n, const float* const* part, float* const* out, long E, int S,

@@ -35,7 +35,6 @@
 namespace tgpk {
 namespace {
 
-constexpr int R32_OOB = (int)0x80000000;   // byte offset that reads as out of range
 constexpr int R32_AROWS = 9 * 64;          // weight rows per stage
 
 typedef __bf16 bf16x2_r32 __attribute__((ext_vector_type(2)));
@@ -199,7 +198,7 @@ __global__ __launch_bounds__(CH == 2 ? 256 : 512) void conv3x3_rows32(
         dma16(rw, dst, doff[u], soff_a);
       } else {
         const bool ok = drow[u] >= 0 && (interior || (unsigned)(hb + drow[u]) < (unsigned)H);
-        dma16(rxg, dst, ok ? base_b + doff[u] : R32_OOB, 0);
+        dma16(rxg, dst, ok ? base_b + doff[u] : kOob, 0);
       }
     }
   };

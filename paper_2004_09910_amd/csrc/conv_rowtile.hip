@@ -35,7 +35,6 @@ namespace {
 constexpr int RT_PITCH = 80;                    // bytes per LDS row (32 channels + pad)
 constexpr int RT_AREG = 16384;                  // weight region: 192 rows, rounded to 16 KiB
 constexpr int RT_MAXC = 1024;                   // output channels whose bias fits in LDS
-constexpr int RT_OOB = (int)0x80000000;         // byte offset that reads as out of range
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
@@ -87,7 +86,7 @@ __global__ __launch_bounds__(256) void conv3x3_rowtile(
     if (u < LA) {
       const int a = off / RT_PITCH, piece = (off % RT_PITCH) / 16;
       const int t3 = a / 64, co = a % 64;
-      aoff[u < LA ? u : 0] = a < 192 && piece < 4 ? ((co * 9 + t3) * Cin + piece * 8) * 2 : RT_OOB;
+      aoff[u < LA ? u : 0] = a < 192 && piece < 4 ? ((co * 9 + t3) * Cin + piece * 8) * 2 : kOob;
     } else {
       const int ob = off - RT_AREG;
       const int q = ob / RT_PITCH, piece = (ob % RT_PITCH) / 16;
@@ -138,7 +137,7 @@ __global__ __launch_bounds__(256) void conv3x3_rowtile(
       } else {
         const int k = u < LA ? 0 : u - LA;
         const bool ok = brow[k] >= 0 && (interior || (unsigned)(hb + brow[k]) < (unsigned)H);
-        dma16(rx, dst, ok ? base_b + boff[k] : RT_OOB, 0);
+        dma16(rx, dst, ok ? base_b + boff[k] : kOob, 0);
       }
     }
     if (++i_ks == nk) {

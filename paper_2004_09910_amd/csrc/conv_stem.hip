@@ -18,8 +18,6 @@
 namespace tgpk {
 namespace {
 
-constexpr int ST_OOB = (int)0x80000000;
-
 struct StemIo {
   const bf16_t* x[kMaxGroup];
   bf16_t* y[kMaxGroup];
@@ -27,12 +25,6 @@ struct StemIo {
   float* out[kMaxGroup];
 };
 
-typedef short st_s16x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) st_s16x4 st_lds_s16x4;
-__device__ __forceinline__ uint2 st_tr16(const unsigned char* p) {
-  return __builtin_bit_cast(
-      uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((st_lds_s16x4*)TGP_LDS(p)));
-}
 
 // Input tensors may start at any even address: a descriptor's base is the
 // 4-byte word the tensor starts in, `lead` (0 or 2) the bytes before it.
@@ -46,7 +38,7 @@ __device__ __forceinline__ StemX stem_x(const bf16_t* x, int bytes) {
   return {__builtin_amdgcn_make_buffer_rsrc((void*)(a - lead), 0, bytes + lead, 0x00020000), lead};
 }
 __device__ __forceinline__ unsigned ld_u16(const StemX& x, int voff, bool ok) {
-  return (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(x.r, ok ? voff + x.lead : ST_OOB, 0, 0);
+  return (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(x.r, ok ? voff + x.lead : kOob, 0, 0);
 }
 __device__ __forceinline__ bf16x8_t pack8(const unsigned (&v)[8]) {
   return as_bf16x8(u32x4{v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16});
@@ -113,7 +105,7 @@ __global__ __launch_bounds__(256) void stem_fwd(StemIo io, int ng, const bf16_t*
     for (int v = 0; v < 16; ++v) {
       const int co = co0 + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
       bv[i][v] = __builtin_bit_cast(
-          float, __builtin_amdgcn_raw_buffer_load_b32(rb, co < Cout ? co * 4 : ST_OOB, 0, 0));
+          float, __builtin_amdgcn_raw_buffer_load_b32(rb, co < Cout ? co * 4 : kOob, 0, 0));
     }
   __syncthreads();                                              // ws is read
   const int npt = (P + 31) / 32, items = ng * npt;
@@ -201,7 +193,7 @@ __global__ __launch_bounds__(64 * NW) void stem_wgrad(StemIo io, int ng, int P, 
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const int p = p0 + 8 * u + rl;
-      dma16(rz, TGP_LDS(sp + u * 1024), p < P && ch < Cout ? (p * Cout + ch) * 2 : ST_OOB, 0);
+      dma16(rz, TGP_LDS(sp + u * 1024), p < P && ch < Cout ? (p * Cout + ch) * 2 : kOob, 0);
     }
     masks[wave][lane] = (unsigned short)tap_mask(p0 + lane, P, H, W);
     unsigned v[4][NT][8];
@@ -225,9 +217,7 @@ __global__ __launch_bounds__(64 * NW) void stem_wgrad(StemIo io, int ng, int P, 
       bf16x8_t a[2];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        const unsigned char* q = sp + fa[i] + kk * 16 * 128;
-        const uint2 lo = st_tr16(q), hi = st_tr16(q + 4 * 128);
-        a[i] = as_bf16x8(u32x4{lo.x, lo.y, hi.x, hi.y});
+        a[i] = as_bf16x8(frag_tr(sp + fa[i] + kk * 16 * 128, 128));
       }
 #pragma unroll
       for (int t = 0; t < NT; ++t) {

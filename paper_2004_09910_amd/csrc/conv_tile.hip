@@ -37,15 +37,6 @@
 namespace tgpk {
 namespace {
 
-constexpr int CT_OOB = (int)0x80000000;   // byte offset that reads as out of range
-
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-// Transpose read: within each group of 16 lanes, lane i receives element
-// i % 4 of the 8-byte blocks addressed by lanes 4 e + i / 4, e = 0..3.
-__device__ __forceinline__ uint2 tr16c(const unsigned char* p) {
-  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)TGP_LDS(p)));
-}
 
 typedef __bf16 bf16x2_ct __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ unsigned pack2_ct(float a, float b) {
@@ -220,7 +211,7 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
     // held in registers they spill the widest configuration
     if (!SPLIT && u0 == 0 && i_ks == 0 && wave == 0)
       dma16(rbias, TGP_LDS(bslots + (i_it % (NS + 1)) * 1024),
-            lane < BN / 4 ? (i_co0 + 4 * lane) * 4 : CT_OOB, 0);
+            lane < BN / 4 ? (i_co0 + 4 * lane) * 4 : kOob, 0);
 #pragma unroll
     for (int u = 0; u < LW; ++u) {
       if (u < u0 || u >= u1) continue;
@@ -228,13 +219,13 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
       auto* dst = TGP_LDS(ring + slot * SB + k * 1024);
       if (k < ACH) {                                            // wave-uniform
         const bool wok = DG ? c0 + (drc[u] & 0xffff) < Cin && i_co0 + 8 * (drc[u] >> 16) < Cout : cok;
-        dma16(rw, dst, wok ? doff[u] + soff_a : CT_OOB, 0);
+        dma16(rw, dst, wok ? doff[u] + soff_a : kOob, 0);
       } else {
         const int rr = drc[u] & 0xffff, col = i_w0 + (drc[u] >> 16) - 1;
         const int hv = hb + rr, nz = TALL ? (hv * cut.invH) >> 20 : 0;   // zero rows above hv
         const bool ok = drc[u] >= 0 && cok && (unsigned)hv < (unsigned)Hv &&
                         (unsigned)col < (unsigned)W && (!TALL || hv - nz * cut.hp < H);
-        dma16(rxg, dst, ok ? base_b + doff[u] - nz * W * Cin * 2 : CT_OOB, 0);
+        dma16(rxg, dst, ok ? base_b + doff[u] - nz * W * Cin * 2 : kOob, 0);
       }
     }
   };
@@ -280,9 +271,7 @@ __global__ __launch_bounds__(WC * WP * 64) void conv3x3_tile(
 #pragma unroll
         for (int i = 0; i < MT; ++i)
           if constexpr (DG) {
-            const unsigned char* pa = st + abase[i] + t * 16 * RAB;
-            const uint2 lo = tr16c(pa), hi = tr16c(pa + 4 * RAB);
-            fa[buf][i] = as_bf16x8(u32x4{lo.x, lo.y, hi.x, hi.y});
+            fa[buf][i] = as_bf16x8(frag_tr(st + abase[i] + t * 16 * RAB, RAB));
           } else {
             fa[buf][i] = as_bf16x8(*(const u32x4*)(st + abase[i] + t * BN * 32));
           }

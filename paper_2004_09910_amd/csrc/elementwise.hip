@@ -20,8 +20,7 @@ hipError_t conv_forward_mfma(const void* x, const void* w, const float* b, void*
                              hipStream_t st);
 size_t wgrad_mfma_partial_floats(const ConvShape& s);
 hipError_t conv_wgrad_mfma(const void* x, const void* dz, float* dw, float* partial,
-                           const ConvShape& s, hipStream_t st, const ReduceJob* extra,
-                           ReduceJob* defer);
+                           const ConvShape& s, hipStream_t st, ReduceJob* defer);
 hipError_t conv_forward_mfma_n(int n, const void* const* x, const void* w, const float* b,
                                void* const* y, const ConvShape& s, int relu, float* const* part,
                                size_t part_cap, hipStream_t st);
@@ -985,22 +984,6 @@ __global__ __launch_bounds__(256) void loss_sum_k(const float* __restrict__ a, i
   if (threadIdx.x == 0) *out = red[0] * scale;
 }
 
-__global__ __launch_bounds__(256) void accumulate_k(float* __restrict__ acc, const float* __restrict__ g,
-                                                    long n, int overwrite) {
-  long e0 = ((long)blockIdx.x * 256 + threadIdx.x) * 4;
-  if (e0 >= n) return;
-  if (e0 + 4 <= n) {
-    float4 v = *(const float4*)(g + e0);
-    if (!overwrite) {
-      float4 a = *(const float4*)(acc + e0);
-      v.x = a.x + v.x; v.y = a.y + v.y; v.z = a.z + v.z; v.w = a.w + v.w;
-    }
-    *(float4*)(acc + e0) = v;
-  } else {
-    for (long e = e0; e < n; ++e) acc[e] = overwrite ? g[e] : acc[e] + g[e];
-  }
-}
-
 // acc_k = r_k or acc_k + r_k with r_k = sum_{s < S_k} g_k[s n_k + e], every
 // entry in one launch.  Tiles blk0[k] .. blk0[k + 1] - 1 serve entry k.  A
 // tile of 1024 threads covers C4 float4 columns with LANES = 1024 / C4
@@ -1231,11 +1214,9 @@ size_t conv_wgrad_partial_floats(int dt, const ConvShape& s) {
 }
 
 hipError_t conv_wgrad(int dt, const void* x, const void* dz, float* dw, float* partial,
-                      const ConvShape& s, hipStream_t st, const ReduceJob* extra,
-                      ReduceJob* defer) {
-  if (defer && extra) return hipErrorInvalidValue;
+                      const ConvShape& s, hipStream_t st, ReduceJob* defer) {
   if (mfma_wgrad_ok(dt, s))
-    return conv_wgrad_mfma(x, dz, dw, partial, s, st, extra, defer);
+    return conv_wgrad_mfma(x, dz, dw, partial, s, st, defer);
   ReduceJob job;
   ReduceJob* const jp = defer ? defer : &job;
   const hipError_t e = small1x1_ok(dt, s, x)
@@ -1244,8 +1225,7 @@ hipError_t conv_wgrad(int dt, const void* x, const void* dz, float* dw, float* p
                            ? conv_stem_wgrad_launch(1, &x, &dz, &dw, &partial, s, st, &jp)
                            : conv_gen_wgrad_launch(dt, 1, &x, &dz, &dw, &partial, s, st, &jp);
   if (e != hipSuccess || defer) return e;
-  if (job.S > 1) return splitk_reduce_launch(job.part, dw, job.E, job.S, st, extra);
-  return extra ? splitk_reduce_launch(extra->part, extra->out, extra->E, extra->S, st) : hipSuccess;
+  return job.S > 1 ? splitk_reduce_launch(job.part, dw, job.E, job.S, st) : hipSuccess;
 }
 
 hipError_t conv_forward_n(int dt, int n, const void* const* x, const void* w, const float* b,
@@ -1299,7 +1279,7 @@ hipError_t conv_wgrad_n(int dt, int n, const void* const* x, const void* const* 
   for (int k = 0; k < n; ++k) all = all && small1x1_ok(dt, s, x[k]);
   if (all) return wgrad1x1_small(dt, n, x, dz, dw, part, s, st, defer);
   for (int k = 0; k < n; ++k) {
-    const hipError_t e = conv_wgrad(dt, x[k], dz[k], dw[k], part[k], s, st, nullptr, defer[k]);
+    const hipError_t e = conv_wgrad(dt, x[k], dz[k], dw[k], part[k], s, st, defer[k]);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -1811,12 +1791,6 @@ hipError_t grad_accumulate_batch(AccBatch b, int overwrite, hipStream_t st) {
   else
     TGP_LAUNCH(ps, reduce_accumulate_k<4>, dim3(grid), dim3(1024), 0, st, b, overwrite,
                (int)blocks);
-  return launch_status();
-}
-
-hipError_t grad_accumulate(float* acc, const float* g, long n, int overwrite, hipStream_t st) {
-  ProfScope ps("grad_accumulate", (double)n, (overwrite ? 8.0 : 12.0) * n, st);
-  TGP_LAUNCH(ps, accumulate_k, dim3(cdiv(n, 1024)), dim3(256), 0, st, acc, g, n, overwrite);
   return launch_status();
 }
 

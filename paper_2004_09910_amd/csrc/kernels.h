@@ -18,9 +18,7 @@ struct ConvShape {
   long pixels() const { return (long)nb * H * W; }
 };
 
-// out[e] = sum_{k < S} part[k E + e] in a fixed order that depends only on
-// (E, S); `extra`, if given, is a second independent sum of the same kind run
-// in the same launch (its order then also depends on the first sum's S).
+// A sum still to run: out[e] = sum_{k < S} part[k E + e].
 struct ReduceJob {
   const float* part;
   float* out;
@@ -39,7 +37,7 @@ hipError_t conv_stem_wgrad_launch(int n, const void* const* x, const void* const
 
 // y = act(conv(x, w) + b); w is KRSC [cout][taps][cin].  Deep shapes split
 // the K loop; their fp32 partials go to `part` (conv_forward_partial_floats
-// floats; part_cap is the space available).
+// floats; part_cap is the space available, and too little an error).
 size_t conv_forward_partial_floats(int dt, const ConvShape& s);
 hipError_t conv_forward(int dt, const void* x, const void* w, const float* b, void* y,
                         const ConvShape& s, int relu, float* part, size_t part_cap,
@@ -88,36 +86,38 @@ extern int g_1x1_cfg;
 hipError_t conv_gen_forward(int dt, int n, const void* const* x, const void* w, const float* b,
                             void* const* y, const ConvShape& s, int relu, bool dg,
                             hipStream_t st);
+size_t conv_gen_wgrad_partial_floats(const ConvShape& s);
+hipError_t conv_gen_wgrad_launch(int dt, int n, const void* const* x, const void* const* dz,
+                                 float* const* dw, float* const* partial, const ConvShape& s,
+                                 hipStream_t st, ReduceJob* const* defer);
 extern int g_rows32_cfg;
 extern int g_rows32_ch;
 extern int g_wgrad_ks;
 extern int g_rowtile_mask;
-// Row-blocked 3x3 weight gradient on 32x32x16 MFMA with transpose LDS reads
-// (bf16; W in {48, 96, 192}, Cin and Cout multiples of 64): whether it
-// supports a shape, the fp32 partial-slice scratch it needs, and the launch
-// (dw = sum over pixels, summed over its K ranges in a fixed order).
+// out[e] = sum_{k < S} part[k E + e] in a fixed order that depends only on (E, S);
+// `extra`, if given, is a second independent sum of the same kind run in the same
+// launch (its order then also depends on the first sum's S).
 hipError_t splitk_reduce_launch(const float* part, float* out, long E, int S, hipStream_t st,
                                const ReduceJob* extra = nullptr);
 // out[k][e] = sum_s part[k][s E + e], n sums of one shape in one launch; a block
 // takes at most 2^lc_max columns (which fixes the order of a sum).
 hipError_t splitk_reduce_n(int n, const float* const* part, float* const* out, long E, int S,
                            hipStream_t st, int lc_max = 6);
+// Row-blocked 3x3 weight gradient on 32x32x16 MFMA with transpose LDS reads
+// (bf16; fixed widths, Cin and Cout multiples of 64): whether it supports a
+// shape, the fp32 partial-slice scratch it needs, and the launch (dw = sum over
+// pixels, summed over its K ranges in a fixed order, or left pending in *defer).
 bool wgrad_rows_ok(const ConvShape& s);
 size_t wgrad_rows_partial_floats(const ConvShape& s);
 hipError_t conv_wgrad_rows_launch(const void* x, const void* dz, float* dw, float* partial,
-                                  const ConvShape& s, hipStream_t st,
-                                  const ReduceJob* extra = nullptr, ReduceJob* defer = nullptr);
+                                  const ConvShape& s, hipStream_t st, ReduceJob* defer = nullptr);
 // n (1 .. kMaxGroup) micro-batches in one launch, each sum left pending in
 // *defer[k].
 hipError_t conv_wgrad_rows_launch_n(int n, const void* const* x, const void* const* dz,
                                     float* const* dw, float* const* partial, const ConvShape& s,
                                     hipStream_t st, ReduceJob* const* defer);
 // The same weight gradient for any image size and channel counts that are
-// multiples of 8, same contracts.
-size_t conv_gen_wgrad_partial_floats(const ConvShape& s);
-hipError_t conv_gen_wgrad_launch(int dt, int n, const void* const* x, const void* const* dz,
-                                 float* const* dw, float* const* partial, const ConvShape& s,
-                                 hipStream_t st, ReduceJob* const* defer);
+// multiples of 8, each sum left pending in *defer[k].
 bool wgrad_tile_ok(const ConvShape& s);
 double wgrad_tile_fill(const ConvShape& s);   // share of what it multiplies that is pixels
 int wgrad_general_splits(const ConvShape& s);
@@ -150,14 +150,11 @@ hipError_t conv_dgrad(int dt, const void* dz, const void* w, const void* wt, voi
                       const ConvShape& s, float* part, size_t part_cap, hipStream_t st);
 // Weight gradient of one micro-batch into dw (float32, KRSC), via split-K
 // partials in `partial` (conv_wgrad_partial_floats floats) reduced in fixed
-// split order.  `extra`, if given, is a pending sum (the bias gradient's)
-// that runs in the same reduction launch.  With `defer` (and no `extra`)
-// only the partials are written and *defer describes the sum still to run
+// split order.  With `defer` only the partials are written and *defer describes the sum still to run
 // (S = 1 with part = dw when the kernel wrote the gradient itself).
 size_t conv_wgrad_partial_floats(int dt, const ConvShape& s);
 hipError_t conv_wgrad(int dt, const void* x, const void* dz, float* dw, float* partial,
-                      const ConvShape& s, hipStream_t st, const ReduceJob* extra = nullptr,
-                      ReduceJob* defer = nullptr);
+                      const ConvShape& s, hipStream_t st, ReduceJob* defer = nullptr);
 
 // The same three operations for n (1 .. kMaxGroup) micro-batches of one
 // layer (the same weights, separate tensors; array element k is micro-batch
@@ -244,9 +241,6 @@ hipError_t mse_forward_backward_n(int dt, int n, const void* const* y, const voi
 hipError_t loss_finalize(const float* parts, int n, float inv_numel, float* loss,
                          hipStream_t st);
 
-// acc = g (overwrite) or acc + g, float32.
-hipError_t grad_accumulate(float* acc, const float* g, long n, int overwrite, hipStream_t st);
-
 // acc_k = r_k (overwrite) or acc_k + r_k, r_k = sum_{s < S_k} g_k[s n_k ..]
 // (the pending split-K sums of one micro-batch's gradients), for up to
 // kMaxAcc tensors in one launch (passed by value).  Each r_k is summed in a
@@ -276,7 +270,7 @@ bool relu_bias_fusable(int dt, int C, const void* dy, const void* dskip, const v
                        const void* dz);
 size_t relu_bias_partial_floats(int dt, long P, int C, int cap);
 // With `defer`, the bias gradient's column sums are left in `partial` and
-// *defer describes the sum still to run (the caller passes it to conv_wgrad).
+// *defer describes the sum still to run.
 // One micro-batch's tensors for the fused ReLU-backward / bias-sum kernels
 // (dy is the pool gradient for the pooled variant).
 struct RbArgs {

@@ -32,6 +32,27 @@ __device__ __forceinline__ f32x4_t mfma16(bf16x8_t a, bf16x8_t b, f32x4_t c) {
 
 #define TGP_LDS(p) ((__attribute__((address_space(3))) void*)(p))
 
+// Byte offset that every buffer descriptor reads as out of range (zeros).
+constexpr int kOob = (int)0x80000000;
+
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+// Transpose read: within each group of 16 lanes, lane i receives element
+// i % 4 of the 8-byte blocks addressed by lanes 4 e + i / 4, e = 0..3.
+__device__ __forceinline__ uint2 lds_tr16(const unsigned char* p) {
+  typedef __attribute__((address_space(3))) s16x4_t lds_s16x4;
+  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)TGP_LDS(p)));
+}
+// A fragment's 8 sum rows of `pitch` bytes from p on.
+__device__ __forceinline__ u32x4 frag_tr(const unsigned char* p, int pitch) {
+  const uint2 lo = lds_tr16(p), hi = lds_tr16(p + 4 * pitch);
+  return u32x4{lo.x, lo.y, hi.x, hi.y};
+}
+
+// XOR swizzle of the eight 16-byte chunks of a 128-byte LDS row, so that
+// eight consecutive rows read at the same logical chunk, and rows eight apart
+// written at the same chunk, hit distinct banks.
+__device__ __forceinline__ int swz(int row, int q) { return q ^ ((row ^ (row >> 3)) & 7); }
+
 // s_waitcnt with only the vector-memory counter limited to N (gfx9 encoding:
 // vmcnt in bits 3:0 and 15:14; expcnt and lgkmcnt left at their maxima).
 template <int N>

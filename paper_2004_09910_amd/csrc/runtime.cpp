@@ -671,7 +671,7 @@ tgp_status run_backward_g(tgp_net* N, int j, int cnt, const int* iv,
         } else {
           HIPCHK(tgpk::conv_wgrad(N->dt, cin_ptr[k], dzk[k], gw,
                                   Lr.defer_w ? (float*)G_(N, B.i, Lr.o_gpart) : B.part, s, st,
-                                  nullptr, Lr.defer_w ? &(*pjs[k])[0] : nullptr),
+                                  Lr.defer_w ? &(*pjs[k])[0] : nullptr),
                  "conv_wgrad");
         }
       }

@@ -33,24 +33,8 @@
 namespace tgpk {
 namespace {
 
-constexpr int WG_OOB = (int)0x80000000;
 
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
-// Transpose read: within each group of 16 lanes, lane i receives element
-// i % 4 of the 8-byte blocks addressed by lanes 4 e + i / 4, e = 0..3.
-__device__ __forceinline__ s16x4 tr16(const unsigned char* p) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)TGP_LDS(p));
-}
-
-__device__ __forceinline__ bf16x8_t frag2(s16x4 lo, s16x4 hi) {
-  const u32x4 v = {__builtin_bit_cast(unsigned, (short __attribute__((ext_vector_type(2)))){lo[0], lo[1]}),
-                   __builtin_bit_cast(unsigned, (short __attribute__((ext_vector_type(2)))){lo[2], lo[3]}),
-                   __builtin_bit_cast(unsigned, (short __attribute__((ext_vector_type(2)))){hi[0], hi[1]}),
-                   __builtin_bit_cast(unsigned, (short __attribute__((ext_vector_type(2)))){hi[2], hi[3]})};
-  return as_bf16x8(v);
-}
 
 constexpr int round32(int v) { return (v + 31) / 32 * 32; }
 
@@ -134,7 +118,7 @@ __global__ __launch_bounds__(256 * KS) void conv_wgrad_rows(WgIo io, int ng, int
     const int lc = (lane & 7) ^ (2 * (row & 3));
     const int rr = row / W, w = row - rr * W;
     const bool ok = row < RPS * W;
-    aoff[u] = ok ? ((rr * W + w) * Cout + 8 * lc) * 2 : WG_OOB;
+    aoff[u] = ok ? ((rr * W + w) * Cout + 8 * lc) * 2 : kOob;
     arow[u] = ok ? rr : -1;
   }
 #pragma unroll
@@ -143,7 +127,7 @@ __global__ __launch_bounds__(256 * KS) void conv_wgrad_rows(WgIo io, int ng, int
     const int lc = (lane & 7) ^ (2 * (row & 3));
     const int rr = row / BW, q = row - rr * BW;
     const bool ok = rr < RPS && q >= 1 && q <= W;
-    boff[u] = ok ? ((rr * W + q - 1) * Cin + 8 * lc) * 2 : WG_OOB;
+    boff[u] = ok ? ((rr * W + q - 1) * Cin + 8 * lc) * 2 : kOob;
     brow[u] = ok ? rr : -1;
   }
   // DMA instructions an issuing wave issues per stage (the waits count
@@ -232,7 +216,7 @@ __global__ __launch_bounds__(256 * KS) void conv_wgrad_rows(WgIo io, int ng, int
       if (!issuer || (AC % ND != 0 && c >= AC)) continue;   // wave-uniform
       auto* dst = TGP_LDS(smem + slot * SB + c * 1024);
       const bool ok = arow[u] >= 0 && h + arow[u] < H;
-      dma16(rzg, dst, ok ? aoff[u] + zsoff : WG_OOB, 0);
+      dma16(rzg, dst, ok ? aoff[u] + zsoff : kOob, 0);
     }
 #pragma unroll
     for (int u = 0; u < LB; ++u) {
@@ -242,7 +226,7 @@ __global__ __launch_bounds__(256 * KS) void conv_wgrad_rows(WgIo io, int ng, int
       const bool ok = brow[u] >= 0 && (unsigned)(hb + brow[u]) < (unsigned)H && h + brow[u] < H;
       // the row offset can be negative for filter row 0 (rows above are out
       // of range there), so it goes into the per-lane offset
-      dma16(rxg, dst, ok ? boff[u] + xsoff : WG_OOB, 0);
+      dma16(rxg, dst, ok ? boff[u] + xsoff : kOob, 0);
     }
     if (++i_st == i_ns) {
       i_st = 0;
@@ -291,10 +275,10 @@ __global__ __launch_bounds__(256 * KS) void conv_wgrad_rows(WgIo io, int ng, int
         if constexpr (KS == 1) kx = xoff(t);
         else if constexpr (KS == 2) kx = kh ? xoff(KS * tt + 1) : xoff(KS * tt);
         else kx = xoff(KS * tt + kh);
-        a[buf] = frag2(tr16(sp + fa + ka), tr16(sp + fa + ka + 4 * 128));
+        a[buf] = as_bf16x8(frag_tr(sp + fa + ka, 128));
 #pragma unroll
         for (int s = 0; s < 3; ++s)
-          b[buf][s] = frag2(tr16(sp + fb[s] + kx), tr16(sp + fb[s] + kx + 4 * 128));
+          b[buf][s] = as_bf16x8(frag_tr(sp + fb[s] + kx, 128));
       };
       load(0, 0);
 #pragma unroll
@@ -446,7 +430,7 @@ __global__ __launch_bounds__(768) void conv_wgrad_rows3(WgIo io, int ng, int nb,
     const int lc = (lane & 7) ^ (2 * (row & 3));
     const int rr = row / W, w = row - rr * W;
     const bool ok = row < RPS * W;
-    aoff[u] = ok ? ((rr * W + w) * Cout + 8 * lc) * 2 : WG_OOB;
+    aoff[u] = ok ? ((rr * W + w) * Cout + 8 * lc) * 2 : kOob;
     arow[u] = ok ? rr : -1;
   }
 #pragma unroll
@@ -455,7 +439,7 @@ __global__ __launch_bounds__(768) void conv_wgrad_rows3(WgIo io, int ng, int nb,
     const int lc = (lane & 7) ^ (2 * (row & 3));
     const int rr = row / BW, q = row - rr * BW;
     const bool ok = rr < RPS + 2 && q >= 1 && q <= W;
-    boff[u] = ok ? ((rr * W + q - 1) * Cin + 8 * lc) * 2 : WG_OOB;
+    boff[u] = ok ? ((rr * W + q - 1) * Cin + 8 * lc) * 2 : kOob;
     brow[u] = ok ? rr : -1;
   }
   // DMA instructions this wave issues per stage (the waits count them)
@@ -529,7 +513,7 @@ __global__ __launch_bounds__(768) void conv_wgrad_rows3(WgIo io, int ng, int nb,
       if (AC % NW != 0 && c >= AC) continue;                 // wave-uniform
       auto* dst = TGP_LDS(smem + slot * SB + c * 1024);
       const bool ok = arow[u] >= 0 && h + arow[u] < H;
-      dma16(rzg, dst, ok ? aoff[u] + zsoff : WG_OOB, 0);
+      dma16(rzg, dst, ok ? aoff[u] + zsoff : kOob, 0);
     }
 #pragma unroll
     for (int u = 0; u < LB; ++u) {
@@ -539,7 +523,7 @@ __global__ __launch_bounds__(768) void conv_wgrad_rows3(WgIo io, int ng, int nb,
       // rows outside the sample's image (above it for h = 0) read zeros; the
       // row offset can be negative, so it goes into the per-lane offset
       const bool ok = brow[u] >= 0 && (unsigned)(hb + brow[u]) < (unsigned)H;
-      dma16(rxg, dst, ok ? boff[u] + xsoff : WG_OOB, 0);
+      dma16(rxg, dst, ok ? boff[u] + xsoff : kOob, 0);
     }
     if (++i_st == i_ns) {
       i_st = 0;
@@ -576,10 +560,10 @@ __global__ __launch_bounds__(768) void conv_wgrad_rows3(WgIo io, int ng, int nb,
       auto load = [&](int t, int buf) __attribute__((always_inline)) {
         const int ka = 16 * t * 128;
         const int kx = xoff(t);
-        a[buf] = frag2(tr16(sp + fa + ka), tr16(sp + fa + ka + 4 * 128));
+        a[buf] = as_bf16x8(frag_tr(sp + fa + ka, 128));
 #pragma unroll
         for (int s = 0; s < 3; ++s)
-          b[buf][s] = frag2(tr16(sp + fb[s] + kx), tr16(sp + fb[s] + kx + 4 * 128));
+          b[buf][s] = as_bf16x8(frag_tr(sp + fb[s] + kx, 128));
       };
       load(0, 0);
 #pragma unroll
@@ -758,8 +742,7 @@ static hipError_t launch_wgrad_rows_w(const WgIo& io, int ng, const ConvShape& s
 }
 
 hipError_t conv_wgrad_rows_launch(const void* x, const void* dz, float* dw, float* partial,
-                                  const ConvShape& s, hipStream_t st, const ReduceJob* extra,
-                                  ReduceJob* defer) {
+                                  const ConvShape& s, hipStream_t st, ReduceJob* defer) {
   if (!wgrad_rows_ok(s)) return hipErrorInvalidValue;
   const WgPlan p = wgrad_rows_plan(s);
   float* out = p.nK > 1 ? partial : dw;
@@ -773,11 +756,10 @@ hipError_t conv_wgrad_rows_launch(const void* x, const void* dz, float* dw, floa
   if (e != hipSuccess) return e;
   if (defer) {
     *defer = ReduceJob{out, dw, (long)s.cout * 9 * s.cin, p.nK};
-    return extra ? hipErrorInvalidValue : hipSuccess;
+    return hipSuccess;
   }
-  if (p.nK == 1)
-    return extra ? splitk_reduce_launch(extra->part, extra->out, extra->E, extra->S, st) : e;
-  return splitk_reduce_launch(partial, dw, (long)s.cout * 9 * s.cin, p.nK, st, extra);
+  if (p.nK == 1) return e;
+  return splitk_reduce_launch(partial, dw, (long)s.cout * 9 * s.cin, p.nK, st);
 }
 
 // n micro-batches in one launch, each sum left pending (*defer[k]): the

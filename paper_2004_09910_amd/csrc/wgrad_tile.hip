@@ -38,20 +38,6 @@
 namespace tgpk {
 namespace {
 
-constexpr int WT_OOB = (int)0x80000000;
-
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-
-// Transpose read: within each group of 16 lanes, lane i receives element
-// i % 4 of the 8-byte blocks addressed by lanes 4 e + i / 4, e = 0..3.
-__device__ __forceinline__ uint2 tr16u(const unsigned char* p) {
-  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)TGP_LDS(p)));
-}
-__device__ __forceinline__ u32x4 frag(const unsigned char* p) {
-  const uint2 lo = tr16u(p), hi = tr16u(p + 4 * 128);
-  return u32x4{lo.x, lo.y, hi.x, hi.y};
-}
 
 // Barrier between LDS writes and other waves' reads of them (or the other way
 // round): this wave's LDS accesses have completed when it arrives, and the
@@ -185,11 +171,11 @@ __global__ __launch_bounds__(64 * kWtNW) void conv_wgrad_tile(WtIo io, int ng, i
       const int r = drc[u] & 0xffff, cc = drc[u] >> 16;
       if (c * 8 < cut.AROWS) {                  // wave-uniform
         const bool ok = drc[u] >= 0 && zc && h + r < H && w0 + cc < W;
-        dma16(rzg, dst, ok ? doff[u] + zb : WT_OOB, 0);
+        dma16(rzg, dst, ok ? doff[u] + zb : kOob, 0);
       } else {
         const bool ok = drc[u] >= 0 && xc && (unsigned)(h - 1 + r) < (unsigned)H &&
                         (unsigned)(w0 + cc - 1) < (unsigned)W;
-        dma16(rxg, dst, ok ? doff[u] + xb : WT_OOB, 0);
+        dma16(rxg, dst, ok ? doff[u] + xb : kOob, 0);
       }
     }
     if (++i_st == i_n) {
@@ -250,9 +236,9 @@ __global__ __launch_bounds__(64 * kWtNW) void conv_wgrad_tile(WtIo io, int ng, i
         u32x4 a[2], b[3];
         const int ka = 16 * t * 128;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) a[i] = frag(sp + fa[i] + ka);
+        for (int i = 0; i < 2; ++i) a[i] = frag_tr(sp + fa[i] + ka, 128);
 #pragma unroll
-        for (int s = 0; s < 3; ++s) b[s] = frag(sp + fb[s] + ka + ue);
+        for (int s = 0; s < 3; ++s) b[s] = frag_tr(sp + fb[s] + ka + ue, 128);
         // units with padding pixels: unit ul of a row (rem real ones), and past
         // it or past an odd count (none); skipped by the waves that have none
         const bool pad = 2 * t + half >= U || uc > ul;
