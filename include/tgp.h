@@ -39,6 +39,11 @@
  *   - All argument and state checks run on the host before anything is
  *     enqueued.  A call that returns an error has enqueued nothing, except
  *     TGP_EHIP, which reports a failed launch (tgp_last_error names it).
+ *   - Zero padding takes part in the sums.  An infinite or NaN weight (in a
+ *     weight gradient: output gradient) times a padding zero is NaN, so the
+ *     outputs (taps) at the image's border may be NaN where a sum over the
+ *     pixels inside the image alone would not be.  Infinities and NaN in
+ *     activations and their gradients reach only what they are paired with.
  *   - A tgp_net is not thread safe.  Results are deterministic: every
  *     reduction has a fixed order, no kernel uses floating-point atomics, and
  *     kernel choice and launch shape depend only on tensor shapes.

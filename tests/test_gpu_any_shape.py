@@ -523,3 +523,48 @@ def test_conv3x3_tiles_across_samples(cin, cout, h, w, b, other):
         tgp.debug_set_fwd_variant(0)
     assert not any(",tall" in n for n in names), names
     assert torch.equal(out[0]["y"], out[1]["y"]) and torch.equal(out[0]["dx"], out[1]["dx"])
+
+
+@pytest.mark.parametrize("dtype,kind,cin,cout,h,w,b", [
+    (BF16, CONV3X3, 40, 72, 21, 37, 2),      # rectangular tiles
+    (BF16, CONV3X3, 40, 328, 5, 7, 37),      # tiles across samples
+    (BF16, CONV3X3, 512, 64, 10, 10, 2),     # split sums
+    (BF16, CONV3X3, 3, 40, 17, 19, 2),       # an image layer
+    (BF16, CONV3X3, 12, 20, 17, 5, 2),       # float32 matrix unit
+    (FP32, CONV3X3, 20, 68, 17, 13, 2),
+    (BF16, CONV1X1, 72, 136, 11, 17, 2),
+    (BF16, CONV1X1, 64, 256, 9, 7, 2),       # weights in registers
+    (FP32, CONV1X1, 130, 70, 5, 7, 2),
+    (BF16, DWCONV3X3, 24, 24, 19, 13, 2),
+])
+def test_infinities_reach_only_what_they_pair_with(dtype, kind, cin, cout, h, w, b):
+    """An infinity in the input (the output gradient) of sample 0, in a corner or
+    inside, changes only the outputs (input gradients) of its 3 x 3 neighbourhood
+    or, in a 1x1 layer, its pixel."""
+    net = one_layer(Layer(kind, cin, cout, relu=False), h, w)
+    sess = Session(net, dtype, init="device")
+    sess.plan(b, 1, specs.CKPT_NEVER)
+    torch.manual_seed(5)
+    td = torch.bfloat16 if dtype == BF16 else torch.float32
+    x = torch.randn(b, h, w, cin, device="cuda").to(td)
+    dy = torch.randn(b, h, w, cout, device="cuda").to(td)
+
+    def step(xs, dys):
+        y, dx = torch.empty_like(dy), torch.empty_like(x)
+        sess.stage_step(1, xs, y, dys, dx, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        return y, dx
+
+    y0, dx0 = step(x, dy)
+    r = 0 if kind == CONV1X1 else 1
+    for ph, pw in ((h - 1, w - 1), (0, w // 2), (h // 2, 0)):
+        x1, dy1 = x.clone(), dy.clone()
+        x1[0, ph, pw, cin - 1] = float("inf")
+        dy1[0, ph, pw, cout - 1] = float("inf")
+        y1, dx1 = step(x1, dy1)
+        for a, c in ((y0, y1), (dx0, dx1)):
+            near = torch.zeros(b, h, w, dtype=torch.bool, device="cuda")
+            near[0, max(ph - r, 0):ph + r + 1, max(pw - r, 0):pw + r + 1] = True
+            assert torch.equal(a[~near], c[~near])
+            assert not torch.isfinite(c[0, ph, pw]).all()
+    sess.close()
