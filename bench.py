@@ -36,13 +36,8 @@ def log(*a):
 # copy of known size.  A summary records a hash of the kernel sources; the
 # bench reports its traffic only while the sources are unchanged.
 PROFILES = os.path.join(HERE, "profiles")
-KERNEL_SOURCES = ["paper_2004_09910_amd/csrc/conv_mfma.hip",
-                  "paper_2004_09910_amd/csrc/conv_rowtile.hip",
-                  "paper_2004_09910_amd/csrc/conv_rows32.hip",
-                  "paper_2004_09910_amd/csrc/wgrad_rows.hip",
-                  "paper_2004_09910_amd/csrc/elementwise.hip",
-                  "paper_2004_09910_amd/csrc/mfma_util.h",
-                  "paper_2004_09910_amd/csrc/common.h"]
+KERNEL_DIR = "paper_2004_09910_amd/csrc/"
+KERNEL_HEADERS = ["mfma_util.h", "common.h"]
 PROFILE_COMMANDS = {
     "trace": "rocprofv3 --kernel-trace --stats --output-format csv -d rocprof_out/prof_kt -o kt "
              "-- python3 bench.py --steps 10 --warmup 2 --no-cpu-baseline",
@@ -65,9 +60,18 @@ N_SIMD = 1024           # MI355X: 256 CUs x 4 SIMDs
 CLOCK_GHZ = 2.4         # MI355X peak engine clock
 
 
-KERNEL_FILES = [("conv3x3_rows32", "conv_rows32.hip"), ("conv_wgrad_rows", "wgrad_rows.hip"),
-                ("conv3x3_rowtile", "conv_rowtile.hip"), ("conv_", "conv_mfma.hip"),
-                ("splitk_reduce", "conv_mfma.hip"), ("", "elementwise.hip")]
+# The file that holds a kernel, by the longest prefix of its name (in a trace, or
+# as its launcher names it).
+KERNEL_FILES = {
+    "conv3x3_rows32": "conv_rows32.hip", "conv3x3_rowtile": "conv_rowtile.hip",
+    "conv3x3_tile": "conv_tile.hip", "split_epilogue": "conv_tile.hip",
+    "conv_wgrad_rows": "wgrad_rows.hip", "conv_wgrad_tile": "wgrad_tile.hip",
+    "conv_gen": "conv_gen.hip", "conv_stem": "conv_stem.hip", "stem_": "conv_stem.hip",
+    "conv1x1_tile": "conv1x1_tile.hip", "wgrad1x1_tile": "conv1x1_tile.hip",
+    "conv1x1_res": "conv_mfma.hip", "conv_fwd_dma": "conv_mfma.hip",
+    "conv_wgrad_mfma": "conv_mfma.hip", "splitk_reduce": "conv_mfma.hip",
+    "wtransform": "conv_mfma.hip", "": "elementwise.hip",
+}
 
 
 def kernel_source_hash(kernel=None):
@@ -75,12 +79,12 @@ def kernel_source_hash(kernel=None):
     shared headers; all kernel sources when no kernel is named)."""
     import hashlib
     h = hashlib.sha256()
-    files = KERNEL_SOURCES
-    if kernel is not None:
-        own = next(f for prefix, f in KERNEL_FILES if kernel.startswith(prefix))
-        files = ["paper_2004_09910_amd/csrc/" + own, "paper_2004_09910_amd/csrc/mfma_util.h",
-                 "paper_2004_09910_amd/csrc/common.h"]
-    for rel in files:
+    csrc = os.path.join(HERE, KERNEL_DIR)
+    if kernel is None:
+        files = sorted(f for f in os.listdir(csrc) if f.endswith(".hip"))
+    else:
+        files = [KERNEL_FILES[max((p for p in KERNEL_FILES if kernel.startswith(p)), key=len)]]
+    for rel in [KERNEL_DIR + f for f in files + KERNEL_HEADERS]:
         with open(os.path.join(HERE, rel), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
@@ -111,6 +115,12 @@ def short_kernel_name(full):
     if head == "conv3x3_rows32" and len(args) == 6:
         n = (f"{head}<{','.join(args[:4])}{',8w' if args[4] == '1' else ''}"
              f"{',rk' if args[5] != '0' else ''}>")
+    elif head == "conv3x3_tile" and len(args) == 9:
+        dg, split, tall = (a in ("true", "1") for a in args[6:])
+        n = (f"{head}<{','.join(args[:6])}{',tall' if tall else ''}{',dg' if dg else ''}"
+             f"{',split' if split else ''}>")
+    elif head == "conv1x1_tile" and len(args) == 6:
+        n = f"{head}<{','.join(args[:4])}{',dg' if args[5] in ('true', '1') else ''}>"
     elif head == "conv_wgrad_rows" and len(args) == 4:
         n = f"{head}<{','.join(args[:3])}{ {'2': ',8w', '3': ',12w'}.get(args[3], '')}>"
     return n
