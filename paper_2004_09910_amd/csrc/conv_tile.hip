@@ -23,12 +23,13 @@
 // transposed copy of the weights is made or kept (64 -> 64 channels at 56 x
 // 56, one sample: one launch of 4 us less of a step of 32).
 //
-// What bounds it: operands into LDS and out of it.  Per tap a wave reads
-// MT + FW fragments of 1 KiB for MT FW MFMAs, so wide layers take MT = 2,
-// FW = 4 (128 channels x 512 pixels a block); few tiles or few channels take
-// the smaller tiles.  The sum of an output runs over (chunk, tap, channel) in
-// every configuration, so the choice does not change values and a
-// recomputation is bit-identical.
+// What bounds it: per tap a wave reads MT + FW fragments of 1 KiB for MT FW MFMAs,
+// so wide layers take MT = FW = 2 (128 channels x 256 pixels a block) or FW = 4 (64 x
+// 512); few tiles or few channels take the smaller tiles.  At 128 channels, 56 x
+// 56 x 8, four micro-batches (64 x 512 tiles) the MFMAs are busy 31% of the time, LDS
+// 30%, and waves wait a third of theirs: one block a CU, whose stages hand over
+// behind a barrier.  The sum of an output runs over (chunk, tap, channel) in every configuration, so the
+// choice does not change values and a recomputation is bit-identical.
 #include "common.h"
 #include "kernels.h"
 #include "mfma_util.h"

@@ -77,7 +77,7 @@ def test_conv3x3_any_shape_groups_are_bitwise():
 def test_wgrad_padding_keeps_infinities_apart(h, w):
     """Input pixels of the last row and column pair with no output at filter
     row 0 / column 0: an infinity there must not reach those taps through the
-    stage's zero padding."""
+    zero padding (the per-tap kernel; the rectangular stages below)."""
     net = one_layer(Layer(CONV3X3, 64, 128, relu=False), h, w)
     sess = Session(net, BF16)
     sess.plan(3, 1, specs.CKPT_NEVER)

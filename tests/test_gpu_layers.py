@@ -236,7 +236,7 @@ def test_conv1x1_and_depthwise():
 
 @pytest.mark.parametrize("cin,h,w,B,m", [(256, 20, 20, 2, 1), (128, 9, 7, 4, 2), (64, 56, 56, 4, 2)])
 def test_conv1x1_resident_weights(cin, h, w, B, m):
-    """The 1x1 kernel with all weights resident in LDS (256 output
+    """The 1x1 kernel with its weights in registers (256 output
     channels): against the oracle on y, dx, dW and db, with a ragged last
     64-pixel tile; and bit for bit the same y and dx as the per-tap kernel
     (forced), whose K order it shares."""
@@ -265,8 +265,8 @@ def test_conv1x1_resident_weights(cin, h, w, B, m):
                                          (24, 6, 6, True)])
 def test_depthwise_shapes(c, h, w, relu):
     """Depthwise 3x3 with one to 256 channel packs per pixel, ragged row
-    strips and column chunks; 24 channels (three packs, not a divisor of the
-    block) takes the per-element kernels."""
+    strips and column chunks; with 24 channels (three packs, not a divisor of
+    256) a block has 255 threads."""
     net = one_layer(Layer(DWCONV3X3, c, c, relu=relu, bias=relu), h, w)
     run_and_check(net, (1,), 1, BF16, 4, 2, f"dwconv3x3 {c} @{h}x{w} relu={relu}")
 
