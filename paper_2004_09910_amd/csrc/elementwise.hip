@@ -121,12 +121,12 @@ __global__ __launch_bounds__(256) void conv1x1_small_fwd_k(Group io, const T* __
 }
 
 // Its data gradient dx[p][ci] = sum_co dz[p][co] w[co][ci]: a thread keeps one
-// channel pack's weights and takes kSmallPix pixels, so that a block writes
+// channel pack's weights and takes PIX pixels, so that a block writes
 // whole rows; bound by that write (64 -> 1 at 192 x 192 x 4: 29 us on the
-// float32 matrix unit, 8.6 here).  blockIdx.y is the micro-batch.  Needs
-// 256 % (Cin / pack) == 0.
-constexpr int kSmallPix = 4;
-template <typename T>
+// float32 matrix unit, 8.6 here).  Four pixels, or one where a launch then has
+// fewer than 128 blocks (32 -> 4 at 13 x 13 x 9: 4.9 -> 4.1 us).  blockIdx.y is the
+// micro-batch.  Needs 256 % (Cin / pack) == 0.
+template <typename T, int PIX>
 __global__ __launch_bounds__(256) void dgrad1x1_small_k(Group io, const T* __restrict__ w,
                                                         long P, int Cin, int Cout) {
   constexpr int N = Pk<T>::N;
@@ -139,17 +139,17 @@ __global__ __launch_bounds__(256) void dgrad1x1_small_k(Group io, const T* __res
 #pragma unroll
     for (int i = 0; i < N; ++i)
       wv[co][i] = co < Cout ? Elt<T>::ld(w + (long)co * Cin + cp * N + i) : 0.f;
-  const long p0 = (long)blockIdx.x * nl * kSmallPix + threadIdx.x / CP;
-  float g[kSmallPix][kSmallCo];
+  const long p0 = (long)blockIdx.x * nl * PIX + threadIdx.x / CP;
+  float g[PIX][kSmallCo];
 #pragma unroll
-  for (int u = 0; u < kSmallPix; ++u)
+  for (int u = 0; u < PIX; ++u)
 #pragma unroll
     for (int co = 0; co < kSmallCo; ++co) {   // past the end: the last pixel, unused
       const long p = p0 + (long)u * nl < P ? p0 + (long)u * nl : P - 1;
       g[u][co] = Elt<T>::ld(dz + p * Cout + (co < Cout ? co : 0));
     }
 #pragma unroll
-  for (int u = 0; u < kSmallPix; ++u) {
+  for (int u = 0; u < PIX; ++u) {
     const long p = p0 + (long)u * nl;
     if (p >= P) break;
     float acc[N];
@@ -1122,12 +1122,16 @@ template <typename T>
 static hipError_t launch_dgrad_small(int n, const void* const* dz, const void* w, void* const* dx,
                                      const ConvShape& s, hipStream_t st) {
   const Group io = make_group(n, dx, dz);
-  const long P = s.pixels(), per = 256 / (s.cin / Pk<T>::N) * kSmallPix;
+  const long P = s.pixels(), nl = 256 / (s.cin / Pk<T>::N);
   if (P == 0) return hipSuccess;
   ProfScope ps("dgrad1x1_small", 2.0 * n * P * s.cout * s.cin,
                (double)sizeof(T) * n * P * (s.cin + s.cout), st);
-  TGP_LAUNCH(ps, dgrad1x1_small_k<T>, dim3(cdiv(P, per), n), dim3(256), 0, st, io, (const T*)w, P,
-             s.cin, s.cout);
+  if (n * cdiv(P, 4 * nl) < 128)
+    TGP_LAUNCH(ps, (dgrad1x1_small_k<T, 1>), dim3(cdiv(P, nl), n), dim3(256), 0, st, io,
+               (const T*)w, P, s.cin, s.cout);
+  else
+    TGP_LAUNCH(ps, (dgrad1x1_small_k<T, 4>), dim3(cdiv(P, 4 * nl), n), dim3(256), 0, st, io,
+               (const T*)w, P, s.cin, s.cout);
   return launch_status();
 }
 static hipError_t conv1x1_small(int dt, int n, const void* const* x, const void* w, const float* b,

@@ -370,6 +370,7 @@ def test_conv3x3_few_input_channels(cin, cout, h, w, B, m):
     (64, 1, 29, 31, 6, 2),
     (256, 3, 17, 40, 6, 3),       # bias sums of rows of three
     (16, 4, 70, 66, 4, 1),
+    (256, 2, 60, 51, 2, 1),       # data gradient in four pixels a thread
 ])
 def test_conv1x1_few_output_channels(dt, cin, cout, h, w, B, m):
     run_and_check(Layer(CONV1X1, cin, cout, relu=False), h, w, dt, B, m,
