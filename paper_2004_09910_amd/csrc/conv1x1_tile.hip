@@ -383,7 +383,7 @@ constexpr Cfg1x1 kCfg1x1[] = {
 
 }  // namespace
 
-int g_1x1_cfg = -1;   // >= 0 forces a configuration (tests and measurement)
+thread_local int g_1x1_cfg = -1;   // >= 0 forces a configuration (tests and measurement)
 
 // Tile for ng micro-batches: the largest whose tiles fill a round of blocks;
 // where 64 x 64 tiles do not, a deep ring, since a block's few loads in flight
@@ -409,15 +409,14 @@ bool conv1x1_tile_ok(const ConvShape& s) {
 template <int MT, int WC, int WP, int FW, int NS, bool DG>
 static hipError_t launch1x1(const Io1x1& io, int ng, const bf16_t* Wt, const float* b,
                             const ConvShape& s, int relu, hipStream_t st) {
-  static char name[64];
-  if (!name[0]) snprintf(name, sizeof name, "conv1x1_tile<%d,%d,%d,%d%s>", MT, WC, WP, FW, DG ? ",dg" : "");
+  static const KernelName name("conv1x1_tile<%d,%d,%d,%d%s>", MT, WC, WP, FW, DG ? ",dg" : "");
   constexpr int BN = 32 * MT * WC, BM = 32 * WP * FW, LDS = NS * (BN + BM) * 128;
   const long P = s.pixels();
   const long items = (long)ng * ((P + BM - 1) / BM) * ((s.cout + BN - 1) / BN);
   if (items >= (1L << 31)) return hipErrorInvalidValue;
   constexpr int occ = LDS * 5 <= 160 * 1024 ? 5 : LDS * 3 <= 160 * 1024 ? 3 : LDS * 2 <= 160 * 1024 ? 2 : 1;
   const int G = (int)(items < 256 * occ ? items : 256 * occ);
-  ProfScope ps(name, 2.0 * ng * P * s.cout * s.cin,
+  ProfScope ps(name.s, 2.0 * ng * P * s.cout * s.cin,
                2.0 * ((double)ng * P * (s.cin + s.cout) + (double)s.cout * s.cin), st);
   TGP_LAUNCH(ps, (conv1x1_tile<MT, WC, WP, FW, NS, DG>), dim3(G), dim3(WC * WP * 64), 0, st, io, ng,
              Wt, b, (int)P, s.cin, s.cout, relu);

@@ -810,8 +810,8 @@ static hipError_t launch_tile_cfg(const FwdPlan& pl, int n, const void* const* x
     g_1x1_cfg = -1;
     return e;
   }
-  g_tile_cfg = cfg >= 501 ? cfg - 501 : -1;
   if (pl.S > 1 && (size_t)pl.S * s.pixels() * s.cout > part_cap) return hipErrorInvalidValue;
+  g_tile_cfg = cfg >= 501 ? cfg - 501 : -1;
   const hipError_t e = conv_forward_tile(n, x, w, b, y, s, relu, dg, pl.S, part, st);
   g_tile_cfg = -1;
   return e;

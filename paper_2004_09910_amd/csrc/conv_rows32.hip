@@ -375,7 +375,7 @@ constexpr int kR32N = sizeof(kR32Cfgs) / sizeof(kR32Cfgs[0]);
 // fragments it runs about 10% slower than the eight-wave layout).  The
 // summation order of every output is the same in all configurations, so
 // the choice does not change values.  Returns an index into kR32Cfgs, or -1.
-int g_rows32_cfg = -1;   // >= 0 forces a configuration (measurement only)
+thread_local int g_rows32_cfg = -1;   // >= 0 forces a configuration (measurement only)
 int g_rows32_ch = 0;     // 1 or 2: only that wave layout (measurement); 0: both
 
 static int rows32_pick(const ConvShape& s, int ng = 1) {
@@ -412,19 +412,14 @@ bool conv_rows32_ok(const ConvShape& s) {
 template <int W, int R, int FW, int NS, int CH, int RK>
 static hipError_t launch_rows32(const R32Io& io, int ng, const bf16_t* Wt, const float* b,
                                 const ConvShape& s, int relu, hipStream_t st) {
-  static const char* name = nullptr;
-  static char buf[64];
-  if (!name) {
-    snprintf(buf, sizeof buf, "conv3x3_rows32<%d,%d,%d,%d%s%s>", W, R, FW, NS,
-             CH == 2 ? "" : ",8w", RK ? ",rk" : "");
-    name = buf;
-  }
+  static const KernelName name("conv3x3_rows32<%d,%d,%d,%d%s%s>", W, R, FW, NS,
+                               CH == 2 ? "" : ",8w", RK ? ",rk" : "");
   if (RK && (s.cin != 16 * RK || s.cout != 64)) return hipErrorInvalidValue;
   const long items = (long)ng * s.nb * ((s.H + R - 1) / R) * (s.cout / 64);
   const int G = (int)(items < 256 ? items : 256);
   if (G == 0) return hipSuccess;
   const long P = (long)ng * s.pixels();
-  ProfScope ps(name, 2.0 * P * s.cout * 9 * s.cin,
+  ProfScope ps(name.s, 2.0 * P * s.cout * 9 * s.cin,
                2.0 * ((double)P * s.cin + 9.0 * s.cin * s.cout + (double)P * s.cout), st);
   TGP_LAUNCH(ps, (conv3x3_rows32<W, R, FW, NS, CH, RK>), dim3(G), dim3(CH == 2 ? 256 : 512), 0, st,
              io, ng, Wt, b, s.nb, s.H, s.cin, s.cout, relu);

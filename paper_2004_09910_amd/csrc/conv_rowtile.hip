@@ -226,7 +226,7 @@ constexpr RtCfg kRtCfgs[] = {{9, 2, 64}, {5, 3, 40}, {3, 4, 32}};
 // TN that fits (the stage must fit its LDS slot), scored by the rounds of
 // 256 tiles a nominal 4-sample micro-batch needs times TN.  Returns the
 // index into kRtCfgs, or -1 when the shape is not supported.
-int g_rowtile_cfg = -1;   // >= 0 forces a configuration (measurement only)
+thread_local int g_rowtile_cfg = -1;   // >= 0 forces a configuration (measurement only)
 
 static int rowtile_pick(const ConvShape& s, int& R) {
   if (s.taps != 9 || s.cin % 32 || s.cout % 64 || s.cout > RT_MAXC) return -1;

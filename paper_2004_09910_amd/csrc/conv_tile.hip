@@ -449,7 +449,7 @@ bool tile_cut(int H, int W, int px, int rows, TileCut& c) {
 
 }  // namespace
 
-int g_tile_cfg = -1;   // >= 0 forces a configuration (tests and measurement)
+thread_local int g_tile_cfg = -1;   // >= 0 forces a configuration (tests and measurement)
 
 // Configurations that have a split-K form, and that have tiles across samples (for
 // a sum split or not).
@@ -529,16 +529,14 @@ template <int MT, int WC, int WP, int FW, int LW, int NS, bool DG, bool SPLIT, b
 static hipError_t launch_tile(const TileIo& io, int ng, const bf16_t* Wt, const float* b,
                               const ConvShape& s, int relu, int S, const TileCut& cut,
                               hipStream_t st) {
-  static char name[64];
-  if (!name[0])
-    snprintf(name, sizeof name, "conv3x3_tile<%d,%d,%d,%d,%d,%d%s%s%s>", MT, WC, WP, FW, LW, NS,
-             TALL ? ",tall" : "", DG ? ",dg" : "", SPLIT ? ",split" : "");
+  static const KernelName name("conv3x3_tile<%d,%d,%d,%d,%d,%d%s%s%s>", MT, WC, WP, FW, LW, NS,
+                               TALL ? ",tall" : "", DG ? ",dg" : "", SPLIT ? ",split" : "");
   constexpr int BN = 32 * MT * WC, NW = WC * WP;
   const long items = (long)ng * (TALL ? 1 : s.nb) * cut.nrb * cut.ns * ((s.cout + BN - 1) / BN) * S;
   constexpr int occ = tile_occ(TileCfg{MT, WC, WP, FW, LW, NS, 0, 0});
   const int G = (int)(items < 256 * occ ? items : 256 * occ);
   const long P = (long)ng * s.pixels();
-  ProfScope ps(name, 2.0 * P * s.cout * 9 * s.cin,
+  ProfScope ps(name.s, 2.0 * P * s.cout * 9 * s.cin,
                2.0 * ((double)P * s.cin + 9.0 * s.cin * s.cout + (double)P * s.cout), st);
   TGP_LAUNCH(ps, (conv3x3_tile<MT, WC, WP, FW, LW, NS, DG, SPLIT, TALL>), dim3(G), dim3(NW * 64), 0, st,
              io, ng, Wt, b, s.nb, s.H, s.W, s.cin, s.cout, relu, S, cut);

@@ -49,7 +49,7 @@ hipError_t conv_forward(int dt, const void* x, const void* w, const float* b, vo
 bool conv_rowtile_ok(const ConvShape& s);
 hipError_t conv_forward_rowtile(const void* x, const void* w, const float* b, void* y,
                                 const ConvShape& s, int relu, hipStream_t st);
-extern int g_rowtile_cfg;
+extern thread_local int g_rowtile_cfg;
 // 32x32x16-MFMA 3x3 convolution on whole-row tiles with all nine taps per
 // 16-channel stage (bf16; W in {24, 48, 96, 192}, Cin % 16 == 0, Cout % 64
 // == 0): whether it supports a shape, and the launch over n (1 ..
@@ -67,7 +67,7 @@ hipError_t conv_forward_tile(int n, const void* const* x, const void* w, const f
                              void* const* y, const ConvShape& s, int relu, bool dg, int S,
                              float* const* part, hipStream_t st);
 int conv_tile_split(const ConvShape& s);
-extern int g_tile_cfg;
+extern thread_local int g_tile_cfg;
 // The same for 1x1 layers (bf16; Cin and Cout multiples of 8), and their
 // weight gradient, each sum left pending in *defer[k].
 bool conv1x1_tile_ok(const ConvShape& s);
@@ -79,7 +79,7 @@ size_t wgrad1x1_tile_partial_floats(const ConvShape& s);
 hipError_t wgrad1x1_tile_launch(int n, const void* const* x, const void* const* dz,
                                 float* const* dw, float* const* partial, const ConvShape& s,
                                 hipStream_t st, ReduceJob* const* defer);
-extern int g_1x1_cfg;
+extern thread_local int g_1x1_cfg;
 // 3x3 and 1x1 convolutions of n micro-batches on float32 MFMA, any shape and
 // storage type (dg: the data gradient, as above); and the weight gradient's
 // partial slices and launch, each sum left pending in *defer[k].
@@ -90,7 +90,7 @@ size_t conv_gen_wgrad_partial_floats(const ConvShape& s);
 hipError_t conv_gen_wgrad_launch(int dt, int n, const void* const* x, const void* const* dz,
                                  float* const* dw, float* const* partial, const ConvShape& s,
                                  hipStream_t st, ReduceJob* const* defer);
-extern int g_rows32_cfg;
+extern thread_local int g_rows32_cfg;
 extern int g_rows32_ch;
 extern int g_wgrad_ks;
 extern int g_rowtile_mask;

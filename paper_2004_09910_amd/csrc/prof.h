@@ -6,6 +6,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
+#include <cstdio>
 
 namespace tgpk {
 
@@ -18,6 +19,14 @@ bool prof_enabled();
 // launchers return in place of hipGetLastError().
 bool launch_skipped();
 hipError_t launch_status();
+
+// The name of a kernel template's instantiation, formatted once (a function's static
+// object: safe where several threads launch).
+struct KernelName {
+  char s[64];
+  template <typename... A>
+  explicit KernelName(const char* format, A... args) { snprintf(s, sizeof s, format, args...); }
+};
 
 class ProfScope {
  public:

@@ -655,11 +655,9 @@ static hipError_t launch_wgrad_rows(const WgIo& io, int ng, const ConvShape& s, 
   const int G = (int)(items < 256 ? items : 256);
   const double flops = 2.0 * ng * s.pixels() * s.cout * 9 * s.cin;
   const double bytes = ng * (2.0 * s.pixels() * (s.cin + s.cout) + 4.0 * p.nK * s.cout * 9 * s.cin);
-  static char name[48];
-  if (!name[0])
-    snprintf(name, sizeof name, "conv_wgrad_rows<%d,%d,%d%s>", W, RPS, NS,
-             KS == 2 ? ",8w" : KS == 3 ? ",12w" : "");
-  ProfScope ps(name, flops, bytes, st);
+  static const KernelName name("conv_wgrad_rows<%d,%d,%d%s>", W, RPS, NS,
+                               KS == 2 ? ",8w" : KS == 3 ? ",12w" : "");
+  ProfScope ps(name.s, flops, bytes, st);
   TGP_LAUNCH(ps, (conv_wgrad_rows<W, RPS, NS, KS>), dim3(G), dim3(256 * KS), 0, st, io, ng, s.nb,
              s.H, s.cin, s.cout, p.R);
   return launch_status();
@@ -707,9 +705,8 @@ static hipError_t launch_wgrad_rows3(const WgIo& io, int ng, const ConvShape& s,
   const int G = (int)(items < 256 ? items : 256);
   const double flops = 2.0 * ng * s.pixels() * s.cout * 9 * s.cin;
   const double bytes = ng * (2.0 * s.pixels() * (s.cin + s.cout) + 4.0 * p.nK * s.cout * 9 * s.cin);
-  static char name[48];
-  if (!name[0]) snprintf(name, sizeof name, "conv_wgrad_rows3<%d,%d,%d>", W, RPS, NS);
-  ProfScope ps(name, flops, bytes, st);
+  static const KernelName name("conv_wgrad_rows3<%d,%d,%d>", W, RPS, NS);
+  ProfScope ps(name.s, flops, bytes, st);
   TGP_LAUNCH(ps, (conv_wgrad_rows3<W, RPS, NS>), dim3(G), dim3(768), 0, st, io, ng, s.nb, s.H,
              s.cin, s.cout, p.R);
   return launch_status();

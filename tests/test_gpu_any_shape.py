@@ -569,3 +569,42 @@ def test_infinities_reach_only_what_they_pair_with(dtype, kind, cin, cout, h, w,
             assert torch.equal(a[~near], c[~near])
             assert not torch.isfinite(c[0, ph, pw]).all()
     sess.close()
+
+
+def test_threads_launch_side_by_side():
+    """Two networks on two threads and streams, of layers whose launches choose
+    among configurations: the bits of one after the other."""
+    import threading
+    made = []
+    for cin, cout, h, w, kind in ((40, 72, 21, 37, CONV3X3), (72, 136, 30, 25, CONV1X1)):
+        sess = Session(one_layer(Layer(kind, cin, cout), h, w), BF16, init="device")
+        sess.plan(2, 1, specs.CKPT_NEVER)
+        x = torch.randn(2, h, w, cin, device="cuda").bfloat16()
+        dy = torch.randn(2, h, w, cout, device="cuda").bfloat16()
+        made.append((sess, x, dy, torch.empty_like(dy), torch.empty_like(x), torch.cuda.Stream()))
+    torch.cuda.synchronize()
+
+    def run(k):
+        sess, x, dy, y, dx, st = made[k]
+        for _ in range(50):
+            sess.stage_step(1, x, y, dy, dx, st.cuda_stream)
+
+    def results():
+        torch.cuda.synchronize()
+        return [t.clone() for s, _, _, y, dx, _ in made for t in (y, dx, s.params[0]["dw"])]
+
+    run(0)
+    run(1)
+    alone = results()
+    for _, _, _, y, dx, _ in made:
+        y.zero_(), dx.zero_()
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=run, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for a, b in zip(alone, results()):
+        assert torch.equal(a, b)
+    for m in made:
+        m[0].close()
