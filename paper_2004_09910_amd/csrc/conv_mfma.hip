@@ -1015,25 +1015,17 @@ hipError_t conv_wgrad_mfma(const void* x, const void* dz, float* dw, float* part
   if (use_wgrad_rows(s)) return conv_wgrad_rows_launch(x, dz, dw, partial, s, st, defer);
   long E = (long)s.cout * s.taps * s.cin;
   if (use_wgrad_tile(s) || wgrad1x1_tile_ok(s)) {
-    ReduceJob job;
-    ReduceJob* const jp = defer ? defer : &job;
-    const hipError_t e = s.taps == 1 ? wgrad1x1_tile_launch(1, &x, &dz, &dw, &partial, s, st, &jp)
-                                     : conv_wgrad_tile_launch(1, &x, &dz, &dw, &partial, s, st, &jp);
-    if (e != hipSuccess || defer) return e;
-    return job.S > 1 ? splitk_reduce_launch(job.part, dw, E, job.S, st) : hipSuccess;
+    return s.taps == 1 ? wgrad1x1_tile_launch(1, &x, &dz, &dw, &partial, s, st, &defer)
+                       : conv_wgrad_tile_launch(1, &x, &dz, &dw, &partial, s, st, &defer);
   }
   WgradPlan pl;
   hipError_t e = launch_wgrad_mfma(1, &x, &dz, &dw, &partial, s, pl, st);
-  if (e != hipSuccess) return e;
-  if (defer) {
-    *defer = ReduceJob{partial, dw, E, pl.S};   // partial == dw when S == 1
-    return hipSuccess;
-  }
-  return pl.S > 1 ? splitk_reduce_launch(partial, dw, E, pl.S, st) : hipSuccess;
+  if (e == hipSuccess) *defer = ReduceJob{partial, dw, E, pl.S};   // partial == dw when S == 1
+  return e;
 }
 
 hipError_t splitk_reduce_n(int n, const float* const* part, float* const* out, long E, int S,
-                           hipStream_t st, int lc_max) {
+                           hipStream_t st) {
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
   SumGroup io;
   for (int k = 0; k < kMaxGroup; ++k) {   // unused entries repeat the first
@@ -1041,7 +1033,7 @@ hipError_t splitk_reduce_n(int n, const float* const* part, float* const* out, l
     io.out[k] = out[k < n ? k : 0];
   }
   int lc = 0;
-  while (lc < lc_max && (1L << lc) < E) ++lc;
+  while (lc < 6 && (1L << lc) < E) ++lc;
   ProfScope ps("splitk_reduce", 0.0, 4.0 * n * E * (S + 1), st);
   TGP_LAUNCH(ps, splitk_reduce_scalar, dim3(cdiv(E, 1L << lc), n), dim3(256), 0, st, io, E, S, lc);
   return launch_status();

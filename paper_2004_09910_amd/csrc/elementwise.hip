@@ -1219,17 +1219,11 @@ size_t conv_wgrad_partial_floats(int dt, const ConvShape& s) {
 
 hipError_t conv_wgrad(int dt, const void* x, const void* dz, float* dw, float* partial,
                       const ConvShape& s, hipStream_t st, ReduceJob* defer) {
-  if (mfma_wgrad_ok(dt, s))
-    return conv_wgrad_mfma(x, dz, dw, partial, s, st, defer);
-  ReduceJob job;
-  ReduceJob* const jp = defer ? defer : &job;
-  const hipError_t e = small1x1_ok(dt, s, x)
-                           ? wgrad1x1_small(dt, 1, &x, &dz, &dw, &partial, s, st, &jp)
-                       : conv_stem_ok(dt, s)
-                           ? conv_stem_wgrad_launch(1, &x, &dz, &dw, &partial, s, st, &jp)
-                           : conv_gen_wgrad_launch(dt, 1, &x, &dz, &dw, &partial, s, st, &jp);
-  if (e != hipSuccess || defer) return e;
-  return job.S > 1 ? splitk_reduce_launch(job.part, dw, job.E, job.S, st) : hipSuccess;
+  if (!defer) return hipErrorInvalidValue;
+  if (mfma_wgrad_ok(dt, s)) return conv_wgrad_mfma(x, dz, dw, partial, s, st, defer);
+  return small1x1_ok(dt, s, x) ? wgrad1x1_small(dt, 1, &x, &dz, &dw, &partial, s, st, &defer)
+         : conv_stem_ok(dt, s) ? conv_stem_wgrad_launch(1, &x, &dz, &dw, &partial, s, st, &defer)
+                               : conv_gen_wgrad_launch(dt, 1, &x, &dz, &dw, &partial, s, st, &defer);
 }
 
 hipError_t conv_forward_n(int dt, int n, const void* const* x, const void* w, const float* b,
@@ -1561,22 +1555,16 @@ static bool rb_group_ok(int n, const RbArgs* a) {
   return true;
 }
 
-// The bias sums of n launched micro-batches: left pending (defer), or those that
-// are not reduced in one launch, 8 columns and 32 lanes a block (512 block sums of
-// 192 channels: 5 us).
+// The bias sums of n launched micro-batches: left pending (defer), or run now.
 static hipError_t rb_finish(int n, const RbArgs* a, long C, int nblk, hipStream_t st) {
-  const float* part[kMaxGroup];
-  float* db[kMaxGroup];
+  ReduceJob jobs[kMaxGroup];
   int now = 0;
   for (int k = 0; k < n; ++k) {
-    if (a[k].defer) {
-      *a[k].defer = ReduceJob{a[k].partial, a[k].db, C, nblk};
-    } else {
-      part[now] = a[k].partial;
-      db[now++] = a[k].db;
-    }
+    const ReduceJob job{a[k].partial, a[k].db, C, nblk};
+    if (a[k].defer) *a[k].defer = job;
+    else jobs[now++] = job;
   }
-  return now ? splitk_reduce_n(now, part, db, C, nblk, st, 3) : hipSuccess;
+  return sum_jobs(now, jobs, st, true);
 }
 
 hipError_t relu_backward_bias_n(int dt, int n, const RbArgs* a, int relu, long P, int C, int cap,
@@ -1769,7 +1757,7 @@ hipError_t loss_finalize(const float* parts, int n, float inv_numel, float* loss
   return launch_status();
 }
 
-hipError_t grad_accumulate_batch(AccBatch b, int overwrite, hipStream_t st) {
+hipError_t grad_accumulate_batch(AccBatch b, int overwrite, hipStream_t st, const char* name) {
   if (b.count < 0 || b.count > kMaxAcc || b.ng < 1 || b.ng > kMaxGroup) return hipErrorInvalidValue;
   long blocks = 0;
   double bytes = 0;
@@ -1787,7 +1775,7 @@ hipError_t grad_accumulate_batch(AccBatch b, int overwrite, hipStream_t st) {
   b.count = used;
   if (used == 0) return hipSuccess;
   if (blocks >= (1L << 31)) return hipErrorInvalidValue;
-  ProfScope ps("reduce_accumulate", 0.0, bytes, st);
+  ProfScope ps(name, 0.0, bytes, st);
   const unsigned grid = (unsigned)(blocks < 512 ? blocks : 512);   // two blocks per CU
   if (b.ng == 1)
     TGP_LAUNCH(ps, reduce_accumulate_k<1>, dim3(grid), dim3(1024), 0, st, b, overwrite,
@@ -1796,6 +1784,22 @@ hipError_t grad_accumulate_batch(AccBatch b, int overwrite, hipStream_t st) {
     TGP_LAUNCH(ps, reduce_accumulate_k<4>, dim3(grid), dim3(1024), 0, st, b, overwrite,
                (int)blocks);
   return launch_status();
+}
+
+hipError_t sum_jobs(int n, const ReduceJob* jobs, hipStream_t st, bool single) {
+  if (n < 0 || n > kMaxGroup) return hipErrorInvalidValue;
+  AccBatch b;
+  b.count = 0;
+  b.ng = 1;
+  for (int k = 0; k < n; ++k) {
+    if (jobs[k].S < (single ? 1 : 2)) continue;
+    b.acc[b.count] = jobs[k].out;
+    b.g[b.count] = jobs[k].part;
+    b.gstride[b.count] = 0;
+    b.n[b.count] = jobs[k].E;
+    b.S[b.count++] = jobs[k].S;
+  }
+  return grad_accumulate_batch(b, 1, st, "reduce_now");
 }
 
 }  // namespace tgpk

@@ -99,18 +99,17 @@ extern int g_rowtile_mask;
 // launch (its order then also depends on the first sum's S).
 hipError_t splitk_reduce_launch(const float* part, float* out, long E, int S, hipStream_t st,
                                const ReduceJob* extra = nullptr);
-// out[k][e] = sum_s part[k][s E + e], n sums of one shape in one launch; a block
-// takes at most 2^lc_max columns (which fixes the order of a sum).
+// out[k][e] = sum_s part[k][s E + e], n sums of one shape in one launch.
 hipError_t splitk_reduce_n(int n, const float* const* part, float* const* out, long E, int S,
-                           hipStream_t st, int lc_max = 6);
+                           hipStream_t st);
 // Row-blocked 3x3 weight gradient on 32x32x16 MFMA with transpose LDS reads
 // (bf16; fixed widths, Cin and Cout multiples of 64): whether it supports a
 // shape, the fp32 partial-slice scratch it needs, and the launch (dw = sum over
-// pixels, summed over its K ranges in a fixed order, or left pending in *defer).
+// pixels, left pending in *defer).
 bool wgrad_rows_ok(const ConvShape& s);
 size_t wgrad_rows_partial_floats(const ConvShape& s);
 hipError_t conv_wgrad_rows_launch(const void* x, const void* dz, float* dw, float* partial,
-                                  const ConvShape& s, hipStream_t st, ReduceJob* defer = nullptr);
+                                  const ConvShape& s, hipStream_t st, ReduceJob* defer);
 // n (1 .. kMaxGroup) micro-batches in one launch, each sum left pending in
 // *defer[k].
 hipError_t conv_wgrad_rows_launch_n(int n, const void* const* x, const void* const* dz,
@@ -149,12 +148,11 @@ hipError_t weight_transform_batch(int dt, WtBatch b, hipStream_t st);
 hipError_t conv_dgrad(int dt, const void* dz, const void* w, const void* wt, void* dx,
                       const ConvShape& s, float* part, size_t part_cap, hipStream_t st);
 // Weight gradient of one micro-batch into dw (float32, KRSC), via split-K
-// partials in `partial` (conv_wgrad_partial_floats floats) reduced in fixed
-// split order.  With `defer` only the partials are written and *defer describes the sum still to run
-// (S = 1 with part = dw when the kernel wrote the gradient itself).
+// partials in `partial` (conv_wgrad_partial_floats floats): *defer describes the
+// sum still to run (S = 1 with part = dw when the kernel wrote the gradient itself).
 size_t conv_wgrad_partial_floats(int dt, const ConvShape& s);
 hipError_t conv_wgrad(int dt, const void* x, const void* dz, float* dw, float* partial,
-                      const ConvShape& s, hipStream_t st, ReduceJob* defer = nullptr);
+                      const ConvShape& s, hipStream_t st, ReduceJob* defer);
 
 // The same three operations for n (1 .. kMaxGroup) micro-batches of one
 // layer (the same weights, separate tensors; array element k is micro-batch
@@ -245,8 +243,8 @@ hipError_t loss_finalize(const float* parts, int n, float inv_numel, float* loss
 // (the pending split-K sums of one micro-batch's gradients), for up to
 // kMaxAcc tensors in one launch (passed by value).  Each r_k is summed in a
 // fixed order that depends on (n_k, S_k) only; it is not always the order
-// of splitk_reduce_launch, so a layer's sums are either always left to the
-// accumulation or always reduced at once.  With ng > 1 the launch does ng
+// of splitk_reduce_launch; sums that may be left to it or run at once take
+// sum_jobs for the latter.  With ng > 1 the launch does ng
 // such accumulations in a row, micro-batch q's slices at g_k + q gstride_k:
 // acc_k (+)= r_k(0), then acc_k += r_k(1), .., the same values as ng
 // launches (overwrite applies to the first).
@@ -261,7 +259,12 @@ struct AccBatch {
   int S[kMaxAcc];
   int blk0[kMaxAcc];   // first block of each entry (filled by the launcher)
 };
-hipError_t grad_accumulate_batch(AccBatch b, int overwrite, hipStream_t st);
+hipError_t grad_accumulate_batch(AccBatch b, int overwrite, hipStream_t st,
+                                 const char* name = "reduce_accumulate");
+// Pending sums run now (n up to kMaxGroup, one launch), in the accumulation's order,
+// so that whether a layer's are kept for it does not change a bit.  Sums of one
+// slice only with `single` (else the slice is the result's own place).
+hipError_t sum_jobs(int n, const ReduceJob* jobs, hipStream_t st, bool single = false);
 
 // relu_backward fused with the bias gradient's column sums (fixed-order
 // two-stage reduction), for layers where relu_bias_fusable() holds.  `cap`

@@ -646,10 +646,7 @@ tgp_status run_backward_g(tgp_net* N, int j, int cnt, const int* iv,
         dfs[k] = Lr.defer_w ? &(*pjs[k])[0] : &jobs[k];
       }
       HIPCHK(tgpk::conv_wgrad_n(N->dt, cnt, cin_ptr, dzk, gws, gps, s, st, dfs), "conv_wgrad_n");
-      for (int k = 0; k < cnt && !Lr.defer_w; ++k)
-        if (jobs[k].S > 1)
-          HIPCHK(tgpk::splitk_reduce_launch(jobs[k].part, gws[k], jobs[k].E, jobs[k].S, st),
-                 "conv_wgrad");
+      if (!Lr.defer_w) HIPCHK(tgpk::sum_jobs(cnt, jobs, st), "conv_wgrad");
     } else if (dw_wrows && (cnt > 1 || Lr.defer_w)) {
       float* gws[MG];
       tgpk::ReduceJob* dfs[MG];
@@ -669,10 +666,12 @@ tgp_status run_backward_g(tgp_net* N, int j, int cnt, const int* iv,
                                 st),
                  "dw_wgrad");
         } else {
+          tgpk::ReduceJob job;
           HIPCHK(tgpk::conv_wgrad(N->dt, cin_ptr[k], dzk[k], gw,
                                   Lr.defer_w ? (float*)G_(N, B.i, Lr.o_gpart) : B.part, s, st,
-                                  Lr.defer_w ? &(*pjs[k])[0] : nullptr),
+                                  Lr.defer_w ? &(*pjs[k])[0] : &job),
                  "conv_wgrad");
+          if (!Lr.defer_w) HIPCHK(tgpk::sum_jobs(1, &job, st), "conv_wgrad");
         }
       }
     }
@@ -1280,22 +1279,46 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
   }
   // per-micro-batch gradients g_i and transformed weights
   size_t max_part = 0, max_col = 0;
+  // Split-K partials stay in the slot for the accumulation to sum when a
+  // layer's slices are at most kDeferBytes per micro-batch (or it writes
+  // none).  The slices counted are those the layer has room for, also where its
+  // kernel writes fewer, so that the slots do not grow with the sum of every
+  // layer's partials: larger ones (deep, wide layers) have a lane buffer of
+  // that size to be reduced at once through.  What their kernels leave of it is
+  // spent on keeping slices, and bias sums, in the slots after all (256 -> 656, 1x1
+  // at 16 x 72 x 8, two micro-batches: a step of 144 us -> SLOTFIG).  Both ways add
+  // in one order.
+  constexpr size_t kDeferBytes = 32u << 20;
+  const size_t slots = N->lanes > 1 ? m : 1;
+  auto general_of = [&](const LayerRt& Lr, const tgpk::ConvShape& s) -> long {
+    return Lr.d.kind == TGP_DWCONV3X3 ? tgpk::direct_wgrad_splits(s.pixels())
+                                      : tgpk::wgrad_room_splits(N->dt, s);
+  };
+  size_t left = 0, reserve = 0;   // bytes of the lane buffers; of them, the slices themselves
+  for (auto& Lr : N->L) {
+    const tgpk::ConvShape s{N->b, Lr.H, Lr.W, Lr.d.cin, Lr.d.cout, Lr.taps};
+    const long general = general_of(Lr, s);
+    if (Lr.d.kind == TGP_DWCONV3X3 || general < 2 || general * Lr.w_elems * 4 <= (long)kDeferBytes)
+      continue;
+    left = std::max<size_t>(left, general * Lr.w_elems * 4);
+    reserve = std::max(reserve, tgpk::conv_wgrad_partial_floats(N->dt, s) * 4);
+  }
+  left = left > reserve ? (left - reserve) * N->lanes : 0;
+  // Takes what `floats` in every slot need more than `least` from what is left.
+  auto keep = [&](size_t floats, size_t least) {
+    const size_t more = floats > least ? slots * (al256(floats * 4) - al256(least * 4)) : 0;
+    if (more > left) return false;
+    left -= more;
+    return true;
+  };
   for (auto& Lr : N->L) {
     tgpk::ConvShape s{N->b, Lr.H, Lr.W, Lr.d.cin, Lr.d.cout, Lr.taps};
     // (a launch covers at most one micro-batch of every lane)
     Lr.has_wt = Lr.d.kind != TGP_DWCONV3X3 &&
                 tgpk::conv_dgrad_uses_wt(N->dt, s, std::min(N->lanes, N->m));
     Lr.o_wt = Lr.has_wt ? takeL(Lr.w_elems * N->esz) : 0;
-    // Split-K partials stay in the slot for the accumulation to sum when a
-    // layer's slices are at most kDeferBytes per micro-batch (or it writes
-    // none); those of larger ones (deep, wide layers) are reduced at once
-    // through a lane buffer, so the slots do not grow with the sum of every
-    // layer's partials.  The slices counted are those the layer has room for,
-    // also where its kernel writes fewer.
-    constexpr size_t kDeferBytes = 32u << 20;
     const long P = (long)N->b * Lr.H * Lr.W;
-    const long general = Lr.d.kind == TGP_DWCONV3X3 ? tgpk::direct_wgrad_splits(P)
-                                                    : tgpk::wgrad_room_splits(N->dt, s);
+    const long general = general_of(Lr, s);
     Lr.defer_w = false;
     size_t pf = 0;   // floats of the weight gradient's partial slices
     if (Lr.d.kind == TGP_DWCONV3X3) {
@@ -1308,6 +1331,12 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
     } else {
       pf = tgpk::conv_wgrad_partial_floats(N->dt, s);
       Lr.defer_w = pf == 0 || std::max<size_t>(pf, general * Lr.w_elems) * 4 <= kDeferBytes;
+    }
+    // (slices the layer has always had room for in the slot)
+    const long spare = Lr.defer_w && (pf || general > 1)
+                           ? general + 1 - std::max(1L, (long)(pf / Lr.w_elems)) : 0;
+    if (Lr.d.kind != TGP_DWCONV3X3 && !Lr.defer_w) {
+      Lr.defer_w = keep(pf, Lr.w_elems);
       if (!Lr.defer_w) max_part = std::max(max_part, pf);
     }
     // The gradient itself and its partial slices share their place: where the
@@ -1325,8 +1354,6 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
     // 138 at once, 189 as separate ReLU and column sums; 16 -> 24 at 224 x 224 x 8, 16
     // blocks: 238, 21, 71.)
     const long Ec = Lr.d.kind == TGP_DWCONV3X3 ? 9 : (long)Lr.d.cin * Lr.taps;   // weights per channel
-    const long spare = Lr.defer_w && (pf || general > 1)
-                           ? general + 1 - std::max(1L, (long)(pf / Lr.w_elems)) : 0;
     const int packs = Lr.d.cout / vecN(N->dt);
     bool in_slot = true;
     Lr.rb_cap = 0;
@@ -1335,7 +1362,7 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
       const long slot = spare > 0 ? std::min(240L, Ec * spare) : 0;
       const long free = std::min(512L, (long)(al256(max_act) / 4 / Lr.d.cout));
       auto rows = [&](long blocks) { return (P + blocks * nl - 1) / (blocks * nl); };
-      in_slot = slot > 0 && (free < 1 || rows(slot) <= rows(free) + 5);
+      in_slot = slot > 0 && (free < 1 || rows(slot) <= rows(free) + 8);
       Lr.rb_cap = (int)(in_slot ? slot : free);
     }
     const bool fuse = Lr.d.bias && (packs == 0 || 256 % packs == 0 || Lr.rb_cap > 0);
@@ -1365,7 +1392,7 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
               (size_t)tgpk::dw_dgrad_mask_rows(N->b, U.H, U.W, U.d.cout) * Lr.d.cout);
       }
     }
-    Lr.defer_b = Lr.o_gcol_floats && in_slot;
+    Lr.defer_b = Lr.o_gcol_floats && (in_slot || keep(Lr.o_gcol_floats, Lr.d.cout));
     // the bias gradient itself, where a call reduces it at once, or its sums
     Lr.o_gb = Lr.d.bias ? takeG(std::max<size_t>(Lr.defer_b ? Lr.o_gcol_floats : 0, Lr.d.cout) * 4) : 0;
     Lr.o_gcol = Lr.o_gb;

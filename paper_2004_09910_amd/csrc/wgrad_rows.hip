@@ -750,13 +750,8 @@ hipError_t conv_wgrad_rows_launch(const void* x, const void* dz, float* dw, floa
     io.out[k] = out;
   }
   hipError_t e = launch_wgrad_rows_w(io, 1, s, p, st);
-  if (e != hipSuccess) return e;
-  if (defer) {
-    *defer = ReduceJob{out, dw, (long)s.cout * 9 * s.cin, p.nK};
-    return hipSuccess;
-  }
-  if (p.nK == 1) return e;
-  return splitk_reduce_launch(partial, dw, (long)s.cout * 9 * s.cin, p.nK, st);
+  if (e == hipSuccess) *defer = ReduceJob{out, dw, (long)s.cout * 9 * s.cin, p.nK};
+  return e;
 }
 
 // n micro-batches in one launch, each sum left pending (*defer[k]): the

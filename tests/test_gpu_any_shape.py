@@ -237,7 +237,7 @@ def test_bias_sums_in_the_slot_or_at_once(dtype, cin, c, h, w, pool, at_once):
                                                     family=EXACT)))
     one = out[0]
     assert ("pool_relu_backward_bias" if pool else "relu_backward_bias") in names, names
-    assert ("splitk_reduce" in names) == at_once, names
+    assert ("reduce_now" in names) == at_once, names
     ref = oracle_stage(net, dtype, 0, len(layers), one["xv"], one["G"], family=EXACT, certify=True)
     check_stage(one, ref, dtype, f"bias sums {cin}->{c} {h}x{w}", EXACT)
     grp = gpu_stage(net, dtype, 4, 2, 0, (len(layers),), 1, lanes=2, group=2, serial=True,
@@ -608,3 +608,18 @@ def test_threads_launch_side_by_side():
         assert torch.equal(a, b)
     for m in made:
         m[0].close()
+
+
+def test_sums_kept_or_run_at_once_have_the_same_bits():
+    """Eight layers whose slices and bias sums fit what the plan of one lane has
+    left, but not all of them with two lanes and sixteen micro-batches."""
+    net = Net("eight", (Layer(CONV1X1, 656, 656),) * 8, 656, 16, 16)
+    one, two = [], []
+    alone = kernels_of(lambda: one.append(gpu_stage(net, BF16, 16, 16, 0, (8,), 1)))
+    group = kernels_of(lambda: two.append(gpu_stage(net, BF16, 16, 16, 0, (8,), 1, lanes=2, group=2,
+                                                    serial=True)))
+    assert "reduce_now" not in alone and "reduce_now" in group, (alone, group)
+    assert torch.equal(one[0]["y"], two[0]["y"]) and torch.equal(one[0]["dx"], two[0]["dx"])
+    for k in one[0]["grads"]:
+        for a, b in zip(one[0]["grads"][k], two[0]["grads"][k]):
+            np.testing.assert_array_equal(a, b)
