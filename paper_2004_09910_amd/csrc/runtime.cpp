@@ -1286,7 +1286,7 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
   // layer's partials: larger ones (deep, wide layers) have a lane buffer of
   // that size to be reduced at once through.  What their kernels leave of it is
   // spent on keeping slices, and bias sums, in the slots after all (256 -> 656, 1x1
-  // at 16 x 72 x 8, two micro-batches: a step of 144 us -> SLOTFIG).  Both ways add
+  // at 16 x 72 x 8, two micro-batches: a step of 144 us -> 128).  Both ways add
   // in one order.
   constexpr size_t kDeferBytes = 32u << 20;
   const size_t slots = N->lanes > 1 ? m : 1;
@@ -1344,15 +1344,16 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
     Lr.o_gw = takeG(std::max<size_t>(Lr.defer_w ? pf : 0, Lr.w_elems) * 4);
     Lr.o_gpart = Lr.o_gw;
     // Blocks of the bias sums.  Where the channel packs divide a 256-thread block
-    // the sums stay in the slot.  Elsewhere they do only if that room, which with
-    // the layer's slices is what the gradient and the slices of the general
-    // kernels take, gives a block about as few rows as a free choice: a
-    // thread's row takes 1.1 us, and sums not in the slot a launch of 4 us
-    // more.  Sums that do not go there are reduced at once, through the buffer that
-    // the layer's data gradient writes afterwards.  (64 -> 192 at 224 x 224 x 8, one
-    // micro-batch, where the slot has room for 64 blocks: pass 716 us in the slot,
-    // 138 at once, 189 as separate ReLU and column sums; 16 -> 24 at 224 x 224 x 8, 16
-    // blocks: 238, 21, 71.)
+    // the sums stay in the slot.  Elsewhere they do if that room, which with the
+    // layer's slices is what the gradient and the slices of the general kernels
+    // take, gives a block about as few rows as a free choice, or if what is left
+    // covers the free choice.  Sums that do not stay there are run at once (a launch
+    // of 4 us more), through the buffer that the layer's data gradient writes
+    // afterwards.  (64 -> 192 at 224 x 224 x 8, one micro-batch, where the slot has room
+    // for 64 blocks: pass 716 us in the slot, 138 at once, 189 as separate ReLU and
+    // column sums; 16 -> 24 at 224 x 224 x 8, 16 blocks: 238, 21, 71.  Eight rows more:
+    // 64 -> 192 at 13 x 72 x 6, a step of 102 us in the slot, 110 at once; 128 -> 192 at 60
+    // x 60 x 7, six more, 108 and 111.)
     const long Ec = Lr.d.kind == TGP_DWCONV3X3 ? 9 : (long)Lr.d.cin * Lr.taps;   // weights per channel
     const int packs = Lr.d.cout / vecN(N->dt);
     bool in_slot = true;
