@@ -1284,8 +1284,8 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
   // none).  The slices counted are those the layer has room for, also where its
   // kernel writes fewer, so that the slots do not grow with the sum of every
   // layer's partials: larger ones (deep, wide layers) have a lane buffer of
-  // that size to be reduced at once through.  What their kernels leave of it is
-  // spent on keeping slices, and bias sums, in the slots after all (256 -> 656, 1x1
+  // that size to be reduced at once through.  What their kernels leave of it,
+  // up to kDeferBytes a slot, is spent on keeping slices and bias sums after all (256 -> 656, 1x1
   // at 16 x 72 x 8, two micro-batches: a step of 144 us -> 128).  Both ways add
   // in one order.
   constexpr size_t kDeferBytes = 32u << 20;
@@ -1303,7 +1303,7 @@ tgp_status tgp_plan(tgp_net* N, int B, int m, int mode, size_t* bytes) {
     left = std::max<size_t>(left, general * Lr.w_elems * 4);
     reserve = std::max(reserve, tgpk::conv_wgrad_partial_floats(N->dt, s) * 4);
   }
-  left = left > reserve ? (left - reserve) * N->lanes : 0;
+  left = left > reserve ? std::min((left - reserve) * N->lanes, slots * kDeferBytes) : 0;
   // Takes what `floats` in every slot need more than `least` from what is left.
   auto keep = [&](size_t floats, size_t least) {
     const size_t more = floats > least ? slots * (al256(floats * 4) - al256(least * 4)) : 0;
